@@ -315,6 +315,19 @@ int themis_sweep(const themis_batch_t *batch, int n_thr, const double *thr,
 int themis_set_sweep_mapping(int mapping);
 
 /*
+ * themis_set_batch_mapping -- the same for themis_plan_batch and, on single
+ * collectives, themis_simulate_batch:
+ *   THEMIS_MAPPING_AUTO : a wavefront per scenario in small batches, one lane
+ *                         per scenario in large ones (the default)
+ *   THEMIS_MAPPING_LANE : one lane per scenario
+ *   THEMIS_MAPPING_WAVE : one wavefront per scenario (per scenario and
+ *                         collective, in the planner)
+ * Results are the same.  Process-wide, meant for measurements and tests.
+ */
+#define THEMIS_MAPPING_WAVE 3
+int themis_set_batch_mapping(int mapping);
+
+/*
  * themis_sweep_best -- what a parameter study reports per scenario and
  * scheduler: the threshold that gives the smallest completion time (Sec. 5.3
  * fixes one Threshold for all experiments; this finds the best one per

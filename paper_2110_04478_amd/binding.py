@@ -77,6 +77,8 @@ def lib():
         L.themis_sweep_best.argtypes = [C.c_uint64, C.c_int, C.c_int, _vp, C.c_int, _vp, _vp, _vp, _vp]
         L.themis_set_sweep_mapping.restype = C.c_int
         L.themis_set_sweep_mapping.argtypes = [C.c_int]
+        L.themis_set_batch_mapping.restype = C.c_int
+        L.themis_set_batch_mapping.argtypes = [C.c_int]
         L.themis_sweep.restype = C.c_int
         L.themis_sweep.argtypes = [C.POINTER(_Batch), C.c_int, _vp, C.c_int, C.c_uint, _vp,
                                    _vp, C.c_size_t, _vp]
@@ -241,12 +243,18 @@ def themis_sweep(b: DeviceBatch, thr: torch.Tensor, policy_mask: int,
     return t_done
 
 
-MAPPING_AUTO, MAPPING_LANE, MAPPING_QUAD = 0, 1, 2
+MAPPING_AUTO, MAPPING_LANE, MAPPING_QUAD, MAPPING_WAVE = 0, 1, 2, 3
 
 
 def themis_set_sweep_mapping(mapping: int) -> None:
     """Lane mapping of themis_sweep's LDS kernel (MAPPING_AUTO / _LANE / _QUAD), process-wide."""
     _check(lib().themis_set_sweep_mapping(int(mapping)))
+
+
+def themis_set_batch_mapping(mapping: int) -> None:
+    """Lanes per scenario of the planner and of single collectives' simulation (MAPPING_AUTO /
+    _LANE / _WAVE), process-wide."""
+    _check(lib().themis_set_batch_mapping(int(mapping)))
 
 
 def themis_metrics_batch(b: DeviceBatch, t_done: torch.Tensor, transfer: torch.Tensor,

@@ -16,6 +16,7 @@
 #include "themis_quad.hpp"
 #include "themis_table.hpp"
 #include "themis_trace.hpp"
+#include "themis_wave.hpp"
 
 // Scratch of themis_simulate_batch_noalloc: device memory the library itself
 // brings along, one copy per GPU that loads the code object.  Host code never
@@ -165,6 +166,38 @@ plan_kernel(themis_batch_t b, uint8_t* __restrict__ orders, double* __restrict__
 #pragma unroll
     for (int k = 0; k < kMaxDims; ++k)
       loads[(size_t)k * b.n + i] = ok ? ((k < s.D) ? load[k] : 0.0) : nan64();
+  }
+}
+
+// One wavefront per scenario and collective: for batches that cannot fill the
+// GPU with one lane each (see plan_on_wavefronts).
+__global__ void __launch_bounds__(kBlock)
+plan_wave_kernel(themis_batch_t b, uint8_t* __restrict__ orders, double* __restrict__ loads) {
+  const TraceView tv = trace_view(b);
+  const uint64_t i = blockIdx.x / tv.mc;
+  const uint32_t q = (uint32_t)(blockIdx.x - i * tv.mc);
+  const uint32_t lane = lane_id();
+  const Scenario s = load_scenario(b, i);
+  const bool rel = b.threshold_mode == THEMIS_THR_REL;
+  const double thr = b.threshold[i];
+  uint32_t Q;
+  const bool ok = collectives_ok(b, tv, i, Q) && s.valid && threshold_ok(thr, rel);
+  uint8_t* row = orders + (size_t)i * tv.slots + (size_t)q * b.max_chunks;
+  double load[kMaxDims] = {0.0, 0.0, 0.0, 0.0};
+  uint32_t filled = 0u;
+  if (ok && q < Q) {
+    const double chunk = collective_size(b, tv, i, q) / (double)s.C;
+    wave_plan(s, chunk, b.inter_policy[i] != THEMIS_INTER_BASELINE, rel, thr, load,
+              [&](uint32_t first, uint32_t code) {
+                if (first + lane < s.C) row[first + lane] = (uint8_t)code;
+              });
+    filled = s.C;
+  }
+  for (uint32_t c = filled + lane; c < b.max_chunks; c += kBlock) row[c] = 0xFFu;
+  // the tracker of the scenario's last collective (an invalid scenario: NaN)
+  if (loads && q == (ok ? Q - 1u : 0u) && lane < (uint32_t)kMaxDims) {
+    const double v = sel4((int)lane, load[0], load[1], load[2], load[3]);
+    loads[(size_t)lane * b.n + i] = ok ? ((int)lane < s.D ? v : 0.0) : nan64();
   }
 }
 
@@ -459,6 +492,157 @@ simulate_kernel(themis_batch_t b, const uint8_t* __restrict__ orders,
           }
       }
     }
+  }
+}
+
+// One wavefront per scenario (themis_wave.hpp): single collectives of up to 64 *
+// kWords chunks in batches too small to fill the GPU with one lane per scenario.
+// kExact: what the event loop does not take (a stage too short to move the
+// clock, sizes outside the normal range) is evaluated right here -- as far as
+// `exact_ok` says so --, and nothing follows this kernel: for the smallest
+// batches, where a second launch costs more than the registers.  Else it is
+// left marked to the follow-up kernel.
+template <uint32_t kWords, bool kQueue, bool kExact>
+__global__ void __launch_bounds__(kBlock)
+simulate_wave_kernel(themis_batch_t b, const uint8_t* __restrict__ orders, double* __restrict__ t_done,
+                     void* __restrict__ queue_order, int entry_bytes, double* __restrict__ busy,
+                     bool exact_ok, unsigned long long hand_over) {
+  using Lds = WaveLds<kWords>;
+  using ExactLds = WaveExactLds<kExact ? kWords : 1u>;
+  __shared__ union Block {
+    Lds events;
+    ExactLds exact;
+    __device__ Block() {}
+  } block;
+  Lds& lds = block.events;
+  const uint64_t i = blockIdx.x;
+  const uint32_t lane = lane_id();
+  const Scenario s = load_scenario(b, i);
+  const bool scf = b.intra_policy[i] == THEMIS_INTRA_SCF;
+  const double S = b.size_bytes[i];
+  const uint32_t D = (uint32_t)s.D, C = s.C;
+  const bool gather = s.ctype == THEMIS_COLL_ALL_GATHER;
+  const uint32_t row_len = 2u * b.max_chunks;
+  uint8_t* rows = queue_order ? (uint8_t*)queue_order + (size_t)i * kMaxDims * row_len * (uint32_t)entry_bytes
+                              : nullptr;
+  auto put = [&](uint32_t k, uint32_t at, uint32_t entry) {
+    if (kQueue) {
+      const uint32_t e = k * row_len + at;
+      if (entry_bytes == 1) rows[e] = (uint8_t)entry;
+      else ((uint16_t*)rows)[e] = (uint16_t)entry;
+    }
+  };
+  WaveResult r;
+#pragma unroll
+  for (int k = 0; k < kMaxDims; ++k) { r.busy[k] = nan64(); r.executed[k] = 0u; }
+  r.t_done = nan64();
+  bool ok = s.valid && finite_positive(S);
+  if (ok) {
+    const uint8_t* row = orders + (size_t)i * b.max_chunks;
+    WaveDim d[kMaxDims];
+#pragma unroll
+    for (int k = 0; k < kMaxDims; ++k) {
+      d[k].finish = nan64();
+      d[k].busy = 0.0;
+      d[k].running = d[k].started = d[k].get = d[k].put = 0u;
+      d[k].lists = 0ull;
+      d[k].head = d[k].tail = d[k].log = 0u;
+    }
+    // a6: every chunk waits at the dimension of its first stage, in chunk-id order
+    uint32_t used = 0u;
+    bool bad = false;
+    for (uint32_t from = 0; from < C; from += 64u) {
+      const uint32_t c = from + lane;
+      const bool exists = c < C;
+      const uint32_t given = exists ? row[c] : 0u;
+      bad = bad || (exists && !order_code_ok(given, s.D));
+      const uint32_t code = gather ? reverse_code(given, s.D) : given;
+      const uint32_t rank = ring_order_rank(code, D) % kWaveOrders;
+      const uint32_t k0 = (code >> (gather ? 2u * (D - 1u) : 0u)) & 3u;
+      used |= exists ? 1u << rank : 0u;
+      const uint32_t rec = c | (rank + (gather ? kWaveOrders : 0u)) << kWaveStateShift;
+#pragma unroll
+      for (uint32_t k = 0; k < (uint32_t)kMaxDims; ++k) {
+        const bool here = exists && k0 == k;
+        const uint64_t m = __builtin_amdgcn_ballot_w64(here);
+        const uint32_t at = d[k].put + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
+                                           __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+        if (here) lds.queue[k][at] = (uint16_t)rec;
+        d[k].put += (uint32_t)__builtin_popcountll(m);
+      }
+    }
+    for (int off = 32; off > 0; off >>= 1) used |= (uint32_t)__shfl_xor((int)used, off);
+    used = first_lane(used);
+    ok = !uniform(bad);
+    if (ok) {
+      __syncthreads();
+      uint32_t link = 0u;
+      if (gather && scf) {
+        // the size of the first wait is the smallest there is: these chunks
+        // are on lists from the start
+#pragma unroll
+        for (uint32_t k = 0; k < (uint32_t)kMaxDims; ++k) {
+          for (uint32_t p = lane; p + 1u < d[k].put; p += 64u)
+            lds.link[lds.queue[k][p] & kWaveIdMask] = lds.queue[k][p + 1u];
+          if (d[k].put != 0u) {
+            d[k].lists = 1ull;
+            d[k].head = lds.queue[k][0];
+            d[k].tail = lds.queue[k][d[k].put - 1u];
+          }
+          d[k].get = d[k].put;
+        }
+        __syncthreads();
+        if (kWords == 1u) link = lds.link[lane];
+      }
+#pragma unroll
+      for (uint32_t k = 0; k < (uint32_t)kMaxDims; ++k) {
+        d[k].queue = lds.queue[k][lane];
+        d[k].put = first_lane(d[k].put);
+        d[k].get = first_lane(d[k].get);
+        d[k].lists = first_lane((uint32_t)d[k].lists);   // (class 0 at most)
+      }
+      const double chunk = S / (double)C;
+      WaveTables t;
+      wave_tables(s, chunk, scf, used, t);
+      bool done = t.normal;
+      if (done) {
+        const uint32_t stages = s.ctype == THEMIS_COLL_ALL_REDUCE ? 2u * D : D;
+        r = scf ? wave_events<kWords, true, kQueue>(t, stages, C, d, link, lds)
+                : wave_events<kWords, false, kQueue>(t, stages, C, d, link, lds);
+        done = r.ok;
+        __syncthreads();
+        if (kQueue && done) {
+#pragma unroll
+          for (uint32_t k = 0; k < (uint32_t)kMaxDims; ++k)
+            for (uint32_t e = lane; e < r.executed[k]; e += kBlock) {
+              const uint32_t rec = lds.log[k][e];
+              put(k, e, ((rec & kWaveIdMask) << 1) | ((rec >> kWaveStateShift) >= kWaveOrders ? 1u : 0u));
+            }
+        }
+      }
+      if (!done) {
+        if constexpr (kExact) {
+          __syncthreads();
+          if (exact_ok)
+            r = wave_exact<kWords>(s, chunk, scf, block.exact, [&](uint32_t c) { return (uint32_t)row[c]; },
+                                   [&](uint32_t k, uint32_t at, uint32_t entry) {
+                                     if (lane == 0u) put(k, at, entry);
+                                   });
+          ok = exact_ok && r.ok;
+        } else {
+          if (lane == 0u) mark_left_to_generic(t_done + i, hand_over);
+          return;
+        }
+      }
+    }
+  }
+  if (lane == 0u) t_done[i] = ok ? r.t_done : nan64();
+  if (busy && lane < (uint32_t)kMaxDims)
+    busy[(size_t)lane * b.n + i] = ok ? sel4((int)lane, r.busy[0], r.busy[1], r.busy[2], r.busy[3]) : nan64();
+  if (kQueue) {
+#pragma unroll
+    for (uint32_t k = 0; k < (uint32_t)kMaxDims; ++k)
+      for (uint32_t e = (ok ? r.executed[k] : 0u) + lane; e < row_len; e += kBlock) put(k, e, 0xFFFFu);
   }
 }
 
@@ -1583,6 +1767,24 @@ static bool sweep_mapping_is_quad(uint32_t cap) {
   return forced != THEMIS_MAPPING_AUTO ? forced == THEMIS_MAPPING_QUAD : cap >= kQuadFromCap;
 }
 
+// Whole wavefronts per scenario (themis_wave.hpp) or one lane each?  A
+// wavefront's event costs a SIMD some 300 clocks (three resident wavefronts),
+// one alone takes 560; with one lane per scenario an event takes about 1,300
+// clocks whatever the number of scenarios, until every SIMD has a wavefront of
+// 64.  Measured on 64 chunks and four dimensions (us, wavefront / lane): 256
+// scenarios 138 / 306, 2,048 164 / 314, 4,096 227 / 311, 8,192 420 / 314; NPU
+// counts that are not powers of two: 137 / 1,835, 226 / 2,274, 416 / 2,272.
+// Planner: 2,048 23 / 26, 4,096 36 / 26 (24 / 144, 36 / 149).
+constexpr uint64_t kWaveSimulate = 4096, kWavePlan = 3072;
+static std::atomic<int> batch_mapping{THEMIS_MAPPING_AUTO};
+static bool on_wavefronts(uint64_t items, uint64_t most) {
+  const int forced = batch_mapping.load(std::memory_order_relaxed);
+  return forced != THEMIS_MAPPING_AUTO ? forced == THEMIS_MAPPING_WAVE && items <= 0x7fffffffull
+                                       : items <= most;
+}
+static bool plan_on_wavefronts(uint64_t items) { return on_wavefronts(items, kWavePlan); }
+static bool simulate_on_wavefronts(uint64_t items) { return on_wavefronts(items, kWaveSimulate); }
+
 }  // namespace themis
 
 using namespace themis;
@@ -1621,7 +1823,9 @@ int themis_plan_batch(const themis_batch_t* batch, uint8_t* orders, double* load
   const TraceView tv = trace_view(*batch);
   if (batch->n * (uint64_t)tv.mc > (uint64_t)0x7fffffff * kBlock) return THEMIS_ERR_UNSUPPORTED;
   Launcher go(stream);
-  if (tv.mc > 1u)
+  if (plan_on_wavefronts(batch->n * tv.mc))
+    go(plan_wave_kernel, (unsigned)(batch->n * tv.mc), kBlock, *batch, orders, loads);
+  else if (tv.mc > 1u)
     go(plan_kernel<true>, blocks_for(batch->n * tv.mc), kBlock, *batch, orders, loads);
   else
     go(plan_kernel<false>, blocks_for(batch->n), kBlock, *batch, orders, loads);
@@ -1678,8 +1882,21 @@ static int simulate_batch_impl(const themis_batch_t* batch, const uint8_t* order
   // A large batch of up to 64 chunks without a workspace keeps the generic pass
   // and its 80 KiB of LDS apart from the table passes.
   const unsigned long long call = next_call_number();
-  go(kernel, blocks_for(batch->n), kBlock, *batch, orders, t_done, queue_order, entry_bytes, busy,
-     call);
+  if (simulate_on_wavefronts(batch->n)) {
+    // (the exact evaluation keeps to what the follow-up passes do: beyond 64
+    // chunks it asks for a workspace)
+    const bool q = queue_order != nullptr, alone = batch->n <= compute_units();
+#define THEMIS_WAVE_KERNEL(W)                                                                        \
+  (alone ? (q ? simulate_wave_kernel<W, true, true> : simulate_wave_kernel<W, false, true>)          \
+         : (q ? simulate_wave_kernel<W, true, false> : simulate_wave_kernel<W, false, false>))
+    go(cap <= 64u ? THEMIS_WAVE_KERNEL(1) : THEMIS_WAVE_KERNEL(8), (unsigned)batch->n, kBlock, *batch,
+       orders, t_done, queue_order, entry_bytes, busy, cap <= 64u || have_ws, call);
+#undef THEMIS_WAVE_KERNEL
+    if (alone) return go.status();
+  } else {
+    go(kernel, blocks_for(batch->n), kBlock, *batch, orders, t_done, queue_order, entry_bytes, busy,
+       call);
+  }
   const unsigned fb = follow_up_blocks(batch->n);
   const Workspace ws = have_ws ? w : Workspace{};
 #define THEMIS_FOLLOW_UP(MODE, A, B, G) \
@@ -1845,6 +2062,13 @@ int themis_set_sweep_mapping(int mapping) {
       mapping != THEMIS_MAPPING_QUAD)
     return THEMIS_ERR_INVALID_ARGUMENT;
   sweep_mapping.store(mapping, std::memory_order_relaxed);
+  return THEMIS_OK;
+}
+
+int themis_set_batch_mapping(int mapping) {
+  if (mapping != THEMIS_MAPPING_AUTO && mapping != THEMIS_MAPPING_LANE && mapping != THEMIS_MAPPING_WAVE)
+    return THEMIS_ERR_INVALID_ARGUMENT;
+  batch_mapping.store(mapping, std::memory_order_relaxed);
   return THEMIS_OK;
 }
 
