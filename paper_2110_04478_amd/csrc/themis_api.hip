@@ -14,6 +14,7 @@
 #include "themis_packed.hpp"
 #include "themis_ring.hpp"
 #include "themis_quad.hpp"
+#include "themis_shared.hpp"
 #include "themis_table.hpp"
 #include "themis_trace.hpp"
 #include "themis_wave.hpp"
@@ -1289,108 +1290,246 @@ __device__ __forceinline__ uint64_t assignment_count(uint32_t D, uint32_t C, uin
   return total;
 }
 
-// One lane per (scenario, assignment): times[i * max_assign + a].  Slots past
-// a scenario's own count hold +inf; NaN marks a scenario that cannot be searched.
-// kTable (L = LayoutTableWide): the follow-up kernel for the scenarios whose
-// NPU counts are not powers of two, on per-order tables: the first kernel
-// marks their slots (see g_marked_call), this one strides over all slots with
-// a grid that just fills the device and returns at once if nothing is marked.
-template <bool kTable, typename L, bool kFix>
-__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(L::kWavesPerSimd)))
-search_eval_kernel(themis_batch_t b, uint64_t max_assign, double* __restrict__ times,
-                   unsigned long long call) {
-  __shared__ uint32_t lds_block[L::kLaneWords * kBlock];
-  if (kTable && nothing_marked(call)) return;
-  const uint64_t total = b.n * max_assign;
-  for (uint64_t e = (uint64_t)blockIdx.x * kBlock + threadIdx.x; e < total;
-       e += (uint64_t)gridDim.x * kBlock) {
-  if (kTable && !is_left_to_generic(times[e])) continue;
-  const uint64_t i = e / max_assign;
-  const uint64_t a = e - i * max_assign;
-  Scenario s = load_scenario(b, i);
-  const bool scf = b.intra_policy[i] == THEMIS_INTRA_SCF;
-  const double S = b.size_bytes[i];
-  const double chunk = S / (double)s.C;
-  FastScenario fs;
-  const bool valid = s.valid && finite_positive(S) && s.C <= 64u;
-  const bool pow2 = valid && fast_eligible(s, chunk, 64u, fs);   // (the same in both kernels)
-  const uint64_t count = valid ? assignment_count((uint32_t)s.D, s.C, max_assign) : 0;
-  if (count == 0) { times[e] = nan64(); continue; }
-  if (a >= count) { times[e] = inf64(); continue; }
-  if (!kTable && !pow2) { mark_left_to_generic(times + e, call); continue; }
-  const uint32_t F = factorial_u32((uint32_t)s.D);
-  // digit c of the assignment number, base D!
-  auto code_at = [&](uint32_t c) {
-    uint64_t rest = a;
-    for (uint32_t j = 0; j < c; ++j) rest /= F;
-    return nth_permutation_code((uint32_t)s.D, (uint32_t)(rest % F));
-  };
-  FastOut fo;
-  fo.queue_order = nullptr;
-  fo.slots = b.max_chunks;
-  FastResult r;
-  if constexpr (kTable) {
-    LaneLds lds;
-    lds.base = (uint8_t*)lds_block + 4u * threadIdx.x;
-    DivModelT<L> model(s, lds, chunk, scf);
-    table_setup_wide<L>(s, scf, lds, code_at, model);
-    r = simulate_fast<L, kNoQueueOrder, false, true>(s, model, lds, fo);
-  } else {
-    const LaneLds lds = lane_lds<L>(lds_block);
-    uint64_t rest = a;
-    for (uint32_t c = 0; c < s.C; ++c) {
+// A scenario's answer (lane 0..63 of a wavefront), NaN / all-ones if !ok.
+__device__ __forceinline__ void search_write(const themis_batch_t& b, uint64_t i, bool ok, double best,
+                                             uint64_t arg, double* best_t, uint8_t* best_orders) {
+  if (threadIdx.x != 0u) return;
+  const uint32_t D = b.ndims[i], C = b.chunks[i];
+  best_t[i] = ok ? best : nan64();
+  if (!best_orders) return;
+  uint8_t* out = best_orders + i * b.max_chunks;
+  const uint32_t F = ok ? factorial_u32(D) : 1u;
+  uint64_t rest = arg;
+  for (uint32_t c = 0; c < b.max_chunks; ++c) {
+    uint32_t code = 0xFFu;
+    if (ok && c < C) {
       const uint64_t q = rest / F;
-      const uint32_t digit = (uint32_t)(rest - q * F);
+      code = nth_permutation_code(D, (uint32_t)(rest - q * F));
       rest = q;
-      L::init_chunk(lds, c, stored_code(s, fs, nth_permutation_code((uint32_t)s.D, digit)),
-                    fs.state0);
     }
-    r = simulate_pow2<L, kNoQueueOrder, false, kFix>(s, Pow2Model(s, fs, scf), lds, fo);
-  }
-  times[e] = r.ok ? r.t_done : nan64();
+    out[c] = (uint8_t)code;
   }
 }
 
-// One wavefront per scenario: smallest time and the lowest assignment number
-// that reaches it.
-__global__ void __launch_bounds__(kBlock)
-search_reduce_kernel(themis_batch_t b, uint64_t max_assign, const double* __restrict__ times,
-                     double* __restrict__ best_t, uint8_t* __restrict__ best_orders) {
-  const uint64_t i = blockIdx.x;
-  const double* row = times + i * max_assign;
-  double best = inf64();
-  uint64_t arg = ~0ull;
-  bool bad = false;
-  for (uint64_t a = threadIdx.x; a < max_assign; a += kBlock) {
-    const double t = row[a];
-    bad |= !(t == t);
-    if (t < best) { best = t; arg = a; }  // ascending a per lane: the first minimum stays
-  }
+// Smallest time of the wavefront and the lowest assignment number that reaches it, in lane 0.
+__device__ __forceinline__ void search_lowest(double& best, uint64_t& arg) {
   for (int off = 32; off > 0; off >>= 1) {
     const double ob = __shfl_down(best, off);
     const uint64_t oa = ((uint64_t)__shfl_down((uint32_t)(arg >> 32), off) << 32) |
                         __shfl_down((uint32_t)arg, off);
-    const int obad = __shfl_down((int)bad, off);
-    bad |= obad != 0;
     if (ob < best || (ob == best && oa < arg)) { best = ob; arg = oa; }
   }
-  if (threadIdx.x != 0) return;
-  const uint32_t D = b.ndims[i], C = b.chunks[i];
-  const bool ok = !bad && arg != ~0ull && D >= 1u && D <= (uint32_t)kMaxDims && C <= b.max_chunks;
-  best_t[i] = ok ? best : nan64();
-  if (best_orders) {
-    uint8_t* out = best_orders + i * b.max_chunks;
-    const uint32_t F = factorial_u32(D);
-    uint64_t rest = arg;
-    for (uint32_t c = 0; c < b.max_chunks; ++c) {
-      uint32_t code = 0xFFu;
-      if (ok && c < C) {
-        const uint64_t q = rest / F;
-        code = nth_permutation_code(D, (uint32_t)(rest - q * F));
+}
+
+// `parts` wavefronts per scenario, each with every parts-th group of 64
+// assignments.  An assignment whose lower bound (SharedBound) is above a time
+// already found cannot be the answer, so only the others are simulated: first
+// the one with the lowest bound of every lane, which puts the limit close to
+// the answer, then what is still below it, gathered 64 at a time so that the
+// lanes of a simulation are full.  On three dimensions and four chunks that
+// leaves 100 of 1,296 assignments (simulating all of them: 3.1 ms for 16,384
+// scenarios, against the limit 0.5 ms).  Where a schedule could take so long that its
+// shortest stage no longer moves the clock nothing is left out, so that the
+// scenario is found to be out of range.
+// kCap: chunk records in LDS; Index: type of an assignment number.
+// Scenarios the shared table does not take (more than 16 size classes, sizes
+// outside the normal range) are marked and go through search_table_kernel and
+// search_finish_kernel.
+template <uint32_t kCap, typename Index>
+__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3)))
+search_kernel(themis_batch_t b, uint64_t max_assign, uint32_t parts, double* __restrict__ times,
+              double* __restrict__ best_t, uint8_t* __restrict__ best_orders, unsigned long long call) {
+  __shared__ __attribute__((aligned(16))) uint8_t ring[kCap * 128u + LayoutRing::kTailBytes];
+  __shared__ SharedTable tab;
+  __shared__ Index queue[2u * kBlock];
+  const uint64_t i = blockIdx.x / parts;
+  const uint32_t part = (uint32_t)(blockIdx.x - i * parts), lane = threadIdx.x;
+  Scenario s = load_scenario(b, i);
+  const bool scf = b.intra_policy[i] == THEMIS_INTRA_SCF;
+  const double S = b.size_bytes[i];
+  const bool valid = s.valid && finite_positive(S) && s.C <= kCap;
+  const uint64_t all = valid ? assignment_count((uint32_t)s.D, s.C, max_assign) : 0u;
+  double* row = times + i * max_assign;
+  // what this wavefront found: the answer itself, or its part of it
+  auto report = [&](bool ok, double best, uint64_t arg) {
+    if (parts == 1u) { search_write(b, i, ok, best, arg, best_t, best_orders); return; }
+    if (lane != 0u) return;
+    row[part] = ok ? best : nan64();
+    ((uint64_t*)row)[parts + part] = arg;
+    if (part == 0u) best_t[i] = 0.0;   // (whatever it held: not a mark)
+  };
+  if (all == 0u) { report(false, nan64(), 0u); return; }
+  const Index count = (Index)all;
+  const double chunk = S / (double)s.C;
+  const SharedSetup setup = shared_table(s, chunk, scf, tab);
+  __syncthreads();
+  if (!setup.ok) {
+    for (uint64_t a = (uint64_t)part * kBlock + lane; a < max_assign; a += (uint64_t)parts * kBlock)
+      row[a] = a < all ? left_to_generic() : inf64();
+    if (part == 0u && lane == 0u) mark_left_to_generic(best_t + i, call);
+    return;
+  }
+  const double longest = (double)s.C * setup.t_max * (1.0 + 1e-9);
+  const bool prune = longest + 0.25 * setup.t_min > longest && longest < inf64();
+
+  const uint32_t D = (uint32_t)s.D, C = s.C, F = factorial_u32(D);
+  const bool both = s.ctype == THEMIS_COLL_ALL_REDUCE;
+  const DivideByOrders by_orders(D);
+  auto bound = [&](Index a) {
+    SharedBound lb;
+    for (uint32_t c = 0; c < C; ++c) {
+      const Index q = by_orders(a);
+      lb.add(tab, tab.rank_of[(uint32_t)(a - q * (Index)F)], both);
+      a = q;
+    }
+    return lb.value(both);
+  };
+  LaneLds lds;
+  lds.base = ring + LayoutRing::lane_term_rec(lane);
+  lds.aux = ring + kCap * 128u + (LayoutRing::lane_term_tail(lane) - LayoutRing::kRecBytes);
+  const SharedModel model{tab, s.ctype == THEMIS_COLL_REDUCE_SCATTER, s.ctype == THEMIS_COLL_ALL_GATHER,
+                          setup.t_min};
+  FastOut none;
+  none.queue_order = nullptr;
+  none.slots = b.max_chunks;
+
+  const Index first = (Index)part * kBlock, step = (Index)parts * kBlock;
+  // (one group per wavefront: all of it at once, no bounds)
+  const bool one_group = count <= step;
+  Index seed = first + lane;
+  bool seeded = one_group && seed < count;
+  if (!one_group) {
+    float lowest = 0.0f;
+    for (Index from = first; from < count; from += step) {
+      const Index a = from + lane;
+      if (a < count) {
+        const float lb = bound(a);
+        if (!seeded || lb < lowest) { lowest = lb; seed = a; seeded = true; }
+      }
+      if (count - from <= step) break;   // (no wrap of the index)
+    }
+  }
+  double best = inf64(), limit = inf64();
+  uint64_t arg = ~0ull;
+  bool bad = false, first_round = true, scanned = one_group || first >= count;
+  Index from = first;
+  uint32_t queued = 0u;
+  for (;;) {
+    Index a = seed;
+    bool active = seeded;
+    if (!first_round) {
+      const float above = (float)limit * (1.0f + 1e-6f);
+      while (queued < kBlock && !scanned) {
+        const Index x = from + lane;
+        const bool take = x < count && x != seed && !(prune && bound(x) > above);
+        const uint64_t m = __builtin_amdgcn_ballot_w64(take);
+        if (take)
+          queue[queued + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
+                                                   __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u))] = x;
+        queued += (uint32_t)__builtin_popcountll(m);
+        scanned = count - from <= step;
+        from += step;
+      }
+      if (queued == 0u) break;
+      __syncthreads();
+      active = lane < queued;
+      a = queue[lane];
+      const Index rest = queue[kBlock + lane];
+      __syncthreads();
+      queue[lane] = rest;
+      queued = queued > kBlock ? queued - kBlock : 0u;
+    }
+    first_round = false;
+    if (active) {
+      Index rest = a;
+      for (uint32_t c = 0; c < C; ++c) {
+        const Index q = by_orders(rest);
+        *LayoutRing::rec(lds, c) = (uint16_t)((uint32_t)tab.rank_of[(uint32_t)(rest - q * (Index)F)] << 3);
         rest = q;
       }
-      out[c] = (uint8_t)code;
+      const FastResult r =
+          ring_loop<true, kNoQueueOrder, false, false, true>(s, model, lds, none, (const uint8_t*)tab.step);
+      bad = bad || !r.ok;
+      if (r.ok && (r.t_done < best || (r.t_done == best && a < arg))) { best = r.t_done; arg = a; }
     }
+    double lowest = best;
+    for (int off = 32; off > 0; off >>= 1) lowest = min_f64(lowest, __shfl_xor(lowest, off));
+    limit = lowest;
+  }
+  bad = __builtin_amdgcn_ballot_w64(bad) != 0ull;
+  search_lowest(best, arg);
+  report(!bad, best, arg);
+}
+
+// The scenarios that search_kernel has marked, on per-order tables of their own
+// in every lane: one lane per (scenario, assignment), times[i * max_assign + a].
+// Strides over all slots with a grid that just fills the device and returns at
+// once if nothing is marked (see g_marked_call).
+__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(LayoutTableWide::kWavesPerSimd)))
+search_table_kernel(themis_batch_t b, uint64_t max_assign, double* __restrict__ times,
+                    unsigned long long call) {
+  using L = LayoutTableWide;
+  __shared__ uint32_t lds_block[L::kLaneWords * kBlock];
+  if (nothing_marked(call)) return;
+  const uint64_t total = b.n * max_assign;
+  for (uint64_t e = (uint64_t)blockIdx.x * kBlock + threadIdx.x; e < total;
+       e += (uint64_t)gridDim.x * kBlock) {
+    if (!is_left_to_generic(times[e])) continue;
+    const uint64_t i = e / max_assign;
+    const uint64_t a = e - i * max_assign;
+    Scenario s = load_scenario(b, i);
+    const bool scf = b.intra_policy[i] == THEMIS_INTRA_SCF;
+    const double chunk = b.size_bytes[i] / (double)s.C;
+    const uint32_t F = factorial_u32((uint32_t)s.D);
+    // digit c of the assignment number, base D!
+    auto code_at = [&](uint32_t c) {
+      uint64_t rest = a;
+      for (uint32_t j = 0; j < c; ++j) rest /= F;
+      return nth_permutation_code((uint32_t)s.D, (uint32_t)(rest % F));
+    };
+    FastOut fo;
+    fo.queue_order = nullptr;
+    fo.slots = b.max_chunks;
+    LaneLds lds;
+    lds.base = (uint8_t*)lds_block + 4u * threadIdx.x;
+    DivModelT<L> model(s, lds, chunk, scf);
+    table_setup_wide<L>(s, scf, lds, code_at, model);
+    const FastResult r = simulate_fast<L, kNoQueueOrder, false, true>(s, model, lds, fo);
+    times[e] = r.ok ? r.t_done : nan64();
+  }
+}
+
+// What is left to do per scenario: the smallest of the times of a marked one,
+// or of the parts it was searched in.
+__global__ void __launch_bounds__(kBlock)
+search_finish_kernel(themis_batch_t b, uint64_t max_assign, uint32_t parts,
+                     const double* __restrict__ times, double* __restrict__ best_t,
+                     uint8_t* __restrict__ best_orders, unsigned long long call) {
+  if (parts == 1u && nothing_marked(call)) return;
+  for (uint64_t i = blockIdx.x; i < b.n; i += gridDim.x) {
+    const double* row = times + i * max_assign;
+    double best = inf64();
+    uint64_t arg = ~0ull;
+    bool bad = false;
+    if (is_left_to_generic(best_t[i])) {
+      for (uint64_t a = threadIdx.x; a < max_assign; a += kBlock) {
+        const double t = row[a];
+        bad |= !(t == t);
+        if (t < best) { best = t; arg = a; }  // ascending a per lane: the first minimum stays
+      }
+    } else if (parts > 1u) {
+      for (uint32_t p = threadIdx.x; p < parts; p += kBlock) {
+        const double t = row[p];
+        const uint64_t a = ((const uint64_t*)row)[parts + p];
+        bad |= !(t == t);
+        if (t < best || (t == best && a < arg)) { best = t; arg = a; }
+      }
+    } else {
+      continue;
+    }
+    bad = __builtin_amdgcn_ballot_w64(bad) != 0ull;
+    search_lowest(best, arg);
+    search_write(b, i, !bad && arg != ~0ull, best, arg, best_t, best_orders);
   }
 }
 
@@ -2092,17 +2231,28 @@ int themis_search_batch(const themis_batch_t* batch, uint64_t max_assignments, d
       workspace_bytes_given < themis_search_workspace_bytes(batch->n, max_assignments))
     return THEMIS_ERR_WORKSPACE;
   double* times = (double*)workspace;
-  const bool fix = batch->fixed_delay != nullptr;
   Launcher go(stream);
-  auto eval = batch->max_chunks <= 16u
-      ? (fix ? search_eval_kernel<false, Layout16, true> : search_eval_kernel<false, Layout16, false>)
-      : (fix ? search_eval_kernel<false, LayoutRing, true> : search_eval_kernel<false, LayoutRing, false>);
   const unsigned long long call = next_call_number();
-  go(eval, blocks_for(evals), kBlock, *batch, max_assignments, times, call);
-  go(search_eval_kernel<true, LayoutTableWide, true>, follow_up_blocks(evals), kBlock, *batch,
-     max_assignments, times, call);
-  go(search_reduce_kernel, (unsigned)batch->n, kBlock, *batch, max_assignments, times, best_t,
-     best_orders);
+  // One wavefront per 64 assignments where the GPU holds all of them in two
+  // turns (twelve wavefronts per CU): a single round, nothing to be gained from
+  // bounds.  Else one per scenario, or several as long as each has some 512
+  // assignments to rule out.
+  const uint64_t room = 12u * (uint64_t)(compute_units() ? compute_units() : 256u);
+  const uint64_t groups = (max_assignments + kBlock - 1u) / kBlock;
+  uint64_t parts = groups;
+  if (groups > 2u * room / batch->n) {
+    parts = room / batch->n;
+    if (parts > max_assignments / 512u) parts = max_assignments / 512u;
+    if (parts < 1u) parts = 1u;
+  }
+  const bool few = batch->max_chunks <= 16u, wide = max_assignments > 0x7fffffffull;
+  auto search = few ? (wide ? search_kernel<16, uint64_t> : search_kernel<16, uint32_t>)
+                    : (wide ? search_kernel<64, uint64_t> : search_kernel<64, uint32_t>);
+  go(search, (unsigned)(batch->n * parts), kBlock, *batch, max_assignments, (uint32_t)parts, times, best_t,
+     best_orders, call);
+  go(search_table_kernel, follow_up_blocks(evals), kBlock, *batch, max_assignments, times, call);
+  go(search_finish_kernel, (unsigned)(batch->n < room ? batch->n : room), kBlock, *batch, max_assignments,
+     (uint32_t)parts, (const double*)times, best_t, best_orders, call);
   return go.status();
 }
 

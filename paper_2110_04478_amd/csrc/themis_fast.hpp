@@ -542,6 +542,8 @@ struct Pow2Model {
   uint64_t ranktab;
   __device__ __forceinline__ Pow2Model(const Scenario& s_, const FastScenario& fs_, bool scf)
       : s(s_), fs(fs_), ranktab(build_rank_table(fs_.epack, scf)) {}
+  __device__ __forceinline__ uint32_t epack() const { return fs.epack; }
+  __device__ __forceinline__ uint64_t ranks() const { return ranktab; }
   __device__ __forceinline__ uint32_t state0() const { return fs.state0; }
   __device__ __forceinline__ bool rs_only() const { return fs.rs_only; }
   __device__ __forceinline__ bool one_phase() const { return fs.rs_only || fs.gather; }

@@ -327,8 +327,11 @@ __device__ inline uint32_t ring_table_entry(uint32_t r, uint32_t behind, uint32_
 // bits 3-7 its order as the lexicographic rank of the four-field code, in
 // place of mask and order fields.  One table read replaces the arithmetic that
 // derives all of that from mask and code at every stage start.
-template <bool kTable, int kQueueOrder, bool kBusy, bool kFix>
-__device__ __forceinline__ FastResult ring_loop(const Scenario& s, const Pow2Model& model,
+// kShared (with kTable): all lanes evaluate the same scenario, on differing
+// orders.  The stage times then sit in the table too, so nothing here depends
+// on the NPU counts being powers of two (Model: SharedModel, themis_shared.hpp).
+template <bool kTable, int kQueueOrder, bool kBusy, bool kFix, bool kShared = false, typename Model>
+__device__ __forceinline__ FastResult ring_loop(const Scenario& s, const Model& model,
                                                 const LaneLds& lds, const FastOut& out,
                                                 const uint8_t* table) {
   static_assert(kQueueOrder == kNoQueueOrder || kQueueOrder == kBytes || kQueueOrder == kStagedBytes,
@@ -338,8 +341,11 @@ __device__ __forceinline__ FastResult ring_loop(const Scenario& s, const Pow2Mod
   const uint32_t C = s.C;
   const uint32_t full = (1u << D) - 1u;
   const double kInf = inf64();
-  const uint32_t epack = model.fs.epack;
-  const uint64_t ranktab = model.ranktab;
+  const uint32_t epack = model.epack();
+  const uint64_t ranktab = model.ranks();
+  // (kShared: times as they are, one way to multiply by them)
+  const double coef[kMaxDims] = {kShared ? 1.0 : s.coef[0], kShared ? 1.0 : s.coef[1],
+                                 kShared ? 1.0 : s.coef[2], kShared ? 1.0 : s.coef[3]};
   // a chunk is finished when its mask comes back to zero (the last All-Gather
   // of an All-Reduce or an All-Gather; a Reduce-Scatter never leaves zero), a
   // stand-alone Reduce-Scatter when it is full
@@ -389,7 +395,12 @@ __device__ __forceinline__ FastResult ring_loop(const Scenario& s, const Pow2Mod
 
   // a6: every chunk waits at the dimension of its first stage, in chunk-id
   // order, in the class of the initial mask
-  {
+  if constexpr (kShared) {
+    for (uint32_t c = 0; c < C; ++c) {
+      const uint32_t low10 = (uint32_t)*L::rec(lds, c) & 0x3ffu;   // the order's rank, no stage behind it
+      push(model.first_list(low10 >> 3), low10 | (c << 10));
+    }
+  } else {
     const uint32_t mask0 = model.state0() & 15u, phase0 = (model.state0() >> 4) & 1u;
     const uint32_t pos0 = 2u * ((uint32_t)__builtin_popcount(mask0) - phase0);
     const uint32_t cls0 = (uint32_t)(ranktab >> (4u * mask0)) & 15u;
@@ -436,8 +447,9 @@ __device__ __forceinline__ FastResult ring_loop(const Scenario& s, const Pow2Mod
         // byte 0: list and finished bit, byte 1: the record's low byte then (one
         // more stage behind it), byte 2: the chunk << 2 (and the phase below it)
         val = __builtin_amdgcn_perm(rh + 1u, he, 0x0c010400u);
-        bytes = __hiloint2double(__double2hiint(model.fs.base) - (int)((e << 10) & 0x03f00000u),
-                                 __double2loint(model.fs.base));
+        if constexpr (kShared) bytes = model.stage_time(rh & 0xffu);
+        else bytes = __hiloint2double(__double2hiint(model.fs.base) - (int)((e << 10) & 0x03f00000u),
+                                      __double2loint(model.fs.base));
       } else {
         const uint32_t kbit = 1u << k;
         const uint32_t mask = rh & 15u;
@@ -457,11 +469,11 @@ __device__ __forceinline__ FastResult ring_loop(const Scenario& s, const Pow2Mod
         // the chunk and its record's low bits then (the stage flips k's bit), above the list
         val = (bfi(0x3ffu, rh ^ kbit, rt) << 7) | q2;
         // (mask & mask2 is mask without k, whichever way the stage flips it)
-        bytes = scale_down(model.fs.base, esum(epack, mask & mask2));
+        if constexpr (!kShared) bytes = scale_down(model.fs.base, esum(epack, mask & mask2));
       }
       // bytes moved on k = resident size before the chunk's Reduce-Scatter on
       // k, i.e. with every reduced dimension but k itself taken off
-      const uint32_t at = ring_start_stage<kBusy, kFix, kStaged>(k, val, now, bytes, s.coef, s.fix, d,
+      const uint32_t at = ring_start_stage<kBusy, kFix, kStaged>(k, val, now, bytes, coef, s.fix, d,
                                                                  ie_lo, ie_hi, place);
       if (kStaged) {
         __builtin_amdgcn_raw_buffer_store_b8((uint8_t)entry, staging, (int)at, 0, 0);

@@ -161,6 +161,8 @@ struct WaveTables {
   uint32_t next[kMaxDims];   // what the completion there does: state, finished, class, dimension
   double t_min;              // smallest stage time of any order in use (all lanes)
   bool normal;               // no size leaves the normal range (all lanes)
+  uint32_t first_class[kMaxDims];  // class of a chunk before its first stage, on dimension k
+  bool few_classes;          // at most 16 classes on every dimension (all lanes)
 };
 
 // orders_used: bit r says that some chunk has the order of rank r.
@@ -220,11 +222,18 @@ __device__ __forceinline__ void wave_tables(const Scenario& s, double chunk, boo
       tmin = min_f64(tmin, t.time[k]);
       if (scf) {
         const double v = phase ? before_ag[k] : before_rs[k];
-        for (uint64_t m = rows; m != 0ull; m &= m - 1ull)
-          cls[k] += lane_get(v, (uint32_t)__builtin_ctzll(m)) < v ? 1u : 0u;
+        // one step per distinct size
+        for (uint64_t m = rows; m != 0ull;) {
+          const double one = lane_get(v, (uint32_t)__builtin_ctzll(m));
+          cls[k] += one < v ? 1u : 0u;
+          m &= ~__builtin_amdgcn_ballot_w64(one == v);
+        }
       }
     }
   }
+  t.few_classes = __builtin_amdgcn_ballot_w64(valid && (cls[0] | cls[1] | cls[2] | cls[3]) > 15u) == 0ull;
+#pragma unroll
+  for (int k = 0; k < kMaxDims; ++k) t.first_class[k] = cls[k];
   if (!valid) tmin = inf64();
   for (int off = 32; off > 0; off >>= 1) tmin = min_f64(tmin, __shfl_xor(tmin, off));
   t.t_min = tmin;

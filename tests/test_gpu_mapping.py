@@ -59,3 +59,28 @@ def test_mappings_agree_with_the_oracle(gpu, oracle, mapping, case):
 @pytest.mark.parametrize("n", [1, 256, 257, 3073, 4096, 4097])
 def test_batch_sizes_around_the_choice_of_the_mapping(gpu, oracle, n):
     check_batch(gpu, oracle, w().mixed(n, seed=820, max_chunks=9, pow2=False))
+
+
+@pytest.mark.parametrize("bound,n,chunks,dims", [(1, 7, 1, 1), (64, 40, 6, 2), (65, 40, 6, 2), (576, 30, 2, 4),
+                                                 (1296, 3, 4, 3), (1296, 7000, 4, 3), (13824, 9, 3, 4)])
+@pytest.mark.parametrize("pow2", [True, False])
+def test_searches_with_one_and_with_several_wavefronts_per_scenario(gpu, oracle, bound, n, chunks, dims, pow2):
+    """themis_search_batch where a wavefront simulates all of its assignments
+    at once, where it rules most of them out by their bounds, and where several
+    share a scenario; collective types and delays among them."""
+    import torch
+    from test_gpu_parity import assert_close
+    W, rng = w(), np.random.default_rng(830 + bound + n)
+    P = [[int(2 ** rng.integers(1, 5)) if pow2 else int(rng.integers(2, 20)) for _ in range(dims)]
+         for _ in range(n)]
+    b = W.make_batch([dims] * n, P, rng.uniform(25e9, 400e9, (n, dims)).tolist(),
+                     np.floor(rng.uniform(2 ** 20, 2 ** 30, n)), rng.integers(max(1, chunks - 1), chunks + 1, n),
+                     1, rng.integers(0, 2, n), 0.0, max_chunks=chunks)
+    b = _with_fixed_delay(_with_collective_types(b, 1), 2)
+    d = gpu.to_device(b)
+    got_t, got_o = gpu.themis_search_batch(d, bound)
+    torch.cuda.synchronize()
+    few = np.arange(n) if n < 100 else rng.permutation(n)[:100]
+    want_t, want_o = oracle.search_batch(b.take(few), bound, threads=8)
+    assert_close("best_t", got_t.cpu().numpy()[few], want_t)
+    assert np.array_equal(got_o.cpu().numpy()[few], want_o)
