@@ -297,12 +297,31 @@ int themis_sweep(const themis_batch_t *batch, int n_thr, const double *thr,
                  void *workspace, size_t workspace_bytes, void *stream);
 
 /*
+ * themis_sweep_with_scratch -- themis_sweep with device memory of its own for
+ * the call to work in: thresholds that give a scenario the same plan are then
+ * found first and simulated once.  Same results; faster from a few thousand
+ * wavefronts on.
+ *   scratch : themis_sweep_scratch_bytes() bytes, 16-byte aligned, like the
+ *             workspace untouched until the stream has drained and one per call
+ *             in flight; NULL or less: as themis_sweep.
+ * themis_sweep_scratch_bytes returns 0 where a sweep of that size would not use
+ * it.
+ */
+size_t themis_sweep_scratch_bytes(uint64_t n, uint32_t max_chunks, int n_thr, unsigned policy_mask);
+int themis_sweep_with_scratch(const themis_batch_t *batch, int n_thr,
+                              const double *thr, int thr_per_scenario,
+                              unsigned policy_mask, double *t_done,
+                              void *workspace, size_t workspace_bytes,
+                              void *scratch, size_t scratch_bytes, void *stream);
+
+/*
  * themis_set_sweep_mapping -- how themis_sweep's LDS kernel spreads the
  * evaluations over the lanes of a wavefront.  The simulation of Sec. 4.6.2 /
  * Sec. 4.3 is the same either way and so are the results; the mappings differ
  * in speed only.
  *   THEMIS_MAPPING_AUTO : the faster one for the batch's chunk capacity (the
- *                         library's choice, the default)
+ *                         library's choice, the default), or a wavefront per
+ *                         evaluation where there are only a few thousand
  *   THEMIS_MAPPING_LANE : one lane per evaluation
  *   THEMIS_MAPPING_QUAD : four lanes per evaluation, one per dimension
  * Process-wide, takes effect with the next call of themis_sweep; meant for

@@ -82,6 +82,11 @@ def lib():
         L.themis_sweep.restype = C.c_int
         L.themis_sweep.argtypes = [C.POINTER(_Batch), C.c_int, _vp, C.c_int, C.c_uint, _vp,
                                    _vp, C.c_size_t, _vp]
+        L.themis_sweep_scratch_bytes.restype = C.c_size_t
+        L.themis_sweep_scratch_bytes.argtypes = [C.c_uint64, C.c_uint32, C.c_int, C.c_uint]
+        L.themis_sweep_with_scratch.restype = C.c_int
+        L.themis_sweep_with_scratch.argtypes = [C.POINTER(_Batch), C.c_int, _vp, C.c_int, C.c_uint,
+                                                _vp, _vp, C.c_size_t, _vp, C.c_size_t, _vp]
         _lib = L
     return _lib
 
@@ -237,9 +242,14 @@ def themis_sweep(b: DeviceBatch, thr: torch.Tensor, policy_mask: int,
     if t_done is None:
         t_done = torch.empty((b.n, n_thr, n_pol), dtype=torch.float64, device=b.device)
     ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
+    # memory in which the thresholds that share a plan are listed (stream-ordered:
+    # torch hands it on only behind this stream's work)
+    need = lib().themis_sweep_scratch_bytes(b.n, b.max_chunks, n_thr, policy_mask)
+    scratch = torch.empty(need, dtype=torch.uint8, device=b.device) if need else None
     s = b.c_struct()
-    _check(lib().themis_sweep(C.byref(s), n_thr, _ptr(thr), 1 if thr_per_scenario else 0,
-                              policy_mask, _ptr(t_done), _ptr(workspace), ws_bytes, _stream()))
+    _check(lib().themis_sweep_with_scratch(C.byref(s), n_thr, _ptr(thr), 1 if thr_per_scenario else 0,
+                                           policy_mask, _ptr(t_done), _ptr(workspace), ws_bytes,
+                                           _ptr(scratch), need, _stream()))
     return t_done
 
 

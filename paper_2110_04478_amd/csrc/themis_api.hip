@@ -521,8 +521,7 @@ simulate_wave_kernel(themis_batch_t b, const uint8_t* __restrict__ orders, doubl
   const Scenario s = load_scenario(b, i);
   const bool scf = b.intra_policy[i] == THEMIS_INTRA_SCF;
   const double S = b.size_bytes[i];
-  const uint32_t D = (uint32_t)s.D, C = s.C;
-  const bool gather = s.ctype == THEMIS_COLL_ALL_GATHER;
+  const uint32_t C = s.C;
   const uint32_t row_len = 2u * b.max_chunks;
   uint8_t* rows = queue_order ? (uint8_t*)queue_order + (size_t)i * kMaxDims * row_len * (uint32_t)entry_bytes
                               : nullptr;
@@ -540,86 +539,19 @@ simulate_wave_kernel(themis_batch_t b, const uint8_t* __restrict__ orders, doubl
   bool ok = s.valid && finite_positive(S);
   if (ok) {
     const uint8_t* row = orders + (size_t)i * b.max_chunks;
-    WaveDim d[kMaxDims];
-#pragma unroll
-    for (int k = 0; k < kMaxDims; ++k) {
-      d[k].finish = nan64();
-      d[k].busy = 0.0;
-      d[k].running = d[k].started = d[k].get = d[k].put = 0u;
-      d[k].lists = 0ull;
-      d[k].head = d[k].tail = d[k].log = 0u;
-    }
-    // a6: every chunk waits at the dimension of its first stage, in chunk-id order
-    uint32_t used = 0u;
-    bool bad = false;
-    for (uint32_t from = 0; from < C; from += 64u) {
-      const uint32_t c = from + lane;
-      const bool exists = c < C;
-      const uint32_t given = exists ? row[c] : 0u;
-      bad = bad || (exists && !order_code_ok(given, s.D));
-      const uint32_t code = gather ? reverse_code(given, s.D) : given;
-      const uint32_t rank = ring_order_rank(code, D) % kWaveOrders;
-      const uint32_t k0 = (code >> (gather ? 2u * (D - 1u) : 0u)) & 3u;
-      used |= exists ? 1u << rank : 0u;
-      const uint32_t rec = c | (rank + (gather ? kWaveOrders : 0u)) << kWaveStateShift;
-#pragma unroll
-      for (uint32_t k = 0; k < (uint32_t)kMaxDims; ++k) {
-        const bool here = exists && k0 == k;
-        const uint64_t m = __builtin_amdgcn_ballot_w64(here);
-        const uint32_t at = d[k].put + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
-                                           __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-        if (here) lds.queue[k][at] = (uint16_t)rec;
-        d[k].put += (uint32_t)__builtin_popcountll(m);
-      }
-    }
-    for (int off = 32; off > 0; off >>= 1) used |= (uint32_t)__shfl_xor((int)used, off);
-    used = first_lane(used);
-    ok = !uniform(bad);
+    const double chunk = S / (double)C;
+    const WaveOutcome outcome =
+        wave_simulate<kWords, kQueue>(s, chunk, scf, lds, [&](uint32_t c) { return (uint32_t)row[c]; }, r);
+    ok = outcome != WaveOutcome::kMalformed;
     if (ok) {
-      __syncthreads();
-      uint32_t link = 0u;
-      if (gather && scf) {
-        // the size of the first wait is the smallest there is: these chunks
-        // are on lists from the start
+      const bool done = outcome == WaveOutcome::kDone;
+      if (kQueue && done) {
 #pragma unroll
-        for (uint32_t k = 0; k < (uint32_t)kMaxDims; ++k) {
-          for (uint32_t p = lane; p + 1u < d[k].put; p += 64u)
-            lds.link[lds.queue[k][p] & kWaveIdMask] = lds.queue[k][p + 1u];
-          if (d[k].put != 0u) {
-            d[k].lists = 1ull;
-            d[k].head = lds.queue[k][0];
-            d[k].tail = lds.queue[k][d[k].put - 1u];
+        for (uint32_t k = 0; k < (uint32_t)kMaxDims; ++k)
+          for (uint32_t e = lane; e < r.executed[k]; e += kBlock) {
+            const uint32_t rec = lds.log[k][e];
+            put(k, e, ((rec & kWaveIdMask) << 1) | ((rec >> kWaveStateShift) >= kWaveOrders ? 1u : 0u));
           }
-          d[k].get = d[k].put;
-        }
-        __syncthreads();
-        if (kWords == 1u) link = lds.link[lane];
-      }
-#pragma unroll
-      for (uint32_t k = 0; k < (uint32_t)kMaxDims; ++k) {
-        d[k].queue = lds.queue[k][lane];
-        d[k].put = first_lane(d[k].put);
-        d[k].get = first_lane(d[k].get);
-        d[k].lists = first_lane((uint32_t)d[k].lists);   // (class 0 at most)
-      }
-      const double chunk = S / (double)C;
-      WaveTables t;
-      wave_tables(s, chunk, scf, used, t);
-      bool done = t.normal;
-      if (done) {
-        const uint32_t stages = s.ctype == THEMIS_COLL_ALL_REDUCE ? 2u * D : D;
-        r = scf ? wave_events<kWords, true, kQueue>(t, stages, C, d, link, lds)
-                : wave_events<kWords, false, kQueue>(t, stages, C, d, link, lds);
-        done = r.ok;
-        __syncthreads();
-        if (kQueue && done) {
-#pragma unroll
-          for (uint32_t k = 0; k < (uint32_t)kMaxDims; ++k)
-            for (uint32_t e = lane; e < r.executed[k]; e += kBlock) {
-              const uint32_t rec = lds.log[k][e];
-              put(k, e, ((rec & kWaveIdMask) << 1) | ((rec >> kWaveStateShift) >= kWaveOrders ? 1u : 0u));
-            }
-        }
       }
       if (!done) {
         if constexpr (kExact) {
@@ -1017,22 +949,214 @@ __device__ __forceinline__ void sweep_store_for_all_thresholds(
   }
 }
 
+// Thresholds that lead to the same plan.  Alg. 1 consults the threshold only to
+// decide whether a chunk keeps the baseline order, so many thresholds of a
+// study give a scenario the same plan (of eight between 0 and 1, four to five
+// different ones on the networks measured), and a plan needs one simulation per
+// queue policy.  sweep_plans_kernel finds, per scenario, which thresholds share
+// a plan and lists one job for each of the different ones.
+struct SweepJob {
+  uint32_t i;      // scenario
+  uint32_t same;   // the thresholds (one bit each) that give this plan
+};
+struct SweepJobs {
+  const SweepJob* list;    // null: no list, every evaluation on its own
+  const uint32_t* count;
+};
+constexpr uint32_t kSweepJobsMaxThr = 32;
+constexpr size_t kSweepJobsHeader = 64;   // the counter
+
+__global__ void sweep_clear_kernel(uint32_t* count) { *count = 0u; }
+
+// One lane per (scenario, threshold), `width` lanes (a power of two) per
+// scenario: all lanes of a scenario plan the same chunk at the same time, and
+// after every chunk each compares its decision with the others'.  A plan is
+// known by which of its chunks deviate from the baseline order: as long as two
+// of them agree their loads are equal, and the order of the next chunk follows
+// from the loads and that one decision.
+// 64 chunks, eight thresholds: 60 us for 65,536 scenarios.
+__global__ void __launch_bounds__(kBlock)
+sweep_plans_kernel(themis_batch_t b, int n_thr, uint32_t width, const double* __restrict__ thr,
+                   int thr_per_scenario, unsigned policy_mask, int n_pol, double* __restrict__ t_done,
+                   SweepJob* __restrict__ list, uint32_t* __restrict__ count) {
+  static_assert(kBlock == kPlanOrders, "one table entry per lane");
+  __shared__ __attribute__((aligned(16))) uint32_t plan_orders[kPlanOrders * kPlanOrderWords];
+  plan_order_entry(threadIdx.x, plan_orders + kPlanOrderWords * threadIdx.x);
+  __syncthreads();
+  const uint32_t lane = threadIdx.x, first = lane & ~(width - 1u);
+  const uint32_t all = width == 32u ? ~0u : (1u << width) - 1u;
+  const uint32_t a = lane - first;
+  const uint64_t i = ((uint64_t)blockIdx.x * kBlock + lane) / width;
+  const bool exists = i < b.n && a < (uint32_t)n_thr;
+  bool valid = false;
+  uint32_t differ = 0u;
+  if (i < b.n) {
+    Scenario s = load_scenario(b, i);
+    s.ctype = THEMIS_COLL_ALL_REDUCE;
+    const bool rel = b.threshold_mode == THEMIS_THR_REL;
+    const uint32_t at = exists ? a : 0u;
+    const double th = thr_per_scenario ? thr[(size_t)at * b.n + i] : thr[at];
+    const double S = b.size_bytes[i];
+    if (s.valid && finite_positive(S)) {
+      valid = exists && threshold_ok(th, rel);
+      const uint32_t baseline = 0xe4u & ((1u << (2 * s.D)) - 1u);
+      auto compare = [&](uint32_t, uint32_t code) {
+        const bool off = code != baseline;
+        const uint32_t others = (uint32_t)(__builtin_amdgcn_ballot_w64(off) >> first);
+        differ |= off ? ~others : others;
+      };
+      const double chunk = S / (double)s.C;
+      double load[kMaxDims];
+      FastScenario fs;
+      if (fast_eligible(s, chunk, THEMIS_MAX_CHUNKS, fs)) {
+        plan_fast<true>(s, fs, true, rel, th, load, compare, plan_orders);
+      } else {
+#pragma unroll
+        for (int k = 0; k < kMaxDims; ++k) load[k] = (k < s.D) ? tracker_start(s, k) : inf64();
+        for (uint32_t c = 0; c < s.C; ++c) compare(c, schedule_chunk(s, chunk, true, rel, th, load));
+      }
+    }
+  }
+  const uint32_t usable = (uint32_t)(__builtin_amdgcn_ballot_w64(valid) >> first) & all;
+  const uint32_t same = ~differ & usable;
+  const bool job = valid && (same & ((1u << a) - 1u)) == 0u;
+  const uint64_t m = __builtin_amdgcn_ballot_w64(job);
+  uint32_t base = 0u;
+  if (m != 0ull && lane == (uint32_t)__builtin_ctzll(m)) base = atomicAdd(count, (uint32_t)__builtin_popcountll(m));
+  if (m != 0ull) base = (uint32_t)__builtin_amdgcn_readlane((int)base, (int)__builtin_ctzll(m));
+  if (job) {
+    const uint32_t place = base + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
+                                                            __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+    list[place] = SweepJob{(uint32_t)i, same};
+  }
+  if (exists && !valid)
+    for (int p = (policy_mask & THEMIS_SWEEP_BASELINE) ? 1 : 0; p < n_pol; ++p)
+      t_done[(i * (uint32_t)n_thr + a) * (uint32_t)n_pol + (uint32_t)p] = nan64();
+}
+
+// Where an evaluation's result goes.  With a list the evaluations are the
+// baseline's (one per scenario, if it is asked for) and then every job under
+// every Themis policy; the index of the first of its thresholds stands for a job.
+struct SweepSlot {
+  uint64_t e;       // index into t_done
+  uint32_t same;    // the thresholds that share the result (0: only e itself)
+  bool exists;
+};
+__device__ __forceinline__ SweepSlot sweep_job_slot(const SweepJobs& jobs, uint64_t j, uint32_t p, int n_thr,
+                                                    unsigned policy_mask, int n_pol) {
+  SweepSlot r;
+  r.exists = j < *jobs.count;
+  const SweepJob job = jobs.list[r.exists ? j : 0u];
+  r.same = job.same;
+  const uint32_t a = (uint32_t)__builtin_ctz(job.same | 0x80000000u);
+  r.e = ((uint64_t)job.i * (uint32_t)n_thr + a) * (uint32_t)n_pol +
+        ((policy_mask & THEMIS_SWEEP_BASELINE) ? 1u : 0u) + p;
+  return r;
+}
+__device__ __forceinline__ uint64_t sweep_evaluations(const themis_batch_t& b, const SweepJobs& jobs, int n_thr,
+                                                      unsigned policy_mask, int n_pol) {
+  if (!jobs.list) return b.n * (uint64_t)n_thr * (uint64_t)n_pol;
+  const bool base = (policy_mask & THEMIS_SWEEP_BASELINE) != 0u;
+  return (base ? b.n : 0u) + (uint64_t)*jobs.count * (uint32_t)(n_pol - (base ? 1 : 0));
+}
+// (the baseline's result is first put under the first threshold that is valid)
+__device__ __forceinline__ uint32_t sweep_first_valid(const themis_batch_t& b, uint64_t i, int n_thr,
+                                                      const double* thr, int thr_per_scenario) {
+  const bool rel = b.threshold_mode == THEMIS_THR_REL;
+  for (int a = 0; a < n_thr; ++a)
+    if (threshold_ok(thr_per_scenario ? thr[(size_t)a * b.n + i] : thr[a], rel)) return (uint32_t)a;
+  return 0u;
+}
+__device__ __forceinline__ SweepSlot sweep_slot(const themis_batch_t& b, const SweepJobs& jobs, uint64_t x,
+                                                int n_thr, const double* thr, int thr_per_scenario,
+                                                unsigned policy_mask, int n_pol) {
+  if (!jobs.list) return SweepSlot{x, 0u, true};
+  const bool base = (policy_mask & THEMIS_SWEEP_BASELINE) != 0u;
+  const uint32_t per = (uint32_t)n_thr * (uint32_t)n_pol, themis = (uint32_t)(n_pol - (base ? 1 : 0));
+  const uint64_t n_base = base ? b.n : 0u;
+  if (x < n_base)
+    return SweepSlot{x * per + sweep_first_valid(b, x, n_thr, thr, thr_per_scenario) * (uint32_t)n_pol, 0u, true};
+  const uint64_t j = (x - n_base) / themis;
+  return sweep_job_slot(jobs, j, (uint32_t)(x - n_base - j * themis), n_thr, policy_mask, n_pol);
+}
+
+// What the follow-up passes have put under the first of the thresholds that
+// share a result goes to the others.
+__global__ void __launch_bounds__(256)
+sweep_spread_kernel(themis_batch_t b, SweepJobs jobs, int n_thr, const double* __restrict__ thr,
+                    int thr_per_scenario, unsigned policy_mask, int n_pol, double* __restrict__ t_done,
+                    unsigned long long call) {
+  if (nothing_marked(call)) return;
+  const uint64_t total = sweep_evaluations(b, jobs, n_thr, policy_mask, n_pol);
+  const uint64_t n_base = (policy_mask & THEMIS_SWEEP_BASELINE) ? b.n : 0u;
+  for (uint64_t x = (uint64_t)blockIdx.x * 256u + threadIdx.x; x < total; x += (uint64_t)gridDim.x * 256u) {
+    const SweepSlot slot = sweep_slot(b, jobs, x, n_thr, thr, thr_per_scenario, policy_mask, n_pol);
+    const double t = t_done[slot.e];
+    if (x < n_base) {
+      // (the others are marked as well where the follow-up passes had to come in)
+      for (int a = 0; a < n_thr; ++a) {
+        double* at = t_done + (x * (uint32_t)n_thr + (uint32_t)a) * (uint32_t)n_pol;
+        if (is_left_to_generic(*at)) *at = t;
+      }
+      continue;
+    }
+    const uint32_t a = (uint32_t)__builtin_ctz(slot.same | 0x80000000u);
+    for (uint32_t m = slot.same & (slot.same - 1u); m != 0u; m &= m - 1u)
+      t_done[slot.e + (uint64_t)((uint32_t)__builtin_ctz(m) - a) * (uint32_t)n_pol] = t;
+  }
+}
+
+// The evaluation a lane takes: `group` consecutive scenarios under one role per
+// workgroup (`at`: the lane's place among them), or, from a list, `group` jobs
+// under one Themis policy, behind the baseline's workgroups.
+__device__ __forceinline__ SweepSlot sweep_lane_slot(const themis_batch_t& b, uint32_t group, uint32_t at,
+                                                     int n_thr, unsigned policy_mask, int n_pol) {
+  const uint32_t roles = sweep_roles((uint32_t)n_thr, (uint32_t)n_pol, policy_mask);
+  const uint64_t i = (uint64_t)(blockIdx.x / roles) * group + at;
+  const bool exists = i < b.n;
+  return SweepSlot{(exists ? i : 0u) * ((uint32_t)n_thr * (uint32_t)n_pol) +
+                       sweep_block_role(blockIdx.x, (uint32_t)n_thr, (uint32_t)n_pol, policy_mask),
+                   0u, exists};
+}
+template <bool kBaseline>
+__device__ __forceinline__ SweepSlot sweep_block_slot(const themis_batch_t& b, const SweepJobs& jobs,
+                                                      uint32_t group, uint32_t at, int n_thr,
+                                                      unsigned policy_mask, int n_pol) {
+  const uint32_t base_blocks = kBaseline ? (uint32_t)((b.n + group - 1u) / group) : 0u;
+  if (kBaseline && blockIdx.x < base_blocks) {
+    const uint64_t i = (uint64_t)blockIdx.x * group + at;
+    const bool exists = i < b.n;
+    return SweepSlot{(exists ? i : 0u) * ((uint32_t)n_thr * (uint32_t)n_pol), 0u, exists};
+  }
+  const uint32_t block = blockIdx.x - base_blocks, themis = (uint32_t)n_pol - (kBaseline ? 1u : 0u);
+  const uint32_t g = block / themis;
+  return sweep_job_slot(jobs, (uint64_t)g * group + at, block - g * themis, n_thr, policy_mask, n_pol);
+}
+template <bool kJobs>
+__device__ __forceinline__ void sweep_store(const SweepSlot& slot, int n_pol, double* t_done, double value) {
+  if (!kJobs) { t_done[slot.e] = value; return; }
+  const uint32_t a = (uint32_t)__builtin_ctz(slot.same | 0x80000000u);
+  for (uint32_t m = slot.same; m != 0u; m &= m - 1u)
+    t_done[slot.e + (uint64_t)((uint32_t)__builtin_ctz(m) - a) * (uint32_t)n_pol] = value;
+}
+
+// kJobs: the evaluations come from a list (SweepJobs), after the baseline's.
 // kBaseline: the sweep has a baseline column (compiled apart: what that
 // column keeps alive across the event loop costs the other columns time).
-template <typename L, bool kFix, bool kBaseline>
+template <typename L, bool kFix, bool kBaseline, bool kJobs>
 __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(L::kWavesPerSimd)))
 sweep_kernel(themis_batch_t b, int n_thr, const double* __restrict__ thr, int thr_per_scenario,
              unsigned policy_mask, int n_pol, double* __restrict__ t_done,
-             unsigned long long hand_over) {
+             unsigned long long hand_over, SweepJobs jobs) {
   __shared__ uint32_t lds_block[L::kLaneWords * kBlock];
   // A wavefront takes 64 consecutive scenarios under one threshold and one
   // scheduler: its lanes read consecutive inputs, and on a batch that keeps to
   // one network they all take the same path through the event loop.
-  const uint32_t per = (uint32_t)n_thr * (uint32_t)n_pol;   // evaluations per scenario
-  const uint32_t roles = sweep_roles((uint32_t)n_thr, (uint32_t)n_pol, policy_mask);
-  const uint64_t i = (uint64_t)(blockIdx.x / roles) * kBlock + threadIdx.x;
-  if (i >= b.n) return;
-  const uint64_t e = i * per + sweep_block_role(blockIdx.x, (uint32_t)n_thr, (uint32_t)n_pol, policy_mask);
+  const SweepSlot slot =
+      kJobs ? sweep_block_slot<kBaseline>(b, jobs, kBlock, threadIdx.x, n_thr, policy_mask, n_pol)
+            : sweep_lane_slot(b, kBlock, threadIdx.x, n_thr, policy_mask, n_pol);
+  if (!slot.exists) return;
+  const uint64_t e = slot.e;
   const SweepItem it = sweep_item(b, e, n_thr, thr, thr_per_scenario, policy_mask, n_pol);
   const bool every_threshold = kBaseline && !it.themis_on;   // (the same for the whole wavefront)
 
@@ -1068,7 +1192,7 @@ sweep_kernel(themis_batch_t b, int n_thr, const double* __restrict__ thr, int th
       if (every_threshold)
         sweep_store_for_all_thresholds(b, it.i, e, n_thr, thr, thr_per_scenario, n_pol, rel, t_done,
                                        r.t_done, 0ull);
-      else t_done[e] = r.t_done;
+      else sweep_store<kJobs>(slot, n_pol, t_done, r.t_done);
       return;
     }
   }
@@ -1081,21 +1205,21 @@ sweep_kernel(themis_batch_t b, int n_thr, const double* __restrict__ thr, int th
 
 // The same with four lanes per evaluation (themis_quad.hpp): a wavefront takes
 // 16 consecutive scenarios under one threshold and one scheduler.
-template <bool kFix, bool kBaseline>
+template <bool kFix, bool kBaseline, bool kJobs>
 __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(LayoutQuad::kWavesPerSimd)))
 sweep_quad_kernel(themis_batch_t b, int n_thr, const double* __restrict__ thr, int thr_per_scenario,
                   unsigned policy_mask, int n_pol, double* __restrict__ t_done,
-                  unsigned long long hand_over) {
+                  unsigned long long hand_over, SweepJobs jobs) {
   using L = LayoutQuad;
   __shared__ uint32_t lds_block[L::kBlockWords];
-  const uint32_t per = (uint32_t)n_thr * (uint32_t)n_pol;   // evaluations per scenario
-  const uint32_t roles = sweep_roles((uint32_t)n_thr, (uint32_t)n_pol, policy_mask);
   const uint32_t quad = threadIdx.x >> 2;
-  const uint64_t i = (uint64_t)(blockIdx.x / roles) * L::kQuads + quad;
-  // a quad without a scenario stays: the wavefront leaves the event loop as a whole
-  const bool exists = i < b.n;
-  const uint64_t e = (exists ? i : 0u) * per +
-                     sweep_block_role(blockIdx.x, (uint32_t)n_thr, (uint32_t)n_pol, policy_mask);
+  const SweepSlot slot =
+      kJobs ? sweep_block_slot<kBaseline>(b, jobs, L::kQuads, quad, n_thr, policy_mask, n_pol)
+            : sweep_lane_slot(b, L::kQuads, quad, n_thr, policy_mask, n_pol);
+  if (kJobs && __builtin_amdgcn_ballot_w64(slot.exists) == 0ull) return;   // (beyond the list)
+  // a quad without an evaluation stays: the wavefront leaves the event loop as a whole
+  const bool exists = slot.exists;
+  const uint64_t e = exists ? slot.e : 0u;
   const SweepItem it = sweep_item(b, e, n_thr, thr, thr_per_scenario, policy_mask, n_pol);
   const bool writer = exists && (threadIdx.x & 3u) == 0u;   // one lane of the quad stores the result
   const bool every_threshold = kBaseline && !it.themis_on;   // (the same for the whole wavefront)
@@ -1134,9 +1258,51 @@ sweep_quad_kernel(themis_batch_t b, int n_thr, const double* __restrict__ thr, i
     return;
   }
   if (!ok) t_done[e] = nan64();
-  else if (fast && r.ok) t_done[e] = r.t_done;
+  else if (fast && r.ok) sweep_store<kJobs>(slot, n_pol, t_done, r.t_done);
   else if (hand_over) mark_left_to_generic(t_done + e, hand_over);
   else t_done[e] = nan64();
+}
+
+// The same with a wavefront per evaluation (themis_wave.hpp): sweeps too small
+// to fill the GPU otherwise.
+template <uint32_t kWords>
+__global__ void __launch_bounds__(kBlock)
+sweep_wave_kernel(themis_batch_t b, int n_thr, const double* __restrict__ thr, int thr_per_scenario,
+                  unsigned policy_mask, int n_pol, double* __restrict__ t_done,
+                  unsigned long long hand_over) {
+  __shared__ WaveLds<kWords> lds;
+  __shared__ uint8_t codes[64u * kWords];
+  const uint32_t lane = lane_id();
+  const uint64_t e = sweep_lane_slot(b, 1u, 0u, n_thr, policy_mask, n_pol).e;
+  const SweepItem it = sweep_item(b, e, n_thr, thr, thr_per_scenario, policy_mask, n_pol);
+  const bool every_threshold = (policy_mask & THEMIS_SWEEP_BASELINE) != 0u && !it.themis_on;
+  Scenario s = load_scenario(b, it.i);
+  s.ctype = THEMIS_COLL_ALL_REDUCE;  // sweeps evaluate All-Reduce only
+  const bool rel = b.threshold_mode == THEMIS_THR_REL;
+  const double S = b.size_bytes[it.i];
+  const bool input_ok = s.valid && finite_positive(S);
+  double value = nan64();
+  bool left = false;
+  if (input_ok && (every_threshold || threshold_ok(it.th, rel))) {
+    const double chunk = S / (double)s.C;
+    double load[kMaxDims];
+    wave_plan(s, chunk, it.themis_on, rel, it.th, load, [&](uint32_t first, uint32_t code) {
+      codes[first + lane] = (uint8_t)code;
+    });
+    __syncthreads();
+    WaveResult r;
+    left = wave_simulate<kWords, false>(s, chunk, it.scf, lds, [&](uint32_t c) { return (uint32_t)codes[c]; }, r) !=
+           WaveOutcome::kDone;
+    value = r.t_done;
+  }
+  if (lane != 0u) return;
+  if (every_threshold && input_ok)
+    sweep_store_for_all_thresholds(b, it.i, e, n_thr, thr, thr_per_scenario, n_pol, rel, t_done, value,
+                                   left ? hand_over : 0ull);
+  else if (every_threshold)
+    for (int a = 0; a < n_thr; ++a) t_done[e + (uint64_t)a * (uint64_t)n_pol] = nan64();
+  else if (left) mark_left_to_generic(t_done + e, hand_over);
+  else t_done[e] = value;
 }
 
 // The generic pass of themis_sweep: the evaluations still marked (kLdsSlots
@@ -1144,13 +1310,15 @@ sweep_quad_kernel(themis_batch_t b, int n_thr, const double* __restrict__ thr, i
 template <uint32_t kLdsSlots>
 __device__ __forceinline__ void sweep_generic_pass(
     const themis_batch_t& b, int n_thr, const double* __restrict__ thr, int thr_per_scenario,
-    unsigned policy_mask, int n_pol, double* __restrict__ t_done, Workspace w, void* lds_block) {
+    unsigned policy_mask, int n_pol, double* __restrict__ t_done, const SweepJobs& jobs, Workspace w, void* lds_block) {
   if (kLdsSlots) w = carve_workspace(lds_block, kBlock, kLdsSlots);
-  const uint64_t total = b.n * (uint64_t)n_thr * (uint64_t)n_pol;
+  const uint64_t total = sweep_evaluations(b, jobs, n_thr, policy_mask, n_pol);
   const uint64_t groups = (total + kBlock - 1) / kBlock;
   for (uint64_t grp = blockIdx.x; grp < groups; grp += gridDim.x) {
-    const uint64_t e = grp * kBlock + threadIdx.x;
-    if (e >= total || !is_left_to_generic(t_done[e])) continue;
+    const uint64_t x = grp * kBlock + threadIdx.x;
+    if (x >= total) continue;
+    const uint64_t e = sweep_slot(b, jobs, x, n_thr, thr, thr_per_scenario, policy_mask, n_pol).e;
+    if (!is_left_to_generic(t_done[e])) continue;
     const uint64_t col = kLdsSlots ? threadIdx.x : e;
     const SweepItem it = sweep_item(b, e, n_thr, thr, thr_per_scenario, policy_mask, n_pol);
     Scenario s = load_scenario(b, it.i);
@@ -1173,10 +1341,10 @@ template <uint32_t kLdsSlots>
 __global__ void __launch_bounds__(kBlock)
 sweep_generic_kernel(themis_batch_t b, int n_thr, const double* __restrict__ thr,
                      int thr_per_scenario, unsigned policy_mask, int n_pol,
-                     double* __restrict__ t_done, Workspace w, unsigned long long call) {
+                     double* __restrict__ t_done, Workspace w, unsigned long long call, SweepJobs jobs) {
   __shared__ double lds_block[kLdsSlots ? generic_lds_bytes(kLdsSlots) / sizeof(double) : 1u];
   if (nothing_marked(call)) return;
-  sweep_generic_pass<kLdsSlots>(b, n_thr, thr, thr_per_scenario, policy_mask, n_pol, t_done, w,
+  sweep_generic_pass<kLdsSlots>(b, n_thr, thr, thr_per_scenario, policy_mask, n_pol, t_done, jobs, w,
                                 lds_block);
 }
 
@@ -1185,14 +1353,16 @@ sweep_generic_kernel(themis_batch_t b, int n_thr, const double* __restrict__ thr
 template <int kVariant>
 __device__ __forceinline__ void sweep_table_pass(
     const themis_batch_t& b, int n_thr, const double* __restrict__ thr, int thr_per_scenario,
-    unsigned policy_mask, int n_pol, double* __restrict__ t_done, void* lds_block) {
+    unsigned policy_mask, int n_pol, double* __restrict__ t_done, const SweepJobs& jobs, void* lds_block) {
   using L = typename TableVariant<kVariant>::L;
   constexpr bool kWide = kVariant != 0;
-  const uint64_t total = b.n * (uint64_t)n_thr * (uint64_t)n_pol;
+  const uint64_t total = sweep_evaluations(b, jobs, n_thr, policy_mask, n_pol);
   const uint64_t groups = (total + kBlock - 1) / kBlock;
   for (uint64_t grp = blockIdx.x; grp < groups; grp += gridDim.x) {
-    const uint64_t e = grp * kBlock + threadIdx.x;
-    if (e >= total || !is_left_to_generic(t_done[e])) continue;
+    const uint64_t x = grp * kBlock + threadIdx.x;
+    if (x >= total) continue;
+    const uint64_t e = sweep_slot(b, jobs, x, n_thr, thr, thr_per_scenario, policy_mask, n_pol).e;
+    if (!is_left_to_generic(t_done[e])) continue;
     const SweepItem it = sweep_item(b, e, n_thr, thr, thr_per_scenario, policy_mask, n_pol);
     Scenario s = load_scenario(b, it.i);
     s.ctype = THEMIS_COLL_ALL_REDUCE;
@@ -1232,20 +1402,20 @@ template <int kTableA, int kTableB, uint32_t kGeneric>
 __global__ void __launch_bounds__(kBlock)
 sweep_follow_up_kernel(themis_batch_t b, int n_thr, const double* __restrict__ thr,
                        int thr_per_scenario, unsigned policy_mask, int n_pol,
-                       double* __restrict__ t_done, Workspace w, unsigned long long call) {
+                       double* __restrict__ t_done, Workspace w, unsigned long long call, SweepJobs jobs) {
   constexpr size_t kBytes_ = max_bytes(max_bytes(table_lds_bytes<kTableA>(), table_lds_bytes<kTableB>()),
                                        kGeneric == kNoGeneric ? 0u : generic_lds_bytes(kGeneric));
   __shared__ double lds_block[kBytes_ ? (kBytes_ + 7u) / 8u : 1u];
   if (nothing_marked(call)) return;
   if constexpr (kTableA >= 0)
-    sweep_table_pass<kTableA>(b, n_thr, thr, thr_per_scenario, policy_mask, n_pol, t_done, lds_block);
+    sweep_table_pass<kTableA>(b, n_thr, thr, thr_per_scenario, policy_mask, n_pol, t_done, jobs, lds_block);
   if constexpr (kTableB >= 0) {
     __syncthreads();
-    sweep_table_pass<kTableB>(b, n_thr, thr, thr_per_scenario, policy_mask, n_pol, t_done, lds_block);
+    sweep_table_pass<kTableB>(b, n_thr, thr, thr_per_scenario, policy_mask, n_pol, t_done, jobs, lds_block);
   }
   if constexpr (kGeneric != kNoGeneric) {
     __syncthreads();
-    sweep_generic_pass<kGeneric>(b, n_thr, thr, thr_per_scenario, policy_mask, n_pol, t_done, w,
+    sweep_generic_pass<kGeneric>(b, n_thr, thr, thr_per_scenario, policy_mask, n_pol, t_done, jobs, w,
                                  lds_block);
   }
 }
@@ -1924,6 +2094,30 @@ static bool on_wavefronts(uint64_t items, uint64_t most) {
 static bool plan_on_wavefronts(uint64_t items) { return on_wavefronts(items, kWavePlan); }
 static bool simulate_on_wavefronts(uint64_t items) { return on_wavefronts(items, kWaveSimulate); }
 
+// A wavefront per evaluation in a sweep of few: the lanes' own planning and
+// their 300 us per 64 chunks otherwise (the line lies where themis_simulate_batch's does).
+static bool sweep_on_wavefronts(uint64_t evaluations) {
+  return sweep_mapping.load(std::memory_order_relaxed) == THEMIS_MAPPING_AUTO && evaluations <= kWaveSimulate;
+}
+
+// Does themis_sweep look for thresholds that share a plan?  From four
+// thresholds on, and where the sweep is more than one turn of the wavefronts
+// that are resident at once: a smaller one takes the time of one wavefront
+// either way.
+static bool sweep_shares_plans(uint64_t n, uint32_t max_chunks, int n_thr, unsigned policy_mask) {
+  if (n_thr < 4 || n_thr > (int)kSweepJobsMaxThr || (policy_mask & ~THEMIS_SWEEP_BASELINE) == 0u || n >= 0xffffffffull)
+    return false;
+  const uint32_t cap = layout_capacity(max_chunks);
+  const bool quad = sweep_mapping_is_quad(cap);
+  if (!quad && cap > 128u) return false;
+  const uint64_t per_cu = quad ? 8u : cap == 128u ? 4u : 12u;
+  const uint64_t group = quad ? LayoutQuad::kQuads : kBlock;
+  const uint64_t waves = (n + group - 1u) / group *
+      sweep_roles((uint32_t)n_thr, (uint32_t)__builtin_popcount(policy_mask & 7u), policy_mask);
+  const unsigned cus = compute_units();
+  return waves > per_cu * (cus ? cus : 256u) * 5u / 4u;
+}
+
 }  // namespace themis
 
 using namespace themis;
@@ -2119,9 +2313,23 @@ int themis_simulate_batch_noalloc(const themis_batch_t* batch, const uint8_t* or
                              (size_t)THEMIS_STATIC_SCRATCH_BYTES, stream);
 }
 
+#define THEMIS_SWEEP_LANES(L) sweep_kernel<L,
+size_t themis_sweep_scratch_bytes(uint64_t n, uint32_t max_chunks, int n_thr, unsigned policy_mask) {
+  if (!sweep_shares_plans(n, max_chunks, n_thr, policy_mask)) return 0;
+  return kSweepJobsHeader + (size_t)n * (size_t)n_thr * sizeof(SweepJob);
+}
+
 int themis_sweep(const themis_batch_t* batch, int n_thr, const double* thr, int thr_per_scenario,
                  unsigned policy_mask, double* t_done, void* workspace,
                  size_t workspace_bytes_given, void* stream) {
+  return themis_sweep_with_scratch(batch, n_thr, thr, thr_per_scenario, policy_mask, t_done, workspace,
+                                   workspace_bytes_given, nullptr, 0, stream);
+}
+
+int themis_sweep_with_scratch(const themis_batch_t* batch, int n_thr, const double* thr, int thr_per_scenario,
+                              unsigned policy_mask, double* t_done, void* workspace,
+                              size_t workspace_bytes_given, void* scratch, size_t scratch_bytes_given,
+                              void* stream) {
   int st = check_batch(batch, false, false);
   if (st != THEMIS_OK) return st;
   if (batch->n_coll) return THEMIS_ERR_UNSUPPORTED;  // sweeps are per single collective
@@ -2129,7 +2337,7 @@ int themis_sweep(const themis_batch_t* batch, int n_thr, const double* thr, int 
     return THEMIS_ERR_INVALID_ARGUMENT;
   if (batch->n == 0) return THEMIS_OK;
   if (!t_done) return THEMIS_ERR_INVALID_ARGUMENT;
-  if ((uintptr_t)workspace & 15u) return THEMIS_ERR_WORKSPACE;
+  if (((uintptr_t)workspace & 15u) || ((uintptr_t)scratch & 15u)) return THEMIS_ERR_WORKSPACE;
   int n_pol = __builtin_popcount(policy_mask & 7u);
   uint64_t evals = batch->n * (uint64_t)n_thr * (uint64_t)n_pol;
   if (evals > (uint64_t)0x7fffffff * kBlock ||
@@ -2141,36 +2349,59 @@ int themis_sweep(const themis_batch_t* batch, int n_thr, const double* thr, int 
   const uint32_t cap = layout_capacity(batch->max_chunks);
   const bool fix = batch->fixed_delay != nullptr;
   const bool base = (policy_mask & THEMIS_SWEEP_BASELINE) != 0u;
-#define THEMIS_SWEEP_KERNEL(L)                                                          \
-  (fix ? (base ? sweep_kernel<L, true, true> : sweep_kernel<L, true, false>)            \
-       : (base ? sweep_kernel<L, false, true> : sweep_kernel<L, false, false>))
-  auto kernel = cap == 16u ? THEMIS_SWEEP_KERNEL(Layout16)
-              : cap == 64u ? THEMIS_SWEEP_KERNEL(LayoutRing)
-              : cap == 128u ? THEMIS_SWEEP_KERNEL(Layout128)
-              : cap == 256u ? THEMIS_SWEEP_KERNEL(LayoutPacked<256>)
-                            : THEMIS_SWEEP_KERNEL(LayoutPacked<512>);
-#undef THEMIS_SWEEP_KERNEL
-  auto quad_kernel = fix ? (base ? sweep_quad_kernel<true, true> : sweep_quad_kernel<true, false>)
-                         : (base ? sweep_quad_kernel<false, true> : sweep_quad_kernel<false, false>);
+  const bool quad = sweep_mapping_is_quad(cap);
+  const uint64_t group = quad ? LayoutQuad::kQuads : kBlock;   // evaluations per wavefront
+  const uint64_t groups = (batch->n + group - 1u) / group;
+  if (groups * (uint64_t)(n_thr * n_pol) > 0x7fffffffull) return THEMIS_ERR_UNSUPPORTED;
+  const size_t need = themis_sweep_scratch_bytes(batch->n, batch->max_chunks, n_thr, policy_mask);
+  const bool share = need != 0u && scratch != nullptr && scratch_bytes_given >= need && (quad || cap <= 128u);
   const unsigned long long call = next_call_number();
   Launcher go(stream);
+  SweepJobs jobs{nullptr, nullptr};
   // (one workgroup per group of scenarios and pair, the baseline once: see sweep_roles)
   const unsigned roles = sweep_roles((uint32_t)n_thr, (uint32_t)n_pol, policy_mask);
-  if (sweep_mapping_is_quad(cap)) {
-    const uint64_t groups = (batch->n + LayoutQuad::kQuads - 1u) / LayoutQuad::kQuads;
-    if (groups * (uint64_t)(n_thr * n_pol) > 0x7fffffffull) return THEMIS_ERR_UNSUPPORTED;
-    go(quad_kernel, (unsigned)groups * roles, kBlock,
-       *batch, n_thr, thr, thr_per_scenario, policy_mask, n_pol, t_done, call);
+  if (share) {
+    uint32_t* count = (uint32_t*)scratch;
+    SweepJob* list = (SweepJob*)((uint8_t*)scratch + kSweepJobsHeader);
+    jobs = SweepJobs{list, count};
+    uint32_t width = 1u;
+    while (width < (uint32_t)n_thr) width *= 2u;
+    go(sweep_clear_kernel, 1u, 1u, count);
+    go(sweep_plans_kernel, blocks_for(batch->n * width), kBlock, *batch, n_thr, width, thr, thr_per_scenario,
+       policy_mask, n_pol, t_done, list, count);
+    // (as many workgroups as there would be jobs if all plans differed)
+    const uint64_t most = (batch->n * (uint64_t)n_thr + group - 1u) / group * (uint64_t)(n_pol - (base ? 1 : 0));
+#define THEMIS_SWEEP_KERNEL(K) \
+  (fix ? (base ? K true, true, true> : K true, false, true>) : (base ? K false, true, true> : K false, false, true>))
+    auto kernel = quad ? THEMIS_SWEEP_KERNEL(sweep_quad_kernel<)
+                : cap == 16u ? THEMIS_SWEEP_KERNEL(THEMIS_SWEEP_LANES(Layout16))
+                : cap == 64u ? THEMIS_SWEEP_KERNEL(THEMIS_SWEEP_LANES(LayoutRing))
+                             : THEMIS_SWEEP_KERNEL(THEMIS_SWEEP_LANES(Layout128));
+    go(kernel, (unsigned)((base ? groups : 0u) + most), kBlock, *batch, n_thr, thr, thr_per_scenario,
+       policy_mask, n_pol, t_done, call, jobs);
+#undef THEMIS_SWEEP_KERNEL
+  } else if (sweep_on_wavefronts(batch->n * roles)) {
+    go(cap <= 64u ? sweep_wave_kernel<1> : sweep_wave_kernel<8>, (unsigned)(batch->n * roles), kBlock, *batch,
+       n_thr, thr, thr_per_scenario, policy_mask, n_pol, t_done, call);
   } else {
-    go(kernel, blocks_for(batch->n) * roles, kBlock, *batch, n_thr, thr, thr_per_scenario,
-       policy_mask, n_pol, t_done, call);
+#define THEMIS_SWEEP_KERNEL(K) \
+  (fix ? (base ? K true, true, false> : K true, false, false>) : (base ? K false, true, false> : K false, false, false>))
+    auto kernel = quad ? THEMIS_SWEEP_KERNEL(sweep_quad_kernel<)
+                : cap == 16u ? THEMIS_SWEEP_KERNEL(THEMIS_SWEEP_LANES(Layout16))
+                : cap == 64u ? THEMIS_SWEEP_KERNEL(THEMIS_SWEEP_LANES(LayoutRing))
+                : cap == 128u ? THEMIS_SWEEP_KERNEL(THEMIS_SWEEP_LANES(Layout128))
+                : cap == 256u ? THEMIS_SWEEP_KERNEL(THEMIS_SWEEP_LANES(LayoutPacked<256>))
+                              : THEMIS_SWEEP_KERNEL(THEMIS_SWEEP_LANES(LayoutPacked<512>));
+#undef THEMIS_SWEEP_KERNEL
+    go(kernel, (unsigned)groups * roles, kBlock, *batch, n_thr, thr, thr_per_scenario, policy_mask, n_pol, t_done,
+       call, jobs);
   }
   // the follow-up passes, in one launch where themis_simulate_batch does the same
   const unsigned fb = follow_up_blocks(evals);
   const Workspace ws = have_ws ? w : Workspace{};
 #define THEMIS_FOLLOW_UP(A, B, G)                                                            \
   go(sweep_follow_up_kernel<A, B, G>, fb, kBlock, *batch, n_thr, thr, thr_per_scenario,      \
-     policy_mask, n_pol, t_done, ws, call)
+     policy_mask, n_pol, t_done, ws, call, jobs)
   if (cap <= 64u) {
     const bool small = blocks_for(evals) <= 2u * compute_units();
     if (have_ws) {
@@ -2183,7 +2414,7 @@ int themis_sweep(const themis_batch_t* batch, int n_thr, const double* thr, int 
       THEMIS_FOLLOW_UP(0, 1, kNoGeneric);
       auto generic = cap <= 16u ? sweep_generic_kernel<16> : sweep_generic_kernel<64>;
       go(generic, fb, kBlock, *batch, n_thr, thr, thr_per_scenario, policy_mask, n_pol, t_done,
-         ws, call);
+         ws, call, jobs);
     }
   } else if (cap == 128u) {
     THEMIS_FOLLOW_UP(2, -1, 0u);
@@ -2193,6 +2424,8 @@ int themis_sweep(const themis_batch_t* batch, int n_thr, const double* thr, int 
     THEMIS_FOLLOW_UP(4, -1, 0u);
   }
 #undef THEMIS_FOLLOW_UP
+  if (share)
+    go(sweep_spread_kernel, fb, 256, *batch, jobs, n_thr, thr, thr_per_scenario, policy_mask, n_pol, t_done, call);
   return go.status();
 }
 

@@ -589,6 +589,86 @@ __device__ __forceinline__ WaveResult wave_events(const WaveTables& t, uint32_t 
   return r;
 }
 
+// One single collective, all 64 lanes with the same arguments; code_at(c): order
+// code of chunk c.  kLog: the records each dimension executes are left in lds.log.
+enum class WaveOutcome { kMalformed, kDone, kNotTaken };   // (some order code; r holds the result; for wave_exact)
+template <uint32_t kWords, bool kLog, typename CodeAt>
+__device__ __forceinline__ WaveOutcome wave_simulate(const Scenario& s, double chunk, bool scf,
+                                                     WaveLds<kWords>& lds, CodeAt code_at, WaveResult& r) {
+  const uint32_t lane = lane_id();
+  const uint32_t D = (uint32_t)s.D, C = s.C;
+  const bool gather = s.ctype == THEMIS_COLL_ALL_GATHER;
+  WaveDim d[kMaxDims];
+#pragma unroll
+  for (int k = 0; k < kMaxDims; ++k) {
+    d[k].finish = nan64();
+    d[k].busy = 0.0;
+    d[k].running = d[k].started = d[k].get = d[k].put = 0u;
+    d[k].lists = 0ull;
+    d[k].head = d[k].tail = d[k].log = 0u;
+  }
+  // a6: every chunk waits at the dimension of its first stage, in chunk-id order
+  uint32_t used = 0u;
+  bool bad = false;
+  for (uint32_t from = 0; from < C; from += 64u) {
+    const uint32_t c = from + lane;
+    const bool exists = c < C;
+    const uint32_t given = exists ? code_at(c) : 0u;
+    bad = bad || (exists && !order_code_ok(given, s.D));
+    const uint32_t code = gather ? reverse_code(given, s.D) : given;
+    const uint32_t rank = ring_order_rank(code, D) % kWaveOrders;
+    const uint32_t k0 = (code >> (gather ? 2u * (D - 1u) : 0u)) & 3u;
+    used |= exists ? 1u << rank : 0u;
+    const uint32_t rec = c | (rank + (gather ? kWaveOrders : 0u)) << kWaveStateShift;
+#pragma unroll
+    for (uint32_t k = 0; k < (uint32_t)kMaxDims; ++k) {
+      const bool here = exists && k0 == k;
+      const uint64_t m = __builtin_amdgcn_ballot_w64(here);
+      const uint32_t at = d[k].put + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
+                                         __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+      if (here) lds.queue[k][at] = (uint16_t)rec;
+      d[k].put += (uint32_t)__builtin_popcountll(m);
+    }
+  }
+  for (int off = 32; off > 0; off >>= 1) used |= (uint32_t)__shfl_xor((int)used, off);
+  used = first_lane(used);
+  if (uniform(bad)) return WaveOutcome::kMalformed;
+  __syncthreads();
+  uint32_t link = 0u;
+  if (gather && scf) {
+    // the size of the first wait is the smallest there is: these chunks
+    // are on lists from the start
+#pragma unroll
+    for (uint32_t k = 0; k < (uint32_t)kMaxDims; ++k) {
+      for (uint32_t p = lane; p + 1u < d[k].put; p += 64u)
+        lds.link[lds.queue[k][p] & kWaveIdMask] = lds.queue[k][p + 1u];
+      if (d[k].put != 0u) {
+        d[k].lists = 1ull;
+        d[k].head = lds.queue[k][0];
+        d[k].tail = lds.queue[k][d[k].put - 1u];
+      }
+      d[k].get = d[k].put;
+    }
+    __syncthreads();
+    if (kWords == 1u) link = lds.link[lane];
+  }
+#pragma unroll
+  for (uint32_t k = 0; k < (uint32_t)kMaxDims; ++k) {
+    d[k].queue = lds.queue[k][lane];
+    d[k].put = first_lane(d[k].put);
+    d[k].get = first_lane(d[k].get);
+    d[k].lists = first_lane((uint32_t)d[k].lists);   // (class 0 at most)
+  }
+  WaveTables t;
+  wave_tables(s, chunk, scf, used, t);
+  if (!t.normal) return WaveOutcome::kNotTaken;
+  const uint32_t stages = s.ctype == THEMIS_COLL_ALL_REDUCE ? 2u * D : D;
+  r = scf ? wave_events<kWords, true, kLog>(t, stages, C, d, link, lds)
+          : wave_events<kWords, false, kLog>(t, stages, C, d, link, lds);
+  __syncthreads();
+  return r.ok ? WaveOutcome::kDone : WaveOutcome::kNotTaken;
+}
+
 // What the event loop does not take (a stage that does not move the clock,
 // sizes outside the normal range, overflow), one wavefront per evaluation, by
 // the definition itself: every pass looks at all chunks, their sizes and

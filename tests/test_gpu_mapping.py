@@ -84,3 +84,34 @@ def test_searches_with_one_and_with_several_wavefronts_per_scenario(gpu, oracle,
     want_t, want_o = oracle.search_batch(b.take(few), bound, threads=8)
     assert_close("best_t", got_t.cpu().numpy()[few], want_t)
     assert np.array_equal(got_o.cpu().numpy()[few], want_o)
+
+
+@pytest.mark.parametrize("n,max_chunks,n_thr,mask,per_scenario,pow2",
+                         [(16001, 9, 8, 7, False, True), (15000, 20, 5, 6, True, False),
+                          (9000, 64, 32, 7, False, True), (5003, 70, 8, 7, False, True),
+                          (2700, 257, 8, 5, False, True), (6000, 3, 8, 2, True, True),
+                          (100, 64, 8, 7, False, False), (3, 512, 8, 7, True, True)])
+def test_sweeps_whose_thresholds_share_plans(gpu, oracle, n, max_chunks, n_thr, mask, per_scenario, pow2):
+    """themis_sweep where it looks for thresholds that give the same plan (from
+    a few thousand wavefronts on), on both mappings, with thresholds that are
+    not valid and scenarios that go to the follow-up passes; and where it takes
+    a wavefront per evaluation."""
+    import torch
+    from test_gpu_parity import assert_close
+    W, rng = w(), np.random.default_rng(840 + n)
+    b = W.mixed(n, seed=841 + n, max_chunks=max_chunks, pow2=pow2)
+    b.size_bytes = np.where(np.arange(n) % 50 == 7, 3e-307, b.size_bytes)   # denormal halvings
+    b.size_bytes[5 % n] = 0.0 if n > 100 else b.size_bytes[5 % n]           # an invalid scenario
+    thr = np.concatenate([[0.0, 0.25, np.nan, 0.25], rng.uniform(0, 1, n_thr - 4)])
+    if per_scenario:
+        thr = np.ascontiguousarray(rng.permuted(np.repeat(thr[:, None], n, axis=1), axis=0))
+    d = gpu.to_device(b)
+    ws = gpu.alloc_workspace(gpu.themis_workspace_bytes(n * n_thr * 3, max_chunks)) if max_chunks > 64 else None
+    out = torch.full((n, n_thr, bin(mask).count("1")), -1.0, dtype=torch.float64, device="cuda")
+    gpu.themis_sweep(d, torch.from_numpy(thr).cuda(), mask, thr_per_scenario=per_scenario, t_done=out,
+                     workspace=ws)
+    torch.cuda.synchronize()
+    few = np.unique(np.concatenate([[5 % n, 7 % n], rng.permutation(n)[:80]]))
+    keep = np.ascontiguousarray(thr[:, few]) if per_scenario else thr
+    want = oracle.sweep(b.take(few), keep, mask, thr_per_scenario=per_scenario, threads=8)
+    assert_close("sweep", out.cpu().numpy()[few], want)
