@@ -1540,7 +1540,8 @@ search_kernel(themis_batch_t b, uint64_t max_assign, uint32_t parts, double* __r
     return;
   }
   const double longest = (double)s.C * setup.t_max * (1.0 + 1e-9);
-  const bool prune = longest + 0.25 * setup.t_min > longest && longest < inf64();
+  // (nor where single precision does not resolve the times)
+  const bool prune = longest + 0.25 * setup.t_min > longest && longest < inf64() && setup.t_min > 1e-30;
 
   const uint32_t D = (uint32_t)s.D, C = s.C, F = factorial_u32(D);
   const bool both = s.ctype == THEMIS_COLL_ALL_REDUCE;

@@ -86,6 +86,21 @@ def test_searches_with_one_and_with_several_wavefronts_per_scenario(gpu, oracle,
     assert np.array_equal(got_o.cpu().numpy()[few], want_o)
 
 
+def test_searches_whose_times_single_precision_does_not_resolve(gpu, oracle):
+    """The bounds that rule assignments out are in single precision: times of
+    1e-45 .. 1e-37 seconds are denormal there."""
+    import torch
+    from test_gpu_parity import assert_close
+    W, rng, n = w(), np.random.default_rng(850), 60
+    b = W.make_batch([3] * n, rng.integers(2, 20, (n, 3)).tolist(), rng.uniform(25e9, 400e9, (n, 3)).tolist(),
+                     10.0 ** rng.uniform(-35, -26, n), [3] * n, 1, rng.integers(0, 2, n), 0.0, max_chunks=3)
+    got_t, got_o = gpu.themis_search_batch(gpu.to_device(b), 216)
+    torch.cuda.synchronize()
+    want_t, want_o = oracle.search_batch(b, 216, threads=8)
+    assert_close("best_t", got_t.cpu().numpy(), want_t)
+    assert np.array_equal(got_o.cpu().numpy(), want_o)
+
+
 @pytest.mark.parametrize("n,max_chunks,n_thr,mask,per_scenario,pow2",
                          [(16001, 9, 8, 7, False, True), (15000, 20, 5, 6, True, False),
                           (9000, 64, 32, 7, False, True), (5003, 70, 8, 7, False, True),
