@@ -1756,13 +1756,16 @@ beam_init_kernel(themis_batch_t b, BeamLayout l, uint8_t* __restrict__ ws) {
 // times[i][p * 24 + j], +inf where there is no such candidate, NaN where the
 // simulation gave up.  kTable: the scenarios the power-of-two path does not
 // take (other NPU counts), on per-order tables; each kernel leaves the other's
-// scenarios alone.
-template <bool kTable, bool kFix>
+// scenarios alone.  kLeft: the scenarios that beam_kernel of call
+// left_by has left open (all of them go on the tables).
+template <bool kTable, bool kFix, bool kLeft>
 __global__ void __launch_bounds__(kBlock)
     __attribute__((amdgpu_waves_per_eu(kTable ? LayoutTableWide::kWavesPerSimd : LayoutRing::kWavesPerSimd)))
-beam_eval_kernel(themis_batch_t b, BeamLayout l, uint8_t* __restrict__ ws, uint32_t m, int half) {
+beam_eval_kernel(themis_batch_t b, BeamLayout l, uint8_t* __restrict__ ws, uint32_t m, int half,
+                 unsigned long long left_by) {
   using L = typename std::conditional<kTable, LayoutTableWide, LayoutRing>::type;
   __shared__ uint32_t lds_block[L::kLaneWords * kBlock];
+  if (kLeft && nothing_marked(left_by)) return;
   const uint64_t e = (uint64_t)blockIdx.x * kBlock + threadIdx.x;
   const uint32_t per = l.width * kBeamOrders;
   if (e >= b.n * per) return;
@@ -1773,13 +1776,13 @@ beam_eval_kernel(themis_batch_t b, BeamLayout l, uint8_t* __restrict__ ws, uint3
   Scenario s = load_scenario(b, i);
   const uint32_t live = ((const uint32_t*)(ws + l.off_live))[i];
   const uint32_t C = s.C;
-  if (live == 0u || m > C) return;                       // nothing to do for this scenario
+  if (live == 0u || (kLeft && live > kBeamMaxWidth) || m > C) return;       // nothing to do for this scenario
   const uint32_t F = factorial_u32((uint32_t)s.D);
   const double chunk = beam_partial_size(b.size_bytes[i], C, m) / (double)m;
   s.C = m;
   FastScenario fs;
   const bool pow2 = fast_eligible(s, chunk, LayoutRing::kCap, fs);
-  if (pow2 == kTable) return;                            // the other kernel's scenario
+  if (!kLeft && pow2 == kTable) return;         // the other kernel's scenario
   if (p >= live || j >= F) { times[e] = inf64(); return; }
   const bool scf = b.intra_policy[i] == THEMIS_INTRA_SCF;
   const uint8_t* digits = ws + l.off_digits[half] + (i * l.width + p) * l.mc;
@@ -1808,14 +1811,17 @@ beam_eval_kernel(themis_batch_t b, BeamLayout l, uint8_t* __restrict__ ws, uint3
 // first, equal times in ascending assignment number (the newest chunk's digit
 // is the most significant, then the kept schedule's own number, known by its
 // rank among the kept ones).
+template <bool kLeft>
 __global__ void __launch_bounds__(kBlock)
-beam_select_kernel(themis_batch_t b, BeamLayout l, uint8_t* __restrict__ ws, uint32_t m, int half) {
+beam_select_kernel(themis_batch_t b, BeamLayout l, uint8_t* __restrict__ ws, uint32_t m, int half,
+                   unsigned long long left_by) {
   __shared__ uint32_t new_key[kBeamMaxWidth];
+  if (kLeft && nothing_marked(left_by)) return;
   const uint64_t i = blockIdx.x;
   uint32_t* live_p = (uint32_t*)(ws + l.off_live) + i;
   const uint32_t live = *live_p;
   const uint32_t D = b.ndims[i], C = b.chunks[i];
-  if (live == 0u || m > C) return;
+  if (live == 0u || (kLeft && live > kBeamMaxWidth) || m > C) return;
   const uint32_t F = factorial_u32(D);
   const double* times = (const double*)(ws + l.off_times) + i * l.width * kBeamOrders;
   const uint8_t* rank_in = ws + l.off_rank[half] + i * l.width;
@@ -1853,6 +1859,209 @@ beam_select_kernel(themis_batch_t b, BeamLayout l, uint8_t* __restrict__ ws, uin
   }
   // a simulation that gave up: the scenario has no answer
   if (threadIdx.x == 0) *live_p = any_bad ? 0u : kept;
+}
+
+// One wavefront per scenario takes the whole beam search of it: per chunk slot m
+// it makes the candidates (kept schedule x order of chunk m - 1), simulates
+// them a lane each on a stage table that all lanes share, and keeps the best.
+// With a lane per candidate of the whole batch and a selection kernel between
+// the steps (above), every candidate is simulated, kept schedules and times go
+// through HBM once per step, and other NPU counts take 60 KiB of LDS per wavefront.
+// 4,096 scenarios: 4-D, width 4, 64 chunks 33.6 -> 29.8 ms; 2-D, width 8, 32
+// chunks 14.8 -> 5.2 ms; of mixed dimensions, width 8, 24 chunks 13.9 -> 10.2 ms.
+//
+// What bounds a step is the chain of events of a simulation round, so it should
+// take one: where there are more candidates than lanes, those with the lowest
+// bounds of their time (SharedBound) go first, and then only what could still
+// be among the `width` best (a third of the candidates on the bench networks
+// at width 4).  Nothing is left out where a stage might not move the clock, so
+// that such a scenario is found to be out of range, and where single precision
+// does not resolve the times.
+//
+// A candidate is kept * D! + order; smaller time first, equal times in
+// ascending assignment number (the newest chunk's digit is the most
+// significant, then the kept schedule's own number, known by its rank among
+// the kept ones).
+// Scenarios the shared table does not take (more than 16 size classes, as four
+// dimensions of other NPU counts have, or sizes outside the normal range) are
+// left to the step-wise kernels above.
+constexpr uint32_t kBeamDone = 0x80000000u;   // (live of a scenario with an answer)
+
+template <uint32_t kWidth>
+struct BeamLds {
+  static constexpr uint32_t kMost = kWidth * kBeamOrders;
+  double time[kMost];
+  uint32_t lb[kMost];          // bits of the bound (positive single precision); all ones: simulated
+  uint32_t tb[kMost];          // bits of the time, rounded up; all ones: not simulated
+  float4 prefix_of[kWidth][(sizeof(SharedBound) + 15u) / 16u];  // the kept schedules' SharedBound
+  uint16_t list[kMost];
+  uint16_t key[kWidth];        // order * 64 + rank of the kept schedule's parent
+  uint8_t parent[kWidth], rank[kWidth];
+  uint8_t digits[2][kWidth][64];
+  __device__ __forceinline__ SharedBound& prefix(uint32_t p) { return *(SharedBound*)prefix_of[p]; }
+};
+
+// Smallest value that at least k of the n values do not exceed (all ones if there are fewer).
+__device__ __forceinline__ uint32_t beam_kth(const uint32_t* v, uint32_t n, uint32_t k) {
+  uint32_t lo = 0u, hi = ~0u;
+  while (lo < hi) {
+    const uint32_t mid = lo + (hi - lo) / 2u;
+    uint32_t count = 0u;
+    for (uint32_t from = 0; from < n; from += kBlock) {
+      const uint32_t x = from + threadIdx.x;
+      count += (uint32_t)__builtin_popcountll(__builtin_amdgcn_ballot_w64(x < n && v[x < n ? x : 0u] <= mid));
+    }
+    if (count >= k) hi = mid; else lo = mid + 1u;
+  }
+  return lo;
+}
+// The places of the values not above `most`, in ascending order, up to `room` of them.
+__device__ __forceinline__ uint32_t beam_gather(const uint32_t* v, uint32_t n, uint32_t most, uint32_t room,
+                                                uint16_t* list) {
+  uint32_t got = 0u;
+  for (uint32_t from = 0; from < n && got < room; from += kBlock) {
+    const uint32_t x = from + threadIdx.x;
+    const bool take = x < n && v[x < n ? x : 0u] <= most;
+    const uint64_t set = __builtin_amdgcn_ballot_w64(take);
+    const uint32_t at = got + __builtin_amdgcn_mbcnt_hi((uint32_t)(set >> 32),
+                                                        __builtin_amdgcn_mbcnt_lo((uint32_t)set, 0u));
+    if (take && at < room) list[at] = (uint16_t)x;
+    got += (uint32_t)__builtin_popcountll(set);
+  }
+  return got < room ? got : room;
+}
+
+template <uint32_t kWidth>
+__global__ void __launch_bounds__(kBlock)
+    __attribute__((amdgpu_waves_per_eu(kWidth <= 4u ? 3 : kWidth <= 16u ? 2 : 1)))
+beam_kernel(themis_batch_t b, BeamLayout l, uint8_t* __restrict__ ws, unsigned long long call) {
+  constexpr uint32_t kCap = LayoutRing::kCap;
+  __shared__ __attribute__((aligned(16))) uint8_t block[kCap * 128u + LayoutRing::kTailBytes];
+  __shared__ SharedTable tab;
+  __shared__ BeamLds<kWidth> k;
+  const uint64_t i = blockIdx.x;
+  const uint32_t lane = threadIdx.x;
+  uint32_t* live_p = (uint32_t*)(ws + l.off_live) + i;
+  Scenario s = load_scenario(b, i);
+  const bool scf = b.intra_policy[i] == THEMIS_INTRA_SCF;
+  const double S = b.size_bytes[i];
+  if (!s.valid || !finite_positive(S) || s.C > kCap) {
+    if (lane == 0u) *live_p = 0u;
+    return;
+  }
+  const uint32_t D = (uint32_t)s.D, C = s.C, F = factorial_u32(D);
+  const bool both = s.ctype == THEMIS_COLL_ALL_REDUCE;
+  FastOut none;
+  none.queue_order = nullptr;
+  none.slots = b.max_chunks;
+  uint32_t live = 1u;   // the empty schedule
+  if (lane == 0u) k.rank[0] = 0u;
+  for (uint32_t m = 1; m <= C; ++m) {
+    const uint32_t half = m & 1u;
+    const double chunk = beam_partial_size(S, C, m) / (double)m;
+    s.C = m;
+    const uint32_t nc = live * F, kept = nc < l.width ? nc : l.width;
+    for (uint32_t x = lane; x < nc; x += kBlock) { k.lb[x] = 0u; k.tb[x] = ~0u; }
+    const SharedSetup setup = shared_table(s, chunk, scf, tab);
+    __syncthreads();
+    if (!setup.ok) {
+      if (lane == 0u) {   // from the start, as beam_init_kernel leaves it
+        *live_p = 1u;
+        (ws + l.off_rank[0])[i * l.width] = 0u;
+        atomicMax(&g_marked_call, call);
+      }
+      return;
+    }
+    const double longest = (double)m * setup.t_max * (1.0 + 1e-9);
+    const bool prune = nc > kBlock && longest + 0.25 * setup.t_min > longest && longest < inf64() &&
+                       setup.t_min > 1e-30;
+    if (prune) {
+      if (lane < live) {
+        SharedBound lb;
+        for (uint32_t c = 0; c + 1u < m; ++c) lb.add(tab, tab.rank_of[k.digits[half][lane][c] & 31u], both);
+        k.prefix(lane) = lb;
+      }
+      __syncthreads();
+      for (uint32_t x = lane; x < nc; x += kBlock) {
+        SharedBound lb = k.prefix(x / F);
+        lb.add(tab, tab.rank_of[x % F], both);
+        k.lb[x] = __float_as_uint(fmaxf(lb.value(both), 0.0f));
+      }
+    }
+    __syncthreads();
+    // at most 64 with the lowest bounds (none of them, if more are equal: then any)
+    uint32_t most = 0xfffffffeu;
+    if (prune) {
+      const uint32_t beyond = beam_kth(k.lb, nc, kBlock + 1u);
+      most = beyond > 0u && beam_kth(k.lb, nc, 1u) < beyond ? beyond - 1u : most;
+    }
+    bool bad = false;
+    for (uint32_t round = 0; round <= nc; ++round) {
+      const uint32_t got = beam_gather(k.lb, nc, most, kBlock, k.list);
+      if (got == 0u) break;
+      __syncthreads();
+      if (lane < got) {
+        const uint32_t x = k.list[lane], p = x / F, j = x - p * F;
+        const uint8_t* row = k.digits[half][p];
+        LaneLds lds;
+        lds.base = block + LayoutRing::lane_term_rec(lane);
+        lds.aux = block + kCap * 128u + (LayoutRing::lane_term_tail(lane) - LayoutRing::kRecBytes);
+        const SharedModel model{tab, s.ctype == THEMIS_COLL_REDUCE_SCATTER,
+                                s.ctype == THEMIS_COLL_ALL_GATHER, setup.t_min};
+        for (uint32_t c = 0; c < m; ++c)
+          *LayoutRing::rec(lds, c) =
+              (uint16_t)((uint32_t)tab.rank_of[(c + 1u == m ? j : (uint32_t)row[c]) & 31u] << 3);
+        const FastResult r =
+            ring_loop<true, kNoQueueOrder, false, false, true>(s, model, lds, none, (const uint8_t*)tab.step);
+        bad = bad || !r.ok;
+        k.time[x] = r.t_done;
+        // (a NaN or negative time is not possible where r.ok)
+        k.tb[x] = __float_as_uint((float)r.t_done * (1.0f + 1e-6f));
+        k.lb[x] = ~0u;
+      }
+      __syncthreads();
+      if (prune) {
+        const uint32_t limit = beam_kth(k.tb, nc, kept);
+        most = limit < 0xfffffffeu ? limit : 0xfffffffeu;
+      }
+    }
+    // a simulation that gave up: the scenario has no answer
+    if (__builtin_amdgcn_ballot_w64(bad) != 0ull) { live = 0u; break; }
+    // the candidates that may be among the kept ones, then each one's place
+    const uint32_t last = beam_kth(k.tb, nc, kept);
+    const uint32_t left = beam_gather(k.tb, nc, last, nc, k.list);
+    __syncthreads();
+    for (uint32_t a = lane; a < left; a += kBlock) {
+      const uint32_t x = k.list[a], px = x / F, jx = x - px * F;
+      const uint32_t kx = jx * kBeamMaxWidth + k.rank[px];
+      const double tx = k.time[x];
+      uint32_t before = 0u;
+      for (uint32_t o = 0; o < left; ++o) {
+        const uint32_t y = k.list[o], py = y / F, jy = y - py * F;
+        const double ty = k.time[y];
+        before += (ty < tx || (ty == tx && jy * kBeamMaxWidth + k.rank[py] < kx)) ? 1u : 0u;
+      }
+      if (before < kept) {
+        k.key[before] = (uint16_t)kx;
+        k.parent[before] = (uint8_t)px;
+        if (before == 0u) ((double*)(ws + l.off_best))[i] = tx;
+      }
+    }
+    __syncthreads();
+    if (lane < kept) {
+      uint32_t smaller = 0u;
+      for (uint32_t q = 0; q < kept; ++q) smaller += k.key[q] < k.key[lane] ? 1u : 0u;
+      k.rank[lane] = (uint8_t)smaller;
+    }
+    for (uint32_t q = 0; q < kept; ++q)
+      if (lane < m)   // (a lane per chunk: at most 64)
+        k.digits[half ^ 1u][q][lane] =
+            lane + 1u < m ? k.digits[half][k.parent[q]][lane] : (uint8_t)(k.key[q] / kBeamMaxWidth);
+    live = kept;
+    __syncthreads();
+  }
+  if (live != 0u && lane < C) (ws + l.off_digits[C & 1u])[i * l.width * l.mc + lane] = k.digits[(C & 1u) ^ 1u][0][lane];
+  if (lane == 0u) *live_p = live != 0u ? kBeamDone : 0u;
 }
 
 // The better of the beam's best schedule and the greedy plan (the beam's on
@@ -2521,14 +2730,33 @@ int themis_beam_search_batch(const themis_batch_t* batch, uint32_t width, double
   const bool fix = batch->fixed_delay != nullptr;
   Launcher go(stream);
   const unsigned per_scenario = (unsigned)((batch->n + 255) / 256);
-  go(beam_init_kernel, per_scenario, 256, *batch, l, ws);
+  // A wavefront per scenario works its candidates off 64 at a time; up to width 4
+  // the bounds make that one round as a rule.  Few scenarios are faster with all
+  // candidates at once: up to two turns of the per-order tables (two wavefronts
+  // per CU), which may have scenarios left to them after it (40 4-D scenarios of
+  // other NPU counts, width 4, 24 chunks: 9.0 against 11.5 ms), and for a wider
+  // beam, which takes several rounds, up to what the GPU holds (20 4-D
+  // scenarios, width 16, 48 chunks: 27 against 38 ms; 800, 64 chunks: 55 either way).
+  const bool by_scenario =
+      blocks_for(lanes) > (width <= 4u ? 4u * 256u : 4u * 256u * (unsigned)LayoutRing::kWavesPerSimd);
   int half = 0;
-  for (uint32_t m = 1; m <= batch->max_chunks; ++m) {
-    go(fix ? beam_eval_kernel<false, true> : beam_eval_kernel<false, false>, blocks_for(lanes),
-       kBlock, *batch, l, ws, m, half);
-    go(beam_eval_kernel<true, true>, blocks_for(lanes), kBlock, *batch, l, ws, m, half);
-    go(beam_select_kernel, (unsigned)batch->n, kBlock, *batch, l, ws, m, half);
-    half ^= 1;
+  if (by_scenario) {
+    const unsigned long long call = next_call_number();
+    // (the width says how much LDS a wavefront takes, and so how many a CU holds)
+    go(width <= 4u ? beam_kernel<4> : width <= 16u ? beam_kernel<16> : beam_kernel<kBeamMaxWidth>,
+       (unsigned)batch->n, kBlock, *batch, l, ws, call);
+    for (uint32_t m = 1; m <= batch->max_chunks; ++m, half ^= 1) {
+      go(beam_eval_kernel<true, true, true>, blocks_for(lanes), kBlock, *batch, l, ws, m, half, call);
+      go(beam_select_kernel<true>, (unsigned)batch->n, kBlock, *batch, l, ws, m, half, call);
+    }
+  } else {
+    go(beam_init_kernel, per_scenario, 256, *batch, l, ws);
+    for (uint32_t m = 1; m <= batch->max_chunks; ++m, half ^= 1) {
+      go(fix ? beam_eval_kernel<false, true, false> : beam_eval_kernel<false, false, false>,
+         blocks_for(lanes), kBlock, *batch, l, ws, m, half, 0ull);
+      go(beam_eval_kernel<true, true, false>, blocks_for(lanes), kBlock, *batch, l, ws, m, half, 0ull);
+      go(beam_select_kernel<false>, (unsigned)batch->n, kBlock, *batch, l, ws, m, half, 0ull);
+    }
   }
   go(beam_finish_kernel, per_scenario, 256, *batch, l, (const uint8_t*)ws, best_t, best_orders);
   return go.status();

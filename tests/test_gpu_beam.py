@@ -47,6 +47,32 @@ def test_beam_search_on_tie_rich_networks(gpu, oracle):
         _run(gpu, oracle, b, width)
 
 
+@pytest.mark.parametrize("width,n,chunks", [(4, 40, 12), (4, 700, 9), (1, 2800, 5), (16, 24, 9), (16, 520, 4),
+                                            (5, 1700, 4), (17, 500, 4), (64, 135, 4), (2, 3, 64), (3, 950, 3)])
+@pytest.mark.parametrize("pow2", [True, False])
+def test_beam_widths_around_the_kernel_variants(gpu, oracle, width, n, chunks, pow2):
+    """The widths between which the kernel's room changes and batches on both sides
+    of the choice between the kernels, with more candidates
+    than lanes (ruled out by bounds) and fewer; all collective types, delays,
+    networks of four dimensions among the others; sizes whose halvings leave the
+    normal range (left to the per-order tables) and whose times single precision
+    does not resolve."""
+    W, rng = w(), np.random.default_rng(860 + width)
+    b = W.mixed(n, seed=861 + width, max_chunks=chunks, pow2=pow2)
+    b.chunks[:] = chunks
+    b.ndims[::2] = 4
+    b.npus[:, ::2] = 2 ** rng.integers(1, 5, (4, (n + 1) // 2)) if pow2 else rng.integers(2, 20, (4, (n + 1) // 2))
+    b.bw[:, ::2] = rng.uniform(25e9, 400e9, (4, (n + 1) // 2))
+    b.collective_type = (np.arange(n) % 3).astype(np.uint8)
+    if n > 3:
+        b.size_bytes = np.where(np.arange(n) % 8 == 5, 3e-307, b.size_bytes)
+        b.size_bytes = np.where(np.arange(n) % 8 == 6, 1e-28, b.size_bytes)
+    else:
+        b.fixed_delay = np.ascontiguousarray(rng.uniform(0, 5e-6, (4, n)))
+    t, _ = _run(gpu, oracle, b, width)
+    assert np.isfinite(t).sum() >= n // 2
+
+
 def test_a_beam_that_drops_nothing_is_the_exhaustive_search(gpu, oracle):
     import torch
     W = w()
