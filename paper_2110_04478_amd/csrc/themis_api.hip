@@ -1638,16 +1638,18 @@ search_kernel(themis_batch_t b, uint64_t max_assign, uint32_t parts, double* __r
 // once if nothing is marked (see g_marked_call).
 __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(LayoutTableWide::kWavesPerSimd)))
 search_table_kernel(themis_batch_t b, uint64_t max_assign, double* __restrict__ times,
-                    unsigned long long call) {
+                    const double* __restrict__ best_t, unsigned long long call) {
   using L = LayoutTableWide;
   __shared__ uint32_t lds_block[L::kLaneWords * kBlock];
   if (nothing_marked(call)) return;
   const uint64_t total = b.n * max_assign;
   for (uint64_t e = (uint64_t)blockIdx.x * kBlock + threadIdx.x; e < total;
        e += (uint64_t)gridDim.x * kBlock) {
-    if (!is_left_to_generic(times[e])) continue;
     const uint64_t i = e / max_assign;
     const uint64_t a = e - i * max_assign;
+    // (search_kernel writes all of a row only where it leaves the scenario; the
+    // others hold whatever the caller's memory held, a mark's bits for instance)
+    if (!is_left_to_generic(best_t[i]) || !is_left_to_generic(times[e])) continue;
     Scenario s = load_scenario(b, i);
     const bool scf = b.intra_policy[i] == THEMIS_INTRA_SCF;
     const double chunk = b.size_bytes[i] / (double)s.C;
@@ -2693,7 +2695,8 @@ int themis_search_batch(const themis_batch_t* batch, uint64_t max_assignments, d
                     : (wide ? search_kernel<64, uint64_t> : search_kernel<64, uint32_t>);
   go(search, (unsigned)(batch->n * parts), kBlock, *batch, max_assignments, (uint32_t)parts, times, best_t,
      best_orders, call);
-  go(search_table_kernel, follow_up_blocks(evals), kBlock, *batch, max_assignments, times, call);
+  go(search_table_kernel, follow_up_blocks(evals), kBlock, *batch, max_assignments, times,
+     (const double*)best_t, call);
   go(search_finish_kernel, (unsigned)(batch->n < room ? batch->n : room), kBlock, *batch, max_assignments,
      (uint32_t)parts, (const double*)times, best_t, best_orders, call);
   return go.status();

@@ -130,3 +130,33 @@ def test_sweeps_whose_thresholds_share_plans(gpu, oracle, n, max_chunks, n_thr, 
     keep = np.ascontiguousarray(thr[:, few]) if per_scenario else thr
     want = oracle.sweep(b.take(few), keep, mask, thr_per_scenario=per_scenario, threads=8)
     assert_close("sweep", out.cpu().numpy()[few], want)
+
+
+@pytest.mark.parametrize("n", [9, 7000])
+def test_search_of_a_workspace_that_holds_marks(gpu, oracle, n):
+    """Every 64th scenario is left to the per-order tables (halvings below the
+    normal range), some are not valid, and the caller's workspace happens to hold
+    the bits with which the first kernel marks what it leaves: only rows that it
+    has written may be taken for marked ones."""
+    import torch
+    from test_gpu_parity import assert_close
+    W, rng, C, bound = w(), np.random.default_rng(870), 3, 216
+    P = rng.integers(2, 20, (n, 3))
+    size = np.floor(rng.uniform(2 ** 20, 2 ** 30, n))
+    size[5::7] = 0.0
+    size[::64] = 1e-308 * C * P[::64].prod(axis=1)
+    b = W.make_batch([3] * n, P.tolist(), rng.uniform(25e9, 400e9, (n, 3)).tolist(), size, C, 1,
+                     rng.integers(0, 2, n), 0.0, max_chunks=C)
+    mark = 0x7ff8a5a55a5a0001
+    ws = torch.full((gpu.themis_search_workspace_bytes(n, bound) // 8,), mark, dtype=torch.int64, device="cuda")
+    got_t, got_o = gpu.themis_search_batch(gpu.to_device(b), bound, ws)
+    torch.cuda.synchronize()
+    few = np.arange(n) if n < 100 else np.unique(np.concatenate([np.arange(0, n, 64), rng.permutation(n)[:60]]))
+    want_t, want_o = oracle.search_batch(b.take(few), bound, threads=8)
+    assert_close("best_t", got_t.cpu().numpy()[few], want_t)
+    assert np.array_equal(got_o.cpu().numpy()[few], want_o)
+    # (the first words of a row hold what the wavefronts of a scenario found)
+    rows = ws.view(n, bound).cpu().numpy()[:, 2 * -(-bound // 64):]
+    kept = (rows == mark).all(axis=1)
+    left = np.arange(n) % 64 == 0
+    assert kept[~left].all() and not kept[left].any()
