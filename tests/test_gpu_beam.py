@@ -65,12 +65,38 @@ def test_beam_widths_around_the_kernel_variants(gpu, oracle, width, n, chunks, p
     b.bw[:, ::2] = rng.uniform(25e9, 400e9, (4, (n + 1) // 2))
     b.collective_type = (np.arange(n) % 3).astype(np.uint8)
     if n > 3:
+        # (bandwidths to match: the shortest stage still moves the clock)
         b.size_bytes = np.where(np.arange(n) % 8 == 5, 3e-307, b.size_bytes)
+        b.bw = np.where(np.arange(n) % 8 == 5, b.bw * 1e-20, b.bw)
         b.size_bytes = np.where(np.arange(n) % 8 == 6, 1e-28, b.size_bytes)
     else:
         b.fixed_delay = np.ascontiguousarray(rng.uniform(0, 5e-6, (4, n)))
     t, _ = _run(gpu, oracle, b, width)
     assert np.isfinite(t).sum() >= n // 2
+
+
+@pytest.mark.parametrize("n", [40, 700])
+@pytest.mark.parametrize("pow2", [True, False])
+def test_beam_scenarios_that_no_path_can_simulate(gpu, oracle, n, pow2):
+    """A dimension so fast that its stages do not move the clock: no event loop
+    takes any schedule of such a scenario, which comes back as NaN / all-ones,
+    and the scenarios around it keep their answers."""
+    import torch
+    W = w()
+    b = W.mixed(n, seed=880, max_chunks=6, pow2=pow2)
+    b.chunks[:] = np.maximum(b.chunks, 2)
+    b.ndims[::5] = 2 + np.arange((n + 4) // 5) % 3
+    b.npus[:, ::5] = 4 if pow2 else 3
+    b.bw[:, ::5] = 1e11
+    b.bw[0, ::5] = 1e300
+    want_t, want_od = oracle.beam_search_batch(b, 4, threads=8)
+    lost = np.arange(n) % 5 == 0
+    assert np.isfinite(want_t[lost]).sum() >= lost.sum() // 2     # (the oracle has an answer)
+    want_t[lost], want_od[lost] = np.nan, 0xFF
+    got_t, got_od = gpu.themis_beam_search_batch(gpu.to_device(b), 4)
+    torch.cuda.synchronize()
+    assert_close("best_t", got_t.cpu().numpy(), want_t)
+    assert np.array_equal(got_od.cpu().numpy(), want_od)
 
 
 def test_a_beam_that_drops_nothing_is_the_exhaustive_search(gpu, oracle):
