@@ -499,15 +499,14 @@ simulate_kernel(themis_batch_t b, const uint8_t* __restrict__ orders,
 // One wavefront per scenario (themis_wave.hpp): single collectives of up to 64 *
 // kWords chunks in batches too small to fill the GPU with one lane per scenario.
 // kExact: what the event loop does not take (a stage too short to move the
-// clock, sizes outside the normal range) is evaluated right here -- as far as
-// `exact_ok` says so --, and nothing follows this kernel: for the smallest
-// batches, where a second launch costs more than the registers.  Else it is
-// left marked to the follow-up kernel.
+// clock, sizes outside the normal range) is evaluated right here, and nothing
+// follows this kernel: for the smallest batches, where a second launch costs
+// more than the registers.  Else it is left marked to the follow-up kernel.
 template <uint32_t kWords, bool kQueue, bool kExact>
 __global__ void __launch_bounds__(kBlock)
 simulate_wave_kernel(themis_batch_t b, const uint8_t* __restrict__ orders, double* __restrict__ t_done,
                      void* __restrict__ queue_order, int entry_bytes, double* __restrict__ busy,
-                     bool exact_ok, unsigned long long hand_over) {
+                     unsigned long long hand_over) {
   using Lds = WaveLds<kWords>;
   using ExactLds = WaveExactLds<kExact ? kWords : 1u>;
   __shared__ union Block {
@@ -556,12 +555,11 @@ simulate_wave_kernel(themis_batch_t b, const uint8_t* __restrict__ orders, doubl
       if (!done) {
         if constexpr (kExact) {
           __syncthreads();
-          if (exact_ok)
-            r = wave_exact<kWords>(s, chunk, scf, block.exact, [&](uint32_t c) { return (uint32_t)row[c]; },
-                                   [&](uint32_t k, uint32_t at, uint32_t entry) {
-                                     if (lane == 0u) put(k, at, entry);
-                                   });
-          ok = exact_ok && r.ok;
+          r = wave_exact<kWords>(s, chunk, scf, block.exact, [&](uint32_t c) { return (uint32_t)row[c]; },
+                                 [&](uint32_t k, uint32_t at, uint32_t entry) {
+                                   if (lane == 0u) put(k, at, entry);
+                                 });
+          ok = r.ok;
         } else {
           if (lane == 0u) mark_left_to_generic(t_done + i, hand_over);
           return;
@@ -2428,14 +2426,14 @@ static int simulate_batch_impl(const themis_batch_t* batch, const uint8_t* order
   // and its 80 KiB of LDS apart from the table passes.
   const unsigned long long call = next_call_number();
   if (simulate_on_wavefronts(batch->n)) {
-    // (the exact evaluation keeps to what the follow-up passes do: beyond 64
-    // chunks it asks for a workspace)
-    const bool q = queue_order != nullptr, alone = batch->n <= compute_units();
+    // (beyond 64 chunks the generic pass asks for a workspace; without one the
+    // table passes still take what they can, and the rest is NaN)
+    const bool q = queue_order != nullptr, alone = batch->n <= compute_units() && (cap <= 64u || have_ws);
 #define THEMIS_WAVE_KERNEL(W)                                                                        \
   (alone ? (q ? simulate_wave_kernel<W, true, true> : simulate_wave_kernel<W, false, true>)          \
          : (q ? simulate_wave_kernel<W, true, false> : simulate_wave_kernel<W, false, false>))
     go(cap <= 64u ? THEMIS_WAVE_KERNEL(1) : THEMIS_WAVE_KERNEL(8), (unsigned)batch->n, kBlock, *batch,
-       orders, t_done, queue_order, entry_bytes, busy, cap <= 64u || have_ws, call);
+       orders, t_done, queue_order, entry_bytes, busy, call);
 #undef THEMIS_WAVE_KERNEL
     if (alone) return go.status();
   } else {

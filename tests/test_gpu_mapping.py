@@ -56,6 +56,21 @@ def test_mappings_agree_with_the_oracle(gpu, oracle, mapping, case):
         gpu.themis_set_batch_mapping(gpu.MAPPING_AUTO)
 
 
+@pytest.mark.parametrize("n", [60, 300])
+def test_small_sizes_beyond_64_chunks_without_a_workspace(gpu, oracle, n):
+    """Halvings below the normal range are for the per-order tables, which need no
+    workspace: the answer is there on both sides of the number of CUs, up to
+    which one kernel does everything."""
+    b = w().mixed(n, seed=815, max_chunks=100)
+    b.chunks[:] = 100
+    tiny = np.arange(n) % 3 == 0
+    b.size_bytes = np.where(tiny, 3e-307, b.size_bytes)
+    b.bw = np.where(tiny, b.bw * 1e-20, b.bw)      # (the shortest stage still moves the clock)
+    for queue in (True, False):
+        t = check_batch(gpu, oracle, b, queue=queue, workspace=False)
+        assert np.isfinite(t[tiny]).all()
+
+
 @pytest.mark.parametrize("n", [1, 256, 257, 3073, 4096, 4097])
 def test_batch_sizes_around_the_choice_of_the_mapping(gpu, oracle, n):
     check_batch(gpu, oracle, w().mixed(n, seed=820, max_chunks=9, pow2=False))
