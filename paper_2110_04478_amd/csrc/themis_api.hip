@@ -2310,6 +2310,33 @@ static bool sweep_on_wavefronts(uint64_t evaluations) {
   return sweep_mapping.load(std::memory_order_relaxed) == THEMIS_MAPPING_AUTO && evaluations <= kWaveSimulate;
 }
 
+// A wavefront per scenario for the beam search (beam_kernel), or a lane per
+// candidate, step by step?  A wavefront works its candidates off 64 at a time,
+// up to width 4 in one round as a rule (bounds); eight of them fit a CU up to
+// width 4, six up to 16.
+//   - Few scenarios are faster with all candidates at once: up to two turns of
+//     the per-order tables (two wavefronts per CU), which may have scenarios left
+//     to them after it (40 4-D scenarios of other NPU counts, width 4, 24 chunks:
+//     9.0 against 11.5 ms), and for a wider beam, which takes several rounds, up
+//     to what the GPU holds (20 4-D scenarios, width 16, 48 chunks: 27 against
+//     38 ms; 800, 64 chunks: 55 either way).
+//   - Narrow beams leave lanes idle (24 candidates at width 1 on four dimensions,
+//     6 on three), where a lane per candidate packs them: width 1 is 1.1 to 2.3
+//     times slower by scenario on three and four dimensions of power-of-two NPU
+//     counts (24 chunks, 4,096 scenarios: 4.2 against 2.8 ms), widths 2 and 3 are
+//     0.65 to 0.98 of it in one turn and up to 1.3 beyond it on four dimensions.
+//   - Width 4 on four dimensions, 24 chunks: 700 to 900 scenarios 1.06 to 1.10,
+//     1,100 to 2,048 0.87 to 1.02, 2,100 to 2,700 (a second turn, nearly empty)
+//     1.06 to 1.09, 4,096 0.94; widths 5 to 8 0.80 in a full turn, up to 1.14 off
+//     one; width 12 0.66 to 0.90.  On two and three dimensions all of these are
+//     0.2 to 0.7, and on other NPU counts of up to three 0.1 to 0.3, so they stay.
+static bool beam_by_scenario(uint64_t n, uint64_t lane_waves, uint32_t width) {
+  const uint64_t cus = compute_units() ? compute_units() : 256u;
+  if (width == 1u) return false;
+  if (width > 4u) return lane_waves > 4u * (uint64_t)LayoutRing::kWavesPerSimd * cus;
+  return lane_waves > 4u * cus && (width == 4u ? n >= 4u * cus : n <= 8u * cus);
+}
+
 // Does themis_sweep look for thresholds that share a plan?  From four
 // thresholds on, and where the sweep is more than one turn of the wavefronts
 // that are resident at once: a smaller one takes the time of one wavefront
@@ -2731,15 +2758,7 @@ int themis_beam_search_batch(const themis_batch_t* batch, uint32_t width, double
   const bool fix = batch->fixed_delay != nullptr;
   Launcher go(stream);
   const unsigned per_scenario = (unsigned)((batch->n + 255) / 256);
-  // A wavefront per scenario works its candidates off 64 at a time; up to width 4
-  // the bounds make that one round as a rule.  Few scenarios are faster with all
-  // candidates at once: up to two turns of the per-order tables (two wavefronts
-  // per CU), which may have scenarios left to them after it (40 4-D scenarios of
-  // other NPU counts, width 4, 24 chunks: 9.0 against 11.5 ms), and for a wider
-  // beam, which takes several rounds, up to what the GPU holds (20 4-D
-  // scenarios, width 16, 48 chunks: 27 against 38 ms; 800, 64 chunks: 55 either way).
-  const bool by_scenario =
-      blocks_for(lanes) > (width <= 4u ? 4u * 256u : 4u * 256u * (unsigned)LayoutRing::kWavesPerSimd);
+  const bool by_scenario = beam_by_scenario(batch->n, blocks_for(lanes), width);
   int half = 0;
   if (by_scenario) {
     const unsigned long long call = next_call_number();

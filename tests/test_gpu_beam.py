@@ -48,7 +48,8 @@ def test_beam_search_on_tie_rich_networks(gpu, oracle):
 
 
 @pytest.mark.parametrize("width,n,chunks", [(4, 40, 12), (4, 700, 9), (1, 2800, 5), (16, 24, 9), (16, 520, 4),
-                                            (5, 1700, 4), (17, 500, 4), (64, 135, 4), (2, 3, 64), (3, 950, 3)])
+                                            (5, 1700, 4), (17, 500, 4), (64, 135, 4), (2, 3, 64), (3, 950, 3),
+                                            (4, 1023, 3), (4, 1024, 6), (2, 2048, 4), (2, 2049, 3)])
 @pytest.mark.parametrize("pow2", [True, False])
 def test_beam_widths_around_the_kernel_variants(gpu, oracle, width, n, chunks, pow2):
     """The widths between which the kernel's room changes and batches on both sides
@@ -75,7 +76,7 @@ def test_beam_widths_around_the_kernel_variants(gpu, oracle, width, n, chunks, p
     assert np.isfinite(t).sum() >= n // 2
 
 
-@pytest.mark.parametrize("n", [40, 700])
+@pytest.mark.parametrize("n", [40, 1100])
 @pytest.mark.parametrize("pow2", [True, False])
 def test_beam_scenarios_that_no_path_can_simulate(gpu, oracle, n, pow2):
     """A dimension so fast that its stages do not move the clock: no event loop
