@@ -963,6 +963,7 @@ struct SweepJobs {
 };
 constexpr uint32_t kSweepJobsMaxThr = 32;
 constexpr size_t kSweepJobsHeader = 64;   // the counter
+constexpr uint32_t kSweepPlansBlock = 8u * kBlock;
 
 __global__ void sweep_clear_kernel(uint32_t* count) { *count = 0u; }
 
@@ -972,19 +973,24 @@ __global__ void sweep_clear_kernel(uint32_t* count) { *count = 0u; }
 // known by which of its chunks deviate from the baseline order: as long as two
 // of them agree their loads are equal, and the order of the next chunk follows
 // from the loads and that one decision.
-// 64 chunks, eight thresholds: 60 us for 65,536 scenarios.
-__global__ void __launch_bounds__(kBlock)
+// The places in the list are handed out by one counter, and an atomic on it
+// takes some 13 ns however many wait.  With one per wavefront that was the time
+// of the kernel on few chunks, so a workgroup is eight wavefronts (whole sweep,
+// 65,536 scenarios, eight thresholds: 2-D, 4 chunks 158 -> 78 us, 16 chunks
+// 309 -> 236 us; 4-D, 64 chunks 1,323 -> 1,279 us).
+__global__ void __launch_bounds__(kSweepPlansBlock)
 sweep_plans_kernel(themis_batch_t b, int n_thr, uint32_t width, const double* __restrict__ thr,
                    int thr_per_scenario, unsigned policy_mask, int n_pol, double* __restrict__ t_done,
                    SweepJob* __restrict__ list, uint32_t* __restrict__ count) {
   static_assert(kBlock == kPlanOrders, "one table entry per lane");
   __shared__ __attribute__((aligned(16))) uint32_t plan_orders[kPlanOrders * kPlanOrderWords];
-  plan_order_entry(threadIdx.x, plan_orders + kPlanOrderWords * threadIdx.x);
+  __shared__ uint32_t places[kSweepPlansBlock / kBlock];   // jobs of each wavefront, then where they go
+  if (threadIdx.x < kPlanOrders) plan_order_entry(threadIdx.x, plan_orders + kPlanOrderWords * threadIdx.x);
   __syncthreads();
-  const uint32_t lane = threadIdx.x, first = lane & ~(width - 1u);
+  const uint32_t lane = lane_id(), wave = threadIdx.x / kBlock, first = lane & ~(width - 1u);
   const uint32_t all = width == 32u ? ~0u : (1u << width) - 1u;
   const uint32_t a = lane - first;
-  const uint64_t i = ((uint64_t)blockIdx.x * kBlock + lane) / width;
+  const uint64_t i = ((uint64_t)blockIdx.x * kSweepPlansBlock + threadIdx.x) / width;
   const bool exists = i < b.n && a < (uint32_t)n_thr;
   bool valid = false;
   uint32_t differ = 0u;
@@ -1019,11 +1025,21 @@ sweep_plans_kernel(themis_batch_t b, int n_thr, uint32_t width, const double* __
   const uint32_t same = ~differ & usable;
   const bool job = valid && (same & ((1u << a) - 1u)) == 0u;
   const uint64_t m = __builtin_amdgcn_ballot_w64(job);
-  uint32_t base = 0u;
-  if (m != 0ull && lane == (uint32_t)__builtin_ctzll(m)) base = atomicAdd(count, (uint32_t)__builtin_popcountll(m));
-  if (m != 0ull) base = (uint32_t)__builtin_amdgcn_readlane((int)base, (int)__builtin_ctzll(m));
+  if (lane == 0u) places[wave] = (uint32_t)__builtin_popcountll(m);
+  __syncthreads();
+  if (threadIdx.x == 0u) {
+    uint32_t sum = 0u;
+    for (uint32_t w = 0; w < kSweepPlansBlock / kBlock; ++w) {
+      const uint32_t jobs = places[w];
+      places[w] = sum;
+      sum += jobs;
+    }
+    const uint32_t base = sum != 0u ? atomicAdd(count, sum) : 0u;
+    for (uint32_t w = 0; w < kSweepPlansBlock / kBlock; ++w) places[w] += base;
+  }
+  __syncthreads();
   if (job) {
-    const uint32_t place = base + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
+    const uint32_t place = places[wave] + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
                                                             __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
     list[place] = SweepJob{(uint32_t)i, same};
   }
@@ -2340,10 +2356,13 @@ static bool beam_by_scenario(uint64_t n, uint64_t lane_waves, uint32_t width) {
 // Does themis_sweep look for thresholds that share a plan?  From four
 // thresholds on, and where the sweep is more than one turn of the wavefronts
 // that are resident at once: a smaller one takes the time of one wavefront
-// either way.
+// either way.  And where there is enough to simulate for the launches it takes
+// (2-D, eight thresholds: 16,384 scenarios of one chunk 27 against 25 us without,
+// of two 30 against 35; 65,536 of one 47 against 60).
 static bool sweep_shares_plans(uint64_t n, uint32_t max_chunks, int n_thr, unsigned policy_mask) {
   if (n_thr < 4 || n_thr > (int)kSweepJobsMaxThr || (policy_mask & ~THEMIS_SWEEP_BASELINE) == 0u || n >= 0xffffffffull)
     return false;
+  if (n * max_chunks < 32768u) return false;
   const uint32_t cap = layout_capacity(max_chunks);
   const bool quad = sweep_mapping_is_quad(cap);
   if (!quad && cap > 128u) return false;
@@ -2604,8 +2623,8 @@ int themis_sweep_with_scratch(const themis_batch_t* batch, int n_thr, const doub
     uint32_t width = 1u;
     while (width < (uint32_t)n_thr) width *= 2u;
     go(sweep_clear_kernel, 1u, 1u, count);
-    go(sweep_plans_kernel, blocks_for(batch->n * width), kBlock, *batch, n_thr, width, thr, thr_per_scenario,
-       policy_mask, n_pol, t_done, list, count);
+    go(sweep_plans_kernel, (unsigned)((batch->n * width + kSweepPlansBlock - 1u) / kSweepPlansBlock),
+       kSweepPlansBlock, *batch, n_thr, width, thr, thr_per_scenario, policy_mask, n_pol, t_done, list, count);
     // (as many workgroups as there would be jobs if all plans differed)
     const uint64_t most = (batch->n * (uint64_t)n_thr + group - 1u) / group * (uint64_t)(n_pol - (base ? 1 : 0));
 #define THEMIS_SWEEP_KERNEL(K) \

@@ -120,6 +120,7 @@ def test_searches_whose_times_single_precision_does_not_resolve(gpu, oracle):
                          [(16001, 9, 8, 7, False, True), (15000, 20, 5, 6, True, False),
                           (9000, 64, 32, 7, False, True), (5003, 70, 8, 7, False, True),
                           (2700, 257, 8, 5, False, True), (6000, 3, 8, 2, True, True),
+                          (17003, 2, 8, 7, True, False), (16385, 2, 8, 7, False, True),
                           (100, 64, 8, 7, False, False), (3, 512, 8, 7, True, True)])
 def test_sweeps_whose_thresholds_share_plans(gpu, oracle, n, max_chunks, n_thr, mask, per_scenario, pow2):
     """themis_sweep where it looks for thresholds that give the same plan (from
