@@ -1067,9 +1067,12 @@ __device__ __forceinline__ SweepSlot sweep_job_slot(const SweepJobs& jobs, uint6
         ((policy_mask & THEMIS_SWEEP_BASELINE) ? 1u : 0u) + p;
   return r;
 }
+// kJobs as in sweep_kernel: the passes below are compiled apart for it, the
+// choice at run time cost them 2 to 6 %.
+template <bool kJobs>
 __device__ __forceinline__ uint64_t sweep_evaluations(const themis_batch_t& b, const SweepJobs& jobs, int n_thr,
                                                       unsigned policy_mask, int n_pol) {
-  if (!jobs.list) return b.n * (uint64_t)n_thr * (uint64_t)n_pol;
+  if (!kJobs) return b.n * (uint64_t)n_thr * (uint64_t)n_pol;
   const bool base = (policy_mask & THEMIS_SWEEP_BASELINE) != 0u;
   return (base ? b.n : 0u) + (uint64_t)*jobs.count * (uint32_t)(n_pol - (base ? 1 : 0));
 }
@@ -1081,10 +1084,11 @@ __device__ __forceinline__ uint32_t sweep_first_valid(const themis_batch_t& b, u
     if (threshold_ok(thr_per_scenario ? thr[(size_t)a * b.n + i] : thr[a], rel)) return (uint32_t)a;
   return 0u;
 }
+template <bool kJobs>
 __device__ __forceinline__ SweepSlot sweep_slot(const themis_batch_t& b, const SweepJobs& jobs, uint64_t x,
                                                 int n_thr, const double* thr, int thr_per_scenario,
                                                 unsigned policy_mask, int n_pol) {
-  if (!jobs.list) return SweepSlot{x, 0u, true};
+  if (!kJobs) return SweepSlot{x, 0u, true};
   const bool base = (policy_mask & THEMIS_SWEEP_BASELINE) != 0u;
   const uint32_t per = (uint32_t)n_thr * (uint32_t)n_pol, themis = (uint32_t)(n_pol - (base ? 1 : 0));
   const uint64_t n_base = base ? b.n : 0u;
@@ -1101,10 +1105,10 @@ sweep_spread_kernel(themis_batch_t b, SweepJobs jobs, int n_thr, const double* _
                     int thr_per_scenario, unsigned policy_mask, int n_pol, double* __restrict__ t_done,
                     unsigned long long call) {
   if (nothing_marked(call)) return;
-  const uint64_t total = sweep_evaluations(b, jobs, n_thr, policy_mask, n_pol);
+  const uint64_t total = sweep_evaluations<true>(b, jobs, n_thr, policy_mask, n_pol);
   const uint64_t n_base = (policy_mask & THEMIS_SWEEP_BASELINE) ? b.n : 0u;
   for (uint64_t x = (uint64_t)blockIdx.x * 256u + threadIdx.x; x < total; x += (uint64_t)gridDim.x * 256u) {
-    const SweepSlot slot = sweep_slot(b, jobs, x, n_thr, thr, thr_per_scenario, policy_mask, n_pol);
+    const SweepSlot slot = sweep_slot<true>(b, jobs, x, n_thr, thr, thr_per_scenario, policy_mask, n_pol);
     const double t = t_done[slot.e];
     if (x < n_base) {
       // (the others are marked as well where the follow-up passes had to come in)
@@ -1321,17 +1325,17 @@ sweep_wave_kernel(themis_batch_t b, int n_thr, const double* __restrict__ thr, i
 
 // The generic pass of themis_sweep: the evaluations still marked (kLdsSlots
 // as in simulate_generic_pass).
-template <uint32_t kLdsSlots>
+template <uint32_t kLdsSlots, bool kJobs>
 __device__ __forceinline__ void sweep_generic_pass(
     const themis_batch_t& b, int n_thr, const double* __restrict__ thr, int thr_per_scenario,
     unsigned policy_mask, int n_pol, double* __restrict__ t_done, const SweepJobs& jobs, Workspace w, void* lds_block) {
   if (kLdsSlots) w = carve_workspace(lds_block, kBlock, kLdsSlots);
-  const uint64_t total = sweep_evaluations(b, jobs, n_thr, policy_mask, n_pol);
+  const uint64_t total = sweep_evaluations<kJobs>(b, jobs, n_thr, policy_mask, n_pol);
   const uint64_t groups = (total + kBlock - 1) / kBlock;
   for (uint64_t grp = blockIdx.x; grp < groups; grp += gridDim.x) {
     const uint64_t x = grp * kBlock + threadIdx.x;
     if (x >= total) continue;
-    const uint64_t e = sweep_slot(b, jobs, x, n_thr, thr, thr_per_scenario, policy_mask, n_pol).e;
+    const uint64_t e = sweep_slot<kJobs>(b, jobs, x, n_thr, thr, thr_per_scenario, policy_mask, n_pol).e;
     if (!is_left_to_generic(t_done[e])) continue;
     const uint64_t col = kLdsSlots ? threadIdx.x : e;
     const SweepItem it = sweep_item(b, e, n_thr, thr, thr_per_scenario, policy_mask, n_pol);
@@ -1351,31 +1355,31 @@ __device__ __forceinline__ void sweep_generic_pass(
   }
 }
 
-template <uint32_t kLdsSlots>
+template <uint32_t kLdsSlots, bool kJobs>
 __global__ void __launch_bounds__(kBlock)
 sweep_generic_kernel(themis_batch_t b, int n_thr, const double* __restrict__ thr,
                      int thr_per_scenario, unsigned policy_mask, int n_pol,
                      double* __restrict__ t_done, Workspace w, unsigned long long call, SweepJobs jobs) {
   __shared__ double lds_block[kLdsSlots ? generic_lds_bytes(kLdsSlots) / sizeof(double) : 1u];
   if (nothing_marked(call)) return;
-  sweep_generic_pass<kLdsSlots>(b, n_thr, thr, thr_per_scenario, policy_mask, n_pol, t_done, jobs, w,
+  sweep_generic_pass<kLdsSlots, kJobs>(b, n_thr, thr, thr_per_scenario, policy_mask, n_pol, t_done, jobs, w,
                                 lds_block);
 }
 
 // The same for themis_sweep: Alg. 1 with real divisions straight into the
 // chunk words, then the table-driven event loop.
-template <int kVariant>
+template <int kVariant, bool kJobs>
 __device__ __forceinline__ void sweep_table_pass(
     const themis_batch_t& b, int n_thr, const double* __restrict__ thr, int thr_per_scenario,
     unsigned policy_mask, int n_pol, double* __restrict__ t_done, const SweepJobs& jobs, void* lds_block) {
   using L = typename TableVariant<kVariant>::L;
   constexpr bool kWide = kVariant != 0;
-  const uint64_t total = sweep_evaluations(b, jobs, n_thr, policy_mask, n_pol);
+  const uint64_t total = sweep_evaluations<kJobs>(b, jobs, n_thr, policy_mask, n_pol);
   const uint64_t groups = (total + kBlock - 1) / kBlock;
   for (uint64_t grp = blockIdx.x; grp < groups; grp += gridDim.x) {
     const uint64_t x = grp * kBlock + threadIdx.x;
     if (x >= total) continue;
-    const uint64_t e = sweep_slot(b, jobs, x, n_thr, thr, thr_per_scenario, policy_mask, n_pol).e;
+    const uint64_t e = sweep_slot<kJobs>(b, jobs, x, n_thr, thr, thr_per_scenario, policy_mask, n_pol).e;
     if (!is_left_to_generic(t_done[e])) continue;
     const SweepItem it = sweep_item(b, e, n_thr, thr, thr_per_scenario, policy_mask, n_pol);
     Scenario s = load_scenario(b, it.i);
@@ -1412,7 +1416,7 @@ __device__ __forceinline__ void sweep_table_pass(
 
 // Everything that follows the LDS kernel of themis_sweep, in one launch (see
 // simulate_follow_up_kernel).
-template <int kTableA, int kTableB, uint32_t kGeneric>
+template <int kTableA, int kTableB, uint32_t kGeneric, bool kJobs>
 __global__ void __launch_bounds__(kBlock)
 sweep_follow_up_kernel(themis_batch_t b, int n_thr, const double* __restrict__ thr,
                        int thr_per_scenario, unsigned policy_mask, int n_pol,
@@ -1422,14 +1426,14 @@ sweep_follow_up_kernel(themis_batch_t b, int n_thr, const double* __restrict__ t
   __shared__ double lds_block[kBytes_ ? (kBytes_ + 7u) / 8u : 1u];
   if (nothing_marked(call)) return;
   if constexpr (kTableA >= 0)
-    sweep_table_pass<kTableA>(b, n_thr, thr, thr_per_scenario, policy_mask, n_pol, t_done, jobs, lds_block);
+    sweep_table_pass<kTableA, kJobs>(b, n_thr, thr, thr_per_scenario, policy_mask, n_pol, t_done, jobs, lds_block);
   if constexpr (kTableB >= 0) {
     __syncthreads();
-    sweep_table_pass<kTableB>(b, n_thr, thr, thr_per_scenario, policy_mask, n_pol, t_done, jobs, lds_block);
+    sweep_table_pass<kTableB, kJobs>(b, n_thr, thr, thr_per_scenario, policy_mask, n_pol, t_done, jobs, lds_block);
   }
   if constexpr (kGeneric != kNoGeneric) {
     __syncthreads();
-    sweep_generic_pass<kGeneric>(b, n_thr, thr, thr_per_scenario, policy_mask, n_pol, t_done, jobs, w,
+    sweep_generic_pass<kGeneric, kJobs>(b, n_thr, thr, thr_per_scenario, policy_mask, n_pol, t_done, jobs, w,
                                  lds_block);
   }
 }
@@ -2656,7 +2660,7 @@ int themis_sweep_with_scratch(const themis_batch_t* batch, int n_thr, const doub
   const unsigned fb = follow_up_blocks(evals);
   const Workspace ws = have_ws ? w : Workspace{};
 #define THEMIS_FOLLOW_UP(A, B, G)                                                            \
-  go(sweep_follow_up_kernel<A, B, G>, fb, kBlock, *batch, n_thr, thr, thr_per_scenario,      \
+  go(share ? sweep_follow_up_kernel<A, B, G, true> : sweep_follow_up_kernel<A, B, G, false>, fb, kBlock, *batch, n_thr, thr, thr_per_scenario,      \
      policy_mask, n_pol, t_done, ws, call, jobs)
   if (cap <= 64u) {
     const bool small = blocks_for(evals) <= 2u * compute_units();
@@ -2668,7 +2672,8 @@ int themis_sweep_with_scratch(const themis_batch_t* batch, int n_thr, const doub
       THEMIS_FOLLOW_UP(0, 1, 64u);
     } else {
       THEMIS_FOLLOW_UP(0, 1, kNoGeneric);
-      auto generic = cap <= 16u ? sweep_generic_kernel<16> : sweep_generic_kernel<64>;
+      auto generic = cap <= 16u ? (share ? sweep_generic_kernel<16, true> : sweep_generic_kernel<16, false>)
+                                : (share ? sweep_generic_kernel<64, true> : sweep_generic_kernel<64, false>);
       go(generic, fb, kBlock, *batch, n_thr, thr, thr_per_scenario, policy_mask, n_pol, t_done,
          ws, call, jobs);
     }
