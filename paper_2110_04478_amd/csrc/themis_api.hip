@@ -2357,6 +2357,13 @@ static bool beam_by_scenario(uint64_t n, uint64_t lane_waves, uint32_t width) {
   return lane_waves > 4u * cus && (width == 4u ? n >= 4u * cus : n <= 8u * cus);
 }
 
+// Lanes per scenario in sweep_plans_kernel.
+static uint32_t sweep_plans_width(int n_thr) {
+  uint32_t width = 1u;
+  while (width < (uint32_t)n_thr) width *= 2u;
+  return width;
+}
+
 // Does themis_sweep look for thresholds that share a plan?  From four
 // thresholds on, and where the sweep is more than one turn of the wavefronts
 // that are resident at once: a smaller one takes the time of one wavefront
@@ -2364,8 +2371,10 @@ static bool beam_by_scenario(uint64_t n, uint64_t lane_waves, uint32_t width) {
 // (2-D, eight thresholds: 16,384 scenarios of one chunk 27 against 25 us without,
 // of two 30 against 35; 65,536 of one 47 against 60).
 static bool sweep_shares_plans(uint64_t n, uint32_t max_chunks, int n_thr, unsigned policy_mask) {
-  if (n_thr < 4 || n_thr > (int)kSweepJobsMaxThr || (policy_mask & ~THEMIS_SWEEP_BASELINE) == 0u || n >= 0xffffffffull)
-    return false;
+  if (n_thr < 4 || n_thr > (int)kSweepJobsMaxThr || (policy_mask & ~THEMIS_SWEEP_BASELINE) == 0u) return false;
+  // sweep_plans_kernel has sweep_plans_width() lanes per scenario, of a grid of less
+  // than 2^32; so the number of jobs and the scenario's index fit 32 bits
+  if (n > 0xfffff000ull / sweep_plans_width(n_thr)) return false;
   if (n * max_chunks < 32768u) return false;
   const uint32_t cap = layout_capacity(max_chunks);
   const bool quad = sweep_mapping_is_quad(cap);
@@ -2624,8 +2633,7 @@ int themis_sweep_with_scratch(const themis_batch_t* batch, int n_thr, const doub
     uint32_t* count = (uint32_t*)scratch;
     SweepJob* list = (SweepJob*)((uint8_t*)scratch + kSweepJobsHeader);
     jobs = SweepJobs{list, count};
-    uint32_t width = 1u;
-    while (width < (uint32_t)n_thr) width *= 2u;
+    const uint32_t width = sweep_plans_width(n_thr);
     go(sweep_clear_kernel, 1u, 1u, count);
     go(sweep_plans_kernel, (unsigned)((batch->n * width + kSweepPlansBlock - 1u) / kSweepPlansBlock),
        kSweepPlansBlock, *batch, n_thr, width, thr, thr_per_scenario, policy_mask, n_pol, t_done, list, count);

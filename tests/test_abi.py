@@ -52,6 +52,17 @@ def test_host_side_helpers():
     assert binding.themis_workspace_bytes(1000, 64) >= 1000 * 64 * 8
 
 
+def test_sweep_scratch_is_only_asked_for_where_it_can_be_used():
+    """The list of plans is built by a power of two of lanes per scenario, in a
+    grid of less than 2^32 lanes, and counted in 32 bits."""
+    from paper_2110_04478_amd import binding
+    need = binding.lib().themis_sweep_scratch_bytes
+    assert need(65536, 64, 8, 7) > 0 and need(100_000_000, 64, 17, 7) > 0
+    assert need(200_000_000, 64, 17, 7) == 0      # 32 lanes each
+    assert need(1 << 28, 64, 16, 6) == 0          # 2^32 plans
+    assert need(65536, 64, 3, 7) == 0 and need(65536, 64, 33, 7) == 0 and need(16, 64, 8, 7) == 0
+
+
 def test_argument_errors_are_reported_without_a_device():
     """NULL / out-of-range arguments are rejected on the host before any HIP
     call, so this needs no GPU."""
