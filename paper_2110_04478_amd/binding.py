@@ -233,19 +233,33 @@ def themis_simulate_batch_noalloc(b: DeviceBatch, orders: torch.Tensor, t_done: 
     return t_done, queue_order, busy
 
 
+def themis_sweep_scratch_bytes(n: int, max_chunks: int, n_thr: int, policy_mask: int) -> int:
+    """Bytes of scratch a sweep of this size can use (0: none)."""
+    return lib().themis_sweep_scratch_bytes(n, max_chunks, n_thr, policy_mask)
+
+
 def themis_sweep(b: DeviceBatch, thr: torch.Tensor, policy_mask: int,
                  thr_per_scenario: bool = False, t_done: Optional[torch.Tensor] = None,
-                 workspace: Optional[torch.Tensor] = None):
-    """Fused plan + simulate -> t_done f64[n, n_thr, n_pol]."""
+                 workspace: Optional[torch.Tensor] = None, scratch: Optional[torch.Tensor] = None):
+    """Fused plan + simulate -> t_done f64[n, n_thr, n_pol].
+
+    scratch: themis_sweep_scratch_bytes() bytes in which the thresholds that share a plan are
+    listed; allocated for the call where it is not given, and done without (same results) where
+    there is no room for it."""
     n_thr = int(thr.shape[0])
     n_pol = bin(policy_mask & 7).count("1")
     if t_done is None:
         t_done = torch.empty((b.n, n_thr, n_pol), dtype=torch.float64, device=b.device)
     ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    # memory in which the thresholds that share a plan are listed (stream-ordered:
-    # torch hands it on only behind this stream's work)
-    need = lib().themis_sweep_scratch_bytes(b.n, b.max_chunks, n_thr, policy_mask)
-    scratch = torch.empty(need, dtype=torch.uint8, device=b.device) if need else None
+    # (a sweep of fewer evaluations is one turn of the GPU's wavefronts and has no use for the
+    # list: not worth the call, 1 us of the 12 that a small sweep takes)
+    if scratch is None and b.n * n_thr >= 8192:
+        try:   # (stream-ordered: torch hands it on only behind this stream's work)
+            scratch = alloc_workspace(themis_sweep_scratch_bytes(b.n, b.max_chunks, n_thr, policy_mask),
+                                      b.device)
+        except torch.OutOfMemoryError:
+            pass
+    need = 0 if scratch is None else scratch.numel() * scratch.element_size()
     s = b.c_struct()
     _check(lib().themis_sweep_with_scratch(C.byref(s), n_thr, _ptr(thr), 1 if thr_per_scenario else 0,
                                            policy_mask, _ptr(t_done), _ptr(workspace), ws_bytes,

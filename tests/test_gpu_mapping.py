@@ -148,6 +148,27 @@ def test_sweeps_whose_thresholds_share_plans(gpu, oracle, n, max_chunks, n_thr, 
     assert_close("sweep", out.cpu().numpy()[few], want)
 
 
+def test_a_sweep_whose_scratch_does_not_fit_goes_without(gpu, monkeypatch):
+    """The list of plans is an extra: a caller whose batch leaves no room for it
+    gets the same results, and one that keeps it around hands it in."""
+    import torch
+    n = 30000
+    d = gpu.to_device(w().mixed(n, seed=871, max_chunks=64))
+    thr = torch.linspace(0.0, 0.5, 8, dtype=torch.float64, device="cuda")
+    need = gpu.themis_sweep_scratch_bytes(n, 64, 8, 7)
+    assert need > 0
+    own = gpu.themis_sweep(d, thr, 7)
+    given = gpu.themis_sweep(d, thr, 7, scratch=torch.empty(need, dtype=torch.uint8, device="cuda"))
+
+    def no_room(*args, **kwargs):
+        raise torch.OutOfMemoryError("no room")
+    monkeypatch.setattr(gpu, "alloc_workspace", no_room)
+    without = gpu.themis_sweep(d, thr, 7)
+    torch.cuda.synchronize()
+    bits = [t.view(torch.int64).cpu() for t in (own, given, without)]
+    assert torch.equal(bits[0], bits[1]) and torch.equal(bits[0], bits[2])
+
+
 @pytest.mark.parametrize("n", [9, 7000])
 def test_search_of_a_workspace_that_holds_marks(gpu, oracle, n):
     """Every 64th scenario is left to the per-order tables (halvings below the
