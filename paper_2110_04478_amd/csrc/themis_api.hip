@@ -2314,6 +2314,10 @@ static bool sweep_mapping_is_quad(uint32_t cap) {
 // scenarios 138 / 306, 2,048 164 / 314, 4,096 227 / 311, 8,192 420 / 314; NPU
 // counts that are not powers of two: 137 / 1,835, 226 / 2,274, 416 / 2,272.
 // Planner: 2,048 23 / 26, 4,096 36 / 26 (24 / 144, 36 / 149).
+// What the lines cost on power-of-two counts, and what they give the others:
+// one chunk on four dimensions, where setting the tables up is most of it, 2,048
+// scenarios 13 / 13, 4,096 18 / 13 (18 / 28), two chunks 21 / 22 (21 / 52); planner
+// at 3,072 28 / 26 on four dimensions (28 / 147), 19 / 26 on two, 11 / 26 on one.
 constexpr uint64_t kWaveSimulate = 4096, kWavePlan = 3072;
 static std::atomic<int> batch_mapping{THEMIS_MAPPING_AUTO};
 static bool on_wavefronts(uint64_t items, uint64_t most) {
@@ -2325,7 +2329,10 @@ static bool plan_on_wavefronts(uint64_t items) { return on_wavefronts(items, kWa
 static bool simulate_on_wavefronts(uint64_t items) { return on_wavefronts(items, kWaveSimulate); }
 
 // A wavefront per evaluation in a sweep of few: the lanes' own planning and
-// their 300 us per 64 chunks otherwise (the line lies where themis_simulate_batch's does).
+// their 300 us per 64 chunks otherwise.  The line lies where themis_simulate_batch's
+// does; 4,080 evaluations on four dimensions of power-of-two counts, us, wavefront /
+// other mapping: 1 chunk 18 / 12 (other counts 18 / 23), 4 28 / 32, 64 235 / 338,
+// 256 1,330 / 1,656, 512 2,640 / 2,285 (2,640 / 7,800; two dimensions 1,260 / 1,757).
 static bool sweep_on_wavefronts(uint64_t evaluations) {
   return sweep_mapping.load(std::memory_order_relaxed) == THEMIS_MAPPING_AUTO && evaluations <= kWaveSimulate;
 }

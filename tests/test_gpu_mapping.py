@@ -71,9 +71,25 @@ def test_small_sizes_beyond_64_chunks_without_a_workspace(gpu, oracle, n):
         assert np.isfinite(t[tiny]).all()
 
 
-@pytest.mark.parametrize("n", [1, 256, 257, 3073, 4096, 4097])
+@pytest.mark.parametrize("n", [1, 256, 257, 2048, 2049, 3072, 3073, 4096, 4097])
 def test_batch_sizes_around_the_choice_of_the_mapping(gpu, oracle, n):
-    check_batch(gpu, oracle, w().mixed(n, seed=820, max_chunks=9, pow2=False))
+    """Both kinds of NPU counts (from 2,049 to 3,072 scenarios each kind is planned
+    on its own mapping); invalid scenarios; one or two chunks."""
+    b = w().mixed(n, seed=820, max_chunks=9, pow2=False)
+    b.npus[:, ::2] = 1 << np.floor(np.log2(b.npus[:, ::2])).astype(np.int64)
+    b.size_bytes[n // 2::97] = 0.0 if n > 1 else b.size_bytes[0]
+    check_batch(gpu, oracle, b)
+    check_batch(gpu, oracle, w().mixed(n, seed=821, max_chunks=2, pow2=False))
+
+
+def test_trace_collectives_planned_on_both_mappings(gpu, oracle):
+    """2,255 collectives of which some scenarios have fewer than others."""
+    b = w().config5(n=205, n_coll=11)
+    b.npus[:, ::2] = [[6], [12], [24], [2]]
+    b.n_coll = (1 + np.arange(b.n) % 11).astype(np.uint32)
+    b.size_bytes = b.size_bytes.copy()
+    b.intra_policy[::3] = 0
+    check_batch(gpu, oracle, b)
 
 
 @pytest.mark.parametrize("bound,n,chunks,dims", [(1, 7, 1, 1), (64, 40, 6, 2), (65, 40, 6, 2), (576, 30, 2, 4),
