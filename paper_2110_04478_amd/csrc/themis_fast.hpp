@@ -190,11 +190,12 @@ __device__ __forceinline__ bool fast_eligible(const Scenario& s, double chunk, u
       et += e;
     }
   }
-  // every halving (doubling, for an All-Gather) must stay a normal number
+  // every halving (doubling, for an All-Gather) must stay a normal number, and
+  // start from one: the scaling works on the exponent field
   uint32_t ex = (uint32_t)((__double_as_longlong(chunk) >> 52) & 0x7ff);
   fs.gather = s.ctype == THEMIS_COLL_ALL_GATHER;
   fs.rs_only = s.ctype == THEMIS_COLL_REDUCE_SCATTER;
-  ok = ok && ex < 0x7ffu && (fs.gather ? ex + et < 0x7ffu : ex > et);
+  ok = ok && ex < 0x7ffu && (fs.gather ? ex > 0u && ex + et < 0x7ffu : ex > et);
   fs.epack = ep;
   fs.etot = et;
   fs.chunk = chunk;

@@ -29,6 +29,7 @@ CASES = {
     "ties, 300 chunks": lambda W: W.dyadic_ties(60, seed=812, max_chunks=300),
     "halvings leave the normal range": lambda W: _tiny(W.mixed(300, seed=813)),
     "the same, few": lambda W: _tiny(W.mixed(60, seed=814, max_chunks=100)),
+    "chunks below the normal range": lambda W: _denormal(_with_collective_types(W.mixed(300, seed=816), 12)),
 }
 
 
@@ -39,6 +40,14 @@ def _tiny(b):
     size[::3] = 3e-307
     bw[0, 1::3] = 1e300
     b.size_bytes, b.bw = size, bw
+    return b
+
+
+def _denormal(b):
+    """Chunk sizes of 1e-308 and less on bandwidths to match: an All-Gather's grow
+    into the normal range, from a size whose exponent field is zero."""
+    b.chunks[:] = np.maximum(b.chunks, 32)
+    b.size_bytes, b.bw = np.full(b.n, 3e-307), b.bw * 1e-20
     return b
 
 
