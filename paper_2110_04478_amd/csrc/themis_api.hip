@@ -1478,10 +1478,9 @@ __device__ __forceinline__ uint64_t assignment_count(uint32_t D, uint32_t C, uin
   return total;
 }
 
-// A scenario's answer (lane 0..63 of a wavefront), NaN / all-ones if !ok.
+// A scenario's answer, NaN / all-ones if !ok (for one lane to write).
 __device__ __forceinline__ void search_write(const themis_batch_t& b, uint64_t i, bool ok, double best,
                                              uint64_t arg, double* best_t, uint8_t* best_orders) {
-  if (threadIdx.x != 0u) return;
   const uint32_t D = b.ndims[i], C = b.chunks[i];
   best_t[i] = ok ? best : nan64();
   if (!best_orders) return;
@@ -1506,6 +1505,133 @@ __device__ __forceinline__ void search_lowest(double& best, uint64_t& arg) {
     const uint64_t oa = ((uint64_t)__shfl_down((uint32_t)(arg >> 32), off) << 32) |
                         __shfl_down((uint32_t)arg, off);
     if (ob < best || (ob == best && oa < arg)) { best = ob; arg = oa; }
+  }
+}
+
+// Up to kSearchFew assignments per scenario: too few lanes of a wavefront, and
+// one simulation too short, for a table per scenario.  The first lane_blocks
+// workgroups take what has power-of-two NPU counts, a lane per assignment and as
+// many whole scenarios as fit 64 lanes; the others look for the rest in `group`
+// scenarios each and simulate those on a shared table one by one (what that does
+// not take goes the way of search_kernel's).  For batches of more scenarios than
+// the GPU holds wavefronts; us, this / search_kernel, on power-of-two counts and on
+// others: 2-D, 16,384 scenarios, 2 chunks 19 / 74 and 92 / 74, 4 chunks 53 / 105 and
+// 136 / 105; 131,072, 4 chunks 294 / 750 and 951 / 755; 3-D, one chunk, 16,384
+// 21 / 69 and 84 / 68; 4-D 51 / 84 and 314 / 300; 1-D, 64 chunks, 131,072 190 / 5,475.
+// 64 assignments are as fast either way, 36 (one scenario in 64 lanes) 119 / 98.
+constexpr uint32_t kSearchFew = 32u;
+template <typename L, bool kFix>
+__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3)))
+search_few_kernel(themis_batch_t b, uint32_t max_assign, uint32_t lane_blocks, uint32_t group,
+                  double* __restrict__ times, double* __restrict__ best_t, uint8_t* __restrict__ best_orders,
+                  unsigned long long call) {
+  constexpr uint32_t kCap = L::kCap;
+  constexpr uint32_t kRingBytes = kCap * 128u + LayoutRing::kTailBytes;
+  struct Shared { uint8_t ring[kRingBytes]; SharedTable tab; };
+  __shared__ union Block {
+    uint32_t lanes[L::kLaneWords * kBlock];
+    __attribute__((aligned(16))) Shared shared;
+    __device__ Block() {}
+  } block;
+  const uint32_t lane = threadIdx.x;
+  FastOut none;
+  none.queue_order = nullptr;
+  none.slots = b.max_chunks;
+  auto count_of = [&](const Scenario& s, double S) {
+    return s.valid && finite_positive(S) && s.C <= kCap
+               ? (uint32_t)assignment_count((uint32_t)s.D, s.C, (uint64_t)max_assign) : 0u;
+  };
+
+  if (blockIdx.x < lane_blocks) {
+    const uint32_t per = kBlock / max_assign, seg = lane / max_assign, a = lane - seg * max_assign;
+    const uint64_t i = (uint64_t)blockIdx.x * per + seg;
+    const bool exists = seg < per && i < b.n;
+    double best = inf64();
+    uint32_t arg = a;
+    bool bad = false, answer = false;   // whether the scenario's answer is given here
+    if (exists) {
+      const Scenario s = load_scenario(b, i);
+      const double S = b.size_bytes[i], chunk = S / (double)s.C;
+      const uint32_t count = count_of(s, S);
+      FastScenario fs;
+      answer = count == 0u || fast_eligible(s, chunk, kCap, fs);
+      bad = count == 0u;
+      if (answer && a < count) {
+        const LaneLds lds = lane_lds<L>(block.lanes);
+        const DivideByOrders by_orders((uint32_t)s.D);
+        const uint32_t F = factorial_u32((uint32_t)s.D);
+        uint32_t rest = a;
+        for (uint32_t c = 0; c < s.C; ++c) {
+          const uint32_t q = by_orders(rest);
+          L::init_chunk(lds, c, stored_code(s, fs, nth_permutation_code((uint32_t)s.D, rest - q * F)), fs.state0);
+          rest = q;
+        }
+        const FastResult r = simulate_pow2<L, kNoQueueOrder, false, kFix>(
+            s, Pow2Model(s, fs, b.intra_policy[i] == THEMIS_INTRA_SCF), lds, none);
+        bad = !r.ok;
+        if (r.ok) best = r.t_done;
+      }
+    }
+    const uint64_t gave_up = __builtin_amdgcn_ballot_w64(bad);
+    for (uint32_t off = 32u; off > 0u; off >>= 1) {   // (the scenario's lanes only)
+      const double ob = __shfl_down(best, off);
+      const uint32_t oa = (uint32_t)__shfl_down((int)arg, off);
+      if (a + off < max_assign && (ob < best || (ob == best && oa < arg))) { best = ob; arg = oa; }
+    }
+    const uint64_t mine = ((1ull << max_assign) - 1ull) << (lane & 63u);   // (of lane a == 0)
+    if (answer && a == 0u) search_write(b, i, (gave_up & mine) == 0ull, best, arg, best_t, best_orders);
+    return;
+  }
+
+  // (which of the group they are: a lane each)
+  const uint64_t first = (uint64_t)(blockIdx.x - lane_blocks) * group;
+  bool other = false;
+  if (lane < group && first + lane < b.n) {
+    const Scenario s = load_scenario(b, first + lane);
+    const double S = b.size_bytes[first + lane];
+    FastScenario fs;
+    other = count_of(s, S) != 0u && !fast_eligible(s, S / (double)s.C, kCap, fs);
+  }
+  for (uint64_t left = __builtin_amdgcn_ballot_w64(other); left != 0ull; left &= left - 1ull) {
+    const uint64_t i = first + (uint32_t)__builtin_ctzll(left);
+    const Scenario s = load_scenario(b, i);
+    const double S = b.size_bytes[i];
+    const uint32_t count = count_of(s, S);
+    const SharedSetup setup = shared_table(s, S / (double)s.C, b.intra_policy[i] == THEMIS_INTRA_SCF,
+                                           block.shared.tab);
+    __syncthreads();
+    if (!setup.ok) {
+      if (lane < max_assign) times[i * max_assign + lane] = lane < count ? left_to_generic() : inf64();
+      if (lane == 0u) mark_left_to_generic(best_t + i, call);
+      __syncthreads();
+      continue;
+    }
+    double best = inf64();
+    uint64_t arg = ~0ull;
+    bool bad = false;
+    if (lane < count) {
+      const DivideByOrders by_orders((uint32_t)s.D);
+      const uint32_t F = factorial_u32((uint32_t)s.D);
+      LaneLds lds;
+      lds.base = block.shared.ring + LayoutRing::lane_term_rec(lane);
+      lds.aux = block.shared.ring + kCap * 128u + (LayoutRing::lane_term_tail(lane) - LayoutRing::kRecBytes);
+      uint32_t rest = lane;
+      for (uint32_t c = 0; c < s.C; ++c) {
+        const uint32_t q = by_orders(rest);
+        *LayoutRing::rec(lds, c) = (uint16_t)((uint32_t)block.shared.tab.rank_of[rest - q * F] << 3);
+        rest = q;
+      }
+      const SharedModel model{block.shared.tab, s.ctype == THEMIS_COLL_REDUCE_SCATTER,
+                              s.ctype == THEMIS_COLL_ALL_GATHER, setup.t_min};
+      const FastResult r = ring_loop<true, kNoQueueOrder, false, false, true>(
+          s, model, lds, none, (const uint8_t*)block.shared.tab.step);
+      bad = !r.ok;
+      if (r.ok) { best = r.t_done; arg = lane; }
+    }
+    bad = __builtin_amdgcn_ballot_w64(bad) != 0ull;
+    search_lowest(best, arg);
+    if (lane == 0u) search_write(b, i, !bad, best, arg, best_t, best_orders);
+    __syncthreads();
   }
 }
 
@@ -1540,8 +1666,8 @@ search_kernel(themis_batch_t b, uint64_t max_assign, uint32_t parts, double* __r
   double* row = times + i * max_assign;
   // what this wavefront found: the answer itself, or its part of it
   auto report = [&](bool ok, double best, uint64_t arg) {
-    if (parts == 1u) { search_write(b, i, ok, best, arg, best_t, best_orders); return; }
     if (lane != 0u) return;
+    if (parts == 1u) { search_write(b, i, ok, best, arg, best_t, best_orders); return; }
     row[part] = ok ? best : nan64();
     ((uint64_t*)row)[parts + part] = arg;
     if (part == 0u) best_t[i] = 0.0;   // (whatever it held: not a mark)
@@ -1720,7 +1846,7 @@ search_finish_kernel(themis_batch_t b, uint64_t max_assign, uint32_t parts,
     }
     bad = __builtin_amdgcn_ballot_w64(bad) != 0ull;
     search_lowest(best, arg);
-    search_write(b, i, !bad && arg != ~0ull, best, arg, best_t, best_orders);
+    if (threadIdx.x == 0u) search_write(b, i, !bad && arg != ~0ull, best, arg, best_t, best_orders);
   }
 }
 
@@ -2749,16 +2875,29 @@ int themis_search_batch(const themis_batch_t* batch, uint64_t max_assignments, d
   const uint64_t room = 12u * (uint64_t)(compute_units() ? compute_units() : 256u);
   const uint64_t groups = (max_assignments + kBlock - 1u) / kBlock;
   uint64_t parts = groups;
-  if (groups > 2u * room / batch->n) {
+  const bool tiny = max_assignments <= kSearchFew && batch->n > room;
+  if (!tiny && groups > 2u * room / batch->n) {
     parts = room / batch->n;
     if (parts > max_assignments / 512u) parts = max_assignments / 512u;
     if (parts < 1u) parts = 1u;
   }
   const bool few = batch->max_chunks <= 16u, wide = max_assignments > 0x7fffffffull;
-  auto search = few ? (wide ? search_kernel<16, uint64_t> : search_kernel<16, uint32_t>)
-                    : (wide ? search_kernel<64, uint64_t> : search_kernel<64, uint32_t>);
-  go(search, (unsigned)(batch->n * parts), kBlock, *batch, max_assignments, (uint32_t)parts, times, best_t,
-     best_orders, call);
+  if (tiny) {
+    const bool fix = batch->fixed_delay != nullptr;
+    const uint64_t per = kBlock / max_assignments, lane_blocks = (batch->n + per - 1u) / per;
+    // (eight turns of wavefronts for the others: enough to even out, few to look in vain)
+    uint64_t group = batch->n / (8u * room);
+    group = group < 1u ? 1u : group > kBlock ? kBlock : group;
+    auto search = few ? (fix ? search_few_kernel<Layout16, true> : search_few_kernel<Layout16, false>)
+                      : (fix ? search_few_kernel<LayoutRing, true> : search_few_kernel<LayoutRing, false>);
+    go(search, (unsigned)(lane_blocks + (batch->n + group - 1u) / group), kBlock, *batch, (uint32_t)max_assignments,
+       (uint32_t)lane_blocks, (uint32_t)group, times, best_t, best_orders, call);
+  } else {
+    auto search = few ? (wide ? search_kernel<16, uint64_t> : search_kernel<16, uint32_t>)
+                      : (wide ? search_kernel<64, uint64_t> : search_kernel<64, uint32_t>);
+    go(search, (unsigned)(batch->n * parts), kBlock, *batch, max_assignments, (uint32_t)parts, times, best_t,
+       best_orders, call);
+  }
   go(search_table_kernel, follow_up_blocks(evals), kBlock, *batch, max_assignments, times,
      (const double*)best_t, call);
   go(search_finish_kernel, (unsigned)(batch->n < room ? batch->n : room), kBlock, *batch, max_assignments,

@@ -126,6 +126,39 @@ def test_searches_with_one_and_with_several_wavefronts_per_scenario(gpu, oracle,
     assert np.array_equal(got_o.cpu().numpy()[few], want_o)
 
 
+@pytest.mark.parametrize("bound,n,chunks,dims", [(1, 3300, 64, 1), (1, 5000, 1, 1), (2, 3073, 1, 2), (16, 3500, 4, 2),
+                                                 (24, 3333, 1, 4), (32, 26000, 5, 2), (30, 3100, 5, 2), (6, 3201, 17, 3)])
+def test_tiny_searches_of_many_scenarios(gpu, oracle, bound, n, chunks, dims):
+    """A lane per assignment and several scenarios to a wavefront (64 of one
+    assignment, ten of six, two of 24 or 30), those of other NPU counts among
+    them, each with fewer assignments than the bound or more, which is no answer;
+    invalid scenarios and sizes below the normal range; in batches whose last
+    wavefronts are not full."""
+    import torch
+    from test_gpu_parity import assert_close
+    W, rng = w(), np.random.default_rng(890 + bound + n)
+    P = np.where(rng.random((n, 1)) < 0.6, 2 ** rng.integers(1, 5, (n, dims)), rng.integers(2, 20, (n, dims)))
+    size = np.floor(rng.uniform(2 ** 20, 2 ** 30, n))
+    size[7::31] = 0.0
+    size[11::37] = 3e-307
+    bw = rng.uniform(25e9, 400e9, (n, dims))
+    bw[11::37] *= 1e-20
+    most = chunks if dims < 3 or chunks == 1 else 2      # (36 assignments: beyond the bound)
+    b = W.make_batch([dims] * n, P.tolist(), bw.tolist(), size, rng.integers(1, most + 1, n), 1,
+                     rng.integers(0, 2, n), 0.0, max_chunks=chunks)
+    b = _with_collective_types(b, 1)
+    few = np.unique(np.concatenate([np.arange(140), np.arange(n - 70, n), rng.permutation(n)[:200]]))
+    delayed = b.take(np.arange(n))
+    delayed.size_bytes[11::37] = 2.0 ** 20    # (beside a delay the tiny stages would not move the clock)
+    for batch in (b, _with_fixed_delay(delayed, 2)):
+        got_t, got_o = gpu.themis_search_batch(gpu.to_device(batch), bound)
+        torch.cuda.synchronize()
+        want_t, want_o = oracle.search_batch(batch.take(few), bound, threads=8)
+        assert_close("best_t", got_t.cpu().numpy()[few], want_t)
+        assert np.array_equal(got_o.cpu().numpy()[few], want_o)
+        assert np.isfinite(want_t).sum() > len(few) // 4
+
+
 def test_searches_whose_times_single_precision_does_not_resolve(gpu, oracle):
     """The bounds that rule assignments out are in single precision: times of
     1e-45 .. 1e-37 seconds are denormal there."""
