@@ -392,8 +392,9 @@ int themis_metrics_batch(const themis_batch_t *batch, const double *t_done,
  * scheduler is from the best schedule.
  *
  * Assignment number a (0 <= a < (D!)^C) gives chunk c the permutation of
- * (0, 1, .., D-1) with lexicographic index (a / (D!)^c) mod D!.  Every
- * assignment is simulated with the scenario's intra_policy (and fixed_delay /
+ * (0, 1, .., D-1) with lexicographic index (a / (D!)^c) mod D!.  The
+ * best of all assignments is found, as if each were simulated (those that a lower
+ * bound of their time rules out are not), with the scenario's intra_policy (and fixed_delay /
  * collective_type, if given); inter_policy and threshold are ignored.
  *
  *   max_assignments : upper bound on (D!)^C over the batch; a scenario with
@@ -404,8 +405,10 @@ int themis_metrics_batch(const themis_batch_t *batch, const double *t_done,
  *   workspace   : themis_search_workspace_bytes(n, max_assignments) bytes
  *                 (one time per scenario and assignment), required.
  * Covers single collectives (n_coll == NULL) of at most 64 chunks, any NPU
- * counts (power-of-two counts on the fast path, others on per-order tables);
- * other scenarios come back as NaN / all-ones.
+ * counts (what the stage table of a scenario does not take, as many networks of
+ * four dimensions with other counts than powers of two, on per-order tables);
+ * other scenarios come back as NaN / all-ones, and so do scenarios one of whose
+ * assignments no event loop takes (see themis_workspace_bytes).
  */
 size_t themis_search_workspace_bytes(uint64_t n, uint64_t max_assignments);
 int themis_search_batch(const themis_batch_t *batch, uint64_t max_assignments,
@@ -438,10 +441,12 @@ int themis_search_batch(const themis_batch_t *batch, uint64_t max_assignments,
  *                 64-byte aligned, required (the kept schedules, one time per
  *                 scenario and candidate, the greedy plan).
  * Covers single collectives (n_coll == NULL) with max_chunks <= 64, any NPU
- * counts (power-of-two counts on the fast path, others on per-order tables).
- * Invalid scenarios, and scenarios one of whose partial schedules neither
- * path can simulate, come back as NaN / all-ones.  Launches 3 kernels per
- * chunk slot; the work is n * width * D! simulations per step.
+ * counts.  Invalid scenarios, and scenarios one of whose partial schedules no
+ * event loop takes (a stage too short to move the clock, say), come back as NaN /
+ * all-ones.  Large batches take a wavefront per scenario for all chunk slots,
+ * without the candidates that a lower bound rules out, and two launches per slot
+ * that return at once unless scenarios were left to them; small batches and
+ * narrow beams three kernels per slot, which simulate every candidate.
  */
 size_t themis_beam_workspace_bytes(uint64_t n, uint32_t max_chunks, uint32_t width);
 int themis_beam_search_batch(const themis_batch_t *batch, uint32_t width, double *best_t,

@@ -25,7 +25,9 @@
 //     taken from an array in chunk order: their size is the largest there is
 //     (the smallest, for a stand-alone All-Gather), so they come after (before)
 //     all lists.
-// An event is some 60 scalar and vector instructions and no memory access.
+// An event is some 60 scalar and vector instructions and, up to 64 chunks, no
+// memory access (beyond them the links and part of the queues are in LDS, and
+// where the records are asked for 64 of them go there at a time).
 #pragma once
 
 #include "themis_generic.hpp"
