@@ -195,7 +195,7 @@ __device__ __forceinline__ bool fast_eligible(const Scenario& s, double chunk, u
   uint32_t ex = (uint32_t)((__double_as_longlong(chunk) >> 52) & 0x7ff);
   fs.gather = s.ctype == THEMIS_COLL_ALL_GATHER;
   fs.rs_only = s.ctype == THEMIS_COLL_REDUCE_SCATTER;
-  ok = ok && ex < 0x7ffu && (fs.gather ? ex > 0u && ex + et < 0x7ffu : ex > et);
+  ok = ok && ex - 1u < 0x7feu && (fs.gather ? ex + et < 0x7ffu : ex > et);
   fs.epack = ep;
   fs.etot = et;
   fs.chunk = chunk;
