@@ -334,10 +334,10 @@ int themis_sweep_with_scratch(const themis_batch_t *batch, int n_thr,
 int themis_set_sweep_mapping(int mapping);
 
 /*
- * themis_set_batch_mapping -- the same for themis_plan_batch and, on single
- * collectives, themis_simulate_batch:
- *   THEMIS_MAPPING_AUTO : a wavefront per scenario in small batches, one lane
- *                         per scenario in large ones (the default)
+ * themis_set_batch_mapping -- the same for themis_plan_batch and
+ * themis_simulate_batch:
+ *   THEMIS_MAPPING_AUTO : a wavefront per scenario (or trace) in small batches,
+ *                         one lane per scenario in large ones (the default)
  *   THEMIS_MAPPING_LANE : one lane per scenario
  *   THEMIS_MAPPING_WAVE : one wavefront per scenario (per scenario and
  *                         collective, in the planner)

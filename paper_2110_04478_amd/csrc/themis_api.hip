@@ -1,6 +1,7 @@
 // C ABI of the library (see include/themis.h) and the kernels behind it.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <atomic>
 #include <cstdlib>
 #include <cstring>
@@ -17,6 +18,7 @@
 #include "themis_shared.hpp"
 #include "themis_table.hpp"
 #include "themis_trace.hpp"
+#include "themis_trace_wave.hpp"
 #include "themis_wave.hpp"
 
 // Scratch of themis_simulate_batch_noalloc: device memory the library itself
@@ -744,16 +746,18 @@ simulate_follow_up_kernel(themis_batch_t b, const uint8_t* __restrict__ orders,
 // the ranked-list path of themis_trace.hpp, else the generic path.
 // ---------------------------------------------------------------------------
 // kExtras: the batch carries release times or fixed delays (one switch for
-// both keeps the number of variants down).
+// both keeps the number of variants down).  call != 0: only the traces that the
+// call's simulate_trace_wave_kernel has left marked.
 template <bool kLdsBitmaps, bool kExtras>
 __global__ void __launch_bounds__(kBlock)
 simulate_trace_kernel(themis_batch_t b, const uint8_t* __restrict__ orders,
                       double* __restrict__ t_done, void* __restrict__ queue_order,
                       int entry_bytes, double* __restrict__ busy, Workspace w, bool have_ws,
-                      uint8_t* __restrict__ trace_area, TraceLayout tl) {
+                      uint8_t* __restrict__ trace_area, TraceLayout tl, unsigned long long call) {
   __shared__ uint32_t lds_block[(kLdsBitmaps ? kTraceLdsWordsBitmaps : kTraceLdsWords) * kBlock];
+  if (call != 0ull && nothing_marked(call)) return;
   uint64_t i = (uint64_t)blockIdx.x * kBlock + threadIdx.x;
-  if (i >= b.n) return;
+  if (i >= b.n || (call != 0ull && !is_left_to_generic(t_done[i]))) return;
   const TraceView tv = trace_view(b);
   Scenario s = load_scenario(b, i);
   const bool scf = b.intra_policy[i] == THEMIS_INTRA_SCF;
@@ -854,6 +858,94 @@ simulate_trace_kernel(themis_batch_t b, const uint8_t* __restrict__ orders,
   }
   if (!have_ws) { write_invalid(out); return; }
   simulate_generic_scenario<false>(b, tv, s, Q, i, i, row, scf, w, out);
+}
+
+// One wavefront per trace (themis_trace_wave.hpp), lds_bytes of LDS: traces that
+// need more, or that the event loop does not take (sizes outside the normal
+// range, a stage too short to move the clock, a release at the very instant of
+// a completion), are left marked.  follow_up: only what an earlier launch of the
+// call, with less LDS, has marked.
+template <bool kLog>
+__global__ void __launch_bounds__(kBlock)
+simulate_trace_wave_kernel(themis_batch_t b, const uint8_t* __restrict__ orders, double* __restrict__ t_done,
+                           void* __restrict__ queue_order, int entry_bytes, double* __restrict__ busy,
+                           uint32_t lds_bytes, bool follow_up, unsigned long long call) {
+  extern __shared__ __attribute__((aligned(16))) uint8_t trace_lds[];
+  const uint64_t i = blockIdx.x;
+  if (follow_up && (nothing_marked(call) || !is_left_to_generic(t_done[i]))) return;
+  const TraceView tv = trace_view(b);
+  const uint32_t lane = lane_id();
+  const Scenario s = load_scenario(b, i);
+  const bool scf = b.intra_policy[i] == THEMIS_INTRA_SCF;
+  const bool gather = s.ctype == THEMIS_COLL_ALL_GATHER;
+  const uint32_t Q = b.n_coll[i];
+  bool ok = s.valid && Q >= 1u && Q <= tv.mc;
+  bool exact = true, releases = false, sizes_ok = true;
+  double smallest = inf64(), largest = 0.0;
+  for (uint32_t q = lane; ok && q < Q; q += kBlock) {
+    const double size = collective_size(b, tv, i, q), release = collective_release(b, tv, i, q);
+    sizes_ok = sizes_ok && finite_positive(size) && release >= 0.0 && release < inf64();
+    releases = releases || release > 0.0;
+    const double chunk = size / (double)s.C;
+    FastScenario fs;
+    exact = exact && fast_eligible(s, chunk, THEMIS_MAX_CHUNKS, fs);
+    smallest = min_f64(smallest, chunk);
+    largest = -min_f64(-largest, -chunk);
+  }
+  ok = ok && __builtin_amdgcn_ballot_w64(!sizes_ok) == 0ull;
+  exact = __builtin_amdgcn_ballot_w64(!exact) == 0ull;
+  releases = uniform(releases);
+  for (int off = 32; off > 0; off >>= 1) {
+    smallest = min_f64(smallest, __shfl_xor(smallest, off));
+    largest = -min_f64(-largest, -__shfl_xor(largest, off));
+  }
+  const uint32_t row_len = 2u * tv.slots;
+  uint8_t* const rows = kLog ? (uint8_t*)queue_order + (size_t)i * kMaxDims * row_len * (uint32_t)entry_bytes : nullptr;
+  WaveResult r;
+#pragma unroll
+  for (int k = 0; k < kMaxDims; ++k) { r.busy[k] = nan64(); r.executed[k] = 0u; }
+  r.t_done = nan64();
+  if (ok) {
+    WaveOutcome outcome = WaveOutcome::kNotTaken;
+    const TraceWaveLayout l = trace_wave_layout(Q * s.C, (uint32_t)s.D, Q, scf, !exact);
+    bool takes = l.bytes <= lds_bytes && lds_offset(trace_lds) == 0u &&
+                 trace_wave_lists((uint32_t)s.D, Q, scf, !exact) <= kTraceMaxRanks;
+    if (!exact) {
+      for (int k = 0; k < s.D; ++k) {
+        if (gather) largest = largest * (double)s.P[k];
+        else smallest = smallest / (double)s.P[k];
+      }
+      takes = takes && uniform(smallest >= 2.2250738585072014e-308 && largest < inf64());
+    }
+    if (takes) {
+      const uint8_t* row = orders + (size_t)i * tv.slots;
+      auto run = [&](auto divide) {
+        return trace_wave_simulate<kLog, decltype(divide)::value>(
+            s, Q, scf, releases, smallest, l, trace_lds,
+            [&](uint32_t q, uint32_t c) { return (uint32_t)row[(size_t)q * b.max_chunks + c]; },
+            [&](uint32_t q) { return collective_size(b, tv, i, q) / (double)s.C; },
+            [&](uint32_t q) { return collective_release(b, tv, i, q); }, rows, row_len,
+            entry_bytes == 2 ? 1u : 0u, r);
+      };
+      outcome = exact ? run(std::false_type{}) : run(std::true_type{});
+    }
+    if (outcome == WaveOutcome::kNotTaken) {
+      if (lane == 0u) mark_left_to_generic(t_done + i, call);
+      return;
+    }
+    ok = outcome == WaveOutcome::kDone;
+  }
+  if (lane == 0u) t_done[i] = ok ? r.t_done : nan64();
+  if (busy && lane < (uint32_t)kMaxDims)
+    busy[(size_t)lane * b.n + i] = ok ? sel4((int)lane, r.busy[0], r.busy[1], r.busy[2], r.busy[3]) : nan64();
+  if (kLog) {
+#pragma unroll
+    for (uint32_t k = 0; k < (uint32_t)kMaxDims; ++k)
+      for (uint32_t e = (ok ? r.executed[k] : 0u) + lane; e < row_len; e += kBlock) {
+        if (entry_bytes == 2) ((uint16_t*)rows)[k * row_len + e] = 0xFFFFu;
+        else rows[k * row_len + e] = 0xFFu;
+      }
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -2352,10 +2444,14 @@ struct Launcher {
   explicit Launcher(void* s) : stream((hipStream_t)s) {}
   template <typename... P, typename... A>
   void operator()(void (*kernel)(P...), unsigned blocks, unsigned threads, A&&... a) {
+    with_lds(0u, kernel, blocks, threads, std::forward<A>(a)...);
+  }
+  template <typename... P, typename... A>
+  void with_lds(unsigned lds_bytes, void (*kernel)(P...), unsigned blocks, unsigned threads, A&&... a) {
     std::tuple<P...> params(std::forward<A>(a)...);  // converted to the kernel's own parameter types
     void* ptrs[sizeof...(P)];
     fill(ptrs, params, std::index_sequence_for<P...>{});
-    const hipError_t e = hipLaunchKernel((const void*)kernel, dim3(blocks), dim3(threads), ptrs, 0, stream);
+    const hipError_t e = hipLaunchKernel((const void*)kernel, dim3(blocks), dim3(threads), ptrs, lds_bytes, stream);
     if (first == hipSuccess) first = e;
   }
   int status() const { return first == hipSuccess ? THEMIS_OK : THEMIS_ERR_DEVICE; }
@@ -2453,6 +2549,60 @@ static bool on_wavefronts(uint64_t items, uint64_t most) {
 }
 static bool plan_on_wavefronts(uint64_t items) { return on_wavefronts(items, kWavePlan); }
 static bool simulate_on_wavefronts(uint64_t items) { return on_wavefronts(items, kWaveSimulate); }
+
+// LDS of the launches that simulate a batch of traces with a wavefront each (0:
+// none).  How much a trace needs depends on its dimensions and NPU counts, which
+// the host does not see: the first launch has enough for up to three dimensions
+// of powers of two, the second also for four, and for three of other counts, the
+// third for what fits at all; each takes what the one before has left marked.
+// One launch does where all the traces are resident with the larger blocks.
+struct TraceWaveLaunches {
+  uint32_t lds[3];
+  const uint32_t* begin() const { return lds; }
+  const uint32_t* end() const { return lds + 3; }
+};
+constexpr uint32_t kLdsOfCu = 160u * 1024u;
+// (four wavefronts on a SIMD by their registers)
+static uint64_t trace_wave_resident(uint32_t lds) {
+  const uint64_t per_cu = lds ? kLdsOfCu / lds : 0u;
+  return (per_cu < 16u ? per_cu : 16u) * (compute_units() ? compute_units() : 256u);
+}
+static TraceWaveLaunches trace_wave_launches(uint64_t n, uint32_t slots, uint32_t max_coll) {
+  const uint32_t most4 = kTraceMaxRanks / (trace_wave_row(4u, true) / 4u);
+  TraceWaveLaunches t;
+  t.lds[0] = trace_wave_layout(slots, 3u, max_coll, true, false).bytes;
+  t.lds[1] = std::max(trace_wave_layout(slots, 3u, max_coll, true, true).bytes,
+                      trace_wave_layout(slots, 4u, max_coll, true, false).bytes);
+  t.lds[2] = std::max(t.lds[1], trace_wave_layout(slots, 4u, std::min(max_coll, most4), true, true).bytes);
+  for (int j = 1; j < 3; ++j)
+    if (t.lds[j] > kLdsOfCu || t.lds[j] == t.lds[j - 1]) t.lds[j] = t.lds[j] > kLdsOfCu ? kLdsOfCu : 0u;
+  if (t.lds[0] > kLdsOfCu) t.lds[0] = 0u;
+  for (int j = 2; j > 0; --j)
+    if (t.lds[j] != 0u && n <= trace_wave_resident(t.lds[j]))
+      for (int i = 0; i < j; ++i) t.lds[i] = 0u;
+  return t;
+}
+// A wavefront per trace, or a lane each?  On wavefronts an event of a trace takes
+// 0.42 us and 18 ns more per wavefront of its CU; they take turns where the LDS of
+// a CU holds fewer than there are traces.  With a lane each it takes 1.5 us and
+// up, 5.2 with release times, whatever the number of traces up to a wavefront of
+// them per CU.  Measured (ms, wavefront / lane; three dimensions unless said):
+//   200 collectives of 64 chunks   64 traces 32 / 108, 1,024 71 / 115, 2,048 141 / 117
+//   100 of 32                      1,024 10.9 / 28.7, 4,096 29 / 30, 16,384 97 / 35
+//   50 of 32, releases             64 4.1 / 49, 2,048 6.1 / 54, 16,384 28 / 55
+//   40 of 16, four dimensions      2,048 4.2 / 8.8, 8,192 11.7 / 10.0
+//   4 of 8                         64 0.11 / 0.33, 4,096 0.17 / 0.34, 8,192 0.32 / 0.35
+static bool trace_on_wavefronts(uint64_t n, uint32_t slots, uint32_t max_coll, bool releases) {
+  const uint32_t lds = trace_wave_layout(slots, 3u, max_coll, true, false).bytes;
+  const int forced = batch_mapping.load(std::memory_order_relaxed);
+  if (lds > kLdsOfCu || n > 0x7fffffffull || forced == THEMIS_MAPPING_LANE) return false;
+  if (forced == THEMIS_MAPPING_WAVE) return true;
+  const double cus = compute_units() ? compute_units() : 256u;
+  const double resident = (double)trace_wave_resident(lds) / cus;         // wavefronts of a CU
+  const double per_cu = std::min(resident, std::max(1.0, (double)n / cus));
+  const double turns = std::max(1.0, (double)n / (cus * resident));
+  return turns * (0.42 + 0.018 * per_cu) < (releases ? 5.2 : 1.5);
+}
 
 // A wavefront per evaluation in a sweep of few: the lanes' own planning and
 // their 300 us per 64 chunks otherwise.  The line lies where themis_simulate_batch's
@@ -2601,8 +2751,20 @@ static int simulate_batch_impl(const themis_batch_t* batch, const uint8_t* order
                         queue_order != nullptr;
     auto trace_kernel = lds_bitmaps ? (extras ? simulate_trace_kernel<true, true> : simulate_trace_kernel<true, false>)
                                     : (extras ? simulate_trace_kernel<false, true> : simulate_trace_kernel<false, false>);
+    unsigned long long call = 0ull;
+    if (have_trace && trace_on_wavefronts(batch->n, tv.slots, batch->max_coll, batch->release_time != nullptr)) {
+      call = next_call_number();
+      bool follow_up = false;
+      for (uint32_t lds : trace_wave_launches(batch->n, tv.slots, batch->max_coll)) {
+        if (lds == 0u) continue;
+        go.with_lds(lds, queue_order ? simulate_trace_wave_kernel<true> : simulate_trace_wave_kernel<false>,
+                    (unsigned)batch->n, kBlock, *batch, orders, t_done, queue_order, entry_bytes, busy, lds,
+                    follow_up, call);
+        follow_up = true;
+      }
+    }
     go(trace_kernel, blocks_for(batch->n), kBlock, *batch, orders, t_done, queue_order,
-       entry_bytes, busy, w, have_ws, trace_area, tl);
+       entry_bytes, busy, w, have_ws, trace_area, tl, call);
     return go.status();
   }
   SimKernel kernel = pick_simulate_kernel(cap, mode, busy != nullptr,

@@ -1,0 +1,76 @@
+"""GPU parity of traces under each lane mapping, whatever the batch size would
+choose: one lane per trace and one wavefront per trace, whose edges are 64
+chunks of a collective, 64 operations of a dimension (the queue orders leave a
+register then, as bytes up to 127 chunk slots), 64 size ranks (a word of the
+bitmap) and 4,096 (its end), and the LDS of a launch, which has enough for up to
+three dimensions of powers of two in the first one."""
+import numpy as np
+import pytest
+
+from test_gpu_parity import (_add_trace, _with_collective_types, _with_fixed_delay, check_batch, gpu,  # noqa: F401
+                             w)
+
+pytestmark = pytest.mark.gpu
+
+
+def _trace(n, seed, max_chunks, max_coll, pow2=True, equal_sizes=False, dims=None, full=False, ties=False):
+    rng = np.random.default_rng(seed)
+    b = w().dyadic_ties(n, seed=seed, max_chunks=max_chunks) if ties else \
+        w().mixed(n, seed=seed, max_chunks=max_chunks, pow2=pow2)
+    b = _add_trace(b, rng, max_coll, pow2_sizes=equal_sizes)
+    if dims:
+        b.ndims[:] = dims
+    if full:
+        b.n_coll[:], b.chunks[:] = max_coll, max_chunks
+    return b
+
+
+def _released(b, seed, step=0.0):
+    rng = np.random.default_rng(seed)
+    b.release_time = np.ascontiguousarray(rng.integers(0, 4, b.coll_size.shape) * step if step else
+                                          rng.uniform(0, 1, b.coll_size.shape) ** 3 * 5e-3)
+    return b
+
+
+CASES = {
+    "one chunk": lambda: _trace(90, 1, 1, 70),
+    "127 slots": lambda: _trace(40, 2, 127, 1, full=True),
+    "128 slots": lambda: _trace(40, 3, 32, 4, full=True),
+    "63 chunks": lambda: _trace(30, 4, 63, 3),
+    "65 chunks": lambda: _trace(30, 5, 65, 5, pow2=False),
+    "512 chunks": lambda: _trace(6, 6, 512, 3, full=True),
+    "256 collectives, 4-D": lambda: _trace(9, 7, 3, 256, dims=4, full=True),
+    "256 collectives, equal sizes": lambda: _trace(9, 8, 3, 256, equal_sizes=True, full=True),
+    "80 and 90 collectives, 4-D, other counts": lambda: _trace(7, 9, 3, 90, pow2=False, dims=4),
+    "other counts, releases": lambda: _released(_trace(90, 10, 17, 8, pow2=False), 1),
+    "types, delays, releases": lambda: _released(_with_fixed_delay(_with_collective_types(
+        _trace(120, 11, 16, 9), 2), 3), 4),
+    "types, other counts": lambda: _with_collective_types(_trace(120, 12, 9, 7, pow2=False), 5),
+    "ties": lambda: _trace(150, 13, 16, 6, equal_sizes=True, ties=True),
+    "ties, releases": lambda: _released(_trace(150, 14, 16, 6, equal_sizes=True, ties=True), 6, step=2.0 ** -12),
+}
+
+
+@pytest.mark.parametrize("case", list(CASES))
+@pytest.mark.parametrize("mapping", ["lane", "wave"])
+def test_traces_agree_with_the_oracle(gpu, oracle, mapping, case):
+    b = CASES[case]()
+    gpu.themis_set_batch_mapping({"lane": gpu.MAPPING_LANE, "wave": gpu.MAPPING_WAVE}[mapping])
+    try:
+        t = check_batch(gpu, oracle, b)
+        assert np.isfinite(t).all()
+        check_batch(gpu, oracle, b, queue=False)
+    finally:
+        gpu.themis_set_batch_mapping(gpu.MAPPING_AUTO)
+
+
+def test_invalid_traces_on_wavefronts(gpu, oracle):
+    """Bad sizes, counts of collectives and networks: NaN and
+    all-ones, with valid traces beside them; stages that do not move the clock and
+    sizes that leave the normal range go on to the other paths."""
+    b = _released(_trace(64, 21, 9, 5), 7)
+    b.coll_size[0, ::8], b.npus[0, 2::8] = 0.0, 1
+    b.n_coll[3::8], b.n_coll[4::8] = 0, 6
+    b.coll_size[:, 5::8] = 3e-307
+    b.bw[0, 6::8] = 1e300
+    check_batch(gpu, oracle, b)
