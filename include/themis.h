@@ -324,8 +324,9 @@ int themis_sweep_with_scratch(const themis_batch_t *batch, int n_thr,
  *                         evaluation where there are only a few thousand
  *   THEMIS_MAPPING_LANE : one lane per evaluation
  *   THEMIS_MAPPING_QUAD : four lanes per evaluation, one per dimension
- * Process-wide, takes effect with the next call of themis_sweep; meant for
- * measurements and tests.  Returns THEMIS_ERR_INVALID_ARGUMENT for any other
+ * LANE and QUAD also fix which of the two themis_simulate_batch takes where it does
+ * not take a wavefront per scenario (beyond 64 chunks there is only QUAD).
+ * Process-wide, takes effect with the next call; meant for measurements and tests.  Returns THEMIS_ERR_INVALID_ARGUMENT for any other
  * value.
  */
 #define THEMIS_MAPPING_AUTO 0

@@ -280,19 +280,129 @@ __device__ __forceinline__ void put_queue_entry(uint8_t* rows, uint32_t at, uint
   else rows[at] = (uint8_t)v;
 }
 
+// All-ones from entry `used` of a row of `row_len` entries on.
+__device__ __forceinline__ void pad_row(uint8_t* row, uint32_t used, uint32_t row_len, int entry_bytes) {
+  uint32_t at = used * (uint32_t)entry_bytes;
+  const uint32_t end = row_len * (uint32_t)entry_bytes;
+  for (; at < end && ((uintptr_t)(row + at) & 7u) != 0u; ++at) row[at] = 0xFFu;
+  for (; at + 8u <= end; at += 8u) *(uint64_t*)(row + at) = ~0ull;
+  for (; at < end; ++at) row[at] = 0xFFu;
+}
+
+// visit(c, code): the order codes of a scenario, by each lane of its quad, four
+// read at a time where the rows are aligned.
+template <typename Visit>
+__device__ __forceinline__ void quad_codes(const themis_batch_t& b, const uint8_t* orders, uint64_t i, uint32_t C,
+                                           Visit visit) {
+  const uint8_t* row = orders + (size_t)i * b.max_chunks;
+  const bool words = (b.max_chunks & 3u) == 0u && ((uintptr_t)orders & 3u) == 0u;
+  for (uint32_t c4 = 0; c4 < C; c4 += 4u) {
+    uint32_t v = 0u;
+    if (words) v = *(const uint32_t*)(row + c4);
+    else
+      for (uint32_t j = 0; j < 4u && c4 + j < C; ++j) v |= (uint32_t)row[c4 + j] << (8u * j);
+#pragma unroll
+    for (uint32_t j = 0; j < 4u; ++j)
+      if (c4 + j < C) visit(c4 + j, (v >> (8u * j)) & 0xffu);
+  }
+}
+
+// What a quad writes about its scenario (mark: left to the kernels that follow,
+// which write everything).
+template <int kQueueOrder>
+__device__ __forceinline__ void quad_outputs(const themis_batch_t& b, uint64_t i, bool done, bool mark,
+                                             const QuadResult& r, double* t_done, uint8_t* row, int entry_bytes,
+                                             double* busy, unsigned long long call) {
+  const uint32_t k = threadIdx.x & 3u;
+  if (mark) {
+    if (k == 0u) mark_left_to_generic(t_done + i, call);
+    return;
+  }
+  if (k == 0u) t_done[i] = done ? r.t_done : nan64();
+  if (busy) busy[(size_t)k * b.n + i] = done ? r.busy : nan64();
+  if (kQueueOrder != kNoQueueOrder) pad_row(row, done ? r.started : 0u, 2u * b.max_chunks, entry_bytes);
+}
+
+// The scenarios first + lane of the lanes in `left` (valid ones of up to kDims
+// dimensions and L::kCap chunks), whatever their NPU counts are (QuadTable), 16 at
+// a time.  What the event loop does not take is marked, unless it is marked already
+// (marked); malformed codes are for the caller's kernel or the generic one.  All
+// lanes of the wavefront; lds: QuadTable::kBytes.
+template <typename L, uint32_t kDims, int kQueueOrder>
+__device__ __forceinline__ void quad_table_rounds(const themis_batch_t& b, const uint8_t* __restrict__ orders,
+                                                  double* __restrict__ t_done, void* __restrict__ queue_order,
+                                                  int entry_bytes, double* __restrict__ busy, uint64_t first,
+                                                  uint64_t left, bool marked, void* lds, unsigned long long call) {
+  using Table = QuadTable<L, kDims>;
+  const uint32_t lane = threadIdx.x & 63u, k = lane & 3u;
+  while (left != 0ull) {
+    // the quads take the next 16: the lane of the j-th sends its number to quad j
+    const uint32_t rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(left >> 32),
+                                                    __builtin_amdgcn_mbcnt_lo((uint32_t)left, 0u));
+    const bool chosen = ((left >> lane) & 1ull) != 0ull && rank < L::kQuads;
+    const uint32_t sent = (uint32_t)__builtin_amdgcn_ds_permute(chosen ? (int)(16u * rank) : 4, (int)lane);
+    const uint32_t which = (uint32_t)__shfl((int)sent, (int)(lane & ~3u));
+    const bool exists = (uint32_t)__builtin_popcountll(left) > lane >> 2;
+    left &= ~__builtin_amdgcn_ballot_w64(chosen);
+    const uint64_t i = exists ? first + which : first;
+    const Scenario s = load_scenario(b, i);
+    const uint32_t D = (uint32_t)s.D;
+    const bool gather = s.ctype == THEMIS_COLL_ALL_GATHER;
+    uint32_t bad = 0u, used = 0u;
+    auto order_of = [&](uint32_t code) {
+      return quad_order(gather ? reverse_code(code, s.D) : code, D) % Table::kOrders;
+    };
+    if (exists)
+      quad_codes(b, orders, i, s.C, [&](uint32_t c, uint32_t code) {
+        if ((c & 3u) != k) return;
+        if (!order_code_ok(code, s.D)) bad = 1u;
+        used |= 1u << order_of(code);
+      });
+    const bool runs = exists && quad_sum(bad) == 0u;
+    used = runs ? quad_or(used) : 0u;
+    const Table model(s, b.size_bytes[i] / (double)s.C, b.intra_policy[i] == THEMIS_INTRA_SCF, used, lds);
+    QuadQueue<L> queue(lds);
+    if (runs)
+      quad_codes(b, orders, i, s.C, [&](uint32_t c, uint32_t code) {
+        if ((code & 3u) == k) queue.add(c | Table::state_of(order_of(code), gather ? 1u : 0u) << 9);
+      });
+    uint8_t* const row = queue_order ? (uint8_t*)queue_order + ((size_t)i * kMaxDims + k) * 2u * b.max_chunks * (uint32_t)entry_bytes
+                                     : nullptr;
+    const uint32_t stages = s.ctype == THEMIS_COLL_ALL_REDUCE ? 2u * D : D;
+    const QuadResult r = simulate_quad<L, kQueueOrder != kNoQueueOrder>(
+        model, queue, model.cls0, runs ? stages * s.C : 0u, model.t_min, [&](uint32_t e, uint32_t entry) {
+          if (kQueueOrder == kShorts) ((uint16_t*)row)[e] = (uint16_t)entry;
+          else row[e] = (uint8_t)entry;
+        });
+    const bool done = runs && r.ok;
+    if (exists && (done || !marked))
+      quad_outputs<kQueueOrder>(b, i, done, !done, r, t_done, row, entry_bytes, busy, call);
+    __syncthreads();
+  }
+}
+
 template <typename L, int kQueueOrder, bool kBusy, bool kFix>
 __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(L::kWavesPerSimd)))
 simulate_kernel(themis_batch_t b, const uint8_t* __restrict__ orders,
                 double* __restrict__ t_done, void* __restrict__ queue_order, int entry_bytes,
                 double* __restrict__ busy, unsigned long long hand_over) {
-  __shared__ uint32_t lds_block[L::kLaneWords * kBlock];
-  uint64_t i = (uint64_t)blockIdx.x * kBlock + threadIdx.x;
-  if (i >= b.n) return;
-  const TraceView tv = trace_view(b);
-  Scenario s = load_scenario(b, i);
+  __shared__ __attribute__((aligned(8))) uint32_t lds_block[L::kLaneWords * kBlock];
+  // (a lane beyond the batch stays for the exchanges between lanes)
+  const uint64_t at = (uint64_t)blockIdx.x * kBlock + threadIdx.x;
+  const bool exists = at < b.n;
+  const uint64_t i = exists ? at : b.n - 1u;
+  const Scenario s = load_scenario(b, i);
   const bool scf = b.intra_policy[i] == THEMIS_INTRA_SCF;
-  uint32_t Q;
-  bool ok = collectives_ok(b, tv, i, Q) && s.valid;
+  const double S = b.size_bytes[i];
+  const bool ok = s.valid && finite_positive(S);
+  FastScenario fs;
+  const bool eligible = fast_eligible(s, S / (double)s.C, L::kCap, fs) && ok && exists;
+  // NPU counts that are not powers of two: four lanes each at the end, up to three
+  // dimensions, else left to the follow-up kernel; with them the other scenarios
+  // of the wavefront where those are few (one round of 16 is cheaper than the lanes' loop)
+  const bool few = __builtin_amdgcn_ballot_w64(exists && ok && !eligible) != 0ull &&
+                   __builtin_popcountll(__builtin_amdgcn_ballot_w64(eligible)) <= 16;
+  const bool fast = eligible && !few;
 
   // Queue orders of a wavefront whose 64 scenarios all exist are staged
   // transposed inside the wavefront's own block of the output (kStagedBytes)
@@ -305,9 +415,9 @@ simulate_kernel(themis_batch_t b, const uint8_t* __restrict__ orders,
   // 128-chunk layout the rows written in place do better (3.14 against 3.44 ms
   // for 262,144 scenarios of 126 chunks).
   constexpr uint32_t kStagedWords = L::kCap / 2u < 32u ? L::kCap / 2u : 32u;
-  const uint32_t rows_bytes = (uint32_t)kMaxDims * 2u * tv.slots * (uint32_t)entry_bytes;
+  const uint32_t rows_bytes = (uint32_t)kMaxDims * 2u * b.max_chunks * (uint32_t)entry_bytes;
   const bool staged = kQueueOrder == kWords && queue_order != nullptr &&
-                      (tv.slots >> 1) <= kStagedWords &&
+                      (b.max_chunks >> 1) <= kStagedWords &&
                       (uint64_t)(blockIdx.x + 1u) * kBlock <= b.n;  // the same for all lanes
   enum { kRowsStaged = 1, kRowsAllOnes = 2, kRowsNotMine = 3 };
   uint32_t rows = kRowsNotMine;
@@ -318,7 +428,7 @@ simulate_kernel(themis_batch_t b, const uint8_t* __restrict__ orders,
   out.busy = busy ? busy + i : nullptr;
   out.busy_stride = b.n;
   out.entry_bytes = entry_bytes;
-  out.slots = tv.slots;
+  out.slots = b.max_chunks;
   out.queue_order = (kQueueOrder != kNoQueueOrder && queue_order)
       ? (void*)((uint8_t*)queue_order + (size_t)i * rows_bytes) : nullptr;
   // an invalid scenario: NaN / all-ones (its rows at the end, if rows are staged in the block)
@@ -329,17 +439,15 @@ simulate_kernel(themis_batch_t b, const uint8_t* __restrict__ orders,
     rows = kRowsAllOnes;
   };
 
-  do {
+  bool left = false;
+  if (exists) do {
     if (!ok) { invalid(); break; }
-    const uint8_t* row = orders + (size_t)i * tv.slots;
-    FastScenario fs;
-    bool fast = !tv.on &&
-                fast_eligible(s, collective_size(b, tv, i, 0) / (double)s.C, L::kCap, fs);
+    const uint8_t* row = orders + (size_t)i * b.max_chunks;
     if (fast) {
       const LaneLds lds = lane_lds<L>(lds_block);
       // order codes -> chunk words (mask 0, Reduce-Scatter phase)
       bool codes_ok = true;
-      if ((tv.slots & 3u) == 0u) {
+      if ((b.max_chunks & 3u) == 0u) {
         const uint32_t* row4 = (const uint32_t*)row;
         for (uint32_t c4 = 0; c4 < s.C; c4 += 4u) {
           uint32_t v = row4[c4 >> 2];
@@ -362,11 +470,11 @@ simulate_kernel(themis_batch_t b, const uint8_t* __restrict__ orders,
       if (!codes_ok) { invalid(); break; }
       FastOut fo;
       fo.queue_order = (uint8_t*)out.queue_order;
-      fo.slots = tv.slots;
+      fo.slots = b.max_chunks;
       // staged: the same address for all lanes plus a 32-bit offset
       FastOut so;
       so.queue_order = (uint8_t*)queue_order + (size_t)blockIdx.x * kBlock * rows_bytes;
-      so.slots = tv.slots;
+      so.slots = b.max_chunks;
       so.lane_offset = IsRing<L>::value ? threadIdx.x : 4u * threadIdx.x;
       so.staging_bytes = (uint32_t)kBlock * rows_bytes;
       FastResult r;
@@ -388,16 +496,13 @@ simulate_kernel(themis_batch_t b, const uint8_t* __restrict__ orders,
           for (int k = 0; k < kMaxDims; ++k) executed[k] = r.executed[k];
         } else if (kQueueOrder != kNoQueueOrder && out.queue_order) {
           for (int k = 0; k < kMaxDims; ++k)
-            for (uint32_t e = r.executed[k]; e < 2u * tv.slots; ++e)
-              put_queue_entry<kQueueOrder>(fo.queue_order, (uint32_t)k * 2u * tv.slots + e, 0xFFFFu);
+            for (uint32_t e = r.executed[k]; e < 2u * b.max_chunks; ++e)
+              put_queue_entry<kQueueOrder>(fo.queue_order, (uint32_t)k * 2u * b.max_chunks + e, 0xFFFFu);
         }
         break;
       }
     }
-    // hand_over != 0: follow-up kernels come (this call's number) and write
-    // everything of this scenario, else nothing can take it
-    if (!hand_over) { invalid(); break; }
-    mark_left_to_generic(t_done + i, hand_over);
+    left = true;
   } while (false);
 
   if constexpr (kQueueOrder == kWords) {
@@ -406,7 +511,7 @@ simulate_kernel(themis_batch_t b, const uint8_t* __restrict__ orders,
       // 256 contiguous bytes per dword), waits until the whole wavefront has
       // all of them in registers, and writes them where they belong, with
       // all-ones from the first unused entry on
-      const uint32_t wpr = tv.slots >> 1;  // dwords per row
+      const uint32_t wpr = b.max_chunks >> 1;  // dwords per row
       // the entries a lane fetches were stored by other lanes of its wavefront
       __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
       const uint32_t* from =
@@ -468,7 +573,7 @@ simulate_kernel(themis_batch_t b, const uint8_t* __restrict__ orders,
         // operations: an All-Reduce of `slots` chunks on four dimensions) need no marks
         bool full_rows = rows == kRowsStaged;
 #pragma unroll
-        for (uint32_t k = 0; k < (uint32_t)kMaxDims; ++k) full_rows = full_rows && executed[k] == 2u * tv.slots;
+        for (uint32_t k = 0; k < (uint32_t)kMaxDims; ++k) full_rows = full_rows && executed[k] == 2u * b.max_chunks;
         const bool marks = __builtin_amdgcn_ballot_w64(!full_rows) != 0ull;  // the same for all lanes
 #pragma unroll
         for (uint32_t k = 0; k < (uint32_t)kMaxDims; ++k)
@@ -494,6 +599,81 @@ simulate_kernel(themis_batch_t b, const uint8_t* __restrict__ orders,
             }
           }
       }
+    }
+  }
+  // (what ran in the lanes' loop and stalled there goes on to the generic path)
+  const bool tables = left && !fast && s.D < 4;
+  if (left && !tables) mark_left_to_generic(t_done + i, hand_over);
+  using L3 = LayoutQuad<L::kCap, 12u, 3u>;
+  static_assert(QuadTable<L3, 3>::kBytes <= sizeof(lds_block), "the tables fit the lanes' block");
+  const uint64_t quads = __builtin_amdgcn_ballot_w64(tables);
+  if (quads != 0ull) {
+    __syncthreads();
+    quad_table_rounds<L3, 3, kQueueOrder>(b, orders, t_done, queue_order, entry_bytes, busy,
+                                          (uint64_t)blockIdx.x * kBlock, quads, false, lds_block, hand_over);
+  }
+}
+
+// Four lanes per scenario (themis_quad.hpp).  kOthers: scenarios of up to three
+// dimensions whose NPU counts are not powers of two are taken here as well (and
+// with them the other ones of up to three dimensions in their wavefront), by
+// tables of their own; else, and on four dimensions, they are left marked.
+template <typename L, int kQueueOrder, bool kFix, bool kOthers>
+__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(L::kWavesPerSimd)))
+simulate_quad_kernel(themis_batch_t b, const uint8_t* __restrict__ orders, double* __restrict__ t_done,
+                     void* __restrict__ queue_order, int entry_bytes, double* __restrict__ busy,
+                     unsigned long long hand_over) {
+  using L3 = LayoutQuad<L::kCap, 12u, 3u>;
+  constexpr uint32_t kLdsBytes = kOthers && QuadTable<L3, 3>::kBytes > L::kBytes ? QuadTable<L3, 3>::kBytes : L::kBytes;
+  __shared__ uint64_t lds_block[(kLdsBytes + 7u) / 8u];
+  const uint32_t k = threadIdx.x & 3u;
+  const uint64_t first = (uint64_t)blockIdx.x * L::kQuads, at = first + (threadIdx.x >> 2);
+  // a quad without a scenario stays: the wavefront leaves the event loop as a whole
+  const bool exists = at < b.n;
+  const uint64_t i = exists ? at : b.n - 1u;
+  const Scenario s = load_scenario(b, i);
+  const uint32_t D = (uint32_t)s.D;
+  const double S = b.size_bytes[i];
+  FastScenario fs;
+  const bool ok = s.valid && finite_positive(S) && exists;
+  const bool eligible = fast_eligible(s, S / (double)s.C, L::kCap, fs) && ok;
+  const bool others = kOthers && __builtin_amdgcn_ballot_w64(ok && !eligible && D < 4u) != 0ull;
+  const bool tables = others && ok && D < 4u;
+  const bool fast = eligible && !tables;
+  if (!others || __builtin_amdgcn_ballot_w64(exists && !tables) != 0ull) {
+    QuadQueue<L> queue(lds_block);
+    uint32_t bad = 0u;
+    if (fast)   // every lane checks one code in four and takes the chunks that start on its own dimension
+      quad_codes(b, orders, i, s.C, [&](uint32_t c, uint32_t code) {
+        if ((c & 3u) == k && !order_code_ok(code, s.D)) bad = 1u;
+        if ((code & 3u) == k)
+          queue.add(c | (quad_order(stored_code(s, fs, code), D) & 31u) << 9 | (fs.gather ? 1u << L::kPhaseBit : 0u));
+      });
+    const bool runs = fast && quad_sum(bad) == 0u;
+    if (!runs) queue.any = false;
+    const Pow2Model pow2(s, fs, b.intra_policy[i] == THEMIS_INTRA_SCF);
+    uint8_t* const row = queue_order ? (uint8_t*)queue_order + ((size_t)i * kMaxDims + k) * 2u * b.max_chunks * (uint32_t)entry_bytes
+                                     : nullptr;
+    const QuadResult r = simulate_quad<L, kQueueOrder != kNoQueueOrder>(
+        QuadPow2<kFix>(s, pow2, k), queue, (uint32_t)(pow2.ranktab >> (4u * (fs.state0 & 15u))) & 15u,
+        runs ? (pow2.one_phase() ? D : 2u * D) * s.C : 0u, pow2.t_min(D),
+        [&](uint32_t e, uint32_t entry) {
+          if (kQueueOrder == kShorts) ((uint16_t*)row)[e] = (uint16_t)entry;
+          else row[e] = (uint8_t)entry;
+        });
+    const bool malformed = fast && !runs, done = runs && r.ok;
+    if (exists && !tables)
+      quad_outputs<kQueueOrder>(b, i, done, ok && !malformed && !done, r, t_done, row, entry_bytes, busy, hand_over);
+  }
+  if constexpr (kOthers) {
+    if (others) {
+      // (one bit per quad, as if 16 lanes had a scenario each)
+      const uint64_t quads = __builtin_amdgcn_ballot_w64(tables && k == 0u);
+      const uint32_t j = threadIdx.x;
+      const uint64_t left = __builtin_amdgcn_ballot_w64(j < L::kQuads && ((quads >> (4u * (j & 15u))) & 1ull) != 0ull);
+      __syncthreads();
+      quad_table_rounds<L3, 3, kQueueOrder>(b, orders, t_done, queue_order, entry_bytes, busy, first, left, false,
+                                            lds_block, hand_over);
     }
   }
 }
@@ -592,14 +772,14 @@ template <uint32_t kLdsSlots>
 __device__ __forceinline__ void simulate_generic_pass(
     const themis_batch_t& b, const uint8_t* __restrict__ orders, double* __restrict__ t_done,
     void* __restrict__ queue_order, int entry_bytes, double* __restrict__ busy, Workspace w,
-    void* lds_block) {
+    void* lds_block, uint32_t group) {
   if (kLdsSlots) w = carve_workspace(lds_block, kBlock, kLdsSlots);
   const TraceView tv = trace_view(b);
-  // a few workgroups walk all groups of 64 scenarios: most groups have nothing marked
-  const uint64_t groups = (b.n + kBlock - 1) / kBlock;
+  // a few workgroups walk all groups of scenarios: most have nothing marked
+  const uint64_t groups = (b.n + group - 1) / group;
   for (uint64_t grp = blockIdx.x; grp < groups; grp += gridDim.x) {
-    const uint64_t i = grp * kBlock + threadIdx.x;
-    if (i >= b.n || !is_left_to_generic(t_done[i])) continue;
+    const uint64_t i = grp * group + threadIdx.x;
+    if (threadIdx.x >= group || i >= b.n || !is_left_to_generic(t_done[i])) continue;
     const uint64_t col = kLdsSlots ? threadIdx.x : i;
     Scenario s = load_scenario(b, i);
     const bool scf = b.intra_policy[i] == THEMIS_INTRA_SCF;
@@ -629,14 +809,56 @@ simulate_generic_kernel(themis_batch_t b, const uint8_t* __restrict__ orders,
                         unsigned long long call) {
   __shared__ double lds_block[kLdsSlots ? generic_lds_bytes(kLdsSlots) / sizeof(double) : 1u];
   if (nothing_marked(call)) return;
-  simulate_generic_pass<kLdsSlots>(b, orders, t_done, queue_order, entry_bytes, busy, w, lds_block);
+  simulate_generic_pass<kLdsSlots>(b, orders, t_done, queue_order, entry_bytes, busy, w, lds_block, kBlock);
 }
 
-// Kernels between the two: marked scenarios whose NPU counts are not powers of
-// two run the same LDS event loop on per-order-code tables (themis_table.hpp),
-// first the variant for at most 8 distinct order codes, then (kWide) the one
-// for any number of them; what they cannot take stays marked for the generic
-// kernel.
+constexpr size_t max_bytes(size_t a, size_t b) { return a > b ? a : b; }
+constexpr uint32_t kNoGeneric = 0xffffffffu;
+
+// Everything that follows the LDS kernel of themis_simulate_batch, in one
+// launch: what is marked in quads on tables of its own, then the generic pass (kGeneric: its chunk slots in
+// LDS, 0: arrays in the workspace, kNoGeneric: none).  A workgroup walks the same
+// groups of `group` scenarios in every pass, so what one pass leaves marked is
+// seen by the next without any ordering between workgroups; the passes share one
+// LDS block of the largest size among them.
+// (On four dimensions the tables of 24 orders and up to 48 sizes per dimension
+// take 37 KiB per wavefront, four wavefronts per CU.)
+template <int kQueueOrder, uint32_t kCap, uint32_t kGeneric>
+__global__ void __launch_bounds__(kBlock)
+simulate_follow_up_kernel(themis_batch_t b, const uint8_t* __restrict__ orders,
+                          double* __restrict__ t_done, void* __restrict__ queue_order,
+                          int entry_bytes, double* __restrict__ busy, Workspace w, uint32_t group,
+                          unsigned long long call) {
+  using L4 = LayoutQuad<kCap, 48u>;
+  using L3 = LayoutQuad<kCap, 12u, 3u>;
+  constexpr size_t kBytes_ = max_bytes(QuadTable<L4, 4>::kBytes, kGeneric == kNoGeneric ? 0u : generic_lds_bytes(kGeneric));
+  static_assert(QuadTable<L3, 3>::kBytes <= QuadTable<L4, 4>::kBytes, "one block for both");
+  __shared__ double lds_block[(kBytes_ + 7u) / 8u];
+  if (nothing_marked(call)) return;
+  const uint64_t groups = (b.n + group - 1u) / group;
+  for (uint64_t grp = blockIdx.x; grp < groups; grp += gridDim.x) {
+    const uint64_t first = grp * group, i = first + threadIdx.x;
+    const bool marked = threadIdx.x < group && i < b.n && is_left_to_generic(t_done[i]);
+    const uint32_t D = marked ? b.ndims[i] : 0u;
+    const uint64_t four = __builtin_amdgcn_ballot_w64(D == 4u);
+    if (four != 0ull)
+      quad_table_rounds<L4, 4, kQueueOrder>(b, orders, t_done, queue_order, entry_bytes, busy, first, four, true,
+                                            lds_block, call);
+    const uint64_t three = __builtin_amdgcn_ballot_w64(D - 1u < 3u);
+    if (three != 0ull)
+      quad_table_rounds<L3, 3, kQueueOrder>(b, orders, t_done, queue_order, entry_bytes, busy, first, three, true,
+                                            lds_block, call);
+  }
+  if constexpr (kGeneric != kNoGeneric) {
+    __syncthreads();
+    simulate_generic_pass<kGeneric>(b, orders, t_done, queue_order, entry_bytes, busy, w, lds_block, group);
+  }
+}
+
+// The sweeps' passes over marked evaluations whose NPU counts are not powers of
+// two (themis_table.hpp), one lane each: first the variant for at most 8 distinct
+// order codes, then (kWide) the one for any number of them; what they cannot take
+// stays marked for the generic pass.
 // kVariant: 0 tables for at most 8 order codes (64 chunks), 1 any number of
 // codes (64 chunks), 2 the same for up to 128 chunks, 3 and 4 16-bit chunk
 // records for up to 256 and 512 chunks.
@@ -649,96 +871,10 @@ struct TableVariant {
                                       LayoutTablePacked<512>>::type>::type>::type>::type;
 };
 
-template <int kQueueOrder, int kVariant>
-__device__ __forceinline__ void simulate_table_pass(
-    const themis_batch_t& b, const uint8_t* __restrict__ orders, double* __restrict__ t_done,
-    void* __restrict__ queue_order, double* __restrict__ busy, void* lds_block) {
-  using L = typename TableVariant<kVariant>::L;
-  constexpr bool kWide = kVariant != 0;
-  constexpr uint32_t kEntryBytes = kQueueOrder == kShorts ? 2u : 1u;
-  const uint64_t groups = (b.n + kBlock - 1) / kBlock;
-  for (uint64_t grp = blockIdx.x; grp < groups; grp += gridDim.x) {
-    const uint64_t i = grp * kBlock + threadIdx.x;
-    if (i >= b.n || !is_left_to_generic(t_done[i])) continue;
-    Scenario s = load_scenario(b, i);
-    const double S = b.size_bytes[i];
-    if (!s.valid || s.C > L::kCap || !finite_positive(S)) continue;
-    const uint8_t* row = orders + (size_t)i * b.max_chunks;
-    bool codes_ok = true;
-    for (uint32_t c = 0; c < s.C; ++c) codes_ok = codes_ok && order_code_ok(row[c], s.D);
-    if (!codes_ok) continue;
-    LaneLds lds;
-    lds.base = (uint8_t*)lds_block + 4u * threadIdx.x;
-    const bool scf = b.intra_policy[i] == THEMIS_INTRA_SCF;
-    const double chunk = S / (double)s.C;
-    auto code_at = [&](uint32_t c) { return (uint32_t)row[c]; };
-    const uint32_t rows_bytes = (uint32_t)kMaxDims * 2u * b.max_chunks * kEntryBytes;
-    FastOut fo;
-    fo.queue_order = (kQueueOrder != kNoQueueOrder && queue_order)
-        ? (uint8_t*)queue_order + (size_t)i * rows_bytes : nullptr;
-    fo.slots = b.max_chunks;
-    FastResult r;
-    if constexpr (kVariant >= 3) {
-      DivModelT<LayoutTableWide> model(s, lds, chunk, scf);
-      table_setup_packed<L>(s, scf, lds, code_at, model);
-      r = simulate_table_packed<L, kQueueOrder, true>(s, model, lds, fo);
-    } else if constexpr (kWide) {
-      DivModelT<L> model(s, lds, chunk, scf);
-      table_setup_wide<L>(s, scf, lds, code_at, model);
-      r = simulate_fast<L, kQueueOrder, true, true>(s, model, lds, fo);
-    } else {
-      TableModel model;
-      if (!table_setup(s, chunk, scf, lds, code_at, model)) continue;
-      r = simulate_fast<L, kQueueOrder, true, true>(s, model, lds, fo);
-    }
-    if (!r.ok) continue;
-    t_done[i] = r.t_done;
-    if (busy) {
-#pragma unroll
-      for (int k = 0; k < kMaxDims; ++k) busy[(size_t)k * b.n + i] = r.busy[k];
-    }
-    if (kQueueOrder != kNoQueueOrder && fo.queue_order) {
-      for (int k = 0; k < kMaxDims; ++k)
-        for (uint32_t e = r.executed[k]; e < 2u * b.max_chunks; ++e)
-          put_queue_entry<kQueueOrder>(fo.queue_order, (uint32_t)k * 2u * b.max_chunks + e, 0xFFFFu);
-    }
-  }
-}
-
-constexpr size_t max_bytes(size_t a, size_t b) { return a > b ? a : b; }
 template <int kVariant>
 constexpr size_t table_lds_bytes() {
   if constexpr (kVariant < 0) return 0u;
   else return (size_t)TableVariant<kVariant>::L::kLaneWords * kBlock * sizeof(uint32_t);
-}
-constexpr uint32_t kNoGeneric = 0xffffffffu;
-
-// Everything that follows the LDS kernel of themis_simulate_batch, in one
-// launch: the table passes kTableA and kTableB (-1: none) and the generic pass
-// (kGeneric: its chunk slots in LDS, 0: arrays in the workspace, kNoGeneric:
-// none).  A workgroup walks the same groups of 64 scenarios in every pass, so
-// what one pass leaves marked is seen by the next without any ordering between
-// workgroups; the passes share one LDS block of the largest size among them.
-template <int kQueueOrder, int kTableA, int kTableB, uint32_t kGeneric>
-__global__ void __launch_bounds__(kBlock)
-simulate_follow_up_kernel(themis_batch_t b, const uint8_t* __restrict__ orders,
-                          double* __restrict__ t_done, void* __restrict__ queue_order,
-                          int entry_bytes, double* __restrict__ busy, Workspace w,
-                          unsigned long long call) {
-  constexpr size_t kBytes_ = max_bytes(max_bytes(table_lds_bytes<kTableA>(), table_lds_bytes<kTableB>()),
-                                       kGeneric == kNoGeneric ? 0u : generic_lds_bytes(kGeneric));
-  __shared__ double lds_block[kBytes_ ? (kBytes_ + 7u) / 8u : 1u];
-  if (nothing_marked(call)) return;
-  if constexpr (kTableA >= 0)
-    simulate_table_pass<kQueueOrder, kTableA>(b, orders, t_done, queue_order, busy, lds_block);
-  if constexpr (kTableB >= 0) {
-    __syncthreads();
-    simulate_table_pass<kQueueOrder, kTableB>(b, orders, t_done, queue_order, busy, lds_block);
-  }
-  if constexpr (kGeneric != kNoGeneric) {
-    __syncthreads();
-    simulate_generic_pass<kGeneric>(b, orders, t_done, queue_order, entry_bytes, busy, w, lds_block);
-  }
 }
 
 // ---------------------------------------------------------------------------
@@ -1316,12 +1452,12 @@ sweep_kernel(themis_batch_t b, int n_thr, const double* __restrict__ thr, int th
 // The same with four lanes per evaluation (themis_quad.hpp): a wavefront takes
 // 16 consecutive scenarios under one threshold and one scheduler.
 template <bool kFix, bool kBaseline, bool kJobs>
-__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(LayoutQuad::kWavesPerSimd)))
+__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(LayoutQuad<512, 16>::kWavesPerSimd)))
 sweep_quad_kernel(themis_batch_t b, int n_thr, const double* __restrict__ thr, int thr_per_scenario,
                   unsigned policy_mask, int n_pol, double* __restrict__ t_done,
                   unsigned long long hand_over, SweepJobs jobs) {
-  using L = LayoutQuad;
-  __shared__ uint32_t lds_block[L::kBlockWords];
+  using L = LayoutQuad<512, 16>;
+  __shared__ uint32_t lds_block[L::kBytes / 4u];
   const uint32_t quad = threadIdx.x >> 2;
   const SweepSlot slot =
       kJobs ? sweep_block_slot<kBaseline>(b, jobs, L::kQuads, quad, n_thr, policy_mask, n_pol)
@@ -1344,18 +1480,20 @@ sweep_quad_kernel(themis_batch_t b, int n_thr, const double* __restrict__ thr, i
   const bool eligible = fast_eligible(s, chunk, L::kCap, fs);
   // (a quad without a valid scenario only keeps the others company: no chunks, no events)
   const bool fast = exists && ok && eligible;
-  uint8_t* base = (uint8_t*)lds_block + 2u * quad;
+  const uint32_t k = threadIdx.x & 3u;
+  QuadQueue<L> queue(lds_block);
   if (fast) {
     // every lane of the quad plans (the same arithmetic, the same result) and
-    // writes the records of the chunks whose id ends in its own two bits
+    // takes the chunks that start on its own dimension
     double load[kMaxDims];
     plan_fast(s, fs, it.themis_on, rel, it.th, load, [&](uint32_t c, uint32_t code) {
-      if ((c & 3u) == (threadIdx.x & 3u)) L::init_chunk(base, c, code, 0u, (uint32_t)s.D);
+      if ((code & 3u) == k) queue.add(c | quad_order(code, (uint32_t)s.D) << 9);
     });
   }
-  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  const QuadResult r = simulate_quad<kFix>(s, Pow2Model(s, fs, it.scf), base, fast);
+  const Pow2Model pow2(s, fs, it.scf);
+  const QuadResult r = simulate_quad<L, false>(QuadPow2<kFix>(s, pow2, k), queue, (uint32_t)pow2.ranktab & 15u,
+                                               fast ? 2u * (uint32_t)s.D * s.C : 0u, pow2.t_min((uint32_t)s.D),
+                                               [](uint32_t, uint32_t) {});
   if (!writer) return;
   if (every_threshold) {
     if (!ok) {
@@ -2472,18 +2610,11 @@ static SimKernel pick_flags(bool busy, bool fix) {
               : (fix ? simulate_kernel<L, kMode, false, true> : simulate_kernel<L, kMode, false, false>);
 }
 
-// Queue-entry store modes a layout is built with: four-at-a-time dword stores
-// need 8-bit entries (at most 127 slots), 16-bit entries start at 128 slots.
+// Queue-entry store modes of the lanes' loops (8-bit entries: up to 64 chunks).
 template <typename L>
 static SimKernel pick_mode(int mode, bool busy, bool fix) {
-  constexpr bool words = L::kCap <= 128u, shorts = L::kCap >= 128u;
-  switch (mode) {
-    case kNoQueueOrder: return pick_flags<L, kNoQueueOrder>(busy, fix);
-    case kBytes: return words ? pick_flags<L, words ? kBytes : kNoQueueOrder>(busy, fix) : nullptr;
-    case kWords: return words ? pick_flags<L, words ? kWords : kBytes>(busy, fix) : nullptr;
-    case kShorts: return shorts ? pick_flags<L, shorts ? kShorts : kBytes>(busy, fix) : nullptr;
-  }
-  return nullptr;
+  return mode == kNoQueueOrder ? pick_flags<L, kNoQueueOrder>(busy, fix)
+       : mode == kBytes ? pick_flags<L, kBytes>(busy, fix) : pick_flags<L, kWords>(busy, fix);
 }
 
 // Smallest LDS layout that holds max_chunks chunks per evaluation (the less
@@ -2494,11 +2625,31 @@ static uint32_t layout_capacity(uint32_t max_chunks) {
 }
 
 static SimKernel pick_simulate_kernel(uint32_t cap, int mode, bool busy, bool fix) {
-  if (cap == 16u) return pick_mode<Layout16>(mode, busy, fix);
-  if (cap == 64u) return pick_mode<LayoutRing>(mode, busy, fix);
-  if (cap == 128u) return pick_mode<Layout128>(mode, busy, fix);
-  if (cap == 256u) return pick_mode<LayoutPacked<256>>(mode, busy, fix);
-  return pick_mode<LayoutPacked<512>>(mode, busy, fix);
+  return cap == 16u ? pick_mode<Layout16>(mode, busy, fix) : pick_mode<LayoutRing>(mode, busy, fix);
+}
+
+// The same with four lanes per scenario.
+template <uint32_t kChunks>
+static SimKernel pick_quad_mode(int mode, bool fix) {
+  using L = LayoutQuad<kChunks, 16>;
+  constexpr int kOne = kChunks <= 128u ? kBytes : kShorts, kTwo = kChunks >= 128u ? kShorts : kBytes;
+  constexpr bool kOthers = kChunks <= 64u;
+#define THEMIS_QUAD_KERNEL(MODE) \
+  (fix ? simulate_quad_kernel<L, MODE, true, kOthers> : simulate_quad_kernel<L, MODE, false, kOthers>)
+  return mode == kNoQueueOrder ? THEMIS_QUAD_KERNEL(kNoQueueOrder) : mode == kShorts ? THEMIS_QUAD_KERNEL(kTwo)
+                                                                                     : THEMIS_QUAD_KERNEL(kOne);
+#undef THEMIS_QUAD_KERNEL
+}
+static SimKernel pick_quad_kernel(uint32_t cap, int mode, bool fix) {
+  return cap <= 64u ? pick_quad_mode<64>(mode, fix) : cap == 128u ? pick_quad_mode<128>(mode, fix)
+       : cap == 256u ? pick_quad_mode<256>(mode, fix) : pick_quad_mode<512>(mode, fix);
+}
+
+// Scenarios a workgroup of the follow-up kernel looks at: 64 where there are as
+// many workgroups as the GPU holds, fewer where it would stay idle.
+static uint32_t follow_up_group(uint64_t n) {
+  const uint64_t resident = 4u * (compute_units() ? compute_units() : 256u);
+  return n > 64u * resident ? 64u : n > 32u * resident ? 32u : 16u;
 }
 
 // The generic area comes first in the workspace, rounded up so that the trace
@@ -2526,6 +2677,24 @@ static std::atomic<int> sweep_mapping{THEMIS_MAPPING_AUTO};
 static bool sweep_mapping_is_quad(uint32_t cap) {
   const int forced = sweep_mapping.load(std::memory_order_relaxed);
   return forced != THEMIS_MAPPING_AUTO ? forced == THEMIS_MAPPING_QUAD : cap >= kQuadFromCap;
+}
+
+// Four lanes per scenario (themis_quad.hpp) or one?  A pass of the quads' loop
+// takes a wavefront some 1,080 clocks on its own and a SIMD 340, for 16 scenarios;
+// the lanes' loop takes 1,300 and 620 for 64.  So quads are faster until the
+// lanes fill the GPU (65,536 scenarios have one wavefront per SIMD), and beyond 64
+// chunks always, where LDS holds back the lanes.  Measured (us, quads / lanes): 64
+// chunks, four dimensions 4,096 scenarios 222 / 307, 16,384 247 / 316, 32,768 273 /
+// 336, 65,536 363 / 336, 262,144 1,161 / 713; 3-D first-in-first-out 65,536 282 / 277;
+// 8 chunks 32,768 48 / 70, 131,072 108 / 81; 128 chunks 16,384 474 / 730, 262,144
+// 2,613 / 2,925; 250 chunks 846 / 1,438 and 3,367 / 4,413; 512 chunks 1,712 / 2,906.
+// Other NPU counts, 64 chunks (us, now / with a lane each on per-order tables): three
+// dimensions 20,000 scenarios 351 / 906, 130,000 1,033 / 2,379, four 993 / 2,549, 2,690 /
+// 8,327.
+constexpr uint64_t kQuadSimulate = 49152;
+static bool simulate_on_quads(uint64_t n, uint32_t cap) {
+  const int forced = sweep_mapping.load(std::memory_order_relaxed);
+  return cap > 64u || (forced != THEMIS_MAPPING_AUTO ? forced == THEMIS_MAPPING_QUAD : n <= kQuadSimulate);
 }
 
 // Whole wavefronts per scenario (themis_wave.hpp) or one lane each?  A
@@ -2663,7 +2832,7 @@ static bool sweep_shares_plans(uint64_t n, uint32_t max_chunks, int n_thr, unsig
   const bool quad = sweep_mapping_is_quad(cap);
   if (!quad && cap > 128u) return false;
   const uint64_t per_cu = quad ? 8u : cap == 128u ? 4u : 12u;
-  const uint64_t group = quad ? LayoutQuad::kQuads : kBlock;
+  const uint64_t group = quad ? LayoutQuad<512, 16>::kQuads : kBlock;
   const uint64_t waves = (n + group - 1u) / group *
       sweep_roles((uint32_t)n_thr, (uint32_t)__builtin_popcount(policy_mask & 7u), policy_mask);
   const unsigned cus = compute_units();
@@ -2767,9 +2936,6 @@ static int simulate_batch_impl(const themis_batch_t* batch, const uint8_t* order
        entry_bytes, busy, w, have_ws, trace_area, tl, call);
     return go.status();
   }
-  SimKernel kernel = pick_simulate_kernel(cap, mode, busy != nullptr,
-                                          batch->fixed_delay != nullptr);
-  if (!kernel) return THEMIS_ERR_DEVICE;
   // Scenarios outside the LDS path (marked in t_done) go through the table
   // passes and what those leave through the generic pass: its arrays in LDS up
   // to 64 chunks, in the workspace beyond.  One launch for all of it where that
@@ -2790,44 +2956,46 @@ static int simulate_batch_impl(const themis_batch_t* batch, const uint8_t* order
        orders, t_done, queue_order, entry_bytes, busy, call);
 #undef THEMIS_WAVE_KERNEL
     if (alone) return go.status();
+  } else if (simulate_on_quads(batch->n, cap)) {
+    go(pick_quad_kernel(cap, mode, batch->fixed_delay != nullptr),
+       (unsigned)((batch->n + kBlock / 4u - 1u) / (kBlock / 4u)), kBlock, *batch, orders, t_done, queue_order,
+       entry_bytes, busy, call);
   } else {
-    go(kernel, blocks_for(batch->n), kBlock, *batch, orders, t_done, queue_order, entry_bytes, busy,
-       call);
+    go(pick_simulate_kernel(cap, mode, busy != nullptr, batch->fixed_delay != nullptr), blocks_for(batch->n), kBlock,
+       *batch, orders, t_done, queue_order, entry_bytes, busy, call);
   }
-  const unsigned fb = follow_up_blocks(batch->n);
   const Workspace ws = have_ws ? w : Workspace{};
-#define THEMIS_FOLLOW_UP(MODE, A, B, G) \
-  go(simulate_follow_up_kernel<MODE, A, B, G>, fb, kBlock, *batch, orders, t_done, queue_order, \
-     entry_bytes, busy, ws, call)
+  const uint32_t group = follow_up_group(batch->n);
+  const unsigned fb = follow_up_blocks((batch->n + group - 1u) / group * kBlock);
+#define THEMIS_FOLLOW_UP(MODE, CAP, G) \
+  go(simulate_follow_up_kernel<MODE, CAP, G>, fb, kBlock, *batch, orders, t_done, queue_order, \
+     entry_bytes, busy, ws, group, call)
   // (8-bit entries up to 64 chunks, either up to 128, 16-bit entries beyond)
-#define THEMIS_FOLLOW_UP_MODES(A, B, G)                                  \
-  switch (mode) {                                                        \
-    case kNoQueueOrder: THEMIS_FOLLOW_UP(kNoQueueOrder, A, B, G); break; \
-    case kWords: THEMIS_FOLLOW_UP(kWords, A, B, G); break;               \
-    default: THEMIS_FOLLOW_UP(kBytes, A, B, G); break;                   \
-  }
+#define THEMIS_FOLLOW_UP_MODES(CAP, G)                                \
+  if (mode == kNoQueueOrder) THEMIS_FOLLOW_UP(kNoQueueOrder, CAP, G); \
+  else THEMIS_FOLLOW_UP(kBytes, CAP, G);
   if (cap <= 64u) {
     const bool small = blocks_for(batch->n) <= 2u * compute_units();
     if (have_ws) {
-      THEMIS_FOLLOW_UP_MODES(0, 1, 0u)
+      THEMIS_FOLLOW_UP_MODES(64, 0u)
     } else if (small && cap <= 16u) {
-      THEMIS_FOLLOW_UP_MODES(0, 1, 16u)
+      THEMIS_FOLLOW_UP_MODES(16, 16u)
     } else if (small) {
-      THEMIS_FOLLOW_UP_MODES(0, 1, 64u)
+      THEMIS_FOLLOW_UP_MODES(64, 64u)
     } else {
-      THEMIS_FOLLOW_UP_MODES(0, 1, kNoGeneric)
+      THEMIS_FOLLOW_UP_MODES(64, kNoGeneric)
       auto generic = cap <= 16u ? simulate_generic_kernel<16> : simulate_generic_kernel<64>;
-      go(generic, fb, kBlock, *batch, orders, t_done, queue_order, entry_bytes, busy, ws, call);
+      go(generic, follow_up_blocks(batch->n), kBlock, *batch, orders, t_done, queue_order, entry_bytes, busy, ws, call);
     }
   } else if (cap == 128u) {
-    if (mode == kShorts) THEMIS_FOLLOW_UP(kShorts, 2, -1, 0u);
-    else THEMIS_FOLLOW_UP_MODES(2, -1, 0u)
+    if (mode == kShorts) THEMIS_FOLLOW_UP(kShorts, 128, 0u);
+    else THEMIS_FOLLOW_UP_MODES(128, 0u)
   } else if (cap == 256u) {
-    if (mode == kNoQueueOrder) THEMIS_FOLLOW_UP(kNoQueueOrder, 3, -1, 0u);
-    else THEMIS_FOLLOW_UP(kShorts, 3, -1, 0u);
+    if (mode == kNoQueueOrder) THEMIS_FOLLOW_UP(kNoQueueOrder, 256, 0u);
+    else THEMIS_FOLLOW_UP(kShorts, 256, 0u);
   } else {
-    if (mode == kNoQueueOrder) THEMIS_FOLLOW_UP(kNoQueueOrder, 4, -1, 0u);
-    else THEMIS_FOLLOW_UP(kShorts, 4, -1, 0u);
+    if (mode == kNoQueueOrder) THEMIS_FOLLOW_UP(kNoQueueOrder, 512, 0u);
+    else THEMIS_FOLLOW_UP(kShorts, 512, 0u);
   }
 #undef THEMIS_FOLLOW_UP_MODES
 #undef THEMIS_FOLLOW_UP
@@ -2914,7 +3082,7 @@ int themis_sweep_with_scratch(const themis_batch_t* batch, int n_thr, const doub
   const bool fix = batch->fixed_delay != nullptr;
   const bool base = (policy_mask & THEMIS_SWEEP_BASELINE) != 0u;
   const bool quad = sweep_mapping_is_quad(cap);
-  const uint64_t group = quad ? LayoutQuad::kQuads : kBlock;   // evaluations per wavefront
+  const uint64_t group = quad ? LayoutQuad<512, 16>::kQuads : kBlock;   // evaluations per wavefront
   const uint64_t groups = (batch->n + group - 1u) / group;
   if (groups * (uint64_t)(n_thr * n_pol) > 0x7fffffffull) return THEMIS_ERR_UNSUPPORTED;
   const size_t need = themis_sweep_scratch_bytes(batch->n, batch->max_chunks, n_thr, policy_mask);

@@ -9,47 +9,52 @@
 // wavefronts per CU, each alone on its SIMD and waiting out every dependent
 // instruction and every LDS read.  Here a wavefront holds 16 evaluations in
 // 20 KiB, eight wavefronts fit a CU, and a lane never has to pick one of four
-// dimensions' registers: the arithmetic of a stage start and of a completion is
-// plain code on the lane's own registers.  What it costs: a pass of the loop
-// still handles one completion instant per evaluation, so four times as many
-// wavefront-passes are needed for the same batch.
+// dimensions' registers.
 //
-// Per evaluation (quad g of the wavefront), half-word i at byte 32 * i + 2 * g
-// of the block (one shift and add; two quads share a dword, which the LDS
-// serves like any other access to one bank):
-//   i = c          record of chunk c, as in LayoutPacked: bits 0-8 next chunk of
-//                  its list (its own id: last), bit 9 phase, bits 10-14 order
-//   i = 512 + q    head of list q = 16 * dimension + class
-//   i = 576 + q    record of the list's last chunk, 0xffff while it is empty
-// The lists of dimension j are popped by lane j only; a completion appends to a
-// list of another dimension (or its own), so appends are made one at a time
-// per quad, in chunk-id order when several stages end at one instant, and the
-// owner learns of them through a quad-wide OR of (dimension, class) bits.
+// A pass of the loop delivers one completion per evaluation: the quad agrees on
+// the chunk (the lowest id among the stages that end now), the lane that owns
+// the dimension it waits for next appends it to its list, and every idle lane
+// with chunks waiting starts one.  All that a lane reads or writes in LDS is its
+// own dimension's, so nothing has to be ordered between lanes, and a pass is two
+// dependent LDS trips: the ends of the list served (and of the one appended to),
+// then the link behind its first chunk together with what the stage does.
+// (Before, with the lane whose stage ends appending, one loop round per completion
+// and the stage derived from the order field: 133 vector instructions a pass, now
+// some 80; 512-chunk sweep of 65,536 networks, 8 thresholds x 2 policies, 47.3 ->
+// 33.9 ms.)
+//
+// A record names a chunk and its state: bits 0-8 the chunk, 9-13 its order's
+// place among those of D dimensions, 14 the phase (up to three dimensions the
+// phase may follow the order in bit 12).  Lists hold records, a link
+// the record of the next chunk, so nothing else is kept per chunk.
+//
+// Per evaluation (quad g of the wavefront): link of chunk c, 16 bits, at byte
+// 32 * c + 2 * g; first | last << 16 of list q = kClasses * dimension + class at
+// byte 32 * kChunks + 64 * q + 4 * g.  (One shift and add; the quads' words of
+// one index are in different banks.)
 #pragma once
 
 #include "themis_packed.hpp"
+#include "themis_ring.hpp"
 
 namespace themis {
 
+template <uint32_t kChunks, uint32_t kClasses, uint32_t kOrderBits = 5>
 struct LayoutQuad {
-  static constexpr uint32_t kCap = 512;
+  static constexpr uint32_t kCap = kChunks, kPerDim = kClasses;
+  static constexpr uint32_t kPhaseBit = 9u + kOrderBits;   // of a record
   static constexpr uint32_t kQuads = (uint32_t)kBlock / 4u;
-  static constexpr uint32_t kHeadBase = kCap;
-  static constexpr uint32_t kTailBase = kCap + 64u;
-  static constexpr uint32_t kHalves = kCap + 128u;
-  static constexpr uint32_t kBlockWords = kHalves / 2u * kQuads;  // 20 KiB per wavefront
-  static constexpr uint32_t kWavesPerSimd = 2;
+  static constexpr uint32_t kEndsAt = 32u * kChunks;
+  static constexpr uint32_t kBytes = kEndsAt + 64u * 4u * kClasses;
   static constexpr uint32_t kIdMask = 0x1ffu;
-  static constexpr uint32_t kEmpty = 0xffffu;  // (a record's bit 15 is never set)
-  static __device__ __forceinline__ uint16_t* half(uint8_t* base, uint32_t i) {
-    return (uint16_t*)(base + (i << 5));
+  static constexpr uint32_t kWavesPerSimd = 2;
+  // link of the chunk of record rec (the shifts end in an address: one instruction each)
+  static __device__ __forceinline__ uint16_t* link(uint8_t* block, uint32_t rec) {
+    return (uint16_t*)(block + (((rec << 5) & (kIdMask << 5)) | ((threadIdx.x >> 2) * 2u)));
   }
-  static __device__ __forceinline__ uint16_t* record(uint8_t* b, uint32_t c) { return half(b, c & kIdMask); }
-  static __device__ __forceinline__ uint16_t* head(uint8_t* b, uint32_t q) { return half(b, kHeadBase + (q & 63u)); }
-  static __device__ __forceinline__ uint16_t* tail(uint8_t* b, uint32_t q) { return half(b, kTailBase + (q & 63u)); }
-  static __device__ __forceinline__ void init_chunk(uint8_t* b, uint32_t c, uint32_t code,
-                                                    uint32_t state0, uint32_t D) {
-    *record(b, c) = (uint16_t)(c | ((state0 >> 4) << 9) | (LayoutPacked<512>::order_field(code, D) << 10));
+  // ends of the lane's list of a class
+  static __device__ __forceinline__ uint32_t* ends(uint8_t* block, uint32_t cls) {
+    return (uint32_t*)(block + kEndsAt + (threadIdx.x >> 2) * 4u + 64u * kPerDim * (threadIdx.x & 3u) + (cls << 6));
   }
 };
 
@@ -81,160 +86,299 @@ __device__ __forceinline__ double quad_min_f64(double v) {
                        (int)quad_swap2((uint32_t)__double2loint(v)));
   return min_f64(v, o);
 }
+// The later of two doubles; of a quiet NaN and a number the number.
+__device__ __forceinline__ double max_f64(double a, double b) {
+  double r;
+  asm("v_max_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+  return r;
+}
+
+// Place of an order code among the orders of D dimensions (lexicographic).
+__device__ __forceinline__ uint32_t quad_order(uint32_t code, uint32_t D) {
+  const uint32_t r = ring_order_rank(code, D);
+  return D >= 4u ? r : D == 3u ? r / 6u * 2u + r % 6u / 2u : r / 6u;
+}
+
+// What the stage of a chunk on dimension k does, as far as it does not depend on
+// the sizes: by (dimensions, stand-alone Reduce-Scatter or not), order + 32 *
+// phase, k.  Bits 0-2 the dimension the chunk waits for next (4: it is finished),
+// 9-14 its state then, 16-21 four times the mask of its reduced dimensions then,
+// 24-27 the mask of the dimensions before k in its order.
+struct QuadStages {
+  uint32_t v[8][64][4];
+  uint8_t code[4][24];   // the order codes themselves, by (dimensions - 1)
+};
+constexpr QuadStages quad_stages() {
+  QuadStages t{};
+  for (uint32_t D = 1; D <= 4; ++D) {
+    uint32_t perm[4] = {0, 1, 2, 3}, n = 0;
+    const uint32_t full = (1u << D) - 1u;
+    for (uint32_t i = 0; i < 256u; ++i) {   // field j of i, last field fastest: lexicographic
+      bool ok = true;
+      uint32_t seen = 0;
+      for (uint32_t j = 0; j < 4u; ++j) {
+        perm[j] = (i >> (2u * (3u - j))) & 3u;
+        if (j < D ? perm[j] >= D || ((seen >> perm[j]) & 1u) != 0u : perm[j] != 0u) ok = false;
+        if (j < D) seen |= 1u << perm[j];
+      }
+      if (!ok) continue;
+      uint32_t before = 0;
+      t.code[D - 1u][n] = 0;
+      for (uint32_t j = 0; j < D; ++j) {
+        t.code[D - 1u][n] = (uint8_t)(t.code[D - 1u][n] | perm[j] << (2u * j));
+        const uint32_t k = perm[j], with = before | (1u << k);
+        for (uint32_t alone = 0; alone < 2u; ++alone) {
+          const bool last = with == full;
+          const uint32_t to = last ? (alone ? 4u : k) : perm[j + 1u < 4u ? j + 1u : 3u];
+          t.v[(D - 1u) * 2u + alone][n][k] =
+              to | (n + (last ? 32u : 0u)) << 9 | (4u * with) << 16 | before << 24;
+          t.v[(D - 1u) * 2u + alone][32u + n][k] =
+              (j == 0u ? 4u : perm[j - (j ? 1u : 0u)]) | (n + 32u) << 9 | (4u * before) << 16 | before << 24;
+        }
+        before = with;
+      }
+      ++n;
+    }
+  }
+  return t;
+}
+__device__ const QuadStages g_quad_stages = quad_stages();
+
+// Stages of a chunk on the lane's dimension where the NPU counts are powers of two.
+template <bool kFix>
+struct QuadPow2 {
+  static constexpr uint32_t kClassMask = 15u;
+  double coef, fix;
+  uint64_t ranktab;
+  uint32_t epack, base_lo, base_hi, at;
+  __device__ __forceinline__ QuadPow2(const Scenario& s, const Pow2Model& m, uint32_t k)
+      : coef(sel4((int)k, s.coef[0], s.coef[1], s.coef[2], s.coef[3])),
+        fix(kFix ? sel4((int)k, s.fix[0], s.fix[1], s.fix[2], s.fix[3]) : 0.0), ranktab(m.ranktab),
+        epack(m.fs.epack), base_lo((uint32_t)__double2loint(m.fs.base)),
+        base_hi((uint32_t)__double2hiint(m.fs.base)),
+        at((((uint32_t)s.D - 1u) * 2u + (m.rs_only() ? 1u : 0u)) * 1024u + 4u * k) {}
+  // rec: the chunk's record; the word that says what its completion does, without the chunk
+  __device__ __forceinline__ uint32_t stage(uint32_t rec, double& time) const {
+    const uint32_t v = *(const uint32_t*)((const uint8_t*)&g_quad_stages + (((rec >> 5) & 0x3f0u) | at));
+    const int e = (int)esum(epack, v >> 24);
+    time = __hiloint2double((int)base_hi + __mul24(e, -0x100000), (int)base_lo) * coef;
+    if (kFix) time = fix + time;
+    const uint32_t cls = (uint32_t)(ranktab >> ((v >> 16) & 63u)) & 15u;
+    return (v & 0x7e07u) | cls << 3;
+  }
+};
+
+// Stages on the lane's dimension from tables of the evaluation itself, whatever
+// its NPU counts are: a division by an arbitrary count rounds, so a chunk's sizes
+// and times depend on its whole order, and are made by the model's own sequence
+// of divisions and multiplications, once per order that some chunk has.
+// In LDS behind the lists (quad g): time of order o on dimension k, binary64, at
+// 128 * (4 * o + k) + 8 * g, and what the completion does, 16 bits as in
+// simulate_quad, at 32 * (4 * state + k) + 2 * g (state: order and phase as in a
+// record); size classes of (state, k) while these are made, 8 bits, at
+// 16 * (4 * state + k) + g.
+// L: layout; kDims: up to three dimensions (six orders, at most twelve sizes that
+// wait for one dimension), or four (24, 48).
+template <typename L, uint32_t kDims>
+struct QuadTable {
+  static constexpr uint32_t kOrders = kDims == 4u ? 24u : 6u;
+  static constexpr uint32_t kStates = (L::kPhaseBit == 14u ? 32u : 8u) + kOrders;
+  static constexpr uint32_t kTimes = L::kBytes, kDoes = kTimes + 512u * kOrders;
+  // (the classes' place is the links', where it is large enough)
+  static constexpr bool kInLinks = 64u * kStates <= L::kEndsAt;
+  static constexpr uint32_t kClassesAt = kInLinks ? 0u : kDoes + 128u * kStates;
+  static constexpr uint32_t kBytes = kDoes + 128u * kStates + (kInLinks ? 0u : 64u * kStates);
+  static_assert(64u * 4u * L::kPerDim >= 512u * kOrders, "the sizes of one phase fit the place of the lists");
+  uint8_t* block;
+  double t_min;
+  uint32_t cls0;
+  static __device__ __forceinline__ uint32_t quad8() { return (threadIdx.x >> 2) * 8u; }
+  static __device__ __forceinline__ double* f64_at(uint8_t* b, uint32_t o, uint32_t k) {
+    return (double*)(b + (o << 9 | k << 7 | quad8()));
+  }
+  static __device__ __forceinline__ uint16_t* does_at(uint8_t* b, uint32_t state, uint32_t k) {
+    return (uint16_t*)(b + kDoes + (state << 7 | k << 5 | (threadIdx.x >> 2) * 2u));
+  }
+  static __device__ __forceinline__ uint8_t* class_at(uint8_t* b, uint32_t state, uint32_t k) {
+    return b + kClassesAt + (state << 6 | k << 4 | threadIdx.x >> 2);
+  }
+  static __device__ __forceinline__ uint32_t state_of(uint32_t order, uint32_t phase) {
+    return order | phase << (L::kPhaseBit - 9u);
+  }
+  // used: bit o says that some chunk has order o.  All lanes of the wavefront.
+  __device__ __forceinline__ QuadTable(const Scenario& s, double chunk, bool scf, uint32_t used, void* lds)
+      : block((uint8_t*)lds), t_min(inf64()), cls0(0u) {
+    const uint32_t k = threadIdx.x & 3u, D = min((uint32_t)s.D, kDims);
+    const bool gather = s.ctype == THEMIS_COLL_ALL_GATHER, rs_only = s.ctype == THEMIS_COLL_REDUCE_SCATTER;
+    uint8_t* const rs = block + kTimes;        // sizes before the Reduce-Scatter stages, then the times
+    uint8_t* const ag = block + L::kEndsAt;    // sizes before the All-Gather stages
+    // sizes: lane j of the quad takes the orders j, j + 4, ..  (NaN, below no
+    // size, where there is none)
+    for (uint32_t o = k; o < kOrders; o += 4u) {
+      const bool has = ((used >> o) & 1u) != 0u;
+      const uint32_t code = has ? (uint32_t)g_quad_stages.code[(D - 1u) & 3u][o] : 0xe4u;
+      double x = has ? chunk : nan64();
+      for (uint32_t j = 0; j < kDims; ++j) {
+        const uint32_t kj = j < D ? (code >> (2u * j)) & 3u : j;
+        *f64_at(rs, o, kj) = j < D && !gather ? x : nan64();
+        if (!gather && j < D) x = x / (double)sel4((int)kj, s.P[0], s.P[1], s.P[2], s.P[3]);
+      }
+      for (uint32_t j = kDims; j-- > 0u;) {
+        const uint32_t kj = j < D ? (code >> (2u * j)) & 3u : j;
+        *f64_at(ag, o, kj) = j < D && !rs_only ? x : nan64();
+        if (j < D) x = x * (double)sel4((int)kj, s.P[0], s.P[1], s.P[2], s.P[3]);
+      }
+    }
+    __syncthreads();
+    // classes: the number of smaller sizes among those that wait for the lane's
+    // dimension, a comparison with each (reads that do not wait for each other)
+    for (uint32_t phase = gather ? 1u : 0u; phase < (rs_only ? 1u : 2u); ++phase) {
+      for (uint32_t m = k < D ? used : 0u; m != 0u; m &= m - 1u) {
+        const uint32_t o = (uint32_t)__builtin_ctz(m);
+        const double v = *f64_at(phase ? ag : rs, o, k);
+        uint32_t r = 0u;
+        if (scf) {
+#pragma unroll
+          for (uint32_t o2 = 0; o2 < kOrders; ++o2)
+            r += (*f64_at(rs, o2, k) < v ? 1u : 0u) + (*f64_at(ag, o2, k) < v ? 1u : 0u);
+        }
+        *class_at(block, state_of(o, phase), k) = (uint8_t)r;
+        // (a chunk waits for its first stage at the same size whatever its order)
+        const uint32_t code = g_quad_stages.code[(D - 1u) & 3u][o];
+        if (((code >> (gather ? 2u * (D - 1u) : 0u)) & 3u) == k && phase == (gather ? 1u : 0u)) cls0 = r;
+      }
+    }
+    __syncthreads();
+    const double coef = sel4((int)k, s.coef[0], s.coef[1], s.coef[2], s.coef[3]);
+    const double fix = sel4((int)k, s.fix[0], s.fix[1], s.fix[2], s.fix[3]);
+    const double grow = gather ? (double)sel4((int)k, s.P[0], s.P[1], s.P[2], s.P[3]) : 1.0;
+    for (uint32_t m = k < D ? used : 0u; m != 0u; m &= m - 1u) {
+      const uint32_t o = (uint32_t)__builtin_ctz(m);
+      const double moved = gather ? *f64_at(ag, o, k) * grow : *f64_at(rs, o, k);
+      double time = moved * coef;
+      if (s.has_fix) time = fix + time;
+      *f64_at(rs, o, k) = time;
+      t_min = min_f64(t_min, time);
+      for (uint32_t phase = gather ? 1u : 0u; phase < (rs_only ? 1u : 2u); ++phase) {
+        const uint32_t v = g_quad_stages.v[(D - 1u) * 2u + (rs_only ? 1u : 0u)][32u * phase + o][k];
+        const uint32_t to = v & 7u, next = state_of(o, (v >> 14) & 1u);
+        const uint32_t cls = to < 4u ? *class_at(block, next, to) : 0u;
+        *does_at(block, state_of(o, phase), k) = (uint16_t)(to | cls << 3 | next << 9);
+      }
+    }
+    t_min = quad_min_f64(t_min);
+    __syncthreads();
+  }
+  __device__ __forceinline__ uint32_t stage(uint32_t rec, double& time) const {
+    const uint32_t k = threadIdx.x & 3u;
+    time = *(const double*)(block + kTimes + ((rec & 0x3e00u & (L::kPhaseBit == 14u ? ~0u : 0xe00u)) | (k << 7 | quad8())));
+    return *(const uint16_t*)(block + kDoes +
+                              (((rec >> 2) & (L::kPhaseBit == 14u ? 0x1f80u : 0x780u)) | (k << 5 | (threadIdx.x >> 2) * 2u)));
+  }
+};
+
+// One evaluation's queues on the lane's dimension, before the simulation: the
+// chunks that start here, in the order of their ids.
+template <typename L>
+struct QuadQueue {
+  uint8_t* block;
+  uint32_t first = 0u, last = 0u;
+  bool any = false;
+  __device__ __forceinline__ explicit QuadQueue(void* lds) : block((uint8_t*)lds) {}
+  __device__ __forceinline__ void add(uint32_t rec) {
+    if (any) *L::link(block, last) = (uint16_t)rec;
+    else first = rec;
+    last = rec;
+    any = true;
+  }
+};
 
 struct QuadResult {
   double t_done;
-  bool ok;  // false: leave the evaluation to the follow-up passes
+  double busy;         // of the lane's dimension
+  uint32_t started;    // operations of the lane's dimension
+  bool ok;             // false: leave the evaluation to the follow-up passes
 };
 
-// All four lanes of a quad call this with the same scenario and model; base is
-// the quad's first byte in the wavefront's block (block + 2 * quad), whose
-// records were written with LayoutQuad::init_chunk().  Power-of-two model only,
-// times only.  Every lane of the wavefront has to be here (the quads exchange
-// values with lane-crossing moves and leave the loop together).
-template <bool kFix>
-__device__ __forceinline__ QuadResult simulate_quad(const Scenario& s, const Pow2Model& model,
-                                                    uint8_t* base, bool take_part) {
-  using L = LayoutQuad;
-  const uint32_t k = threadIdx.x & 3u;  // the lane's dimension
-  const uint32_t D = (uint32_t)s.D;
-  const uint32_t C = take_part ? s.C : 0u;
-  const uint32_t full = (1u << D) - 1u;
-  const uint32_t kbit = 1u << k;
-  const double kInf = inf64();
-  const uint32_t epack = model.fs.epack;
-  const uint64_t ranktab = model.ranktab;
-  const bool rs_only = model.rs_only();
-  const double coef = sel4((int)k, s.coef[0], s.coef[1], s.coef[2], s.coef[3]);
-  const double fix = kFix ? sel4((int)k, s.fix[0], s.fix[1], s.fix[2], s.fix[3]) : 0.0;
-
-  double f = nan64();    // finish time of the stage the dimension serves, NaN when idle
-  uint32_t sv = 0u;      // that stage: bits 0-5 list to join, 6-11 upper record bits then,
-                         // 12 chunk is done, 15-23 the chunk
-  uint32_t cm = 0u;      // bit c: list 16 * k + c holds chunks
-  uint32_t started = 0u;
-
-  for (uint32_t c = 0; c < 16u; ++c) *L::tail(base, 16u * k + c) = (uint16_t)L::kEmpty;
-
-  // chunk c (upper record bits `up`: phase | order << 1) becomes the last of list q
-  auto push = [&](uint32_t q, uint32_t c, uint32_t up) {
-    uint16_t* tp = L::tail(base, q);
-    const uint32_t t = *tp;
-    const bool had = t != L::kEmpty;
-    const uint32_t rec = c | (up << 9);
-    *L::record(base, c) = (uint16_t)rec;  // own id: end of list
-    uint16_t* dst = had ? L::record(base, t & L::kIdMask) : L::head(base, q);
-    *dst = (uint16_t)(had ? ((t & ~L::kIdMask) | c) : c);
-    *tp = (uint16_t)rec;
-  };
-
-  // a6: every chunk waits at the dimension of its first stage, in chunk-id
-  // order; each lane takes the chunks that start on its own dimension
-  {
-    const uint32_t mask0 = model.state0() & 15u, phase0 = (model.state0() >> 4) & 1u;
-    const uint32_t pos0 = (uint32_t)__builtin_popcount(mask0) - phase0;
-    const uint32_t cls0 = (uint32_t)(ranktab >> (4u * mask0)) & 15u;
-    for (uint32_t c = 0; c < C; ++c) {
-      const uint32_t up = (uint32_t)*L::record(base, c) >> 9;
-      if (PackedOrder(up >> 1).at(pos0) == k) {
-        push(16u * k + cls0, c, up);
-        cm |= 1u << cls0;
-      }
-    }
+// All four lanes of a quad call this with the same scenario and their own
+// dimension's queue; cls0: the size class its chunks wait in.  Every lane of the
+// wavefront has to be here (the quads exchange values with lane-crossing moves
+// and leave the loop together), with `stages` = 0 where there is nothing to do.
+// put(i, entry): the lane's dimension has started operation i (kPut).
+template <typename L, bool kPut, typename Model, typename Put>
+__device__ __forceinline__ QuadResult simulate_quad(const Model& model, QuadQueue<L>& queue, uint32_t cls0,
+                                                    uint32_t stages, double t_min, Put put) {
+  const uint32_t k = threadIdx.x & 3u;   // the lane's dimension
+  uint8_t* const block = queue.block;
+  using Mask = typename std::conditional<(L::kPerDim > 32u), uint64_t, uint32_t>::type;
+  Mask lists = 0;          // bit c: list of class c holds chunks
+  if (queue.any) {
+    *L::ends(block, cls0) = queue.first | queue.last << 16;
+    lists = (Mask)1 << cls0;
   }
-  // the other lanes' records are written: their links must not be read before
-  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-
-  double now = 0.0;
-  bool went_on = true;  // every stage moved the clock
+  double f = nan64();      // finish time of the stage the dimension serves, NaN when idle
+  double busy = 0.0, now = 0.0;
+  uint32_t sv = 0u;        // that stage: chunk << 16 | what its completion does
+  uint32_t started = 0u;
   const uint32_t max_steps = 2u * (uint32_t)kMaxDims * L::kCap + 16u;
   for (uint32_t step = 0; step <= max_steps; ++step) {
-    // a7: an idle dimension with waiting chunks starts the first chunk of its
-    // lowest class (smallest resident size); all dimensions at once
-    if (!(f == f) && cm != 0u) {
-      const uint32_t cls = (uint32_t)__builtin_ctz(cm);
-      const uint32_t q = 16u * k + cls;
-      uint16_t* hp = L::head(base, q);
-      const uint32_t h = *hp;
-      const uint32_t w = *L::record(base, h);
-      const uint32_t nx = w & L::kIdMask;
-      if (nx == h) {
-        cm &= ~(1u << cls);
-        *L::tail(base, q) = (uint16_t)L::kEmpty;
-      } else {
-        *hp = (uint16_t)nx;
-      }
-      const bool ag = ((w >> 9) & 1u) != 0u;
-      const PackedOrder ord(w >> 10);
-      // where k stands in the chunk's order, and the dimensions before it
-      const bool p0 = k == ord.o0, p1 = k == ord.o1, p2 = k == ord.o2;
-      const uint32_t before = p0 ? 0u : p1 ? (1u << ord.o0) : p2 ? ord.first_two
-                                                                 : (ord.first_two | (1u << ord.o2));
-      // what the completion of this stage will do (as in simulate_packed)
-      const uint32_t with_k = before | kbit;
-      const bool last_rs = !ag && with_k == full;
-      const bool finished = ag ? p0 : (last_rs && rs_only);
-      const uint32_t mask = ag ? before : with_k;
-      const uint32_t prev = p1 ? ord.o0 : p2 ? ord.o1 : ord.o2;
-      const uint32_t succ = p0 ? ord.o1 : p1 ? ord.o2 : ord.o3;
-      const uint32_t kn = last_rs ? k : ag ? prev : succ;
-      const uint32_t up = (w >> 9) | (last_rs ? 1u : 0u);
-      const uint32_t qn = 16u * kn + ((uint32_t)(ranktab >> (4u * mask)) & 15u);
-      sv = qn | ((up & 63u) << 6) | (finished ? 0x1000u : 0u) | (h << 15);
-      // bytes moved on k = resident size before the chunk's Reduce-Scatter on k
-      double t = scale_down(model.fs.base, esum(epack, before)) * coef;
-      if (kFix) t = fix + t;
-      f = now + t;
-      went_on = went_on && f > now;
-      ++started;
-    }
-    // (appends below read what the pops above have stored)
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     // a8: the clock moves to the earliest completion of the evaluation
     const double next = quad_min_f64(f);
-    const bool running = next < kInf;   // NaN: nothing runs; +inf: overflow
-    if (__builtin_amdgcn_ballot_w64(running) == 0ull) break;
-    if (running) now = next;
-    // the stages that end now hand their chunks on, one at a time per quad, the
-    // lowest chunk id first, so that equal arrival times are appended in
-    // chunk-id order
-    bool pending = running && f == next;
-    if (pending) f = nan64();
-    uint32_t told_lo = 0u, told_hi = 0u;  // bit 16 * (dimension & 1) + class, dimensions 0-1 | 2-3
-    do {
-      // (every lane takes part in the exchange: no lane-crossing move may sit
-      // behind a condition that differs inside a quad)
-      const uint32_t key = pending ? sv : ~0u;
-      const uint32_t first = quad_min_u32(key);
-      const bool mine = pending && key == first;
-      if (mine) {
-        if ((sv & 0x1000u) == 0u) {
-          const uint32_t qn = sv & 63u;
-          push(qn, sv >> 15, (sv >> 6) & 63u);
-          const uint32_t bit = 1u << (qn & 31u);
-          told_lo |= qn < 32u ? bit : 0u;
-          told_hi |= qn < 32u ? 0u : bit;
-        }
-        pending = false;
-      }
-      // the next append of the quad must find this one's stores
-      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-    } while (__builtin_amdgcn_ballot_w64(pending) != 0ull);
-    told_lo = quad_or(told_lo);
-    told_hi = quad_or(told_hi);
-    cm |= ((k & 2u ? told_hi : told_lo) >> (16u * (k & 1u))) & 0xffffu;
+    const uint64_t running = __builtin_amdgcn_ballot_w64(next == next);
+    if (step != 0u && running == 0ull) break;
+    now = max_f64(now, next);
+    // of the stages that end now the one of the lowest chunk hands it on
+    const bool ends = f == next;
+    const uint64_t ending = __builtin_amdgcn_ballot_w64(ends);
+    const uint32_t key = ends ? sv : ~0u;
+    const uint32_t given = quad_min_u32(key);
+    if (ends && key == given) f = nan64();
+    // (dimension 4 and, where nothing ends, 7: nobody's)
+    const bool append = (given & 7u) == k;
+    const uint32_t to = (given >> 3) & 63u;
+    const Mask to_bit = (Mask)1 << to;
+    const bool had = (lists & to_bit) != 0;
+    if (append) lists |= to_bit;
+    // an idle dimension with waiting chunks starts the first chunk of its lowest
+    // class (smallest resident size), once all completions of the instant are delivered
+    bool starts = !(f == f) && lists != 0;
+    if (__builtin_popcountll(ending) * 4 != __builtin_popcountll(running)) {   // more than one in some quad
+      uint32_t mine = (uint32_t)(ending >> (threadIdx.x & 60u)) & 15u;
+      asm volatile("" : "+v"(mine));   // (rare: a branch, not selects in every pass)
+      starts = starts && (mine & (mine - 1u)) == 0u;
+    }
+    const uint32_t from = sizeof(Mask) == 8u ? (uint32_t)__builtin_ctzll(lists) : (uint32_t)__builtin_ctz((uint32_t)lists);
+    uint32_t* const from_at = L::ends(block, from);
+    uint32_t* const to_at = L::ends(block, to);
+    const uint32_t ends_from = *from_at, ends_to = *to_at;   // (used only where there is such a list)
+    const uint32_t rec = (given & 0x7e00u) | given >> 16;
+    if (append) {
+      if (had) *L::link(block, ends_to >> 16) = (uint16_t)rec;
+      *to_at = (had ? ends_to & 0xffffu : rec) | rec << 16;
+    }
+    if (starts) {
+      const bool same = append && to == from;
+      const uint32_t head = same && !had ? rec : ends_from & 0xffffu;
+      const uint32_t last = same ? rec : ends_from >> 16;
+      const uint32_t link = *L::link(block, head);
+      double time;
+      const uint32_t does = model.stage(head, time);
+      if (head == last) lists &= lists - 1u;
+      else *(uint16_t*)from_at = (uint16_t)link;
+      f = now + time;
+      busy = busy + time;
+      sv = (head & L::kIdMask) << 16 | does;
+      if (kPut) put(started, (head & L::kIdMask) << 1 | ((head >> L::kPhaseBit) & 1u));
+      ++started;
+    }
   }
-
   QuadResult res;
-  const double t_min = model.t_min(D);
-  const uint32_t stages = model.one_phase() ? D : 2u * D;
-  const bool settled = !(f == f) && cm == 0u && went_on;
-  const uint32_t started_all = quad_sum(started);
-  const uint32_t settled_all = quad_min_u32(settled ? 1u : 0u);
-  res.ok = started_all == stages * s.C && settled_all == 1u && (now + 0.25 * t_min > now);
   res.t_done = now;
+  res.busy = busy;
+  res.started = started;
+  // every stage ran and completed, and none was too short to move the clock
+  const uint32_t settled = quad_min_u32(!(f == f) && lists == 0 ? 1u : 0u);
+  res.ok = quad_sum(started) == stages && settled != 0u && now < inf64() && now + 0.25 * t_min > now;
   return res;
 }
 

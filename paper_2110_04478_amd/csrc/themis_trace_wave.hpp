@@ -408,30 +408,20 @@ __device__ __forceinline__ WaveOutcome trace_wave_simulate(const Scenario& s, ui
   __syncthreads();
 
   // collectives in the order of their releases (ties: by number)
-  double mine[kTraceMaxColl / 64u];
-#pragma unroll
-  for (uint32_t j = 0; j < kTraceMaxColl / 64u; ++j) {
-    const uint32_t q = lane + 64u * j;
-    mine[j] = 0.0;
-    if (q >= Q) continue;
-    mine[j] = has_release ? release[q] : 0.0;
+  for (uint32_t q = lane; q < Q; q += 64u) {
     uint32_t at = q;
     if (has_release) {
+      const double v = release[q];
       at = 0u;
-      for (uint32_t p = 0; p < Q; ++p) at += release[p] < mine[j] || (release[p] == mine[j] && p < q) ? 1u : 0u;
+      for (uint32_t p = 0; p < Q; ++p) at += release[p] < v || (release[p] == v && p < q) ? 1u : 0u;
+      sorted[at] = v;
     }
     order[at] = (uint16_t)q;
   }
   __syncthreads();
-  if (has_release) {
-#pragma unroll
-    for (uint32_t j = 0; j < kTraceMaxColl / 64u; ++j)
-      if (lane + 64u * j < Q) mine[j] = release[order[lane + 64u * j]];
-    __syncthreads();
-#pragma unroll
-    for (uint32_t j = 0; j < kTraceMaxColl / 64u; ++j)
-      if (lane + 64u * j < Q) release[lane + 64u * j] = mine[j];
-  }
+  if (has_release)
+    for (uint32_t q = lane; q < Q; q += 64u) release[q] = sorted[q];
+  __syncthreads();
 
   // Size ranks: the number of smaller sizes among those that can wait (equal
   // sizes share a rank).  The collectives' sizes under one mask (division mode:

@@ -1,0 +1,60 @@
+"""GPU parity of single collectives on each of the two mappings of large batches,
+whatever the batch size would choose: one lane per scenario (up to 64 chunks),
+and four.  A wavefront holds 16 scenarios in quads, so the edges are 16
+scenarios, the chunk capacities, and the scenarios of other NPU counts: of up to
+three dimensions in a second turn of their wavefront (with the powers of two
+where those are few: 16 in a wavefront of lanes), of four dimensions in the
+follow-up kernel, on tables of up to 24 orders and 48 sizes per dimension."""
+import numpy as np
+import pytest
+
+from test_gpu_mapping import CASES as MAPPING_CASES
+from test_gpu_parity import (check_batch, gpu, w, _with_collective_types,  # noqa: F401
+                             _with_fixed_delay)
+
+pytestmark = pytest.mark.gpu
+
+
+def _mixed_counts(n, seed, every, dims=None, max_chunks=40):
+    """Powers of two, and every so many scenarios other NPU counts."""
+    b = w().mixed(n, seed=seed, max_chunks=max_chunks)
+    if dims:
+        b.ndims[:] = dims
+    other = np.arange(n) % every != 0
+    b.npus[:, other] = np.random.default_rng(seed).integers(3, 40, (4, int(other.sum())))
+    return b
+
+
+CASES = dict(MAPPING_CASES)
+CASES.update({
+    "1 scenario": lambda W: W.mixed(1, seed=901),
+    "17 scenarios": lambda W: W.mixed(17, seed=902, pow2=False),
+    "8 of 64 powers of two": lambda W: _mixed_counts(135, 903, 8),
+    "32 of 64 powers of two": lambda W: _mixed_counts(135, 904, 2),
+    "four dimensions, other counts": lambda W: _mixed_counts(200, 905, 5, dims=4, max_chunks=64),
+    "four dimensions, 100 chunks": lambda W: _mixed_counts(70, 906, 3, dims=4, max_chunks=100),
+    "three dimensions, 300 chunks": lambda W: _mixed_counts(40, 907, 3, dims=3, max_chunks=300),
+    "types, delays, other counts": lambda W: _with_fixed_delay(_with_collective_types(
+        _mixed_counts(300, 908, 3), 13), 14),
+})
+
+
+@pytest.mark.parametrize("case", list(CASES))
+@pytest.mark.parametrize("mapping", ["lane", "quad"])
+def test_lanes_and_quads_agree_with_the_oracle(gpu, oracle, mapping, case):
+    b = CASES[case](w())
+    gpu.themis_set_batch_mapping(gpu.MAPPING_LANE)
+    gpu.themis_set_sweep_mapping({"lane": gpu.MAPPING_LANE, "quad": gpu.MAPPING_QUAD}[mapping])
+    try:
+        check_batch(gpu, oracle, b)
+        check_batch(gpu, oracle, b, queue=False, workspace=b.max_chunks > 64)
+    finally:
+        gpu.themis_set_batch_mapping(gpu.MAPPING_AUTO)
+        gpu.themis_set_sweep_mapping(gpu.MAPPING_AUTO)
+
+
+@pytest.mark.parametrize("n,chunks", [(16385, 2), (32769, 2), (49152, 2), (49153, 2), (65537, 2), (17000, 70)])
+def test_batch_sizes_around_the_lines(gpu, oracle, n, chunks):
+    """Where the mapping changes, and where the follow-up kernel's workgroups look
+    at more scenarios each; all kinds of NPU counts."""
+    check_batch(gpu, oracle, _mixed_counts(n, 910 + chunks, 2, max_chunks=chunks), threads=16)
