@@ -624,7 +624,7 @@ simulate_quad_kernel(themis_batch_t b, const uint8_t* __restrict__ orders, doubl
                      void* __restrict__ queue_order, int entry_bytes, double* __restrict__ busy,
                      unsigned long long hand_over) {
   using L3 = LayoutQuad<L::kCap, 12u, 3u>;
-  constexpr uint32_t kLdsBytes = kOthers && QuadTable<L3, 3>::kBytes > L::kBytes ? QuadTable<L3, 3>::kBytes : L::kBytes;
+  constexpr uint32_t kLdsBytes = kOthers && QuadTable<L3, 3>::kBytes > QuadPow2<L, kFix>::kBytes ? QuadTable<L3, 3>::kBytes : QuadPow2<L, kFix>::kBytes;
   __shared__ uint64_t lds_block[(kLdsBytes + 7u) / 8u];
   const uint32_t k = threadIdx.x & 3u;
   const uint64_t first = (uint64_t)blockIdx.x * L::kQuads, at = first + (threadIdx.x >> 2);
@@ -639,7 +639,10 @@ simulate_quad_kernel(themis_batch_t b, const uint8_t* __restrict__ orders, doubl
   const bool eligible = fast_eligible(s, S / (double)s.C, L::kCap, fs) && ok;
   const bool others = kOthers && __builtin_amdgcn_ballot_w64(ok && !eligible && D < 4u) != 0ull;
   const bool tables = others && ok && D < 4u;
-  const bool fast = eligible && !tables;
+  // a few powers of two of four dimensions beside other counts go with those
+  const bool few = __builtin_popcountll(__builtin_amdgcn_ballot_w64(eligible && !tables)) <= 16 &&
+                   __builtin_amdgcn_ballot_w64(ok && !eligible && D == 4u) != 0ull;
+  const bool fast = eligible && !tables && !few;
   if (!others || __builtin_amdgcn_ballot_w64(exists && !tables) != 0ull) {
     QuadQueue<L> queue(lds_block);
     uint32_t bad = 0u;
@@ -647,7 +650,7 @@ simulate_quad_kernel(themis_batch_t b, const uint8_t* __restrict__ orders, doubl
       quad_codes(b, orders, i, s.C, [&](uint32_t c, uint32_t code) {
         if ((c & 3u) == k && !order_code_ok(code, s.D)) bad = 1u;
         if ((code & 3u) == k)
-          queue.add(c | (quad_order(stored_code(s, fs, code), D) & 31u) << 9 | (fs.gather ? 1u << L::kPhaseBit : 0u));
+          queue.add(c | ((quad_row(D) + quad_order(stored_code(s, fs, code), D)) & 31u) << 9 | (fs.gather ? 1u << L::kPhaseBit : 0u));
       });
     const bool runs = fast && quad_sum(bad) == 0u;
     if (!runs) queue.any = false;
@@ -655,7 +658,7 @@ simulate_quad_kernel(themis_batch_t b, const uint8_t* __restrict__ orders, doubl
     uint8_t* const row = queue_order ? (uint8_t*)queue_order + ((size_t)i * kMaxDims + k) * 2u * b.max_chunks * (uint32_t)entry_bytes
                                      : nullptr;
     const QuadResult r = simulate_quad<L, kQueueOrder != kNoQueueOrder>(
-        QuadPow2<kFix>(s, pow2, k), queue, (uint32_t)(pow2.ranktab >> (4u * (fs.state0 & 15u))) & 15u,
+        QuadPow2<L, kFix>(s, pow2, k, lds_block), queue, (uint32_t)(pow2.ranktab >> (4u * (fs.state0 & 15u))) & 15u,
         runs ? (pow2.one_phase() ? D : 2u * D) * s.C : 0u, pow2.t_min(D),
         [&](uint32_t e, uint32_t entry) {
           if (kQueueOrder == kShorts) ((uint16_t*)row)[e] = (uint16_t)entry;
@@ -1457,7 +1460,7 @@ sweep_quad_kernel(themis_batch_t b, int n_thr, const double* __restrict__ thr, i
                   unsigned policy_mask, int n_pol, double* __restrict__ t_done,
                   unsigned long long hand_over, SweepJobs jobs) {
   using L = LayoutQuad<512, 16>;
-  __shared__ uint32_t lds_block[L::kBytes / 4u];
+  __shared__ uint32_t lds_block[QuadPow2<L, kFix>::kBytes / 4u];
   const uint32_t quad = threadIdx.x >> 2;
   const SweepSlot slot =
       kJobs ? sweep_block_slot<kBaseline>(b, jobs, L::kQuads, quad, n_thr, policy_mask, n_pol)
@@ -1487,11 +1490,11 @@ sweep_quad_kernel(themis_batch_t b, int n_thr, const double* __restrict__ thr, i
     // takes the chunks that start on its own dimension
     double load[kMaxDims];
     plan_fast(s, fs, it.themis_on, rel, it.th, load, [&](uint32_t c, uint32_t code) {
-      if ((code & 3u) == k) queue.add(c | quad_order(code, (uint32_t)s.D) << 9);
+      if ((code & 3u) == k) queue.add(c | (quad_row((uint32_t)s.D) + quad_order(code, (uint32_t)s.D)) << 9);
     });
   }
   const Pow2Model pow2(s, fs, it.scf);
-  const QuadResult r = simulate_quad<L, false>(QuadPow2<kFix>(s, pow2, k), queue, (uint32_t)pow2.ranktab & 15u,
+  const QuadResult r = simulate_quad<L, false>(QuadPow2<L, kFix>(s, pow2, k, lds_block), queue, (uint32_t)pow2.ranktab & 15u,
                                                fast ? 2u * (uint32_t)s.D * s.C : 0u, pow2.t_min((uint32_t)s.D),
                                                [](uint32_t, uint32_t) {});
   if (!writer) return;
@@ -2680,18 +2683,17 @@ static bool sweep_mapping_is_quad(uint32_t cap) {
 }
 
 // Four lanes per scenario (themis_quad.hpp) or one?  A pass of the quads' loop
-// takes a wavefront some 1,080 clocks on its own and a SIMD 340, for 16 scenarios;
+// takes a wavefront some 980 clocks on its own and a SIMD 350, for 16 scenarios;
 // the lanes' loop takes 1,300 and 620 for 64.  So quads are faster until the
 // lanes fill the GPU (65,536 scenarios have one wavefront per SIMD), and beyond 64
-// chunks always, where LDS holds back the lanes.  Measured (us, quads / lanes): 64
-// chunks, four dimensions 4,096 scenarios 222 / 307, 16,384 247 / 316, 32,768 273 /
-// 336, 65,536 363 / 336, 262,144 1,161 / 713; 3-D first-in-first-out 65,536 282 / 277;
-// 8 chunks 32,768 48 / 70, 131,072 108 / 81; 128 chunks 16,384 474 / 730, 262,144
-// 2,613 / 2,925; 250 chunks 846 / 1,438 and 3,367 / 4,413; 512 chunks 1,712 / 2,906.
-// Other NPU counts, 64 chunks (us, now / with a lane each on per-order tables): three
-// dimensions 20,000 scenarios 351 / 906, 130,000 1,033 / 2,379, four 993 / 2,549, 2,690 /
-// 8,327.
-constexpr uint64_t kQuadSimulate = 49152;
+// chunks always, where LDS held back the lanes.  Measured (us, quads / lanes): 64
+// chunks, four dimensions 8,192 scenarios 224 / 317, 32,768 273 / 336, 65,536 351 /
+// 353, 262,144 1,192 / 747; 3-D first-in-first-out 65,536 271 / 282; 8 chunks 32,768
+// 48 / 70, 131,072 108 / 81; 128 chunks 16,384 474 / 730, 262,144 2,613 / 2,925; 250
+// chunks 20,001 932 / 1,530; 512 chunks 32,768 1,853 / 3,246.  Other NPU counts, 64
+// chunks (us, now / with a lane each on per-order tables): three dimensions 20,000
+// scenarios 351 / 906, 130,000 1,033 / 2,379, four 993 / 2,549, 2,690 / 8,327.
+constexpr uint64_t kQuadSimulate = 65536;
 static bool simulate_on_quads(uint64_t n, uint32_t cap) {
   const int forced = sweep_mapping.load(std::memory_order_relaxed);
   return cap > 64u || (forced != THEMIS_MAPPING_AUTO ? forced == THEMIS_MAPPING_QUAD : n <= kQuadSimulate);

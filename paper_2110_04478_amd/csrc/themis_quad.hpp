@@ -20,8 +20,10 @@
 // then the link behind its first chunk together with what the stage does.
 // (Before, with the lane whose stage ends appending, one loop round per completion
 // and the stage derived from the order field: 133 vector instructions a pass, now
-// some 80; 512-chunk sweep of 65,536 networks, 8 thresholds x 2 policies, 47.3 ->
-// 33.9 ms.)
+// some 65; 512-chunk sweep of 65,536 networks, 8 thresholds x 2 policies, 47.3 ->
+// 29.7 ms.  A wavefront alone on its SIMD takes 980 clocks a pass, four on one 350
+// each: the first is the chain of dependent instructions and the two trips, the
+// second issue.)
 //
 // A record names a chunk and its state: bits 0-8 the chunk, 9-13 its order's
 // place among those of D dimensions, 14 the phase (up to three dimensions the
@@ -47,7 +49,7 @@ struct LayoutQuad {
   static constexpr uint32_t kEndsAt = 32u * kChunks;
   static constexpr uint32_t kBytes = kEndsAt + 64u * 4u * kClasses;
   static constexpr uint32_t kIdMask = 0x1ffu;
-  static constexpr uint32_t kWavesPerSimd = 2;
+  static constexpr uint32_t kWavesPerSimd = kChunks <= 128u ? 4u : 2u;
   // link of the chunk of record rec (the shifts end in an address: one instruction each)
   static __device__ __forceinline__ uint16_t* link(uint8_t* block, uint32_t rec) {
     return (uint16_t*)(block + (((rec << 5) & (kIdMask << 5)) | ((threadIdx.x >> 2) * 2u)));
@@ -100,14 +102,18 @@ __device__ __forceinline__ uint32_t quad_order(uint32_t code, uint32_t D) {
 }
 
 // What the stage of a chunk on dimension k does, as far as it does not depend on
-// the sizes: by (dimensions, stand-alone Reduce-Scatter or not), order + 32 *
-// phase, k.  Bits 0-2 the dimension the chunk waits for next (4: it is finished),
-// 9-14 its state then, 16-21 four times the mask of its reduced dimensions then,
-// 24-27 the mask of the dimensions before k in its order.
+// the sizes: by row + 32 * phase, k; the rows of the orders of D dimensions start
+// at quad_row(D), where those of four leave room (an order of one dimension has
+// the third column of one of two).  Bits 1-3 the dimension the chunk waits for
+// next (4: it is finished), 9-14 its row and phase then, 17-22 four times the mask
+// of its reduced dimensions then; bits 0, 8, 16, 24: dimension 0, 1, 2, 3 comes
+// before k in its order.
 struct QuadStages {
-  uint32_t v[8][64][4];
+  uint32_t v[64][4];
   uint8_t code[4][24];   // the order codes themselves, by (dimensions - 1)
 };
+__host__ __device__ constexpr uint32_t quad_row(uint32_t D) { return D >= 4u ? 0u : D == 3u ? 24u : 30u; }
+__host__ __device__ constexpr uint32_t quad_column(uint32_t D) { return D == 1u ? 2u : 0u; }
 constexpr QuadStages quad_stages() {
   QuadStages t{};
   for (uint32_t D = 1; D <= 4; ++D) {
@@ -123,18 +129,18 @@ constexpr QuadStages quad_stages() {
       }
       if (!ok) continue;
       uint32_t before = 0;
+      const uint32_t row = quad_row(D) + n;
       t.code[D - 1u][n] = 0;
       for (uint32_t j = 0; j < D; ++j) {
         t.code[D - 1u][n] = (uint8_t)(t.code[D - 1u][n] | perm[j] << (2u * j));
-        const uint32_t k = perm[j], with = before | (1u << k);
-        for (uint32_t alone = 0; alone < 2u; ++alone) {
-          const bool last = with == full;
-          const uint32_t to = last ? (alone ? 4u : k) : perm[j + 1u < 4u ? j + 1u : 3u];
-          t.v[(D - 1u) * 2u + alone][n][k] =
-              to | (n + (last ? 32u : 0u)) << 9 | (4u * with) << 16 | before << 24;
-          t.v[(D - 1u) * 2u + alone][32u + n][k] =
-              (j == 0u ? 4u : perm[j - (j ? 1u : 0u)]) | (n + 32u) << 9 | (4u * before) << 16 | before << 24;
-        }
+        const uint32_t k = perm[j], with = before | (1u << k), column = k + quad_column(D);
+        const bool last = with == full;
+        uint32_t bits = 0;
+        for (uint32_t d = 0; d < 4u; ++d) bits |= ((before >> d) & 1u) << (8u * d);
+        t.v[row][column] = (last ? k : perm[j + 1u < 4u ? j + 1u : 3u]) << 1 | (row + (last ? 32u : 0u)) << 9 |
+                           (4u * with) << 17 | bits;
+        t.v[32u + row][column] =
+            (j == 0u ? 4u : perm[j - (j ? 1u : 0u)]) << 1 | (row + 32u) << 9 | (4u * before) << 17 | bits;
         before = with;
       }
       ++n;
@@ -144,27 +150,49 @@ constexpr QuadStages quad_stages() {
 }
 __device__ const QuadStages g_quad_stages = quad_stages();
 
-// Stages of a chunk on the lane's dimension where the NPU counts are powers of two.
-template <bool kFix>
+// Stages of a chunk on the lane's dimension where the NPU counts are powers of
+// two (records hold quad_row() + order).  A stage takes 2^-e times as long as on the
+// whole chunk, e the sum of log2 P over the dimensions before: the product with the
+// power of two may come after the one with the latency as long as no result leaves
+// the normal range (t_min).
+// A running stage, as the quad passes it on: bits 1-3 the dimension the chunk waits
+// for then (4: none), 9-14 its row and phase then, 16-21 the list it joins, 22-30 the
+// chunk.
+// The stage table is in LDS behind the lists (1 KiB, 60 clocks nearer than the
+// caches) where that costs no wavefront: up to 256 chunks.
+template <typename L, bool kFix>
 struct QuadPow2 {
-  static constexpr uint32_t kClassMask = 15u;
-  double coef, fix;
+  static constexpr bool kTableInLds = L::kCap <= 256u;
+  static constexpr uint32_t kBytes = L::kBytes + (kTableInLds ? 1024u : 0u);
+  double whole, fix;
   uint64_t ranktab;
-  uint32_t epack, base_lo, base_hi, at;
-  __device__ __forceinline__ QuadPow2(const Scenario& s, const Pow2Model& m, uint32_t k)
-      : coef(sel4((int)k, s.coef[0], s.coef[1], s.coef[2], s.coef[3])),
-        fix(kFix ? sel4((int)k, s.fix[0], s.fix[1], s.fix[2], s.fix[3]) : 0.0), ranktab(m.ranktab),
-        epack(m.fs.epack), base_lo((uint32_t)__double2loint(m.fs.base)),
-        base_hi((uint32_t)__double2hiint(m.fs.base)),
-        at((((uint32_t)s.D - 1u) * 2u + (m.rs_only() ? 1u : 0u)) * 1024u + 4u * k) {}
-  // rec: the chunk's record; the word that says what its completion does, without the chunk
+  int less;         // -log2 P_k in byte k
+  const uint8_t* table;
+  uint32_t at, wanted;
+  __device__ __forceinline__ QuadPow2(const Scenario& s, const Pow2Model& m, uint32_t k, void* lds)
+      : whole(m.fs.base * sel4((int)k, s.coef[0], s.coef[1], s.coef[2], s.coef[3])),
+        fix(kFix ? sel4((int)k, s.fix[0], s.fix[1], s.fix[2], s.fix[3]) : 0.0), ranktab(m.ranktab), less(0),
+        table(kTableInLds ? (const uint8_t*)lds + L::kBytes : (const uint8_t*)&g_quad_stages),
+        at(4u * ((k + quad_column((uint32_t)s.D)) & 3u)),
+        // a stand-alone Reduce-Scatter is finished where the phase would turn
+        wanted(m.rs_only() ? 14u | 0x4000u : 14u) {
+#pragma unroll
+    for (uint32_t d = 0; d < 4u; ++d) less |= (int)((0u - (m.fs.epack >> (8u * d) & 0xffu) & 0xffu) << (8u * d));
+    if (kTableInLds)
+      for (uint32_t j = 0; j < 4u; ++j)
+        ((uint32_t*)((uint8_t*)lds + L::kBytes))[64u * j + threadIdx.x % 64u] = (&g_quad_stages.v[0][0])[64u * j + threadIdx.x % 64u];
+    __syncthreads();
+  }
+  __device__ __forceinline__ bool goes_to(uint32_t given, uint32_t k) const { return (given & wanted) == 2u * k; }
+  static __device__ __forceinline__ uint32_t list(uint32_t given) { return (given >> 16) & 63u; }
+  static __device__ __forceinline__ uint32_t record(uint32_t given) { return (given & 0x7e00u) | given >> 22; }
+  // rec: the chunk's record in the low half
   __device__ __forceinline__ uint32_t stage(uint32_t rec, double& time) const {
-    const uint32_t v = *(const uint32_t*)((const uint8_t*)&g_quad_stages + (((rec >> 5) & 0x3f0u) | at));
-    const int e = (int)esum(epack, v >> 24);
-    time = __hiloint2double((int)base_hi + __mul24(e, -0x100000), (int)base_lo) * coef;
+    const uint32_t v = *(const uint32_t*)(table + (((rec >> 5) & 0x3f0u) | at));
+    time = ldexp(whole, __builtin_amdgcn_sdot4((int)(v & 0x01010101u), less, 0, false));
     if (kFix) time = fix + time;
-    const uint32_t cls = (uint32_t)(ranktab >> ((v >> 16) & 63u)) & 15u;
-    return (v & 0x7e07u) | cls << 3;
+    const uint32_t cls = (uint32_t)(ranktab >> ((v >> 17) & 63u)) & 15u;
+    return (v & 0x7e0eu) | (rec & 0x1ffu) << 22 | cls << 16;
   }
 };
 
@@ -173,9 +201,10 @@ struct QuadPow2 {
 // and times depend on its whole order, and are made by the model's own sequence
 // of divisions and multiplications, once per order that some chunk has.
 // In LDS behind the lists (quad g): time of order o on dimension k, binary64, at
-// 128 * (4 * o + k) + 8 * g, and what the completion does, 16 bits as in
-// simulate_quad, at 32 * (4 * state + k) + 2 * g (state: order and phase as in a
-// record); size classes of (state, k) while these are made, 8 bits, at
+// 128 * (4 * o + k) + 8 * g, and what the completion does, 16 bits (0-2 the dimension
+// the chunk waits for then, 3-8 the list it joins, 9-14 its state), at
+// 32 * (4 * state + k) + 2 * g (state: order and phase as in a record); a running
+// stage is these bits and the chunk from bit 16 on; size classes of (state, k) while these are made, 8 bits, at
 // 16 * (4 * state + k) + g.
 // L: layout; kDims: up to three dimensions (six orders, at most twelve sizes that
 // wait for one dimension), or four (24, 48).
@@ -260,8 +289,9 @@ struct QuadTable {
       *f64_at(rs, o, k) = time;
       t_min = min_f64(t_min, time);
       for (uint32_t phase = gather ? 1u : 0u; phase < (rs_only ? 1u : 2u); ++phase) {
-        const uint32_t v = g_quad_stages.v[(D - 1u) * 2u + (rs_only ? 1u : 0u)][32u * phase + o][k];
-        const uint32_t to = v & 7u, next = state_of(o, (v >> 14) & 1u);
+        const uint32_t v = g_quad_stages.v[32u * phase + quad_row(D) + o][k + quad_column(D)];
+        const uint32_t turned = (v >> 14) & 1u, next = state_of(o, turned);
+        const uint32_t to = rs_only && turned != 0u ? 4u : (v >> 1) & 7u;
         const uint32_t cls = to < 4u ? *class_at(block, next, to) : 0u;
         *does_at(block, state_of(o, phase), k) = (uint16_t)(to | cls << 3 | next << 9);
       }
@@ -269,11 +299,15 @@ struct QuadTable {
     t_min = quad_min_f64(t_min);
     __syncthreads();
   }
+  static __device__ __forceinline__ bool goes_to(uint32_t given, uint32_t k) { return (given & 7u) == k; }
+  static __device__ __forceinline__ uint32_t list(uint32_t given) { return (given >> 3) & 63u; }
+  static __device__ __forceinline__ uint32_t record(uint32_t given) { return (given & 0x7e00u) | given >> 16; }
   __device__ __forceinline__ uint32_t stage(uint32_t rec, double& time) const {
     const uint32_t k = threadIdx.x & 3u;
-    time = *(const double*)(block + kTimes + ((rec & 0x3e00u & (L::kPhaseBit == 14u ? ~0u : 0xe00u)) | (k << 7 | quad8())));
-    return *(const uint16_t*)(block + kDoes +
-                              (((rec >> 2) & (L::kPhaseBit == 14u ? 0x1f80u : 0x780u)) | (k << 5 | (threadIdx.x >> 2) * 2u)));
+    time = *(const double*)(block + kTimes + ((rec & (L::kPhaseBit == 14u ? 0x3e00u : 0xe00u)) | (k << 7 | quad8())));
+    const uint32_t v = *(const uint16_t*)(block + kDoes + (((rec >> 2) & (L::kPhaseBit == 14u ? 0x1f80u : 0x780u)) |
+                                                           (k << 5 | (threadIdx.x >> 2) * 2u)));
+    return v | (rec & 0x1ffu) << 16;
   }
 };
 
@@ -318,24 +352,22 @@ __device__ __forceinline__ QuadResult simulate_quad(const Model& model, QuadQueu
   }
   double f = nan64();      // finish time of the stage the dimension serves, NaN when idle
   double busy = 0.0, now = 0.0;
-  uint32_t sv = 0u;        // that stage: chunk << 16 | what its completion does
+  uint32_t sv = 0u;        // that stage, as the model passes it on
   uint32_t started = 0u;
-  const uint32_t max_steps = 2u * (uint32_t)kMaxDims * L::kCap + 16u;
-  for (uint32_t step = 0; step <= max_steps; ++step) {
-    // a8: the clock moves to the earliest completion of the evaluation
-    const double next = quad_min_f64(f);
-    const uint64_t running = __builtin_amdgcn_ballot_w64(next == next);
-    if (step != 0u && running == 0ull) break;
+  // One pass.  next: the earliest completion of the evaluation (NaN: nothing runs),
+  // running: the lanes for which that is a number.
+  auto pass = [&](double next, uint64_t running) {
+    // a8: the clock moves there
     now = max_f64(now, next);
     // of the stages that end now the one of the lowest chunk hands it on
     const bool ends = f == next;
     const uint64_t ending = __builtin_amdgcn_ballot_w64(ends);
     const uint32_t key = ends ? sv : ~0u;
     const uint32_t given = quad_min_u32(key);
-    if (ends && key == given) f = nan64();
+    if (ends && key == given) f = __hiloint2double(0x7ff80000, __double2loint(f));
     // (dimension 4 and, where nothing ends, 7: nobody's)
-    const bool append = (given & 7u) == k;
-    const uint32_t to = (given >> 3) & 63u;
+    const bool append = model.goes_to(given, k);
+    const uint32_t to = Model::list(given);
     const Mask to_bit = (Mask)1 << to;
     const bool had = (lists & to_bit) != 0;
     if (append) lists |= to_bit;
@@ -350,35 +382,45 @@ __device__ __forceinline__ QuadResult simulate_quad(const Model& model, QuadQueu
     const uint32_t from = sizeof(Mask) == 8u ? (uint32_t)__builtin_ctzll(lists) : (uint32_t)__builtin_ctz((uint32_t)lists);
     uint32_t* const from_at = L::ends(block, from);
     uint32_t* const to_at = L::ends(block, to);
-    const uint32_t ends_from = *from_at, ends_to = *to_at;   // (used only where there is such a list)
-    const uint32_t rec = (given & 0x7e00u) | given >> 16;
+    uint32_t ends_from = *from_at, ends_to = *to_at;   // (either is used only where there is such a list)
+    asm volatile("" : "+v"(ends_from), "+v"(ends_to));   // (read together, not each where it is needed)
     if (append) {
+      const uint32_t rec = Model::record(given);
       if (had) *L::link(block, ends_to >> 16) = (uint16_t)rec;
-      *to_at = (had ? ends_to & 0xffffu : rec) | rec << 16;
+      const uint32_t ends_now = __builtin_amdgcn_perm(rec, had ? ends_to : rec, 0x05040100u);
+      *to_at = ends_now;
+      if (to == from) ends_from = ends_now;
     }
     if (starts) {
-      const bool same = append && to == from;
-      const uint32_t head = same && !had ? rec : ends_from & 0xffffu;
-      const uint32_t last = same ? rec : ends_from >> 16;
-      const uint32_t link = *L::link(block, head);
+      const uint32_t link = *L::link(block, ends_from);
       double time;
-      const uint32_t does = model.stage(head, time);
-      if (head == last) lists &= lists - 1u;
-      else *(uint16_t*)from_at = (uint16_t)link;
+      sv = model.stage(ends_from, time);
+      const bool last = ends_from == __builtin_amdgcn_alignbit(ends_from, ends_from, 16u);   // of its list
+      lists &= last ? lists - 1u : ~(Mask)0;
+      if (!last) *(uint16_t*)from_at = (uint16_t)link;
       f = now + time;
       busy = busy + time;
-      sv = (head & L::kIdMask) << 16 | does;
-      if (kPut) put(started, (head & L::kIdMask) << 1 | ((head >> L::kPhaseBit) & 1u));
+      if (kPut) put(started, (ends_from & L::kIdMask) << 1 | ((ends_from >> L::kPhaseBit) & 1u));
       ++started;
     }
+  };
+  pass(nan64(), 0ull);
+  // (every pass in which something runs completes a stage)
+  for (uint32_t left = 2u * (uint32_t)kMaxDims * L::kCap + 16u; left != 0u; --left) {
+    const double next = quad_min_f64(f);
+    const uint64_t running = __builtin_amdgcn_ballot_w64(next == next);
+    if (running == 0ull) break;
+    pass(next, running);
   }
   QuadResult res;
   res.t_done = now;
   res.busy = busy;
   res.started = started;
-  // every stage ran and completed, and none was too short to move the clock
+  // every stage ran and completed, and none was too short to move the clock, or
+  // to be a normal number
   const uint32_t settled = quad_min_u32(!(f == f) && lists == 0 ? 1u : 0u);
-  res.ok = quad_sum(started) == stages && settled != 0u && now < inf64() && now + 0.25 * t_min > now;
+  res.ok = quad_sum(started) == stages && settled != 0u && now < inf64() && now + 0.25 * t_min > now &&
+           t_min >= 2.2250738585072014e-308;
   return res;
 }
 

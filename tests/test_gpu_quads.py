@@ -34,6 +34,7 @@ CASES.update({
     "four dimensions, other counts": lambda W: _mixed_counts(200, 905, 5, dims=4, max_chunks=64),
     "four dimensions, 100 chunks": lambda W: _mixed_counts(70, 906, 3, dims=4, max_chunks=100),
     "three dimensions, 300 chunks": lambda W: _mixed_counts(40, 907, 3, dims=3, max_chunks=300),
+    "two of 16 powers of two, four dimensions": lambda W: _mixed_counts(200, 909, 8, dims=4, max_chunks=30),
     "types, delays, other counts": lambda W: _with_fixed_delay(_with_collective_types(
         _mixed_counts(300, 908, 3), 13), 14),
 })
@@ -53,7 +54,7 @@ def test_lanes_and_quads_agree_with_the_oracle(gpu, oracle, mapping, case):
         gpu.themis_set_sweep_mapping(gpu.MAPPING_AUTO)
 
 
-@pytest.mark.parametrize("n,chunks", [(16385, 2), (32769, 2), (49152, 2), (49153, 2), (65537, 2), (17000, 70)])
+@pytest.mark.parametrize("n,chunks", [(16385, 2), (32769, 2), (65536, 2), (65537, 2), (65600, 3), (17000, 70)])
 def test_batch_sizes_around_the_lines(gpu, oracle, n, chunks):
     """Where the mapping changes, and where the follow-up kernel's workgroups look
     at more scenarios each; all kinds of NPU counts."""
