@@ -18,6 +18,7 @@
 #include "themis_shared.hpp"
 #include "themis_table.hpp"
 #include "themis_trace.hpp"
+#include "themis_trace_quad.hpp"
 #include "themis_trace_wave.hpp"
 #include "themis_wave.hpp"
 
@@ -997,6 +998,71 @@ simulate_trace_kernel(themis_batch_t b, const uint8_t* __restrict__ orders,
   }
   if (!have_ws) { write_invalid(out); return; }
   simulate_generic_scenario<false>(b, tv, s, Q, i, i, row, scf, w, out);
+}
+
+// Four lanes per trace (themis_trace_quad.hpp): traces released together, NPU counts
+// that are powers of two, up to `dims` dimensions; what is left is marked.
+// follow_up: only what an earlier launch of the call, for fewer dimensions, has marked.
+template <bool kPut>
+__global__ void __launch_bounds__(kBlock)
+simulate_trace_quad_kernel(themis_batch_t b, const uint8_t* __restrict__ orders, double* __restrict__ t_done,
+                           void* __restrict__ queue_order, int entry_bytes, double* __restrict__ busy,
+                           uint8_t* __restrict__ trace_area, uint32_t stride, uint32_t dims, bool follow_up,
+                           unsigned long long call) {
+  extern __shared__ __attribute__((aligned(16))) uint8_t trace_lds[];
+  if (follow_up && nothing_marked(call)) return;
+  const TraceView tv = trace_view(b);
+  const uint32_t k = threadIdx.x & 3u;
+  const uint64_t at = (uint64_t)blockIdx.x * (kBlock / 4u) + (threadIdx.x >> 2);
+  const bool exists = at < b.n && (!follow_up || is_left_to_generic(t_done[at]));
+  if (__builtin_amdgcn_ballot_w64(exists) == 0ull) return;
+  const uint64_t i = at < b.n ? at : b.n - 1u;
+  const Scenario s = load_scenario(b, i);
+  const bool scf = b.intra_policy[i] == THEMIS_INTRA_SCF;
+  const uint32_t Q = b.n_coll[i];
+  bool ok = s.valid && Q >= 1u && Q <= tv.mc;
+  FastScenario fs;
+  bool takes = (uint32_t)s.D <= dims, valid = true;
+  double smallest = inf64();
+  for (uint32_t q = k; ok && q < Q; q += 4u) {
+    const double size = collective_size(b, tv, i, q), chunk = size / (double)s.C;
+    valid = valid && finite_positive(size);
+    takes = takes && fast_eligible(s, chunk, THEMIS_MAX_CHUNKS, fs);
+    smallest = min_f64(smallest, chunk);
+  }
+  fast_eligible(s, ok ? collective_size(b, tv, i, 0u) / (double)s.C : 1.0, THEMIS_MAX_CHUNKS, fs);
+  ok = ok && quad_min_u32(valid ? 1u : 0u) != 0u;
+  takes = quad_min_u32(takes ? 1u : 0u) != 0u;
+  smallest = quad_min_f64(smallest);
+  const bool runs = exists && ok && takes;
+  const TraceQuadLayout l = trace_quad_layout(tv.slots, dims, tv.mc);
+  const uint8_t* const row = orders + (size_t)i * tv.slots;
+  const bool dwords = (b.max_chunks & 3u) == 0u && ((uintptr_t)orders & 3u) == 0u;
+  uint8_t* const entries = queue_order ? (uint8_t*)queue_order + ((size_t)i * kMaxDims + k) * 2u * tv.slots * (uint32_t)entry_bytes
+                                       : nullptr;
+  const TraceQuadResult r = simulate_trace_quad<kPut>(
+      s, fs, runs ? Q : 0u, scf, smallest, l, trace_lds, trace_area + (size_t)blockIdx.x * (kBlock / 4u) * stride, stride,
+      [&](uint32_t q, uint32_t c) {
+        const uint8_t* at_c = row + (size_t)q * b.max_chunks + c;
+        if (dwords) return *(const uint32_t*)at_c;
+        uint32_t v = 0u;
+        for (uint32_t j = 0; j < 4u && c + j < s.C; ++j) v |= (uint32_t)at_c[j] << (8u * j);
+        return v;
+      },
+      [&](uint32_t q) { return collective_size(b, tv, i, q) / (double)s.C; },
+      [&](uint32_t e, uint32_t entry) {
+        if (entry_bytes == 2) ((uint16_t*)entries)[e] = (uint16_t)entry;
+        else entries[e] = (uint8_t)entry;
+      });
+  if (!exists) return;
+  const bool done = runs && r.ok;
+  if (ok && !done) {   // (malformed codes: written by the kernel that follows)
+    if (k == 0u) mark_left_to_generic(t_done + i, call);
+    return;
+  }
+  if (k == 0u) t_done[i] = done ? r.t_done : nan64();
+  if (busy) busy[(size_t)k * b.n + i] = done ? r.busy : nan64();
+  if (kPut) pad_row(entries, done ? r.started : 0u, 2u * tv.slots, entry_bytes);
 }
 
 // One wavefront per trace (themis_trace_wave.hpp), lds_bytes of LDS: traces that
@@ -2729,8 +2795,6 @@ static bool simulate_on_wavefronts(uint64_t items) { return on_wavefronts(items,
 // One launch does where all the traces are resident with the larger blocks.
 struct TraceWaveLaunches {
   uint32_t lds[3];
-  const uint32_t* begin() const { return lds; }
-  const uint32_t* end() const { return lds + 3; }
 };
 constexpr uint32_t kLdsOfCu = 160u * 1024u;
 // (four wavefronts on a SIMD by their registers)
@@ -2753,26 +2817,41 @@ static TraceWaveLaunches trace_wave_launches(uint64_t n, uint32_t slots, uint32_
       for (int i = 0; i < j; ++i) t.lds[i] = 0u;
   return t;
 }
-// A wavefront per trace, or a lane each?  On wavefronts an event of a trace takes
-// 0.42 us and 18 ns more per wavefront of its CU; they take turns where the LDS of
-// a CU holds fewer than there are traces.  With a lane each it takes 1.5 us and
-// up, 5.2 with release times, whatever the number of traces up to a wavefront of
-// them per CU.  Measured (ms, wavefront / lane; three dimensions unless said):
-//   200 collectives of 64 chunks   64 traces 32 / 108, 1,024 71 / 115, 2,048 141 / 117
-//   100 of 32                      1,024 10.9 / 28.7, 4,096 29 / 30, 16,384 97 / 35
-//   50 of 32, releases             64 4.1 / 49, 2,048 6.1 / 54, 16,384 28 / 55
-//   40 of 16, four dimensions      2,048 4.2 / 8.8, 8,192 11.7 / 10.0
-//   4 of 8                         64 0.11 / 0.33, 4,096 0.17 / 0.34, 8,192 0.32 / 0.35
-static bool trace_on_wavefronts(uint64_t n, uint32_t slots, uint32_t max_coll, bool releases) {
-  const uint32_t lds = trace_wave_layout(slots, 3u, max_coll, true, false).bytes;
-  const int forced = batch_mapping.load(std::memory_order_relaxed);
-  if (lds > kLdsOfCu || n > 0x7fffffffull || forced == THEMIS_MAPPING_LANE) return false;
-  if (forced == THEMIS_MAPPING_WAVE) return true;
+// How a batch of traces is simulated.  On wavefronts an event of a trace takes 0.42
+// us and 18 ns more per wavefront of its CU; they take turns where the LDS of a CU
+// holds fewer than there are traces.  On quads it takes 0.65 us, up to 0.9 where
+// they fill the GPU (16,384 traces).  With a lane each it takes 1.5 us and up, 5.2
+// with release times, up to a wavefront of them per CU.  Measured (ms, wavefront /
+// quad / lane; three dimensions unless said):
+//   200 collectives of 64 chunks   64 traces 31 / 50 / 110, 1,024 68 / 52 / 117, 16,384 - / 68 / 139
+//   100 of 32                      1,024 11.0 / 13.2 / 28.5, 4,096 29 / 13 / 30, 16,384 97 / 17.5 / 35
+//   50 of 32                       1,500 6.4 / 6.4 / 14.4, 3,000 7.1 / 6.4 / 14.5, 65,536 - / 22 / 87
+//   50 of 32, releases             64 4.1 / - / 49, 2,048 6.1 / - / 54, 16,384 28 / - / 55
+//   40 of 16, four dimensions      2,048 4.2 / 4.1 / 8.8, 16,384 21 / 5.9 / 10.9
+//   4 of 8                         64 0.11 / 0.16 / 0.33, 4,096 0.17 / 0.16 / 0.35
+// Quads take what is released together on powers of two; what they leave (the
+// host does not see the NPU counts) goes to wavefronts or lanes as if they were not.
+struct TracePlan {
+  bool waves, quads, waves_after;
+};
+static TracePlan trace_plan(const themis_batch_t& b, uint32_t slots, uint32_t region_bytes) {
+  const int batch = batch_mapping.load(std::memory_order_relaxed), lanes = sweep_mapping.load(std::memory_order_relaxed);
+  const bool releases = b.release_time != nullptr;
+  TracePlan p;
+  p.quads = lanes != THEMIS_MAPPING_LANE && !releases && trace_quad_layout(slots, 4u, b.max_coll).region <= region_bytes &&
+            trace_quad_layout(slots, 3u, b.max_coll).lds <= kLdsOfCu;
+  const uint32_t lds = trace_wave_layout(slots, 3u, b.max_coll, true, false).bytes;
+  if (lds > kLdsOfCu || b.n > 0x7fffffffull || batch == THEMIS_MAPPING_LANE) {
+    p.waves = p.waves_after = false;
+    return p;
+  }
   const double cus = compute_units() ? compute_units() : 256u;
-  const double resident = (double)trace_wave_resident(lds) / cus;         // wavefronts of a CU
-  const double per_cu = std::min(resident, std::max(1.0, (double)n / cus));
-  const double turns = std::max(1.0, (double)n / (cus * resident));
-  return turns * (0.42 + 0.018 * per_cu) < (releases ? 5.2 : 1.5);
+  const double resident = (double)trace_wave_resident(lds) / cus;   // wavefronts of a CU
+  const double per_cu = std::min(resident, std::max(1.0, (double)b.n / cus));
+  const double event = std::max(1.0, (double)b.n / (cus * resident)) * (0.42 + 0.018 * per_cu);
+  p.waves_after = event < (releases ? 5.2 : 1.5);
+  p.waves = batch == THEMIS_MAPPING_WAVE || (p.quads ? event < 0.55 : p.waves_after);
+  return p;
 }
 
 // A wavefront per evaluation in a sweep of few: the lanes' own planning and
@@ -2923,16 +3002,27 @@ static int simulate_batch_impl(const themis_batch_t* batch, const uint8_t* order
     auto trace_kernel = lds_bitmaps ? (extras ? simulate_trace_kernel<true, true> : simulate_trace_kernel<true, false>)
                                     : (extras ? simulate_trace_kernel<false, true> : simulate_trace_kernel<false, false>);
     unsigned long long call = 0ull;
-    if (have_trace && trace_on_wavefronts(batch->n, tv.slots, batch->max_coll, batch->release_time != nullptr)) {
-      call = next_call_number();
+    if (have_trace) {
+      const TracePlan plan = trace_plan(*batch, tv.slots, tl.bytes);
+      if (plan.waves || plan.quads) call = next_call_number();
       bool follow_up = false;
-      for (uint32_t lds : trace_wave_launches(batch->n, tv.slots, batch->max_coll)) {
-        if (lds == 0u) continue;
-        go.with_lds(lds, queue_order ? simulate_trace_wave_kernel<true> : simulate_trace_wave_kernel<false>,
-                    (unsigned)batch->n, kBlock, *batch, orders, t_done, queue_order, entry_bytes, busy, lds,
-                    follow_up, call);
-        follow_up = true;
-      }
+      if (!plan.waves && plan.quads)
+        for (uint32_t dims : {3u, 4u}) {
+          const uint32_t lds = trace_quad_layout(tv.slots, dims, batch->max_coll).lds;
+          if (lds > kLdsOfCu) continue;
+          go.with_lds(lds, queue_order ? simulate_trace_quad_kernel<true> : simulate_trace_quad_kernel<false>,
+                      (unsigned)((batch->n + kBlock / 4u - 1u) / (kBlock / 4u)), kBlock, *batch, orders, t_done,
+                      queue_order, entry_bytes, busy, trace_area, tl.bytes, dims, follow_up, call);
+          follow_up = true;
+        }
+      if (plan.waves || (plan.quads && plan.waves_after))
+        for (uint32_t lds : trace_wave_launches(batch->n, tv.slots, batch->max_coll).lds) {
+          if (lds == 0u) continue;
+          go.with_lds(lds, queue_order ? simulate_trace_wave_kernel<true> : simulate_trace_wave_kernel<false>,
+                      (unsigned)batch->n, kBlock, *batch, orders, t_done, queue_order, entry_bytes, busy, lds,
+                      follow_up, call);
+          follow_up = true;
+        }
     }
     go(trace_kernel, blocks_for(batch->n), kBlock, *batch, orders, t_done, queue_order,
        entry_bytes, busy, w, have_ws, trace_area, tl, call);

@@ -1,5 +1,7 @@
-"""GPU parity of traces under each lane mapping, whatever the batch size would
-choose: one lane per trace and one wavefront per trace, whose edges are 64
+"""GPU parity of traces under each mapping, whatever the batch size would choose:
+one lane per trace, four (a quad: what is released together on powers of two,
+sixteen traces to a wavefront, four dimensions in a launch of their own), and one
+wavefront per trace, whose edges are 64
 chunks of a collective, 64 operations of a dimension (the queue orders leave a
 register then, as bytes up to 127 chunk slots), 64 size ranks (a word of the
 bitmap) and 4,096 (its end), and the LDS of a launch, which has enough for up to
@@ -32,6 +34,18 @@ def _released(b, seed, step=0.0):
     return b
 
 
+def _bottleneck(b):
+    """One dimension so slow that hundreds of chunks wait for it, on lists they share
+    and on many others."""
+    b.bw[1] *= 0.02
+    return b
+
+
+def _fifo(b):
+    b.intra_policy[:] = 0
+    return b
+
+
 CASES = {
     "one chunk": lambda: _trace(90, 1, 1, 70),
     "127 slots": lambda: _trace(40, 2, 127, 1, full=True),
@@ -46,22 +60,28 @@ CASES = {
     "types, delays, releases": lambda: _released(_with_fixed_delay(_with_collective_types(
         _trace(120, 11, 16, 9), 2), 3), 4),
     "types, other counts": lambda: _with_collective_types(_trace(120, 12, 9, 7, pow2=False), 5),
+    "1 trace": lambda: _trace(1, 15, 20, 12, dims=3),
+    "17 traces, long queues": lambda: _bottleneck(_trace(17, 16, 30, 40, dims=3)),
+    "four dimensions, delays": lambda: _with_fixed_delay(_bottleneck(_trace(40, 17, 21, 20, dims=4)), 8),
+    "first-in-first-out": lambda: _fifo(_trace(60, 18, 33, 11)),
     "ties": lambda: _trace(150, 13, 16, 6, equal_sizes=True, ties=True),
     "ties, releases": lambda: _released(_trace(150, 14, 16, 6, equal_sizes=True, ties=True), 6, step=2.0 ** -12),
 }
 
 
 @pytest.mark.parametrize("case", list(CASES))
-@pytest.mark.parametrize("mapping", ["lane", "wave"])
+@pytest.mark.parametrize("mapping", ["lane", "quad", "wave"])
 def test_traces_agree_with_the_oracle(gpu, oracle, mapping, case):
     b = CASES[case]()
-    gpu.themis_set_batch_mapping({"lane": gpu.MAPPING_LANE, "wave": gpu.MAPPING_WAVE}[mapping])
+    gpu.themis_set_batch_mapping(gpu.MAPPING_WAVE if mapping == "wave" else gpu.MAPPING_LANE)
+    gpu.themis_set_sweep_mapping(gpu.MAPPING_QUAD if mapping == "quad" else gpu.MAPPING_LANE)
     try:
         t = check_batch(gpu, oracle, b)
         assert np.isfinite(t).all()
         check_batch(gpu, oracle, b, queue=False)
     finally:
         gpu.themis_set_batch_mapping(gpu.MAPPING_AUTO)
+        gpu.themis_set_sweep_mapping(gpu.MAPPING_AUTO)
 
 
 def test_invalid_traces_on_wavefronts(gpu, oracle):
