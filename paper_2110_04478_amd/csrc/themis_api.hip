@@ -96,6 +96,34 @@ __device__ __forceinline__ bool nothing_marked(unsigned long long call) {
   return *(volatile unsigned long long*)&g_marked_call < call;
 }
 
+// Work of some lanes of a wavefront, taken by its quads 16 at a time, the longest
+// first: a turn takes as long as its longest (100,003 ragged scenarios of any NPU
+// counts, both simulation kernels: 1,503 us in the order they come, 995 so).
+struct QuadTurns {
+  uint64_t left;
+  uint32_t place;   // of the lane's own work (all-ones: none)
+  __device__ __forceinline__ QuadTurns(uint64_t lanes, uint32_t length) : left(lanes), place(0u) {
+    const uint32_t lane = threadIdx.x & 63u;
+    for (uint64_t m = lanes; m != 0ull; m &= m - 1ull) {
+      const uint32_t j = (uint32_t)__builtin_ctzll(m);
+      const uint32_t other = (uint32_t)__builtin_amdgcn_readlane((int)length, (int)j);
+      place += other > length || (other == length && j < lane) ? 1u : 0u;
+    }
+    if (((lanes >> lane) & 1ull) == 0ull) place = ~0u;
+  }
+  // which: the lane whose work the quad takes; false: none is left for it.  All lanes.
+  __device__ __forceinline__ bool take(uint32_t& which) {
+    const uint32_t lane = threadIdx.x & 63u;
+    const bool chosen = place < kBlock / 4u;
+    const uint32_t sent = (uint32_t)__builtin_amdgcn_ds_permute(chosen ? (int)(16u * place) : 4, (int)lane);
+    which = (uint32_t)__shfl((int)sent, (int)(lane & ~3u));
+    const bool exists = (uint32_t)__builtin_popcountll(left) > lane >> 2;
+    left &= ~__builtin_amdgcn_ballot_w64(chosen);
+    place = place == ~0u || chosen ? ~0u : place - kBlock / 4u;
+    return exists;
+  }
+};
+
 // ---------------------------------------------------------------------------
 // themis_plan_batch: Alg. 1 per scenario (hot-path steps a1-a5).
 // ---------------------------------------------------------------------------
@@ -103,73 +131,123 @@ __device__ __forceinline__ bool nothing_marked(unsigned long long call) {
 // scenario -- the tracker starts afresh for every collective (Alg. 1 line 2),
 // so the collectives of a trace are planned independently, and a batch of a
 // few thousand traces has too few scenarios to fill the GPU.
+// One or four wavefronts for 64 of them: the first plans those whose NPU counts are
+// powers of two, a lane each, and all of them the others, four lanes each, 16 at a
+// time (see plan_waves).
+constexpr uint32_t kPlanWaves = 4u;
 template <bool kPerCollective>
-__global__ void __launch_bounds__(kBlock)
+__global__ void __launch_bounds__(kPlanWaves* kBlock)
 plan_kernel(themis_batch_t b, uint8_t* __restrict__ orders, double* __restrict__ loads) {
-  // the planner's order table, one entry per lane of the workgroup
+  // the planner's order table, one entry per lane of the workgroup's first wavefront
   static_assert(kBlock == kPlanOrders, "one table entry per lane");
   __shared__ __attribute__((aligned(16))) uint32_t plan_orders[kPlanOrders * kPlanOrderWords];
-  plan_order_entry(threadIdx.x, plan_orders + kPlanOrderWords * threadIdx.x);
-  __syncthreads();
+  const uint32_t lane = threadIdx.x & 63u;
+  const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x / kBlock));
+  uint32_t waves = blockDim.x / kBlock;
+  if (wave == 0u) plan_order_entry(lane, plan_orders + kPlanOrderWords * lane);
+  if (wave == 0u) __builtin_amdgcn_wave_barrier();
   const TraceView tv = trace_view(b);
-  const uint64_t e = (uint64_t)blockIdx.x * kBlock + threadIdx.x;
-  const uint64_t i = kPerCollective ? e / tv.mc : e;
-  if (i >= b.n) return;
-  const uint32_t q_first = kPerCollective ? (uint32_t)(e - i * tv.mc) : 0u;
-  const uint32_t q_end = kPerCollective ? q_first + 1u : tv.mc;
-  Scenario s = load_scenario(b, i);
+  const uint64_t first = (uint64_t)blockIdx.x * kBlock, e = first + lane;
+  auto scenario_of = [&](uint64_t at) { return kPerCollective ? at / tv.mc : at; };
   const bool rel = b.threshold_mode == THEMIS_THR_REL;
-  const double thr = b.threshold[i];
-  const bool themis_on = b.inter_policy[i] != THEMIS_INTER_BASELINE;
-  uint32_t Q;
-  bool ok = collectives_ok(b, tv, i, Q) && s.valid && threshold_ok(thr, rel);
-
-  uint8_t* row = orders + (size_t)i * tv.slots;
-  double load[kMaxDims] = {0.0, 0.0, 0.0, 0.0};
-  if (!ok) {
-    for (uint32_t c = q_first * b.max_chunks; c < q_end * b.max_chunks; ++c) row[c] = 0xFFu;
-  } else {
-    // rows are written four codes at a time when they are 4-byte aligned
-    const bool words = (b.max_chunks & 3u) == 0u;
-    for (uint32_t q = q_first; q < q_end; ++q) {
-      uint8_t* r = row + (size_t)q * b.max_chunks;
-      uint32_t filled = 0;
-      if (q < Q) {
-        const double chunk = collective_size(b, tv, i, q) / (double)s.C;
-        FastScenario fs;
-        if (fast_eligible(s, chunk, THEMIS_MAX_CHUNKS, fs)) {
-          uint32_t acc = 0;
-          plan_fast<true>(s, fs, themis_on, rel, thr, load, [&](uint32_t c, uint32_t code) {
-            if (words) {
-              acc |= code << (8u * (c & 3u));
-              if ((c & 3u) == 3u) { ((uint32_t*)r)[c >> 2] = acc; acc = 0; }
-            } else {
-              r[c] = (uint8_t)code;
-            }
-          }, plan_orders);
-          if (words && (s.C & 3u)) {  // pad the last partial word with unused-slot marks
-            acc |= 0xFFFFFFFFu << (8u * (s.C & 3u));
-            ((uint32_t*)r)[s.C >> 2] = acc;
-            filled = (s.C | 3u) + 1u;
-          } else {
-            filled = s.C;
-          }
-        } else {
+  // a collective's codes, and from there to the end of its row
+  auto pad = [&](uint8_t* r, uint32_t filled) {
+    for (uint32_t c = filled; c < b.max_chunks; ++c) r[c] = 0xFFu;
+  };
+  // rows are written four codes at a time when they are 4-byte aligned
+  const bool words = (b.max_chunks & 3u) == 0u;
+  auto pad_word = [&](uint8_t* r, uint32_t C, uint32_t acc) -> uint32_t {
+    if (words && (C & 3u)) {  // pad the last partial word with unused-slot marks
+      acc |= 0xFFFFFFFFu << (8u * (C & 3u));
+      ((uint32_t*)r)[C >> 2] = acc;
+      return (C | 3u) + 1u;
+    }
+    return C;
+  };
+  if (waves > 1u) {   // the others leave at once where all counts are powers of two
+    bool other = false;
+    if (scenario_of(e) < b.n) {
+      const uint32_t D = b.ndims[scenario_of(e)];
 #pragma unroll
-          for (int k = 0; k < kMaxDims; ++k) load[k] = (k < s.D) ? tracker_start(s, k) : inf64();
-          for (uint32_t c = 0; c < s.C; ++c)
-            r[c] = (uint8_t)schedule_chunk(s, chunk, themis_on, rel, thr, load);
-          filled = s.C;
-        }
+      for (uint32_t k = 0; k < (uint32_t)kMaxDims; ++k)
+        other = other || (k < D && !is_pow2(b.npus[(size_t)k * b.n + scenario_of(e)]));
+    }
+    if (__builtin_amdgcn_ballot_w64(other) == 0ull) waves = 1u;
+    if (wave >= waves) return;
+  }
+  bool left = false;   // NPU counts that are not powers of two: for the quads below
+  uint32_t chunks = 0u;
+  if (scenario_of(e) < b.n) {
+    const uint64_t i = scenario_of(e);
+    const uint32_t q = kPerCollective ? (uint32_t)(e - i * tv.mc) : 0u;
+    const Scenario s = load_scenario(b, i);
+    const double thr = b.threshold[i];
+    uint32_t Q;
+    const bool ok = collectives_ok(b, tv, i, Q) && s.valid && threshold_ok(thr, rel);
+    uint8_t* r = orders + (size_t)i * tv.slots + (size_t)q * b.max_chunks;
+    double load[kMaxDims] = {0.0, 0.0, 0.0, 0.0};
+    uint32_t filled = 0u;
+    if (ok && q < Q) {
+      const double chunk = collective_size(b, tv, i, q) / (double)s.C;
+      FastScenario fs;
+      left = !fast_eligible(s, chunk, THEMIS_MAX_CHUNKS, fs);
+      chunks = s.C;
+      if (!left && wave == 0u) {
+        uint32_t acc = 0;
+        plan_fast<true>(s, fs, b.inter_policy[i] != THEMIS_INTER_BASELINE, rel, thr, load, [&](uint32_t c, uint32_t code) {
+          if (words) {
+            acc |= code << (8u * (c & 3u));
+            if ((c & 3u) == 3u) { ((uint32_t*)r)[c >> 2] = acc; acc = 0; }
+          } else {
+            r[c] = (uint8_t)code;
+          }
+        }, plan_orders);
+        filled = pad_word(r, s.C, acc);
       }
-      for (uint32_t c = filled; c < b.max_chunks; ++c) r[c] = 0xFFu;
+    }
+    if (!left && wave == 0u) {
+      pad(r, filled);
+      // the tracker of the scenario's last collective (an invalid scenario: NaN)
+      if (loads && (!kPerCollective || q == (ok ? Q - 1u : 0u))) {
+#pragma unroll
+        for (int k = 0; k < kMaxDims; ++k)
+          loads[(size_t)k * b.n + i] = ok ? ((k < s.D) ? load[k] : 0.0) : nan64();
+      }
     }
   }
-  // the tracker of the scenario's last collective (an invalid scenario: NaN)
-  if (loads && (!kPerCollective || q_first == (ok ? Q - 1u : 0u))) {
+  const uint64_t others = __builtin_amdgcn_ballot_w64(left);
+  QuadTurns turns(others, chunks);
+  for (uint32_t turn = 0; turns.left != 0ull; ++turn) {
+    uint32_t which;
+    const bool exists = turns.take(which);
+    if (turn % waves != wave) continue;
+    const uint64_t at = exists ? first + which : first, i = scenario_of(at);
+    const uint32_t q = kPerCollective ? (uint32_t)(at - i * tv.mc) : 0u, k = threadIdx.x & 3u;
+    const Scenario s = load_scenario(b, i);
+    const double chunk = collective_size(b, tv, i, q) / (double)s.C;
+    uint8_t* r = orders + (size_t)i * tv.slots + (size_t)q * b.max_chunks;
+    double least = chunk, load;
 #pragma unroll
-    for (int k = 0; k < kMaxDims; ++k)
-      loads[(size_t)k * b.n + i] = ok ? ((k < s.D) ? load[k] : 0.0) : nan64();
+    for (int d = 0; d < kMaxDims; ++d)
+      if (d < s.D) least = least / (double)s.P[d];
+    uint32_t acc = 0u;
+    auto emit = [&](uint32_t c, uint32_t code) {
+      acc |= code << (8u * (c & 3u));
+      if (k != 0u) return;
+      if (!words) r[c] = (uint8_t)code;
+      else if ((c & 3u) == 3u) { ((uint32_t*)r)[c >> 2] = acc; acc = 0u; }
+    };
+    const bool themis_on = b.inter_policy[i] != THEMIS_INTER_BASELINE;
+    const uint32_t C = exists ? s.C : 0u;
+    if (__builtin_amdgcn_ballot_w64(exists && !(least >= 2.2250738585072014e-308)) == 0ull)
+      plan_quad<false>(s, chunk, themis_on, rel, b.threshold[i], C, load, emit);
+    else
+      plan_quad<true>(s, chunk, themis_on, rel, b.threshold[i], C, load, emit);
+    if (exists) {
+      if (k == 0u) pad(r, pad_word(r, C, acc));
+      const uint32_t Q = tv.on ? b.n_coll[i] : 1u;
+      if (loads && (!kPerCollective || q + 1u == Q)) loads[(size_t)k * b.n + i] = k < (uint32_t)s.D ? load : 0.0;
+    }
   }
 }
 
@@ -336,15 +414,15 @@ __device__ __forceinline__ void quad_table_rounds(const themis_batch_t& b, const
                                                   uint64_t left, bool marked, void* lds, unsigned long long call) {
   using Table = QuadTable<L, kDims>;
   const uint32_t lane = threadIdx.x & 63u, k = lane & 3u;
-  while (left != 0ull) {
-    // the quads take the next 16: the lane of the j-th sends its number to quad j
-    const uint32_t rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(left >> 32),
-                                                    __builtin_amdgcn_mbcnt_lo((uint32_t)left, 0u));
-    const bool chosen = ((left >> lane) & 1ull) != 0ull && rank < L::kQuads;
-    const uint32_t sent = (uint32_t)__builtin_amdgcn_ds_permute(chosen ? (int)(16u * rank) : 4, (int)lane);
-    const uint32_t which = (uint32_t)__shfl((int)sent, (int)(lane & ~3u));
-    const bool exists = (uint32_t)__builtin_popcountll(left) > lane >> 2;
-    left &= ~__builtin_amdgcn_ballot_w64(chosen);
+  uint32_t events = 0u;
+  if (((left >> lane) & 1ull) != 0ull) {
+    const uint64_t i = first + lane;
+    const bool one_phase = b.collective_type && b.collective_type[i] != THEMIS_COLL_ALL_REDUCE;
+    events = b.chunks[i] * b.ndims[i] * (one_phase ? 1u : 2u);
+  }
+  for (QuadTurns turns(left, events); turns.left != 0ull;) {
+    uint32_t which;
+    const bool exists = turns.take(which);
     const uint64_t i = exists ? first + which : first;
     const Scenario s = load_scenario(b, i);
     const uint32_t D = (uint32_t)s.D;
@@ -2784,6 +2862,12 @@ static bool on_wavefronts(uint64_t items, uint64_t most) {
   return forced != THEMIS_MAPPING_AUTO ? forced == THEMIS_MAPPING_WAVE && items <= 0x7fffffffull
                                        : items <= most;
 }
+// Wavefronts of plan_kernel for 64 scenarios: four where one each would leave the
+// SIMDs with two or fewer (64 chunks, us, one / four: 65,536 4-D scenarios of other
+// NPU counts 145 / 102, 100,003 ragged ones 143 / 128; 65,536 of powers of two 35 / 36).
+static unsigned plan_waves(uint64_t n) {
+  return blocks_for(n) <= 8u * (compute_units() ? compute_units() : 256u) ? kPlanWaves : 1u;
+}
 static bool plan_on_wavefronts(uint64_t items) { return on_wavefronts(items, kWavePlan); }
 static bool simulate_on_wavefronts(uint64_t items) { return on_wavefronts(items, kWaveSimulate); }
 
@@ -2960,10 +3044,9 @@ int themis_plan_batch(const themis_batch_t* batch, uint8_t* orders, double* load
   Launcher go(stream);
   if (plan_on_wavefronts(batch->n * tv.mc))
     go(plan_wave_kernel, (unsigned)(batch->n * tv.mc), kBlock, *batch, orders, loads);
-  else if (tv.mc > 1u)
-    go(plan_kernel<true>, blocks_for(batch->n * tv.mc), kBlock, *batch, orders, loads);
   else
-    go(plan_kernel<false>, blocks_for(batch->n), kBlock, *batch, orders, loads);
+    go(tv.mc > 1u ? plan_kernel<true> : plan_kernel<false>, blocks_for(batch->n * tv.mc),
+       (tv.mc > 1u ? 1u : plan_waves(batch->n)) * kBlock, *batch, orders, loads);
   return go.status();
 }
 

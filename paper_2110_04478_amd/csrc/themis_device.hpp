@@ -109,6 +109,20 @@ __device__ __forceinline__ double tracker_start(const Scenario& s, int k) {
   return s.ctype == THEMIS_COLL_ALL_REDUCE ? s.fix[k] + s.fix[k] : s.fix[k];
 }
 
+// x / P for an NPU count P, y = 1 / P rounded, no result outside the normal range:
+// the correctly rounded quotient in three operations instead of the division's
+// thirty.  q = RN(x * y) is within two units in the last place of x / P, so r = x - q * P
+// is a multiple of q's unit of at most 35 bits, exact; q + r * y then differs from
+// x / P by less than 2^-51 units, and x / P, unless it is a number itself, is no closer
+// than 2^-33 units to the middle of two numbers (x - m * P is a multiple of half a
+// unit, and not zero: m has 54 significant bits).  (The general theorem: Peter
+// Markstein, "Computation of elementary functions on the IBM RISC System/6000
+// processor", 1990.)
+__device__ __forceinline__ double divide_by_count(double x, double P, double y) {
+  const double q = x * y;
+  return __builtin_fma(__builtin_fma(-q, P, x), y, q);
+}
+
 // One step of Alg. 1's Scheduler.Schedule for the chunk that comes next, given
 // the Dim Load Tracker contents load[0..3] (unused dimensions hold +inf on
 // entry and are left untouched).  Returns the order code and adds the chunk's

@@ -88,6 +88,24 @@ __device__ __forceinline__ double quad_min_f64(double v) {
                        (int)quad_swap2((uint32_t)__double2loint(v)));
   return min_f64(v, o);
 }
+// The double of the quad's lane k ^ j.
+__device__ __forceinline__ double quad_other(double v, uint32_t j) {
+  const uint32_t hi = (uint32_t)__double2hiint(v), lo = (uint32_t)__double2loint(v);
+  const auto swap3 = [](uint32_t x) { return (uint32_t)__builtin_amdgcn_mov_dpp((int)x, 0x1b, 0xf, 0xf, true); };
+  return j == 1u ? __hiloint2double((int)quad_swap1(hi), (int)quad_swap1(lo))
+       : j == 2u ? __hiloint2double((int)quad_swap2(hi), (int)quad_swap2(lo))
+                 : __hiloint2double((int)swap3(hi), (int)swap3(lo));
+}
+// The double of the one lane of the quad that says so.
+__device__ __forceinline__ double quad_pick(double v, bool mine) {
+  return __hiloint2double((int)quad_or(mine ? (uint32_t)__double2hiint(v) : 0u),
+                          (int)quad_or(mine ? (uint32_t)__double2loint(v) : 0u));
+}
+// Largest value of the wavefront.
+__device__ __forceinline__ uint32_t quad_wave_max(uint32_t v) {
+  for (int off = 32; off > 0; off >>= 1) v = max(v, (uint32_t)__shfl_xor((int)v, off));
+  return v;
+}
 // The later of two doubles; of a quiet NaN and a number the number.
 __device__ __forceinline__ double max_f64(double a, double b) {
   double r;
@@ -310,6 +328,58 @@ struct QuadTable {
     return v | (rec & 0x1ffu) << 16;
   }
 };
+
+// Alg. 1 with four lanes per collective, NPU counts that are not powers of two:
+// lane k keeps dimension k's load, its place in the order is the number of loads
+// below it, and it divides the chunk by the counts of the dimensions before it.
+// All lanes of the wavefront; chunks: 0 where there is nothing to plan.
+// kExact: IEEE divisions, for sizes that leave the normal range.
+// emit(c, code): the same in the four lanes.  load: of the lane's dimension.
+template <bool kExact, typename Emit>
+__device__ __forceinline__ void plan_quad(const Scenario& s, double chunk, bool themis, bool rel, double thr,
+                                          uint32_t chunks, double& load, Emit emit) {
+  const uint32_t k = threadIdx.x & 3u, D = (uint32_t)s.D;
+  const bool used = k < D, gather = s.ctype == THEMIS_COLL_ALL_GATHER, twice = s.ctype == THEMIS_COLL_ALL_REDUCE;
+  const double coef = sel4((int)k, s.coef[0], s.coef[1], s.coef[2], s.coef[3]);
+  const double mine = (double)sel4((int)k, s.P[0], s.P[1], s.P[2], s.P[3]);
+  double inverse[kMaxDims];
+#pragma unroll
+  for (int d = 0; d < kMaxDims; ++d) inverse[d] = 1.0 / (double)s.P[d];
+  // the threshold where this dimension is the least loaded
+  const double below = rel ? thr * ((gather ? chunk * mine : chunk) * coef) : thr;
+  const double fix = sel4((int)k, s.fix[0], s.fix[1], s.fix[2], s.fix[3]);
+  load = used ? (twice ? fix + fix : fix) : inf64();
+  const uint32_t most = (uint32_t)__builtin_amdgcn_readfirstlane((int)quad_wave_max(chunks));
+  for (uint32_t c = 0; c < most; ++c) {
+    uint32_t before = 0u;   // the dimensions before this one in the stable ascending order
+#pragma unroll
+    for (uint32_t j = 1; j < 4u; ++j) {
+      const uint32_t other = k ^ j;
+      const double l = quad_other(load, j);
+      before += l < load || (l == load && other < k) ? 1u : 0u;
+    }
+    const double lo = quad_min_f64(load), hi = -quad_min_f64(used ? -load : inf64());
+    const double at_least = quad_pick(below, before == 0u);
+    const bool sorted = themis && !(hi - lo < at_least);
+    const uint32_t rank = sorted ? before : k;
+    const uint32_t place = gather ? D - 1u - rank : rank;
+    const uint32_t code = quad_or(used ? k << (2u * place) : 0u);
+    double x = chunk;
+#pragma unroll
+    for (uint32_t j = 0; j < 3u; ++j) {
+      const int d = (int)((code >> (2u * j)) & 3u);
+      const double P = (double)sel4(d, s.P[0], s.P[1], s.P[2], s.P[3]);
+      double next;
+      if (kExact) next = gather ? x * P : x / P;
+      else next = gather ? x * P : divide_by_count(x, P, sel4(d, inverse[0], inverse[1], inverse[2], inverse[3]));
+      x = j < place ? next : x;
+    }
+    if (gather) x = x * mine;
+    const double t = x * coef;
+    if (used && c < chunks) load = load + (twice ? t + t : t);
+    if (c < chunks) emit(c, code);
+  }
+}
 
 // One evaluation's queues on the lane's dimension, before the simulation: the
 // chunks that start here, in the order of their ids.

@@ -25,16 +25,7 @@
 // dimensions take 62 KiB (the links and states 38, the lists 19), two wavefronts.
 //
 // NPU counts that are not powers of two (kDivide): a stage's bytes are the
-// chunk's, divided once per dimension reduced before.  x / P is computed as
-//   q = RN(x * y), r = x - q * P, RN(q + r * y)   with y = RN(1 / P),
-// which is the correctly rounded quotient: q is within two units in the last
-// place of x / P and P is an integer below 2^32, so r is a multiple of q's unit
-// with at most 35 bits and exact; q + r * y then differs from x / P by less than
-// 2^-51 units, while x / P, unless it is a number itself, is no closer than 2^-33
-// units to the middle of two numbers (x - m * P is a multiple of half a unit, and
-// is not zero: m has 54 significant bits, m * P could not be x).
-// (Peter Markstein, "Computation of elementary functions on the IBM RISC
-// System/6000 processor", 1990, for the general theorem.)
+// chunk's, divided once per dimension reduced before, as divide_by_count() does.
 #pragma once
 
 #include "themis_generic.hpp"

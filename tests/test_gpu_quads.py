@@ -25,6 +25,13 @@ def _mixed_counts(n, seed, every, dims=None, max_chunks=40):
     return b
 
 
+def _large_counts(b, seed):
+    """NPU counts over all of their 32 bits (divisions by inverses in the planner)."""
+    rng = np.random.default_rng(seed)
+    b.npus = np.ascontiguousarray((2 ** rng.uniform(1, 32, b.npus.shape)).astype(np.uint32) | 1)
+    return b
+
+
 CASES = dict(MAPPING_CASES)
 CASES.update({
     "1 scenario": lambda W: W.mixed(1, seed=901),
@@ -35,6 +42,7 @@ CASES.update({
     "four dimensions, 100 chunks": lambda W: _mixed_counts(70, 906, 3, dims=4, max_chunks=100),
     "three dimensions, 300 chunks": lambda W: _mixed_counts(40, 907, 3, dims=3, max_chunks=300),
     "two of 16 powers of two, four dimensions": lambda W: _mixed_counts(200, 909, 8, dims=4, max_chunks=30),
+    "NPU counts of 32 bits": lambda W: _large_counts(_with_collective_types(W.mixed(300, seed=920), 15), 16),
     "types, delays, other counts": lambda W: _with_fixed_delay(_with_collective_types(
         _mixed_counts(300, 908, 3), 13), 14),
 })

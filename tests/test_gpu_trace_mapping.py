@@ -9,6 +9,7 @@ three dimensions of powers of two in the first one."""
 import numpy as np
 import pytest
 
+from test_gpu_quads import _large_counts
 from test_gpu_parity import (_add_trace, _with_collective_types, _with_fixed_delay, check_batch, gpu,  # noqa: F401
                              w)
 
@@ -59,6 +60,7 @@ CASES = {
     "other counts, releases": lambda: _released(_trace(90, 10, 17, 8, pow2=False), 1),
     "types, delays, releases": lambda: _released(_with_fixed_delay(_with_collective_types(
         _trace(120, 11, 16, 9), 2), 3), 4),
+    "NPU counts of 32 bits": lambda: _large_counts(_trace(60, 19, 9, 5), 9),
     "types, other counts": lambda: _with_collective_types(_trace(120, 12, 9, 7, pow2=False), 5),
     "1 trace": lambda: _trace(1, 15, 20, 12, dims=3),
     "17 traces, long queues": lambda: _bottleneck(_trace(17, 16, 30, 40, dims=3)),
