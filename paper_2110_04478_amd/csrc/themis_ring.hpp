@@ -329,7 +329,8 @@ __device__ inline uint32_t ring_table_entry(uint32_t r, uint32_t behind, uint32_
 // derives all of that from mask and code at every stage start.
 // kShared (with kTable): all lanes evaluate the same scenario, on differing
 // orders.  The stage times then sit in the table too, so nothing here depends
-// on the NPU counts being powers of two (Model: SharedModel, themis_shared.hpp).
+// on the NPU counts being powers of two (Model: SharedModel, themis_shared.hpp),
+// and the records need no initialisation: the model gives the chunks' orders.
 template <bool kTable, int kQueueOrder, bool kBusy, bool kFix, bool kShared = false, typename Model>
 __device__ __forceinline__ FastResult ring_loop(const Scenario& s, const Model& model,
                                                 const LaneLds& lds, const FastOut& out,
@@ -396,9 +397,31 @@ __device__ __forceinline__ FastResult ring_loop(const Scenario& s, const Model& 
   // a6: every chunk waits at the dimension of its first stage, in chunk-id
   // order, in the class of the initial mask
   if constexpr (kShared) {
+    // All chunks start with the same size, so each dimension has one list, whose
+    // ends stay in registers: the link to c is the upper byte of the record of
+    // the chunk before it (a record without stages behind it has bits 8-9 zero),
+    // and nothing is read back.
+    uint32_t heads = 0u, tails = 0u, some = 0u;   // byte k: of dimension k's list
     for (uint32_t c = 0; c < C; ++c) {
-      const uint32_t low10 = (uint32_t)*L::rec(lds, c) & 0x3ffu;   // the order's rank, no stage behind it
-      push(model.first_list(low10 >> 3), low10 | (c << 10));
+      const uint32_t rank = model.rank_at(c);
+      const uint32_t at = model.first_dim(rank) << 3;
+      const bool had = ((some >> at) & 1u) != 0u;
+      const uint32_t last = had ? (tails >> at) & 63u : c;
+      *L::rec(lds, c) = (uint16_t)(rank << 3 | c << 10);
+      ((uint8_t*)L::rec(lds, last))[1] = (uint8_t)(c << 2);
+      heads |= (had ? 0u : c) << at;
+      tails = bfi(0xffu << at, c << at, tails);
+      some |= 1u << at;
+    }
+#pragma unroll
+    for (uint32_t k = 0; k < (uint32_t)kMaxDims; ++k) {
+      if ((some >> (8u * k)) & 1u) {
+        const uint32_t q = 16u * k + model.first_class(k), last = (tails >> (8u * k)) & 63u;
+        ((uint8_t*)L::rec(lds, last))[1] = (uint8_t)(((heads >> (8u * k)) & 63u) << 2);
+        *L::tail(lds, q) = (uint8_t)last;
+        if (k < 2u) ne_lo |= 1u << q;
+        else ne_hi |= 1u << (q - 32u);
+      }
     }
   } else {
     const uint32_t mask0 = model.state0() & 15u, phase0 = (model.state0() >> 4) & 1u;

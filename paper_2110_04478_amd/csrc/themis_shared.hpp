@@ -9,7 +9,6 @@
 //   step      what the stage does, as in ring_loop's table
 //   time      its duration
 // and per order rank
-//   first     list a chunk joins before its first stage
 //   load[k]   time the chunk keeps dimension k busy
 //   head[k]   time of its stages before the first one on k
 //   tail[k]   time of its stages after the last one on k
@@ -25,28 +24,40 @@ struct SharedTable {
   uint16_t step[kWaveOrders * 8u];
   float4 load[kWaveOrders], head[kWaveOrders], tail[kWaveOrders];
   float serial[kWaveOrders];
-  uint8_t first[32];
   uint8_t rank_of[32];   // order rank of the permutation with lexicographic index j
-};
-
-// The model ring_loop<kShared> runs on.
-struct SharedModel {
-  const SharedTable& tab;
-  bool rs, gather;
-  double tmin;
-  __device__ __forceinline__ uint32_t epack() const { return 0u; }
-  __device__ __forceinline__ uint64_t ranks() const { return 0ull; }
-  __device__ __forceinline__ bool rs_only() const { return rs; }
-  __device__ __forceinline__ bool one_phase() const { return rs || gather; }
-  __device__ __forceinline__ uint32_t first_list(uint32_t rank) const { return tab.first[rank & 31u]; }
-  __device__ __forceinline__ double stage_time(uint32_t at) const { return tab.time[at]; }
-  __device__ __forceinline__ double t_min(uint32_t) const { return tmin; }
 };
 
 struct SharedSetup {
   double t_min;      // smallest stage time
   double t_max;      // no schedule of C chunks takes longer than C * t_max
   bool ok;           // the ring loop can run on the table
+  // where a chunk waits first: bits 0 and 1 of the dimension, a bit per order
+  // rank, and the class there, four bits per dimension (all chunks start with
+  // the same size)
+  uint32_t first_dim[2], first_class;
+};
+
+// The model ring_loop<kShared> runs on.  at(c): rank of chunk c's order, asked
+// once for every chunk in ascending order.
+template <typename RankAt>
+struct SharedModel {
+  const SharedTable& tab;
+  const SharedSetup& setup;
+  int ctype;
+  RankAt& at;
+  __device__ __forceinline__ SharedModel(const SharedTable& t, const SharedSetup& u, int type, RankAt& a)
+      : tab(t), setup(u), ctype(type), at(a) {}
+  __device__ __forceinline__ uint32_t epack() const { return 0u; }
+  __device__ __forceinline__ uint64_t ranks() const { return 0ull; }
+  __device__ __forceinline__ bool rs_only() const { return ctype == THEMIS_COLL_REDUCE_SCATTER; }
+  __device__ __forceinline__ bool one_phase() const { return ctype != THEMIS_COLL_ALL_REDUCE; }
+  __device__ __forceinline__ uint32_t rank_at(uint32_t c) const { return at(c) & 31u; }
+  __device__ __forceinline__ uint32_t first_dim(uint32_t rank) const {
+    return ((setup.first_dim[0] >> rank) & 1u) | ((setup.first_dim[1] >> rank) & 1u) << 1;
+  }
+  __device__ __forceinline__ uint32_t first_class(uint32_t k) const { return (setup.first_class >> (4u * k)) & 15u; }
+  __device__ __forceinline__ double stage_time(uint32_t at) const { return tab.time[at]; }
+  __device__ __forceinline__ double t_min(uint32_t) const { return setup.t_min; }
 };
 
 // Fills the table for all orders of the scenario (all 64 lanes are here and
@@ -92,9 +103,6 @@ __device__ __forceinline__ SharedSetup shared_table(const Scenario& s, double ch
         ((float*)&tab.head[rank])[k] = gather ? after : before;
         ((float*)&tab.tail[rank])[k] = both || gather ? before : after;
         before += tk;
-        if (p == (gather ? D - 1u : 0u))
-          tab.first[rank] = (uint8_t)(16 * k + (int)sel4(k, t.first_class[0], t.first_class[1],
-                                                         t.first_class[2], t.first_class[3]));
       }
     }
     if (phase == (gather ? 1u : 0u)) tab.serial[rank] = both ? 2.0f * sum : sum;
@@ -108,6 +116,18 @@ __device__ __forceinline__ SharedSetup shared_table(const Scenario& s, double ch
     total = other > total ? other : total;
   }
   SharedSetup r;
+  const bool starts = mine && phase == (gather ? 1u : 0u);
+  const uint32_t kf = (code >> (gather ? 2u * D - 2u : 0u)) & 3u, shift = gather ? kWaveOrders : 0u;
+  r.first_class = 0u;
+#pragma unroll
+  for (uint32_t k = 0; k < (uint32_t)kMaxDims; ++k) {
+    const uint64_t on = __builtin_amdgcn_ballot_w64(starts && kf == k);
+    if (on != 0ull)
+      r.first_class |= ((uint32_t)__builtin_amdgcn_readlane((int)t.first_class[k], __builtin_ctzll(on)) & 15u)
+                       << (4u * k);
+  }
+  r.first_dim[0] = (uint32_t)(__builtin_amdgcn_ballot_w64(starts && (kf & 1u) != 0u) >> shift);
+  r.first_dim[1] = (uint32_t)(__builtin_amdgcn_ballot_w64(starts && (kf & 2u) != 0u) >> shift);
   r.t_min = t.t_min;
   r.t_max = total;
   r.ok = t.normal && t.few_classes;
@@ -134,6 +154,18 @@ struct SharedBound {
       tail.z = fminf(tail.z, t.z); tail.w = fminf(tail.w, t.w);
     }
     serial = fmaxf(serial, tab.serial[rank]);
+  }
+  // the chunks that the lane `off` away has added
+  __device__ __forceinline__ void join(int off, bool both) {
+    load.x += __shfl_xor(load.x, off); load.y += __shfl_xor(load.y, off);
+    load.z += __shfl_xor(load.z, off); load.w += __shfl_xor(load.w, off);
+    head.x = fminf(head.x, __shfl_xor(head.x, off)); head.y = fminf(head.y, __shfl_xor(head.y, off));
+    head.z = fminf(head.z, __shfl_xor(head.z, off)); head.w = fminf(head.w, __shfl_xor(head.w, off));
+    if (!both) {
+      tail.x = fminf(tail.x, __shfl_xor(tail.x, off)); tail.y = fminf(tail.y, __shfl_xor(tail.y, off));
+      tail.z = fminf(tail.z, __shfl_xor(tail.z, off)); tail.w = fminf(tail.w, __shfl_xor(tail.w, off));
+    }
+    serial = fmaxf(serial, __shfl_xor(serial, off));
   }
   __device__ __forceinline__ float value(bool both) const {
     const float4 t = both ? head : tail;
