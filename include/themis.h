@@ -325,9 +325,9 @@ int themis_sweep_with_scratch(const themis_batch_t *batch, int n_thr,
  *   THEMIS_MAPPING_LANE : one lane per evaluation
  *   THEMIS_MAPPING_QUAD : four lanes per evaluation, one per dimension
  * LANE and QUAD also fix which of the two themis_simulate_batch takes where it does
- * not take a wavefront per scenario (beyond 64 chunks there is only QUAD).
- * Process-wide, takes effect with the next call; meant for measurements and tests.  Returns THEMIS_ERR_INVALID_ARGUMENT for any other
- * value.
+ * not take a wavefront per scenario.  Beyond 64 chunks there is only QUAD, for
+ * either.  Process-wide, takes effect with the next call; meant for measurements
+ * and tests.  Returns THEMIS_ERR_INVALID_ARGUMENT for any other value.
  */
 #define THEMIS_MAPPING_AUTO 0
 #define THEMIS_MAPPING_LANE 1

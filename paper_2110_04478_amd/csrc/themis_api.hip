@@ -12,7 +12,6 @@
 #include "themis_device.hpp"
 #include "themis_fast.hpp"
 #include "themis_generic.hpp"
-#include "themis_packed.hpp"
 #include "themis_ring.hpp"
 #include "themis_quad.hpp"
 #include "themis_shared.hpp"
@@ -334,8 +333,7 @@ __device__ __forceinline__ LaneLds lane_lds(uint32_t* lds_block) {
 template <typename L>
 __device__ __forceinline__ void init_chunk(const LaneLds& lds, uint32_t c, uint32_t code,
                                            uint32_t state0, uint32_t D) {
-  if constexpr (L::kPacked) L::init_chunk(lds, c, code, state0, D);
-  else L::init_chunk(lds, c, code, state0);
+  L::init_chunk(lds, c, code, state0);
 }
 
 // The power-of-two event loop that goes with the layout.
@@ -346,8 +344,6 @@ __device__ __forceinline__ FastResult simulate_pow2(const Scenario& s, const Pow
     // entries leave one by one: collected dwords become single bytes
     constexpr int kMode = kQueueOrder == kWords ? (int)kBytes : kQueueOrder;
     return simulate_ring<kMode, kBusy, kFix>(s, model, lds, out);
-  } else if constexpr (L::kPacked) {
-    return simulate_packed<L, kQueueOrder, kBusy, kFix>(s, model, lds, out);
   } else {
     return simulate_fast<L, kQueueOrder, kBusy, kFix, Pow2Model>(s, model, lds, out);
   }
@@ -557,7 +553,7 @@ simulate_kernel(themis_batch_t b, const uint8_t* __restrict__ orders,
       so.lane_offset = IsRing<L>::value ? threadIdx.x : 4u * threadIdx.x;
       so.staging_bytes = (uint32_t)kBlock * rows_bytes;
       FastResult r;
-      if constexpr (kQueueOrder == kWords && !L::kPacked) {
+      if constexpr (kQueueOrder == kWords) {
         r = staged ? simulate_pow2<L, kStagedBytes, kBusy, kFix>(s, Pow2Model(s, fs, scf), lds, so)
                    : simulate_pow2<L, kWords, kBusy, kFix>(s, Pow2Model(s, fs, scf), lds, fo);
       } else {
@@ -1598,12 +1594,12 @@ sweep_kernel(themis_batch_t b, int n_thr, const double* __restrict__ thr, int th
 
 // The same with four lanes per evaluation (themis_quad.hpp): a wavefront takes
 // 16 consecutive scenarios under one threshold and one scheduler.
-template <bool kFix, bool kBaseline, bool kJobs>
-__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(LayoutQuad<512, 16>::kWavesPerSimd)))
+template <uint32_t kChunks, bool kFix, bool kBaseline, bool kJobs>
+__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(LayoutQuad<kChunks, 16>::kWavesPerSimd)))
 sweep_quad_kernel(themis_batch_t b, int n_thr, const double* __restrict__ thr, int thr_per_scenario,
                   unsigned policy_mask, int n_pol, double* __restrict__ t_done,
                   unsigned long long hand_over, SweepJobs jobs) {
-  using L = LayoutQuad<512, 16>;
+  using L = LayoutQuad<kChunks, 16>;
   __shared__ uint32_t lds_block[QuadPow2<L, kFix>::kBytes / 4u];
   const uint32_t quad = threadIdx.x >> 2;
   const SweepSlot slot =
@@ -2848,14 +2844,17 @@ static unsigned follow_up_blocks(uint64_t items) {
   return all < cap ? all : cap;
 }
 
-// Which mapping themis_sweep's LDS kernel uses for a layout capacity: four
-// lanes per evaluation from kQuadFromCap chunks on, one lane below, unless
-// themis_set_sweep_mapping() has fixed one of them.
-constexpr uint32_t kQuadFromCap = 256;
+// Which mapping themis_sweep's LDS kernel uses for a layout capacity: beyond 64
+// chunks four lanes per evaluation, where LDS held back the lanes (four wavefronts
+// per CU at 128 chunks, three at 256, two at 512; quads 16, 12 and 8).  Measured (us,
+// lane / quads): 100 chunks, all schedulers and 8 thresholds, 300 4-D scenarios 506 /
+// 320, 30,000 2,208 / 1,779; 60,000 of 128 chunks, Themis schedulers, 5,400 / 4,355; 70
+// chunks 2,734 / 1,974; 30,001 of 200 chunks 10,508 / 4,479.  At 64 chunks the lanes
+// are faster: twelve wavefronts per CU.
 static std::atomic<int> sweep_mapping{THEMIS_MAPPING_AUTO};
 static bool sweep_mapping_is_quad(uint32_t cap) {
   const int forced = sweep_mapping.load(std::memory_order_relaxed);
-  return forced != THEMIS_MAPPING_AUTO ? forced == THEMIS_MAPPING_QUAD : cap >= kQuadFromCap;
+  return cap > 64u || forced == THEMIS_MAPPING_QUAD;
 }
 
 // Four lanes per scenario (themis_quad.hpp) or one?  A pass of the quads' loop
@@ -3027,9 +3026,8 @@ static bool sweep_shares_plans(uint64_t n, uint32_t max_chunks, int n_thr, unsig
   if (n * max_chunks < 32768u) return false;
   const uint32_t cap = layout_capacity(max_chunks);
   const bool quad = sweep_mapping_is_quad(cap);
-  if (!quad && cap > 128u) return false;
-  const uint64_t per_cu = quad ? 8u : cap == 128u ? 4u : 12u;
-  const uint64_t group = quad ? LayoutQuad<512, 16>::kQuads : kBlock;
+  const uint64_t per_cu = quad ? 8u : 12u;
+  const uint64_t group = quad ? kBlock / 4u : kBlock;
   const uint64_t waves = (n + group - 1u) / group *
       sweep_roles((uint32_t)n_thr, (uint32_t)__builtin_popcount(policy_mask & 7u), policy_mask);
   const unsigned cus = compute_units();
@@ -3253,6 +3251,7 @@ int themis_simulate_batch_noalloc(const themis_batch_t* batch, const uint8_t* or
 }
 
 #define THEMIS_SWEEP_LANES(L) sweep_kernel<L,
+#define THEMIS_SWEEP_QUADS(CAP) sweep_quad_kernel<CAP,
 size_t themis_sweep_scratch_bytes(uint64_t n, uint32_t max_chunks, int n_thr, unsigned policy_mask) {
   if (!sweep_shares_plans(n, max_chunks, n_thr, policy_mask)) return 0;
   return kSweepJobsHeader + (size_t)n * (size_t)n_thr * sizeof(SweepJob);
@@ -3289,16 +3288,22 @@ int themis_sweep_with_scratch(const themis_batch_t* batch, int n_thr, const doub
   const bool fix = batch->fixed_delay != nullptr;
   const bool base = (policy_mask & THEMIS_SWEEP_BASELINE) != 0u;
   const bool quad = sweep_mapping_is_quad(cap);
-  const uint64_t group = quad ? LayoutQuad<512, 16>::kQuads : kBlock;   // evaluations per wavefront
+  const uint64_t group = quad ? kBlock / 4u : kBlock;   // evaluations per wavefront
   const uint64_t groups = (batch->n + group - 1u) / group;
   if (groups * (uint64_t)(n_thr * n_pol) > 0x7fffffffull) return THEMIS_ERR_UNSUPPORTED;
   const size_t need = themis_sweep_scratch_bytes(batch->n, batch->max_chunks, n_thr, policy_mask);
-  const bool share = need != 0u && scratch != nullptr && scratch_bytes_given >= need && (quad || cap <= 128u);
+  const bool share = need != 0u && scratch != nullptr && scratch_bytes_given >= need;
   const unsigned long long call = next_call_number();
   Launcher go(stream);
   SweepJobs jobs{nullptr, nullptr};
   // (one workgroup per group of scenarios and pair, the baseline once: see sweep_roles)
   const unsigned roles = sweep_roles((uint32_t)n_thr, (uint32_t)n_pol, policy_mask);
+  // Layout of the quads.  The one of 256 chunks has twelve wavefronts per CU, the one
+  // of 512 eight, and where these hold all of a sweep the latter is the faster by up
+  // to 7 % (200 chunks, 4-D, us, 256 / 512: 600 scenarios, 646 wavefronts, 682 / 631;
+  // 2,000, 2,125 wavefronts, 831 / 1,215; 30,001 4,479 / 5,595).
+  const uint32_t quad_cap = !quad ? 0u : cap <= 128u ? 128u
+      : groups * roles <= 8u * (compute_units() ? compute_units() : 256u) ? 512u : cap;
   if (share) {
     uint32_t* count = (uint32_t*)scratch;
     SweepJob* list = (SweepJob*)((uint8_t*)scratch + kSweepJobsHeader);
@@ -3311,10 +3316,11 @@ int themis_sweep_with_scratch(const themis_batch_t* batch, int n_thr, const doub
     const uint64_t most = (batch->n * (uint64_t)n_thr + group - 1u) / group * (uint64_t)(n_pol - (base ? 1 : 0));
 #define THEMIS_SWEEP_KERNEL(K) \
   (fix ? (base ? K true, true, true> : K true, false, true>) : (base ? K false, true, true> : K false, false, true>))
-    auto kernel = quad ? THEMIS_SWEEP_KERNEL(sweep_quad_kernel<)
+    auto kernel = quad_cap == 512u ? THEMIS_SWEEP_KERNEL(THEMIS_SWEEP_QUADS(512))
+                : quad_cap == 256u ? THEMIS_SWEEP_KERNEL(THEMIS_SWEEP_QUADS(256))
+                : quad ? THEMIS_SWEEP_KERNEL(THEMIS_SWEEP_QUADS(128))
                 : cap == 16u ? THEMIS_SWEEP_KERNEL(THEMIS_SWEEP_LANES(Layout16))
-                : cap == 64u ? THEMIS_SWEEP_KERNEL(THEMIS_SWEEP_LANES(LayoutRing))
-                             : THEMIS_SWEEP_KERNEL(THEMIS_SWEEP_LANES(Layout128));
+                             : THEMIS_SWEEP_KERNEL(THEMIS_SWEEP_LANES(LayoutRing));
     go(kernel, (unsigned)((base ? groups : 0u) + most), kBlock, *batch, n_thr, thr, thr_per_scenario,
        policy_mask, n_pol, t_done, call, jobs);
 #undef THEMIS_SWEEP_KERNEL
@@ -3324,12 +3330,11 @@ int themis_sweep_with_scratch(const themis_batch_t* batch, int n_thr, const doub
   } else {
 #define THEMIS_SWEEP_KERNEL(K) \
   (fix ? (base ? K true, true, false> : K true, false, false>) : (base ? K false, true, false> : K false, false, false>))
-    auto kernel = quad ? THEMIS_SWEEP_KERNEL(sweep_quad_kernel<)
+    auto kernel = quad_cap == 512u ? THEMIS_SWEEP_KERNEL(THEMIS_SWEEP_QUADS(512))
+                : quad_cap == 256u ? THEMIS_SWEEP_KERNEL(THEMIS_SWEEP_QUADS(256))
+                : quad ? THEMIS_SWEEP_KERNEL(THEMIS_SWEEP_QUADS(128))
                 : cap == 16u ? THEMIS_SWEEP_KERNEL(THEMIS_SWEEP_LANES(Layout16))
-                : cap == 64u ? THEMIS_SWEEP_KERNEL(THEMIS_SWEEP_LANES(LayoutRing))
-                : cap == 128u ? THEMIS_SWEEP_KERNEL(THEMIS_SWEEP_LANES(Layout128))
-                : cap == 256u ? THEMIS_SWEEP_KERNEL(THEMIS_SWEEP_LANES(LayoutPacked<256>))
-                              : THEMIS_SWEEP_KERNEL(THEMIS_SWEEP_LANES(LayoutPacked<512>));
+                             : THEMIS_SWEEP_KERNEL(THEMIS_SWEEP_LANES(LayoutRing));
 #undef THEMIS_SWEEP_KERNEL
     go(kernel, (unsigned)groups * roles, kBlock, *batch, n_thr, thr, thr_per_scenario, policy_mask, n_pol, t_done,
        call, jobs);

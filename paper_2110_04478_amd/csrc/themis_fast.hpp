@@ -76,7 +76,7 @@ struct Classes16 {
   }
 };
 
-// Per-lane LDS layouts with 8-bit chunk ids (kChunks <= 128; 0xFF ends a list).
+// Per-lane LDS layouts with 8-bit chunk ids (0xFF ends a list).
 //
 // Layout64 (80 dwords, 20 KiB per wavefront, 8 wavefronts per CU; the table
 // layouts for other NPU counts build on it, power-of-two scenarios of up to 64
@@ -87,14 +87,11 @@ struct Classes16 {
 //     byte 2  chunk c: order code
 //     byte 3  list q: head chunk
 //   dwords 64..79  u8 tail[64]: last chunk of list q
-// LayoutByte<128> (144 dwords, 4 wavefronts per CU): the same with 128 chunk
-// dwords, of which the first 64 carry the list heads.
 // LayoutByte<16> (48 dwords, 12 KiB per wavefront, 13 wavefronts per CU; the
 // kernel runs faster the more wavefronts share a SIMD): 16 chunk dwords with
 // byte 3 unused, then u8 head[64] and u8 tail[64].
 template <uint32_t kChunks>
 struct LayoutByte {
-  static constexpr bool kPacked = false;  // 32-bit chunk words, simulate_fast
   static constexpr uint32_t kCap = kChunks;
   static_assert(kChunks <= 128, "chunk ids and the list end mark share 8 bits");
   static constexpr bool kHeadInChunkWord = kChunks >= 64;
@@ -132,7 +129,6 @@ struct LayoutByte {
 };
 using Layout64 = LayoutByte<64>;
 using Layout16 = LayoutByte<16>;
-using Layout128 = LayoutByte<128>;
 
 // Per-evaluation constants of the fast path.
 //

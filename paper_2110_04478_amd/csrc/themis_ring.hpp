@@ -42,7 +42,6 @@
 namespace themis {
 
 struct LayoutRing {
-  static constexpr bool kPacked = false;
   static constexpr bool kRing = true;
   static constexpr uint32_t kCap = 64;
   static constexpr uint32_t kRecBytes = kCap * 128u;   // 64 records x 64 lanes x 2 bytes

@@ -222,7 +222,6 @@ struct Classes64 {
 
 template <uint32_t kChunks>
 struct LayoutTableWideT {
-  static constexpr bool kPacked = false;
   static constexpr uint32_t kCap = kChunks;
   static_assert(kChunks == 64 || kChunks == 128, "8-bit links; ids as in LayoutByte");
   static constexpr uint32_t kSlots = 24;
@@ -376,9 +375,8 @@ __device__ inline void table_setup_wide(const Scenario& s, bool scf, const LaneL
 
 // ---------------------------------------------------------------------------
 // More than 128 chunks with NPU counts that are not powers of two: 16-bit
-// chunk records as in themis_packed.hpp, with the chunk's slot where that
-// file keeps the order (a slot stands for one order code, kept in a small
-// table), 64 classes per dimension as in the wide variant, and a stage time's
+// chunk records with the chunk's slot (a slot stands for one order code, kept
+// in a small table) from which its stage follows, 64 classes per dimension as in the wide variant, and a stage time's
 // divisions redone at each dispatch.
 //   record: bits 0-8 next chunk of its list (its own id: the last one),
 //           bit 9 phase, bits 10-14 slot
@@ -473,8 +471,7 @@ __device__ inline void table_setup_packed(const Scenario& s, bool scf, const Lan
   }
 }
 
-// The event loop of simulate_packed() on slots: same contract as
-// simulate_fast (result.ok false leaves the evaluation to the generic path).
+// The event loop on these records: same contract as simulate_fast (result.ok false leaves the evaluation to the generic path).
 // A chunk in the Reduce-Scatter phase at position pos of its order waits for
 // stage pos, in the All-Gather phase for stage 2 D - 1 - pos.
 template <typename L, int kQueueOrder, bool kBusy, typename Model>

@@ -9,7 +9,7 @@ import numpy as np
 import pytest
 
 from test_gpu_mapping import CASES as MAPPING_CASES
-from test_gpu_parity import (check_batch, gpu, w, _with_collective_types,  # noqa: F401
+from test_gpu_parity import (assert_close, check_batch, gpu, w, _with_collective_types,  # noqa: F401
                              _with_fixed_delay)
 
 pytestmark = pytest.mark.gpu
@@ -67,3 +67,23 @@ def test_batch_sizes_around_the_lines(gpu, oracle, n, chunks):
     """Where the mapping changes, and where the follow-up kernel's workgroups look
     at more scenarios each; all kinds of NPU counts."""
     check_batch(gpu, oracle, _mixed_counts(n, 910 + chunks, 2, max_chunks=chunks), threads=16)
+
+
+@pytest.mark.parametrize("max_chunks,n", [(65, 33), (127, 50), (128, 17), (129, 33), (256, 17), (257, 16)])
+def test_sweeps_on_quads_at_the_chunk_capacities(gpu, oracle, max_chunks, n):
+    """Every kind of NPU counts at both ends of each capacity, all of its chunks
+    used by some scenarios; the last wavefront has empty quads."""
+    import torch
+    thr = np.array([0.0, 1.0 / 16.0, 0.5])
+    gpu.themis_set_sweep_mapping(gpu.MAPPING_QUAD)
+    try:
+        for delay in (False, True):
+            b = _mixed_counts(n, 930 + max_chunks, 2, max_chunks=max_chunks)
+            b.chunks[::3] = max_chunks
+            if delay:
+                b = _with_fixed_delay(b, 17)
+            sw = gpu.themis_sweep(gpu.to_device(b), torch.tensor(thr, device="cuda"), 7)
+            torch.cuda.synchronize()
+            assert_close("sweep", sw.cpu().numpy(), oracle.sweep(b, thr, 7, threads=8))
+    finally:
+        gpu.themis_set_sweep_mapping(gpu.MAPPING_AUTO)

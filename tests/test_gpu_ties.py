@@ -103,8 +103,8 @@ SIZES = {16: 500, 64: 500, 128: 300, 256: 130, 512: 100}
 @pytest.mark.parametrize("max_chunks", [16, 64, 128, 256, 512])
 def test_simultaneous_completions_on_every_lds_layout(gpu, oracle, max_chunks):
     """All-Reduce plans of Alg. 1 on the tie-rich networks, one chunk capacity
-    per LDS layout: up to 128 chunks the event loop of simulate_fast, beyond it
-    simulate_packed.  Reaches the branch at the end of their delivery loops
+    per LDS layout: up to 64 chunks a lane's event loop, beyond it the one of
+    four lanes.  Reaches the branch at the end of their delivery loops
     that takes the next completion of the same instant (the smallest
     chunk << 2 | dimension among the stages left in `done`), and the appends
     that keep every list in (arrival, chunk id) order when several chunks
