@@ -95,6 +95,14 @@ __device__ __forceinline__ bool nothing_marked(unsigned long long call) {
   return *(volatile unsigned long long*)&g_marked_call < call;
 }
 
+// HIP takes fewer than 2^32 threads along one direction of a grid.  Kernels with four
+// lanes per scenario or evaluation reach that four times as early as those with one
+// (64 million scenarios of a sweep under 17 pairs of threshold and scheduler), so their
+// workgroups are laid out in rows (Launcher::in_rows); those beyond the last one that is
+// wanted find nothing to do.
+constexpr uint32_t kGridRow = 1u << 25;
+__device__ __forceinline__ uint32_t block_index() { return blockIdx.y * kGridRow + blockIdx.x; }
+
 // Work of some lanes of a wavefront, taken by its quads 16 at a time, the longest
 // first: a turn takes as long as its longest (100,003 ragged scenarios of any NPU
 // counts, both simulation kernels: 1,503 us in the order they come, 995 so).
@@ -702,7 +710,8 @@ simulate_quad_kernel(themis_batch_t b, const uint8_t* __restrict__ orders, doubl
   constexpr uint32_t kLdsBytes = kOthers && QuadTable<L3, 3>::kBytes > QuadPow2<L, kFix>::kBytes ? QuadTable<L3, 3>::kBytes : QuadPow2<L, kFix>::kBytes;
   __shared__ uint64_t lds_block[(kLdsBytes + 7u) / 8u];
   const uint32_t k = threadIdx.x & 3u;
-  const uint64_t first = (uint64_t)blockIdx.x * L::kQuads, at = first + (threadIdx.x >> 2);
+  const uint64_t first = (uint64_t)block_index() * L::kQuads, at = first + (threadIdx.x >> 2);
+  if (first >= b.n) return;
   // a quad without a scenario stays: the wavefront leaves the event loop as a whole
   const bool exists = at < b.n;
   const uint64_t i = exists ? at : b.n - 1u;
@@ -1087,7 +1096,7 @@ simulate_trace_quad_kernel(themis_batch_t b, const uint8_t* __restrict__ orders,
   if (follow_up && nothing_marked(call)) return;
   const TraceView tv = trace_view(b);
   const uint32_t k = threadIdx.x & 3u;
-  const uint64_t at = (uint64_t)blockIdx.x * (kBlock / 4u) + (threadIdx.x >> 2);
+  const uint64_t first = (uint64_t)block_index() * (kBlock / 4u), at = first + (threadIdx.x >> 2);
   const bool exists = at < b.n && (!follow_up || is_left_to_generic(t_done[at]));
   if (__builtin_amdgcn_ballot_w64(exists) == 0ull) return;
   const uint64_t i = at < b.n ? at : b.n - 1u;
@@ -1115,7 +1124,7 @@ simulate_trace_quad_kernel(themis_batch_t b, const uint8_t* __restrict__ orders,
   uint8_t* const entries = queue_order ? (uint8_t*)queue_order + ((size_t)i * kMaxDims + k) * 2u * tv.slots * (uint32_t)entry_bytes
                                        : nullptr;
   const TraceQuadResult r = simulate_trace_quad<kPut>(
-      s, fs, runs ? Q : 0u, scf, smallest, l, trace_lds, trace_area + (size_t)blockIdx.x * (kBlock / 4u) * stride, stride,
+      s, fs, runs ? Q : 0u, scf, smallest, l, trace_lds, trace_area + (size_t)first * stride, stride,
       [&](uint32_t q, uint32_t c) {
         const uint8_t* at_c = row + (size_t)q * b.max_chunks + c;
         if (dwords) return *(const uint32_t*)at_c;
@@ -1498,26 +1507,26 @@ sweep_spread_kernel(themis_batch_t b, SweepJobs jobs, int n_thr, const double* _
 // The evaluation a lane takes: `group` consecutive scenarios under one role per
 // workgroup (`at`: the lane's place among them), or, from a list, `group` jobs
 // under one Themis policy, behind the baseline's workgroups.
-__device__ __forceinline__ SweepSlot sweep_lane_slot(const themis_batch_t& b, uint32_t group, uint32_t at,
-                                                     int n_thr, unsigned policy_mask, int n_pol) {
+__device__ __forceinline__ SweepSlot sweep_lane_slot(const themis_batch_t& b, uint32_t workgroup, uint32_t group,
+                                                     uint32_t at, int n_thr, unsigned policy_mask, int n_pol) {
   const uint32_t roles = sweep_roles((uint32_t)n_thr, (uint32_t)n_pol, policy_mask);
-  const uint64_t i = (uint64_t)(blockIdx.x / roles) * group + at;
+  const uint64_t i = (uint64_t)(workgroup / roles) * group + at;
   const bool exists = i < b.n;
   return SweepSlot{(exists ? i : 0u) * ((uint32_t)n_thr * (uint32_t)n_pol) +
-                       sweep_block_role(blockIdx.x, (uint32_t)n_thr, (uint32_t)n_pol, policy_mask),
+                       sweep_block_role(workgroup, (uint32_t)n_thr, (uint32_t)n_pol, policy_mask),
                    0u, exists};
 }
 template <bool kBaseline>
 __device__ __forceinline__ SweepSlot sweep_block_slot(const themis_batch_t& b, const SweepJobs& jobs,
-                                                      uint32_t group, uint32_t at, int n_thr,
-                                                      unsigned policy_mask, int n_pol) {
+                                                      uint32_t workgroup, uint32_t group, uint32_t at,
+                                                      int n_thr, unsigned policy_mask, int n_pol) {
   const uint32_t base_blocks = kBaseline ? (uint32_t)((b.n + group - 1u) / group) : 0u;
-  if (kBaseline && blockIdx.x < base_blocks) {
-    const uint64_t i = (uint64_t)blockIdx.x * group + at;
+  if (kBaseline && workgroup < base_blocks) {
+    const uint64_t i = (uint64_t)workgroup * group + at;
     const bool exists = i < b.n;
     return SweepSlot{(exists ? i : 0u) * ((uint32_t)n_thr * (uint32_t)n_pol), 0u, exists};
   }
-  const uint32_t block = blockIdx.x - base_blocks, themis = (uint32_t)n_pol - (kBaseline ? 1u : 0u);
+  const uint32_t block = workgroup - base_blocks, themis = (uint32_t)n_pol - (kBaseline ? 1u : 0u);
   const uint32_t g = block / themis;
   return sweep_job_slot(jobs, (uint64_t)g * group + at, block - g * themis, n_thr, policy_mask, n_pol);
 }
@@ -1542,8 +1551,8 @@ sweep_kernel(themis_batch_t b, int n_thr, const double* __restrict__ thr, int th
   // scheduler: its lanes read consecutive inputs, and on a batch that keeps to
   // one network they all take the same path through the event loop.
   const SweepSlot slot =
-      kJobs ? sweep_block_slot<kBaseline>(b, jobs, kBlock, threadIdx.x, n_thr, policy_mask, n_pol)
-            : sweep_lane_slot(b, kBlock, threadIdx.x, n_thr, policy_mask, n_pol);
+      kJobs ? sweep_block_slot<kBaseline>(b, jobs, blockIdx.x, kBlock, threadIdx.x, n_thr, policy_mask, n_pol)
+            : sweep_lane_slot(b, blockIdx.x, kBlock, threadIdx.x, n_thr, policy_mask, n_pol);
   if (!slot.exists) return;
   const uint64_t e = slot.e;
   const SweepItem it = sweep_item(b, e, n_thr, thr, thr_per_scenario, policy_mask, n_pol);
@@ -1603,9 +1612,9 @@ sweep_quad_kernel(themis_batch_t b, int n_thr, const double* __restrict__ thr, i
   __shared__ uint32_t lds_block[QuadPow2<L, kFix>::kBytes / 4u];
   const uint32_t quad = threadIdx.x >> 2;
   const SweepSlot slot =
-      kJobs ? sweep_block_slot<kBaseline>(b, jobs, L::kQuads, quad, n_thr, policy_mask, n_pol)
-            : sweep_lane_slot(b, L::kQuads, quad, n_thr, policy_mask, n_pol);
-  if (kJobs && __builtin_amdgcn_ballot_w64(slot.exists) == 0ull) return;   // (beyond the list)
+      kJobs ? sweep_block_slot<kBaseline>(b, jobs, block_index(), L::kQuads, quad, n_thr, policy_mask, n_pol)
+            : sweep_lane_slot(b, block_index(), L::kQuads, quad, n_thr, policy_mask, n_pol);
+  if (__builtin_amdgcn_ballot_w64(slot.exists) == 0ull) return;   // (beyond the list, or the grid's last row)
   // a quad without an evaluation stays: the wavefront leaves the event loop as a whole
   const bool exists = slot.exists;
   const uint64_t e = exists ? slot.e : 0u;
@@ -1664,7 +1673,7 @@ sweep_wave_kernel(themis_batch_t b, int n_thr, const double* __restrict__ thr, i
   __shared__ WaveLds<kWords> lds;
   __shared__ uint8_t codes[64u * kWords];
   const uint32_t lane = lane_id();
-  const uint64_t e = sweep_lane_slot(b, 1u, 0u, n_thr, policy_mask, n_pol).e;
+  const uint64_t e = sweep_lane_slot(b, blockIdx.x, 1u, 0u, n_thr, policy_mask, n_pol).e;
   const SweepItem it = sweep_item(b, e, n_thr, thr, thr_per_scenario, policy_mask, n_pol);
   const bool every_threshold = (policy_mask & THEMIS_SWEEP_BASELINE) != 0u && !it.themis_on;
   Scenario s = load_scenario(b, it.i);
@@ -2759,17 +2768,32 @@ struct Launcher {
   void operator()(void (*kernel)(P...), unsigned blocks, unsigned threads, A&&... a) {
     with_lds(0u, kernel, blocks, threads, std::forward<A>(a)...);
   }
+  // Dynamic LDS, and as many workgroups as there are: the kernel numbers them with block_index().
+  template <typename... P, typename... A>
+  void in_rows(unsigned lds_bytes, void (*kernel)(P...), uint64_t blocks, unsigned threads, A&&... a) {
+    const uint64_t rows = (blocks + kGridRow - 1u) / kGridRow;
+    if (rows > (1ull << 32) / kGridRow) {   // (block_index() has 32 bits)
+      if (first == hipSuccess) first = hipErrorInvalidConfiguration;
+      return;
+    }
+    launch(lds_bytes, kernel, rows > 1u ? dim3(kGridRow, (unsigned)rows) : dim3((unsigned)blocks), threads,
+           std::forward<A>(a)...);
+  }
   template <typename... P, typename... A>
   void with_lds(unsigned lds_bytes, void (*kernel)(P...), unsigned blocks, unsigned threads, A&&... a) {
-    std::tuple<P...> params(std::forward<A>(a)...);  // converted to the kernel's own parameter types
-    void* ptrs[sizeof...(P)];
-    fill(ptrs, params, std::index_sequence_for<P...>{});
-    const hipError_t e = hipLaunchKernel((const void*)kernel, dim3(blocks), dim3(threads), ptrs, lds_bytes, stream);
-    if (first == hipSuccess) first = e;
+    launch(lds_bytes, kernel, dim3(blocks), threads, std::forward<A>(a)...);
   }
   int status() const { return first == hipSuccess ? THEMIS_OK : THEMIS_ERR_DEVICE; }
 
  private:
+  template <typename... P, typename... A>
+  void launch(unsigned lds_bytes, void (*kernel)(P...), dim3 grid, unsigned threads, A&&... a) {
+    std::tuple<P...> params(std::forward<A>(a)...);  // converted to the kernel's own parameter types
+    void* ptrs[sizeof...(P)];
+    fill(ptrs, params, std::index_sequence_for<P...>{});
+    const hipError_t e = hipLaunchKernel((const void*)kernel, grid, dim3(threads), ptrs, lds_bytes, stream);
+    if (first == hipSuccess) first = e;
+  }
   template <typename T, size_t... I>
   static void fill(void** ptrs, T& params, std::index_sequence<I...>) {
     ((ptrs[I] = (void*)&std::get<I>(params)), ...);
@@ -2887,10 +2911,11 @@ static bool simulate_on_quads(uint64_t n, uint32_t cap) {
 // scenarios 13 / 13, 4,096 18 / 13 (18 / 28), two chunks 21 / 22 (21 / 52); planner
 // at 3,072 28 / 26 on four dimensions (28 / 147), 19 / 26 on two, 11 / 26 on one.
 constexpr uint64_t kWaveSimulate = 4096, kWavePlan = 3072;
+constexpr uint64_t kMostWavefronts = 0xffffffffull / kBlock;   // of a launch with a workgroup each
 static std::atomic<int> batch_mapping{THEMIS_MAPPING_AUTO};
 static bool on_wavefronts(uint64_t items, uint64_t most) {
   const int forced = batch_mapping.load(std::memory_order_relaxed);
-  return forced != THEMIS_MAPPING_AUTO ? forced == THEMIS_MAPPING_WAVE && items <= 0x7fffffffull
+  return forced != THEMIS_MAPPING_AUTO ? forced == THEMIS_MAPPING_WAVE && items <= kMostWavefronts
                                        : items <= most;
 }
 // Wavefronts of plan_kernel for 64 scenarios: four where one each would leave the
@@ -2956,7 +2981,7 @@ static TracePlan trace_plan(const themis_batch_t& b, uint32_t slots, uint32_t re
   p.quads = lanes != THEMIS_MAPPING_LANE && !releases && trace_quad_layout(slots, 4u, b.max_coll).region <= region_bytes &&
             trace_quad_layout(slots, 3u, b.max_coll).lds <= kLdsOfCu;
   const uint32_t lds = trace_wave_layout(slots, 3u, b.max_coll, true, false).bytes;
-  if (lds > kLdsOfCu || b.n > 0x7fffffffull || batch == THEMIS_MAPPING_LANE) {
+  if (lds > kLdsOfCu || b.n > kMostWavefronts || batch == THEMIS_MAPPING_LANE) {
     p.waves = p.waves_after = false;
     return p;
   }
@@ -3123,9 +3148,9 @@ static int simulate_batch_impl(const themis_batch_t* batch, const uint8_t* order
         for (uint32_t dims : {3u, 4u}) {
           const uint32_t lds = trace_quad_layout(tv.slots, dims, batch->max_coll).lds;
           if (lds > kLdsOfCu) continue;
-          go.with_lds(lds, queue_order ? simulate_trace_quad_kernel<true> : simulate_trace_quad_kernel<false>,
-                      (unsigned)((batch->n + kBlock / 4u - 1u) / (kBlock / 4u)), kBlock, *batch, orders, t_done,
-                      queue_order, entry_bytes, busy, trace_area, tl.bytes, dims, follow_up, call);
+          go.in_rows(lds, queue_order ? simulate_trace_quad_kernel<true> : simulate_trace_quad_kernel<false>,
+                     (batch->n + kBlock / 4u - 1u) / (kBlock / 4u), kBlock, *batch, orders, t_done, queue_order,
+                     entry_bytes, busy, trace_area, tl.bytes, dims, follow_up, call);
           follow_up = true;
         }
       if (plan.waves || (plan.quads && plan.waves_after))
@@ -3162,9 +3187,9 @@ static int simulate_batch_impl(const themis_batch_t* batch, const uint8_t* order
 #undef THEMIS_WAVE_KERNEL
     if (alone) return go.status();
   } else if (simulate_on_quads(batch->n, cap)) {
-    go(pick_quad_kernel(cap, mode, batch->fixed_delay != nullptr),
-       (unsigned)((batch->n + kBlock / 4u - 1u) / (kBlock / 4u)), kBlock, *batch, orders, t_done, queue_order,
-       entry_bytes, busy, call);
+    go.in_rows(0u, pick_quad_kernel(cap, mode, batch->fixed_delay != nullptr),
+               (batch->n + kBlock / 4u - 1u) / (kBlock / 4u), kBlock, *batch, orders, t_done, queue_order,
+               entry_bytes, busy, call);
   } else {
     go(pick_simulate_kernel(cap, mode, busy != nullptr, batch->fixed_delay != nullptr), blocks_for(batch->n), kBlock,
        *batch, orders, t_done, queue_order, entry_bytes, busy, call);
@@ -3304,6 +3329,14 @@ int themis_sweep_with_scratch(const themis_batch_t* batch, int n_thr, const doub
   // 2,000, 2,125 wavefronts, 831 / 1,215; 30,001 4,479 / 5,595).
   const uint32_t quad_cap = !quad ? 0u : cap <= 128u ? 128u
       : groups * roles <= 8u * (compute_units() ? compute_units() : 256u) ? 512u : cap;
+  auto evaluate = [&](auto kernel, uint64_t workgroups) {
+    if (quad)
+      go.in_rows(0u, kernel, workgroups, kBlock, *batch, n_thr, thr, thr_per_scenario, policy_mask, n_pol, t_done,
+                 call, jobs);
+    else
+      go(kernel, (unsigned)workgroups, kBlock, *batch, n_thr, thr, thr_per_scenario, policy_mask, n_pol, t_done,
+         call, jobs);
+  };
   if (share) {
     uint32_t* count = (uint32_t*)scratch;
     SweepJob* list = (SweepJob*)((uint8_t*)scratch + kSweepJobsHeader);
@@ -3321,9 +3354,8 @@ int themis_sweep_with_scratch(const themis_batch_t* batch, int n_thr, const doub
                 : quad ? THEMIS_SWEEP_KERNEL(THEMIS_SWEEP_QUADS(128))
                 : cap == 16u ? THEMIS_SWEEP_KERNEL(THEMIS_SWEEP_LANES(Layout16))
                              : THEMIS_SWEEP_KERNEL(THEMIS_SWEEP_LANES(LayoutRing));
-    go(kernel, (unsigned)((base ? groups : 0u) + most), kBlock, *batch, n_thr, thr, thr_per_scenario,
-       policy_mask, n_pol, t_done, call, jobs);
 #undef THEMIS_SWEEP_KERNEL
+    evaluate(kernel, (base ? groups : 0u) + most);
   } else if (sweep_on_wavefronts(batch->n * roles)) {
     go(cap <= 64u ? sweep_wave_kernel<1> : sweep_wave_kernel<8>, (unsigned)(batch->n * roles), kBlock, *batch,
        n_thr, thr, thr_per_scenario, policy_mask, n_pol, t_done, call);
@@ -3336,8 +3368,7 @@ int themis_sweep_with_scratch(const themis_batch_t* batch, int n_thr, const doub
                 : cap == 16u ? THEMIS_SWEEP_KERNEL(THEMIS_SWEEP_LANES(Layout16))
                              : THEMIS_SWEEP_KERNEL(THEMIS_SWEEP_LANES(LayoutRing));
 #undef THEMIS_SWEEP_KERNEL
-    go(kernel, (unsigned)groups * roles, kBlock, *batch, n_thr, thr, thr_per_scenario, policy_mask, n_pol, t_done,
-       call, jobs);
+    evaluate(kernel, groups * roles);
   }
   // the follow-up passes, in one launch where themis_simulate_batch does the same
   const unsigned fb = follow_up_blocks(evals);

@@ -87,3 +87,32 @@ def test_sweeps_on_quads_at_the_chunk_capacities(gpu, oracle, max_chunks, n):
             assert_close("sweep", sw.cpu().numpy(), oracle.sweep(b, thr, 7, threads=8))
     finally:
         gpu.themis_set_sweep_mapping(gpu.MAPPING_AUTO)
+
+
+@pytest.mark.parametrize("shared", [False, True])
+def test_a_sweep_of_more_workgroups_than_one_row_of_the_grid(gpu, oracle, shared):
+    """34 million scenarios of up to two chunks under 17 pairs of threshold and scheduler:
+    36 million workgroups, in two rows (with a list of plans: the baseline's and one
+    per scenario).  The scenarios repeat, so every row of the result has its oracle."""
+    import torch
+    n, period = 34_000_003, 4096
+    b = _mixed_counts(period, 940, 1, max_chunks=2)   # (powers of two)
+    b.max_chunks = 65
+    thr = np.linspace(0.0, 0.7, 8)
+    want = torch.from_numpy(oracle.sweep(b, thr, 7, threads=8)).to("cuda")
+    d = gpu.to_device(b)
+    at = torch.arange(n, device="cuda") % period
+    for f in ("ndims", "size_bytes", "inter_policy", "intra_policy", "threshold", "npus", "bw", "chunks"):
+        v = getattr(d, f)
+        unsigned = v.dtype == torch.uint32
+        v = (v.view(torch.int32) if unsigned else v)[..., at].contiguous()
+        setattr(d, f, v.view(torch.uint32) if unsigned else v)
+    d.n = n
+    scratch = None if shared else torch.empty(16, dtype=torch.uint8, device="cuda")   # (16 bytes: too small for a list)
+    t = gpu.themis_sweep(d, torch.from_numpy(thr).to("cuda"), 7, scratch=scratch)
+    torch.cuda.synchronize()
+    for k in range(0, n, 1024 * period):
+        got = t[k:k + 1024 * period]
+        exp = want.repeat(-(-got.shape[0] // period), 1, 1)[:got.shape[0]]
+        bad = ~torch.isclose(got, exp, rtol=1e-12, atol=0.0, equal_nan=True)
+        assert not bool(bad.any()), k + int(bad.nonzero()[0, 0])
