@@ -31,10 +31,11 @@
 // phase may follow the order in bit 12).  Lists hold records, a link
 // the record of the next chunk, so nothing else is kept per chunk.
 //
-// Per evaluation (quad g of the wavefront): link of chunk c, 16 bits, at byte
-// 32 * c + 2 * g; first | last << 16 of list q = kClasses * dimension + class at
-// byte 32 * kChunks + 64 * q + 4 * g.  (One shift and add; the quads' words of
-// one index are in different banks.)
+// Per evaluation (quad g of the wavefront): first | last << 16 of list q = kClasses *
+// dimension + class at byte 64 * q + 4 * g; behind the lists the link of chunk c, 16
+// bits, at byte 32 * c + 2 * g.  (One shift and add; the quads' words of one index are
+// in different banks.  A dimension where nothing waits reads a list behind its own
+// without a use for it: one of the next dimension, or links.)
 #pragma once
 
 #include "themis_fast.hpp"
@@ -47,17 +48,17 @@ struct LayoutQuad {
   static constexpr uint32_t kCap = kChunks, kPerDim = kClasses;
   static constexpr uint32_t kPhaseBit = 9u + kOrderBits;   // of a record
   static constexpr uint32_t kQuads = (uint32_t)kBlock / 4u;
-  static constexpr uint32_t kEndsAt = 32u * kChunks;
-  static constexpr uint32_t kBytes = kEndsAt + 64u * 4u * kClasses;
+  static constexpr uint32_t kLinksAt = 64u * 4u * kClasses;
+  static constexpr uint32_t kBytes = kLinksAt + 32u * kChunks;
   static constexpr uint32_t kIdMask = 0x1ffu;
   static constexpr uint32_t kWavesPerSimd = kChunks <= 128u ? 4u : 2u;
   // link of the chunk of record rec (the shifts end in an address: one instruction each)
   static __device__ __forceinline__ uint16_t* link(uint8_t* block, uint32_t rec) {
-    return (uint16_t*)(block + (((rec << 5) & (kIdMask << 5)) | ((threadIdx.x >> 2) * 2u)));
+    return (uint16_t*)(block + kLinksAt + (((rec << 5) & (kIdMask << 5)) | ((threadIdx.x >> 2) * 2u)));
   }
   // ends of the lane's list of a class
   static __device__ __forceinline__ uint32_t* ends(uint8_t* block, uint32_t cls) {
-    return (uint32_t*)(block + kEndsAt + (threadIdx.x >> 2) * 4u + 64u * kPerDim * (threadIdx.x & 3u) + (cls << 6));
+    return (uint32_t*)(block + (threadIdx.x >> 2) * 4u + 64u * kPerDim * (threadIdx.x & 3u) + (cls << 6));
   }
 };
 
@@ -175,7 +176,7 @@ __device__ const QuadStages g_quad_stages = quad_stages();
 // power of two may come after the one with the latency as long as no result leaves
 // the normal range (t_min).
 // A running stage, as the quad passes it on: bits 1-3 the dimension the chunk waits
-// for then (4: none), 9-14 its row and phase then, 16-21 the list it joins, 22-30 the
+// for then (4: none), 9-14 its row and phase then, 16-20 the list it joins, 22-30 the
 // chunk.
 // The stage table is in LDS behind the lists (1 KiB, 60 clocks nearer than the
 // caches) where that costs no wavefront: up to 256 chunks.
@@ -183,6 +184,7 @@ template <typename L, bool kFix>
 struct QuadPow2 {
   static constexpr bool kTableInLds = L::kCap <= 256u;
   static constexpr uint32_t kBytes = L::kBytes + (kTableInLds ? 1024u : 0u);
+  static constexpr uint32_t kNobody = ~0u;   // above all stages, for dimension 7, list 31 (a place behind the lists)
   double whole, fix;
   uint64_t ranktab;
   int less;         // -log2 P_k in byte k
@@ -203,7 +205,7 @@ struct QuadPow2 {
     __syncthreads();
   }
   __device__ __forceinline__ bool goes_to(uint32_t given, uint32_t k) const { return (given & wanted) == 2u * k; }
-  static __device__ __forceinline__ uint32_t list(uint32_t given) { return (given >> 16) & 63u; }
+  static __device__ __forceinline__ uint32_t list(uint32_t given) { return (given >> 16) & 31u; }
   static __device__ __forceinline__ uint32_t record(uint32_t given) { return (given & 0x7e00u) | given >> 22; }
   // rec: the chunk's record in the low half
   __device__ __forceinline__ uint32_t stage(uint32_t rec, double& time) const {
@@ -233,10 +235,11 @@ struct QuadTable {
   static constexpr uint32_t kStates = (L::kPhaseBit == 14u ? 32u : 8u) + kOrders;
   static constexpr uint32_t kTimes = L::kBytes, kDoes = kTimes + 512u * kOrders;
   // (the classes' place is the links', where it is large enough)
-  static constexpr bool kInLinks = 64u * kStates <= L::kEndsAt;
-  static constexpr uint32_t kClassesAt = kInLinks ? 0u : kDoes + 128u * kStates;
+  static constexpr bool kInLinks = 64u * kStates <= 32u * L::kCap;
+  static constexpr uint32_t kClassesAt = kInLinks ? L::kLinksAt : kDoes + 128u * kStates;
   static constexpr uint32_t kBytes = kDoes + 128u * kStates + (kInLinks ? 0u : 64u * kStates);
   static_assert(64u * 4u * L::kPerDim >= 512u * kOrders, "the sizes of one phase fit the place of the lists");
+  static constexpr uint32_t kNobody = 0xffff0004u;   // above all stages, for dimension 4, list 0
   uint8_t* block;
   double t_min;
   uint32_t cls0;
@@ -259,7 +262,7 @@ struct QuadTable {
     const uint32_t k = threadIdx.x & 3u, D = min((uint32_t)s.D, kDims);
     const bool gather = s.ctype == THEMIS_COLL_ALL_GATHER, rs_only = s.ctype == THEMIS_COLL_REDUCE_SCATTER;
     uint8_t* const rs = block + kTimes;        // sizes before the Reduce-Scatter stages, then the times
-    uint8_t* const ag = block + L::kEndsAt;    // sizes before the All-Gather stages
+    uint8_t* const ag = block;                 // sizes before the All-Gather stages, in the place of the lists
     // sizes: lane j of the quad takes the orders j, j + 4, ..  (NaN, below no
     // size, where there is none)
     for (uint32_t o = k; o < kOrders; o += 4u) {
@@ -416,10 +419,14 @@ __device__ __forceinline__ QuadResult simulate_quad(const Model& model, QuadQueu
   const uint32_t k = threadIdx.x & 3u;   // the lane's dimension
   uint8_t* const block = queue.block;
   using Mask = typename std::conditional<(L::kPerDim > 32u), uint64_t, uint32_t>::type;
-  Mask lists = 0;          // bit c: list of class c holds chunks
+  // bit c: list of class c holds chunks; one bit behind the classes is always set, so that
+  // there is a lowest one (the fourth: the place is in the banks of classes 3, 7, ..,
+  // not in those of class 0, which is read the most)
+  constexpr Mask kNone = (Mask)1 << (L::kPerDim + 3u);
+  Mask lists = kNone;
   if (queue.any) {
     *L::ends(block, cls0) = queue.first | queue.last << 16;
-    lists = (Mask)1 << cls0;
+    lists |= (Mask)1 << cls0;
   }
   double f = nan64();      // finish time of the stage the dimension serves, NaN when idle
   double busy = 0.0, now = 0.0;
@@ -433,10 +440,10 @@ __device__ __forceinline__ QuadResult simulate_quad(const Model& model, QuadQueu
     // of the stages that end now the one of the lowest chunk hands it on
     const bool ends = f == next;
     const uint64_t ending = __builtin_amdgcn_ballot_w64(ends);
-    const uint32_t key = ends ? sv : ~0u;
+    const uint32_t key = ends ? sv : Model::kNobody;
     const uint32_t given = quad_min_u32(key);
     if (ends && key == given) f = __hiloint2double(0x7ff80000, __double2loint(f));
-    // (dimension 4 and, where nothing ends, 7: nobody's)
+    // (dimension 4, and that of kNobody where nothing ends: no lane's)
     const bool append = model.goes_to(given, k);
     const uint32_t to = Model::list(given);
     const Mask to_bit = (Mask)1 << to;
@@ -444,7 +451,7 @@ __device__ __forceinline__ QuadResult simulate_quad(const Model& model, QuadQueu
     if (append) lists |= to_bit;
     // an idle dimension with waiting chunks starts the first chunk of its lowest
     // class (smallest resident size), once all completions of the instant are delivered
-    bool starts = !(f == f) && lists != 0;
+    bool starts = !(f == f) && lists != kNone;
     if (__builtin_popcountll(ending) * 4 != __builtin_popcountll(running)) {   // more than one in some quad
       uint32_t mine = (uint32_t)(ending >> (threadIdx.x & 60u)) & 15u;
       asm volatile("" : "+v"(mine));   // (rare: a branch, not selects in every pass)
@@ -489,7 +496,7 @@ __device__ __forceinline__ QuadResult simulate_quad(const Model& model, QuadQueu
   res.started = started;
   // every stage ran and completed, and none was too short to move the clock, or
   // to be a normal number
-  const uint32_t settled = quad_min_u32(!(f == f) && lists == 0 ? 1u : 0u);
+  const uint32_t settled = quad_min_u32(!(f == f) && lists == kNone ? 1u : 0u);
   res.ok = quad_sum(started) == stages && settled != 0u && now < inf64() && now + 0.25 * t_min > now &&
            t_min >= 2.2250738585072014e-308;
   return res;

@@ -197,7 +197,7 @@ __device__ __forceinline__ TraceQuadResult simulate_trace_quad(const Scenario& s
   const int grown = fs.gather ? (int)fs.etot : 0;
   const uint32_t column = 4u * ((k + quad_column(D)) & 3u);
   const uint32_t wanted = fs.rs_only ? 7u | 32u << 3 : 7u;   // (see QuadPow2)
-  uint32_t c_inv = (uint32_t)((0x80000000ull + C - 1u) / C);
+  uint32_t c_inv = (uint32_t)((0x80000000ull + C - 1u) / max(C, 1u));   // (an invalid trace may have none)
   asm volatile("" : "+v"(c_inv));   // (32 bits)
   constexpr uint32_t kNone = ~0u;
   const uint32_t last_word = l.words - 1u;
@@ -251,7 +251,8 @@ __device__ __forceinline__ TraceQuadResult simulate_trace_quad(const Scenario& s
     const bool queued = append && !direct;
     const uint32_t begun = direct ? rec : head;
     const uint32_t q = __umulhi((begun >> 6) << 1, c_inv);
-    const uint32_t wr = (r >> 6) & 63u, wl = (low >> 6) & 63u;
+    // (some word where nothing waits)
+    const uint32_t wr = (r >> 6) & 63u, wl = min(low >> 6, last_word);
     const uint64_t bit_r = 1ull << (r & 63u);
     const uint64_t all = queued ? summary | 1ull << wr : summary, others = all & ~(1ull << wl);
     const uint32_t w2 = min((uint32_t)__builtin_ctzll(others | 1ull << 63), last_word);
@@ -293,7 +294,7 @@ __device__ __forceinline__ TraceQuadResult simulate_trace_quad(const Scenario& s
           if (in_word == 0ull) summary = others;
           low = summary != 0ull ? base << 6 | (uint32_t)__builtin_ctzll(from) : kNone;
           next_at = low != kNone ? ends_at + 32u * low : next_at;
-          asked_for = 2u;
+          asked_for = low != kNone ? 2u : 0u;   // (the head stays a record where nothing is left)
         }
         asked = pair(next_at);
       }

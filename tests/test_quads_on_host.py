@@ -1,0 +1,136 @@
+"""The event loops with four lanes per scenario and per trace, run on the CPU: the
+headers' own code, a wavefront as 64 coroutines (tests/host_wave), against the oracle.
+LDS block and workspace are bordered by memory that cannot be touched, and shifts by
+more than a word has bits, first bits of zero and divisions by zero end the program:
+no lane may read outside of its layout, also where a quad has no scenario, where
+nothing ends in it and where nothing waits."""
+import os
+import re
+import subprocess
+
+import numpy as np
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+CSRC = os.path.join(os.path.dirname(HERE), "paper_2110_04478_amd", "csrc")
+HEADERS = ("themis_device.hpp", "themis_fast.hpp", "themis_ring.hpp", "themis_quad.hpp", "themis_generic.hpp", "themis_trace.hpp",
+           "themis_trace_quad.hpp")
+INSTEAD = {"v_min_f64": "r = fmin(a, b);", "v_max_f64": "r = fmax(a, b);", "": ""}
+
+
+def _without_assembly(text):
+    """Each asm statement becomes what it stands for, or an abort()."""
+    out, at = [], 0
+    for m in re.finditer(r"\basm\b\s*(?:volatile)?\s*\(", text):
+        if m.start() < at:
+            continue
+        depth, end = 1, m.end()
+        while depth:
+            depth += {"(": 1, ")": -1}.get(text[end], 0)
+            end += 1
+        first = re.match(r'\s*"(\w*)', text[m.end():])
+        out += [text[at:m.start()], INSTEAD.get(first.group(1) if first else None, "abort();")]
+        at = text.index(";", end) + 1
+    return "".join(out) + text[at:]
+
+
+@pytest.fixture(scope="module")
+def queues(tmp_path_factory):
+    d = tmp_path_factory.mktemp("host_wave")
+    (d / "hip").mkdir()
+    (d / "hip" / "hip_runtime.h").write_text(open(os.path.join(HERE, "host_wave", "hip_runtime.h")).read())
+    for h in HEADERS:
+        (d / h).write_text(_without_assembly(open(os.path.join(CSRC, h)).read()))
+    subprocess.run(["g++", "-std=c++17", "-O1", "-ffp-contract=off", "-w", "-fsanitize=shift-exponent,builtin,integer-divide-by-zero",
+                    "-fsanitize-undefined-trap-on-error", "-I", str(d), "-I", os.path.join(HERE, "..", "include"),
+                    "-o", str(d / "queues"), os.path.join(HERE, "host_wave", "queues.cpp")], check=True)
+
+    def run(b, orders, *kind):
+        """-> (t_done, busy [4, n], taken, queue orders) of the batch."""
+        n, trace = b.n, b.n_coll is not None
+        with open(d / "in", "wb") as f:
+            for a, dt in ((b.ndims, np.uint8), (b.npus, np.uint32), (b.bw, np.float64), (b.size_bytes, np.float64),
+                          (b.chunks, np.uint32), (b.intra_policy, np.uint8),
+                          (np.zeros((4, n)) if b.fixed_delay is None else b.fixed_delay, np.float64),
+                          (np.zeros(n) if b.collective_type is None else b.collective_type, np.uint8)):
+                f.write(np.ascontiguousarray(a, dtype=dt).tobytes())
+            if trace:
+                f.write(np.ascontiguousarray(b.n_coll, dtype=np.uint32).tobytes())
+                f.write(np.ascontiguousarray(b.coll_size, dtype=np.float64).tobytes())
+            f.write(np.ascontiguousarray(orders, dtype=np.uint8).tobytes())
+        sizes = [n, b.max_chunks] + ([b.max_coll] if trace else [])
+        p = subprocess.run([str(d / "queues"), "trace" if trace else "single", *map(str, kind), *map(str, sizes),
+                            str(d / "in"), str(d / "out")], capture_output=True, text=True, timeout=300)
+        assert p.returncode == 0 and p.stdout == "ran\n", (p.returncode, p.stdout[-500:])
+        raw = open(d / "out", "rb").read()
+        rows = np.frombuffer(raw, dtype=np.dtype([("t", "<f8"), ("busy", "<f8", 4), ("taken", "<u4")]), count=n)
+        entries = np.frombuffer(raw, dtype="<u2", offset=rows.nbytes).reshape(n, 4, -1)
+        return rows["t"], rows["busy"].T, rows["taken"], entries
+
+    return run
+
+
+def _mixed(n, seed, max_chunks, dims=None, pow2=True, delays=True):
+    from paper_2110_04478_amd import workloads
+    rng = np.random.default_rng(seed)
+    b = workloads.mixed(n, seed=seed, max_chunks=max_chunks, pow2=pow2)
+    if dims:
+        b.ndims = np.minimum(b.ndims, dims) if dims < 4 else np.full(n, 4, np.uint8)
+    b.collective_type = rng.integers(0, 3, n).astype(np.uint8)
+    if delays:
+        b.fixed_delay = np.ascontiguousarray(rng.uniform(0, 2e-6, (4, n)))
+    return b
+
+
+def _ties(n, seed, max_chunks):
+    from paper_2110_04478_amd import workloads
+    return workloads.dyadic_ties(n, seed=seed, max_chunks=max_chunks)
+
+
+def _any_orders(b, seed):
+    """Permutations that no planner makes."""
+    rng = np.random.default_rng(seed)
+    orders = np.full((b.n, b.max_chunks), 0xff, np.uint8)
+    for i in range(b.n):
+        for c in range(int(b.chunks[i])):
+            p = rng.permutation(int(b.ndims[i]))
+            orders[i, c] = sum(int(k) << (2 * j) for j, k in enumerate(p))
+    return orders
+
+
+def _check(oracle, queues, b, orders, *kind):
+    t, busy, taken, entries = queues(b, orders, *kind)
+    want_t, want_entries, want_busy = oracle.simulate_batch(b, orders)
+    assert taken.all() and np.array_equal(t, want_t)
+    for k in range(4):
+        assert np.array_equal(np.where(k < b.ndims, busy[k], 0.0), np.where(k < b.ndims, want_busy[k], 0.0))
+    assert np.array_equal(entries, want_entries)
+
+
+@pytest.mark.parametrize("cap,chunks,n", [(64, 9, 30), (64, 64, 11), (128, 128, 11), (256, 200, 11), (512, 300, 11)])
+@pytest.mark.parametrize("kind", ["powers of two", "ties", "any orders", "tables"])
+def test_single_collectives(oracle, queues, cap, chunks, n, kind):
+    if kind == "tables":   # every NPU count, ties among them, up to three dimensions and four
+        for dims in (3, 4):
+            b = _mixed(n, 40 + cap, chunks, dims=dims, pow2=False)
+            _check(oracle, queues, b, _any_orders(b, cap), cap, dims)
+            b = _ties(n, 60 + cap, chunks)
+            b.ndims = np.minimum(b.ndims, dims)
+            _check(oracle, queues, b, _any_orders(b, 7), cap, dims)
+        return
+    b = _ties(n, 20 + cap, chunks) if kind == "ties" else _mixed(n, 30 + cap, chunks)
+    orders = _any_orders(b, cap) if kind == "any orders" else oracle.plan_batch(b)[0]
+    _check(oracle, queues, b, orders, cap, 0)
+
+
+@pytest.mark.parametrize("max_chunks,max_coll,dims,n", [(1, 1, 3, 14), (5, 1, 4, 14), (9, 6, 3, 14), (16, 20, 4, 11), (8, 40, 3, 11)])
+def test_traces(oracle, queues, max_chunks, max_coll, dims, n):
+    rng = np.random.default_rng(max_coll)
+    for ties in (False, True):
+        b = _ties(n, 80 + max_coll, max_chunks) if ties else _mixed(n, 90 + max_coll, max_chunks, dims=dims)
+        b.ndims = np.minimum(b.ndims, dims)
+        b.max_coll = max_coll
+        b.n_coll = rng.integers(1, max_coll + 1, n).astype(np.uint32)
+        b.coll_size = 2.0 ** rng.integers(16, 22, (max_coll, n)) if ties else rng.uniform(1e5, 1e9, (max_coll, n))
+        b.release_time = None
+        _check(oracle, queues, b, oracle.plan_batch(b)[0], dims)
