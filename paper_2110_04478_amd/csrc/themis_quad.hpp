@@ -52,13 +52,17 @@ struct LayoutQuad {
   static constexpr uint32_t kBytes = kLinksAt + 32u * kChunks;
   static constexpr uint32_t kIdMask = 0x1ffu;
   static constexpr uint32_t kWavesPerSimd = kChunks <= 128u ? 4u : 2u;
+  // (a list's ends are written as a word and, where a chunk leaves, as its lower half, and
+  // what makes a scenario's tables has used the place for sizes)
+  typedef uint16_t __attribute__((may_alias)) Half;
+  typedef uint32_t __attribute__((may_alias)) Word;
   // link of the chunk of record rec (the shifts end in an address: one instruction each)
-  static __device__ __forceinline__ uint16_t* link(uint8_t* block, uint32_t rec) {
-    return (uint16_t*)(block + kLinksAt + (((rec << 5) & (kIdMask << 5)) | ((threadIdx.x >> 2) * 2u)));
+  static __device__ __forceinline__ Half* link(uint8_t* block, uint32_t rec) {
+    return (Half*)(block + kLinksAt + (((rec << 5) & (kIdMask << 5)) | ((threadIdx.x >> 2) * 2u)));
   }
   // ends of the lane's list of a class
-  static __device__ __forceinline__ uint32_t* ends(uint8_t* block, uint32_t cls) {
-    return (uint32_t*)(block + (threadIdx.x >> 2) * 4u + 64u * kPerDim * (threadIdx.x & 3u) + (cls << 6));
+  static __device__ __forceinline__ Word* ends(uint8_t* block, uint32_t cls) {
+    return (Word*)(block + (threadIdx.x >> 2) * 4u + 64u * kPerDim * (threadIdx.x & 3u) + (cls << 6));
   }
 };
 
@@ -458,8 +462,8 @@ __device__ __forceinline__ QuadResult simulate_quad(const Model& model, QuadQueu
       starts = starts && (mine & (mine - 1u)) == 0u;
     }
     const uint32_t from = sizeof(Mask) == 8u ? (uint32_t)__builtin_ctzll(lists) : (uint32_t)__builtin_ctz((uint32_t)lists);
-    uint32_t* const from_at = L::ends(block, from);
-    uint32_t* const to_at = L::ends(block, to);
+    typename L::Word* const from_at = L::ends(block, from);
+    typename L::Word* const to_at = L::ends(block, to);
     uint32_t ends_from = *from_at, ends_to = *to_at;   // (either is used only where there is such a list)
     asm volatile("" : "+v"(ends_from), "+v"(ends_to));   // (read together, not each where it is needed)
     if (append) {
@@ -475,7 +479,7 @@ __device__ __forceinline__ QuadResult simulate_quad(const Model& model, QuadQueu
       sv = model.stage(ends_from, time);
       const bool last = ends_from == __builtin_amdgcn_alignbit(ends_from, ends_from, 16u);   // of its list
       lists &= last ? lists - 1u : ~(Mask)0;
-      if (!last) *(uint16_t*)from_at = (uint16_t)link;
+      if (!last) *(typename L::Half*)from_at = (uint16_t)link;
       f = now + time;
       busy = busy + time;
       if (kPut) put(started, (ends_from & L::kIdMask) << 1 | ((ends_from >> L::kPhaseBit) & 1u));

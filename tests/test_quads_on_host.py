@@ -134,3 +134,39 @@ def test_traces(oracle, queues, max_chunks, max_coll, dims, n):
         b.coll_size = 2.0 ** rng.integers(16, 22, (max_coll, n)) if ties else rng.uniform(1e5, 1e9, (max_coll, n))
         b.release_time = None
         _check(oracle, queues, b, oracle.plan_batch(b)[0], dims)
+
+
+PROBE = """
+#include "themis_quad.hpp"
+using namespace themis;
+__global__ void probe(double* t, const Scenario* s, const FastScenario* fs) {
+  using L = LayoutQuad<512, 16>;
+  __shared__ uint32_t block[QuadPow2<L, true>::kBytes / 4u];
+  QuadQueue<L> queue(block);
+  for (uint32_t c = 0; c < s->C; ++c) queue.add(c);
+  const Pow2Model m(*s, *fs, true);
+  t[threadIdx.x] = simulate_quad<L, false>(QuadPow2<L, true>(*s, m, threadIdx.x & 3u, block), queue, 0u, s->C, 1.0,
+                                           [](uint32_t, uint32_t) {}).t_done;
+}
+"""
+
+
+def test_links_and_list_ends_may_alias_each_other(tmp_path):
+    """A list's ends are written as a word and, where a chunk leaves, as its lower half: the
+    compiler must not take the two for accesses to different objects (in the
+    intermediate code of such a kernel every access to LDS is one that may alias
+    anything)."""
+    from paper_2110_04478_amd.csrc import build
+    if not os.path.exists(build.HIPCC):
+        pytest.skip("no hipcc here")
+    (tmp_path / "probe.hip").write_text(PROBE)
+    flags = [f for f in build.FLAGS if f not in ("-shared", "-fPIC")]
+    text = subprocess.run([build.HIPCC, *flags, "-S", "-emit-llvm", "--cuda-device-only", "-o", "-",
+                           str(tmp_path / "probe.hip")], check=True, capture_output=True, text=True).stdout
+    accesses = re.findall(r"(?:load|store) i(?:16|32) ?.*addrspace\(3\).*", text)
+    assert len(accesses) >= 5, len(accesses)
+    for a in accesses:
+        tag = re.search(r"!tbaa (!\d+)", a)
+        access = tag and re.search(r"^%s = !\{(!\d+)," % re.escape(tag.group(1)), text, re.M).group(1)
+        kind = access and re.search(r'^%s = !\{!"([^"]*)"' % re.escape(access), text, re.M).group(1)
+        assert kind in (None, "omnipotent char"), (kind, a)
