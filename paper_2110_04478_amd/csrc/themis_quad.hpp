@@ -188,6 +188,7 @@ template <typename L, bool kFix>
 struct QuadPow2 {
   static constexpr bool kTableInLds = L::kCap <= 256u;
   static constexpr uint32_t kBytes = L::kBytes + (kTableInLds ? 1024u : 0u);
+  static constexpr double kShortest = 2.2250738585072014e-308;   // (see above)
   static constexpr uint32_t kNobody = ~0u;   // above all stages, for dimension 7, list 31 (a place behind the lists)
   double whole, fix;
   uint64_t ranktab;
@@ -243,6 +244,7 @@ struct QuadTable {
   static constexpr uint32_t kClassesAt = kInLinks ? L::kLinksAt : kDoes + 128u * kStates;
   static constexpr uint32_t kBytes = kDoes + 128u * kStates + (kInLinks ? 0u : 64u * kStates);
   static_assert(64u * 4u * L::kPerDim >= 512u * kOrders, "the sizes of one phase fit the place of the lists");
+  static constexpr double kShortest = 0.0;   // times may leave the normal range
   static constexpr uint32_t kNobody = 0xffff0004u;   // above all stages, for dimension 4, list 0
   uint8_t* block;
   double t_min;
@@ -498,11 +500,11 @@ __device__ __forceinline__ QuadResult simulate_quad(const Model& model, QuadQueu
   res.t_done = now;
   res.busy = busy;
   res.started = started;
-  // every stage ran and completed, and none was too short to move the clock, or
-  // to be a normal number
+  // every stage ran and completed, and none was too short to move the clock, or for
+  // the model
   const uint32_t settled = quad_min_u32(!(f == f) && lists == kNone ? 1u : 0u);
   res.ok = quad_sum(started) == stages && settled != 0u && now < inf64() && now + 0.25 * t_min > now &&
-           t_min >= 2.2250738585072014e-308;
+           t_min >= Model::kShortest;
   return res;
 }
 

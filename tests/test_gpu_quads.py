@@ -116,3 +116,23 @@ def test_a_sweep_of_more_workgroups_than_one_row_of_the_grid(gpu, oracle, shared
         exp = want.repeat(-(-got.shape[0] // period), 1, 1)[:got.shape[0]]
         bad = ~torch.isclose(got, exp, rtol=1e-12, atol=0.0, equal_nan=True)
         assert not bool(bad.any()), k + int(bad.nonzero()[0, 0])
+
+
+@pytest.mark.parametrize("max_chunks", [70, 300])
+def test_times_below_the_normal_range_need_no_workspace(gpu, oracle, max_chunks):
+    """Beyond 64 chunks on four lanes per scenario: the smallest stage is below the
+    normal range, every clock value above zero, and no generic path to fall back on."""
+    import torch
+    b = w().mixed(100, seed=950, max_chunks=max_chunks)
+    b.bw *= 1.5e308 / b.bw.max()
+    b.size_bytes *= 1e3 / b.size_bytes.max()
+    gpu.themis_set_batch_mapping(gpu.MAPPING_LANE)
+    try:
+        t = check_batch(gpu, oracle, b, workspace=False)
+        assert (t < 1e-299).all() and np.array_equal(t, oracle.simulate_batch(b, oracle.plan_batch(b)[0])[0])
+        thr = np.array([0.0, 0.25])
+        sw = gpu.themis_sweep(gpu.to_device(b), torch.tensor(thr, device="cuda"), 7)
+        torch.cuda.synchronize()
+        assert np.array_equal(sw.cpu().numpy(), oracle.sweep(b, thr, 7, threads=8))
+    finally:
+        gpu.themis_set_batch_mapping(gpu.MAPPING_AUTO)

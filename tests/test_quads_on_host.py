@@ -136,6 +136,27 @@ def test_traces(oracle, queues, max_chunks, max_coll, dims, n):
         _check(oracle, queues, b, oracle.plan_batch(b)[0], dims)
 
 
+def _short_times(n, max_chunks, dims):
+    """Stage times below the smallest normal number, sizes above it."""
+    b = _mixed(n, 120 + dims, max_chunks, dims=dims, delays=False)
+    b.bw = b.bw * (1.5e308 / b.bw.max())
+    b.size_bytes = b.size_bytes * (1e3 / b.size_bytes.max())
+    return b
+
+
+@pytest.mark.parametrize("dims", [3, 4])
+def test_times_below_the_normal_range(oracle, queues, dims):
+    """A scaled product rounds twice there: the loop for powers of two leaves such
+    scenarios, the one on tables (the model's own operations) takes them."""
+    b = _short_times(22, 90, dims)
+    orders = oracle.plan_batch(b)[0]
+    want = oracle.simulate_batch(b, orders)[0]
+    assert (want < 1e-299).all() and (want > 0).all()
+    t, _, taken, _ = queues(b, orders, 128, 0)
+    assert (taken == 0).sum() > b.n // 2 and np.array_equal(t[taken == 1], want[taken == 1])
+    _check(oracle, queues, b, orders, 128, dims)
+
+
 PROBE = """
 #include "themis_quad.hpp"
 using namespace themis;
