@@ -151,8 +151,12 @@ plan_kernel(themis_batch_t b, uint8_t* __restrict__ orders, double* __restrict__
   const uint32_t lane = threadIdx.x & 63u;
   const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x / kBlock));
   uint32_t waves = blockDim.x / kBlock;
-  if (wave == 0u) plan_order_entry(lane, plan_orders + kPlanOrderWords * lane);
-  if (wave == 0u) __builtin_amdgcn_wave_barrier();
+  if (wave == 0u) {   // (the only one that reads it; a wavefront's LDS accesses keep their order)
+    plan_order_entry(lane, plan_orders + kPlanOrderWords * lane);
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  }
   const TraceView tv = trace_view(b);
   const uint64_t first = (uint64_t)blockIdx.x * kBlock, e = first + lane;
   auto scenario_of = [&](uint64_t at) { return kPerCollective ? at / tv.mc : at; };
