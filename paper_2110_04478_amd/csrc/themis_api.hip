@@ -2888,7 +2888,7 @@ static bool sweep_mapping_is_quad(uint32_t cap) {
 // Four lanes per scenario (themis_quad.hpp) or one?  A pass of the quads' loop
 // takes a wavefront some 980 clocks on its own and a SIMD 350, for 16 scenarios;
 // the lanes' loop takes 1,300 and 620 for 64.  So quads are faster until the
-// lanes fill the GPU (65,536 scenarios have one wavefront per SIMD), and beyond 64
+// lanes fill the GPU (a wavefront on each SIMD: 65,536 scenarios on 256 CUs), and beyond 64
 // chunks always, where LDS held back the lanes.  Measured (us, quads / lanes): 64
 // chunks, four dimensions 8,192 scenarios 224 / 317, 32,768 273 / 336, 65,536 351 /
 // 353, 262,144 1,192 / 747; 3-D first-in-first-out 65,536 271 / 282; 8 chunks 32,768
@@ -2896,10 +2896,10 @@ static bool sweep_mapping_is_quad(uint32_t cap) {
 // chunks 20,001 932 / 1,530; 512 chunks 32,768 1,853 / 3,246.  Other NPU counts, 64
 // chunks (us, now / with a lane each on per-order tables): three dimensions 20,000
 // scenarios 351 / 906, 130,000 1,033 / 2,379, four 993 / 2,549, 2,690 / 8,327.
-constexpr uint64_t kQuadSimulate = 65536;
 static bool simulate_on_quads(uint64_t n, uint32_t cap) {
   const int forced = sweep_mapping.load(std::memory_order_relaxed);
-  return cap > 64u || (forced != THEMIS_MAPPING_AUTO ? forced == THEMIS_MAPPING_QUAD : n <= kQuadSimulate);
+  const uint64_t lanes = 4u * (uint64_t)kBlock * (compute_units() ? compute_units() : 256u);
+  return cap > 64u || (forced != THEMIS_MAPPING_AUTO ? forced == THEMIS_MAPPING_QUAD : n <= lanes);
 }
 
 // Whole wavefronts per scenario (themis_wave.hpp) or one lane each?  A

@@ -130,3 +130,13 @@ def test_traces_of_large_batches_are_launched(launches):
 def test_a_grid_that_block_numbers_do_not_reach_is_an_error(launches):
     got = launches([("simulate", (1 << 36) + 16, 65, {})])[0]
     assert got[0] != 0
+
+
+@pytest.mark.parametrize("cus", [256, 64, 20])
+def test_four_lanes_per_scenario_until_one_each_fill_the_gpu(launches, cus):
+    """Up to 64 chunks the line between the two is a wavefront of lanes on every SIMD,
+    whatever part of the GPU the device is (below 4,097 scenarios, a wavefront each)."""
+    line = 256 * cus
+    quads, lanes = launches([("simulate", line, 64, {}), ("simulate", line + 1, 64, {})], cus=cus)
+    assert any("simulate_quad_kernel" in l[0] for l in quads[1])
+    assert not any("simulate_quad_kernel" in l[0] for l in lanes[1]) and any("simulate_kernel" in l[0] for l in lanes[1])
