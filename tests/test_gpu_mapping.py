@@ -1,5 +1,6 @@
 """GPU parity of the planner and of single collectives' simulation under each
-lane mapping, whatever the batch size would choose: one lane per scenario and
+mapping, whatever the batch size would choose: one lane per scenario (beyond 64
+chunks four, in the simulation; test_gpu_quads.py has four lanes throughout) and
 one wavefront per scenario (whose 64 lanes, 64-entry registers and 512-chunk
 LDS arrays put the edges at 64, 65, 128 and 512 chunks).  Smallest and ragged
 chunk counts, both policies, all collective types, delays, other NPU counts,
@@ -56,6 +57,7 @@ def _denormal(b):
 def test_mappings_agree_with_the_oracle(gpu, oracle, mapping, case):
     b = CASES[case](w())
     gpu.themis_set_batch_mapping({"lane": gpu.MAPPING_LANE, "wave": gpu.MAPPING_WAVE}[mapping])
+    gpu.themis_set_sweep_mapping({"lane": gpu.MAPPING_LANE, "wave": gpu.MAPPING_AUTO}[mapping])
     try:
         check_batch(gpu, oracle, b)
         check_batch(gpu, oracle, b, queue=False)
@@ -63,6 +65,7 @@ def test_mappings_agree_with_the_oracle(gpu, oracle, mapping, case):
             check_batch(gpu, oracle, w().config5(n=9, n_coll=5))
     finally:
         gpu.themis_set_batch_mapping(gpu.MAPPING_AUTO)
+        gpu.themis_set_sweep_mapping(gpu.MAPPING_AUTO)
 
 
 @pytest.mark.parametrize("n", [60, 300])

@@ -25,6 +25,18 @@ def gpu():
     return binding
 
 
+@pytest.fixture(params=["auto", "lane", "quad"])
+def mapping(gpu, request):
+    """The ways a batch's scenarios are spread over lanes: by its size (a wavefront each
+    for what a test has), a lane each (beyond 64 chunks: four), four lanes each."""
+    gpu.themis_set_batch_mapping(gpu.MAPPING_AUTO if request.param == "auto" else gpu.MAPPING_LANE)
+    gpu.themis_set_sweep_mapping({"auto": gpu.MAPPING_AUTO, "lane": gpu.MAPPING_LANE,
+                                  "quad": gpu.MAPPING_QUAD}[request.param])
+    yield request.param
+    gpu.themis_set_batch_mapping(gpu.MAPPING_AUTO)
+    gpu.themis_set_sweep_mapping(gpu.MAPPING_AUTO)
+
+
 def w():
     from paper_2110_04478_amd import workloads
     return workloads
@@ -105,12 +117,13 @@ def test_ragged_mixed_batches(gpu, oracle, n, thr_mode):
 
 @pytest.mark.parametrize("max_chunks", [8, 22, 64, 126])
 @pytest.mark.parametrize("offset", [0, 1, 4, 8])
-def test_queue_orders_at_any_address(gpu, oracle, max_chunks, offset):
+def test_queue_orders_at_any_address(gpu, oracle, mapping, max_chunks, offset):
     """The queue-order array may start at any byte: rows of whole wavefronts are
     put in place sixteen bytes at a time only where the address and the row
     length allow it, four or one at a time otherwise. 64 * 9 + 11 scenarios:
     whole wavefronts and a ragged last one; NPU counts that are not powers of
-    two leave some scenarios of a wavefront to the second kernel."""
+    two leave some scenarios of a wavefront of lanes to its quads or the second
+    kernel."""
     import torch
     b = w().mixed(64 * 9 + 11, seed=77 + max_chunks, max_chunks=max_chunks, pow2=False)
     keep = np.arange(b.n) % 3 == 0          # two of three scenarios get powers of two
@@ -156,11 +169,11 @@ def test_non_power_of_two_npus(gpu, oracle):
 
 
 @pytest.mark.parametrize("ctype", [0, 1, 2])
-def test_three_dimensional_networks_with_arbitrary_npu_counts(gpu, oracle, ctype):
+def test_three_dimensional_networks_with_arbitrary_npu_counts(gpu, oracle, mapping, ctype):
     """NPU counts such as 3, 6, 12, 24, 72: resident sizes depend on the order
-    of the divisions.  With at most 8 distinct order codes per scenario (always
-    the case up to three dimensions) the LDS event loop runs on per-order-code
-    tables; sizes that divide evenly make many equal Smallest-Chunk-First keys."""
+    of the divisions, and the event loops run on tables per order code (four lanes
+    per scenario: the layout of six orders and twelve sizes); sizes that divide
+    evenly make many equal Smallest-Chunk-First keys."""
     import torch
     W = w()
     n = 3000
@@ -185,10 +198,10 @@ def test_three_dimensional_networks_with_arbitrary_npu_counts(gpu, oracle, ctype
 
 
 @pytest.mark.parametrize("max_chunks", [64, 100, 128])
-def test_four_dimensional_networks_with_arbitrary_npu_counts(gpu, oracle, max_chunks):
+def test_four_dimensional_networks_with_arbitrary_npu_counts(gpu, oracle, mapping, max_chunks):
     """4-D networks with NPU counts like 3, 6, 10, 48, 72: Themis plans use well
-    over 8 distinct orders, random plans all 24 -- the variant with 64 size
-    classes per dimension (up to 128 chunks; 8- and 16-bit queue entries).
+    over 8 distinct orders, random plans all 24 -- the tables of 24 orders and 48
+    sizes per dimension (up to 128 chunks; 8- and 16-bit queue entries).
     Evenly dividing sizes give equal keys.  No workspace is passed: nothing
     may be left to the generic scan."""
     import torch
@@ -292,7 +305,7 @@ def test_empty_batch(gpu):
     assert orders.shape[0] == 0 and t.shape[0] == 0
 
 
-def test_invalid_scenarios_come_back_as_nan(gpu, oracle):
+def test_invalid_scenarios_come_back_as_nan(gpu, oracle, mapping):
     b = w().mixed(256, seed=9)
     b.npus[1, 3] = 1             # P < 2 (only matters if D > 1)
     b.ndims[3] = 3
@@ -312,11 +325,14 @@ def test_invalid_scenarios_come_back_as_nan(gpu, oracle):
     assert np.isfinite(t[0])
 
 
-def test_arbitrary_orders_are_accepted_and_malformed_ones_rejected(gpu, oracle):
-    """themis_simulate_batch takes any valid permutation per chunk."""
+def test_arbitrary_orders_are_accepted_and_malformed_ones_rejected(gpu, oracle, mapping):
+    """themis_simulate_batch takes any valid permutation per chunk; a scenario with a
+    malformed code is invalid, whatever runs beside it."""
     import torch
     b = w().mixed(300, seed=21)
     rng = np.random.default_rng(3)
+    other = np.arange(b.n) % 100 >= 60        # (wavefronts of powers of two, mixed ones, and of other counts)
+    b.npus[:, other] = rng.integers(3, 40, (4, int(other.sum())))
     orders = np.full((b.n, b.slots), 0xFF, np.uint8)
     for i in range(b.n):
         D = int(b.ndims[i])
@@ -325,12 +341,14 @@ def test_arbitrary_orders_are_accepted_and_malformed_ones_rejected(gpu, oracle):
             orders[i, c] = sum(int(k) << (2 * j) for j, k in enumerate(perm))
     orders[7, 0] = 0xFF                      # malformed
     orders[8, 0] = 0x00 if b.ndims[8] > 1 else 0x01
+    bad = np.arange(20, b.n, 7)              # the last chunk's too
+    orders[bad, b.chunks[bad] - 1] = 0xFF
     o_t, o_qo, o_busy = oracle.simulate_batch(b, orders, threads=8)
     d = gpu.to_device(b)
     ws = gpu.alloc_workspace(gpu.themis_workspace_bytes(d.n, d.max_chunks, 0))
     t, qo, busy = gpu.themis_simulate_batch(d, torch.from_numpy(orders).cuda(), workspace=ws)
     torch.cuda.synchronize()
-    assert np.isnan(o_t[7]) and np.isnan(o_t[8])
+    assert np.isnan(o_t[[7, 8]]).all() and np.isnan(o_t[bad]).all() and np.isfinite(o_t).sum() > 200
     assert_close("t_done", t.cpu().numpy(), o_t)
     assert np.array_equal(widen_queue(qo), o_qo)
     assert_close("busy", busy.cpu().numpy(), o_busy)
@@ -338,7 +356,7 @@ def test_arbitrary_orders_are_accepted_and_malformed_ones_rejected(gpu, oracle):
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("max_chunks", [200, 257, 512])
-def test_arbitrary_orders_with_hundreds_of_chunks(gpu, oracle, max_chunks):
+def test_arbitrary_orders_with_hundreds_of_chunks(gpu, oracle, mapping, max_chunks):
     """Any permutation per chunk, all three collective types and both queue
     policies on the LDS layouts for more than 128 chunks (16-bit queue
     entries), where a chunk's state is derived from its order, not stored."""
@@ -850,7 +868,7 @@ def test_provisioning_classes_match_oracle(gpu, oracle):
     assert np.array_equal(got.cpu().numpy(), want)
 
 
-def test_extreme_magnitudes_fall_back_to_the_generic_path(gpu, oracle):
+def test_extreme_magnitudes_fall_back_to_the_generic_path(gpu, oracle, mapping):
     """Power-of-two networks whose stage times differ by hundreds of orders of
     magnitude: some stages are too short to move the clock, some times
     overflow.  The LDS path must notice and hand these scenarios to the generic
@@ -974,7 +992,7 @@ def test_kernel_launches_per_call(gpu):
 
 @pytest.mark.parametrize("max_chunks,pow2,thr_mode", [(2, True, 0), (64, True, 1), (64, False, 0),
                                                       (100, True, 1)])
-def test_special_values(gpu, oracle, max_chunks, pow2, thr_mode):
+def test_special_values(gpu, oracle, mapping, max_chunks, pow2, thr_mode):
     """Thresholds 0 / denormal / huge / infinite / negative / NaN, sizes of one
     byte, 2^60 bytes, 1e-300 bytes (halvings leave the normal range), zero and
     infinity, bandwidths 60 orders of magnitude apart: valid ones must match
@@ -1007,10 +1025,10 @@ def test_special_values(gpu, oracle, max_chunks, pow2, thr_mode):
 
 
 @pytest.mark.parametrize("ctype", [0, 1, 2])
-def test_wavefronts_that_share_one_network(gpu, oracle, ctype):
+def test_wavefronts_that_share_one_network(gpu, oracle, mapping, ctype):
     """Parameter studies put one topology into every lane of a wavefront, only
-    bandwidths, sizes, chunk counts and thresholds differ: such wavefronts take
-    what a stage does from an (order, stage) table the wavefront builds once.
+    bandwidths, sizes, chunk counts and thresholds differ: with a lane per scenario such
+    wavefronts take what a stage does from an (order, stage) table the wavefront builds once.
     Every dimension count, both queue policies, each collective type, planned
     and arbitrary orders (all D! permutations inside a scenario), fixed delays,
     a ragged last wavefront, an invalid scenario inside a wavefront, and a

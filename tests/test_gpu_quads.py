@@ -72,7 +72,8 @@ def test_batch_sizes_around_the_lines(gpu, oracle, n, chunks):
 @pytest.mark.parametrize("max_chunks,n", [(65, 33), (127, 50), (128, 17), (129, 33), (256, 17), (257, 16)])
 def test_sweeps_on_quads_at_the_chunk_capacities(gpu, oracle, max_chunks, n):
     """Every kind of NPU counts at both ends of each capacity, all of its chunks
-    used by some scenarios; the last wavefront has empty quads."""
+    used by some scenarios; the last wavefront has empty quads.  (So few wavefronts
+    take the layout of 512 chunks where they could take that of 256.)"""
     import torch
     thr = np.array([0.0, 1.0 / 16.0, 0.5])
     gpu.themis_set_sweep_mapping(gpu.MAPPING_QUAD)
@@ -87,6 +88,28 @@ def test_sweeps_on_quads_at_the_chunk_capacities(gpu, oracle, max_chunks, n):
             assert_close("sweep", sw.cpu().numpy(), oracle.sweep(b, thr, 7, threads=8))
     finally:
         gpu.themis_set_sweep_mapping(gpu.MAPPING_AUTO)
+
+
+@pytest.mark.parametrize("max_chunks", [65, 128, 129, 256, 257, 512])
+def test_large_sweeps_on_quads_at_the_chunk_capacities(gpu, oracle, max_chunks):
+    """More wavefronts than the layout of 512 chunks holds at once, so each capacity runs
+    on its own layout, with a list of plans and without one, with delays and without;
+    every second network is of other NPU counts."""
+    import torch
+    n, rng = 5003, np.random.default_rng(960 + max_chunks)
+    thr = np.concatenate([[0.0, 0.25], rng.uniform(0, 1, 6)])
+    few = np.unique(np.concatenate([[0, n - 1], rng.permutation(n)[:40]]))
+    for delay in (False, True):
+        b = _mixed_counts(n, 970 + max_chunks, 2, max_chunks=max_chunks)
+        b.chunks[::3] = max_chunks
+        if delay:
+            b = _with_fixed_delay(b, 18)
+        want = oracle.sweep(b.take(few), thr, 7, threads=16)
+        assert gpu.themis_sweep_scratch_bytes(n, max_chunks, len(thr), 7) > 16
+        for scratch in (None, torch.empty(16, dtype=torch.uint8, device="cuda")):   # (16 bytes: no list)
+            t = gpu.themis_sweep(gpu.to_device(b), torch.from_numpy(thr).to("cuda"), 7, scratch=scratch)
+            torch.cuda.synchronize()
+            assert_close("sweep", t.cpu().numpy()[few], want)
 
 
 @pytest.mark.parametrize("shared", [False, True])

@@ -17,7 +17,7 @@ import itertools
 import numpy as np
 import pytest
 
-from test_gpu_parity import (assert_close, check_batch, gpu, w, widen_queue,  # noqa: F401
+from test_gpu_parity import (assert_close, check_batch, gpu, mapping, w, widen_queue,  # noqa: F401
                              _with_collective_types)
 
 pytestmark = pytest.mark.gpu
@@ -101,12 +101,12 @@ SIZES = {16: 500, 64: 500, 128: 300, 256: 130, 512: 100}
 
 
 @pytest.mark.parametrize("max_chunks", [16, 64, 128, 256, 512])
-def test_simultaneous_completions_on_every_lds_layout(gpu, oracle, max_chunks):
+def test_simultaneous_completions_on_every_lds_layout(gpu, oracle, mapping, max_chunks):
     """All-Reduce plans of Alg. 1 on the tie-rich networks, one chunk capacity
-    per LDS layout: up to 64 chunks a lane's event loop, beyond it the one of
-    four lanes.  Reaches the branch at the end of their delivery loops
-    that takes the next completion of the same instant (the smallest
-    chunk << 2 | dimension among the stages left in `done`), and the appends
+    per LDS layout, on every mapping.  Reaches the branches of the delivery loops
+    that take the next completion of the same instant (a lane's loop: the smallest
+    chunk << 2 | dimension among the stages left in `done`; four lanes: a pass in
+    which nothing starts; a wavefront: the lowest of several), and the appends
     that keep every list in (arrival, chunk id) order when several chunks
     arrive at one instant.  The count below shows the inputs do that."""
     n = SIZES[max_chunks]
@@ -131,7 +131,7 @@ def test_simultaneous_completions_on_every_lds_layout(gpu, oracle, max_chunks):
 
 
 @pytest.mark.parametrize("max_chunks", [16, 64, 128, 256, 512])
-def test_simultaneous_completions_all_collective_types_and_delays(gpu, oracle, max_chunks):
+def test_simultaneous_completions_all_collective_types_and_delays(gpu, oracle, mapping, max_chunks):
     """The same branches with stand-alone Reduce-Scatter and All-Gather
     collectives mixed in, with and without fixed per-stage delays that are
     multiples of 2^-14 s (the kFix variants of the stage-start blocks), and with
@@ -146,8 +146,8 @@ def test_simultaneous_completions_all_collective_types_and_delays(gpu, oracle, m
     _check_given_orders(gpu, oracle, b, _arbitrary_orders(b, 12))
 
 
-def test_simultaneous_completions_in_traces(gpu, oracle):
-    """Traces on the tie-rich networks (ranked-list path, simulate_trace_fast):
+def test_simultaneous_completions_in_traces(gpu, oracle, mapping):
+    """Traces on the tie-rich networks (the ranked lists of each mapping):
     collective sizes a power of two apart share resident sizes across
     collectives, several collectives are released at one instant, and release
     instants are multiples of the stage times, so releases coincide with each
@@ -173,11 +173,12 @@ def test_simultaneous_completions_in_traces(gpu, oracle):
         check_batch(gpu, oracle, _dyadic_delays(_with_collective_types(b, 9), 10))
 
 
-def test_tie_rich_networks_with_other_npu_counts(gpu, oracle):
+def test_tie_rich_networks_with_other_npu_counts(gpu, oracle, mapping):
     """The table-driven loops (NPU counts that are not powers of two run the same
     event loop on per-order tables): NPU counts 3, 6 and 12 with bandwidths
     2^a * (P-1)/P keep the per-byte latencies powers of two, and sizes that are
-    multiples of 3^4 * 2^m divide evenly, so equal times and sizes abound."""
+    multiples of 3^4 * 2^m divide evenly, so equal times and sizes abound; planned
+    and arbitrary orders (up to 24 tables and 48 sizes per dimension)."""
     W = w()
     rng = np.random.default_rng(33)
     for max_chunks, n in ((64, 400), (128, 200), (256, 60)):
@@ -187,10 +188,13 @@ def test_tie_rich_networks_with_other_npu_counts(gpu, oracle):
         b.npus = np.ascontiguousarray(rng.choice([3, 6, 12, 4], (4, n)).astype(np.uint32))
         b.bw = np.ascontiguousarray(a * ((b.npus - 1.0) / b.npus))
         b.size_bytes = b.size_bytes * 81.0
-        check_batch(gpu, oracle, _with_collective_types(b, 2), workspace=False)
+        check_batch(gpu, oracle, b, workspace=False)
+        b = _with_collective_types(b, 2)
+        check_batch(gpu, oracle, b, workspace=False)
+        _check_given_orders(gpu, oracle, b, _arbitrary_orders(b, 13))
 
 
-def test_tie_rich_traces_with_other_npu_counts(gpu, oracle):
+def test_tie_rich_traces_with_other_npu_counts(gpu, oracle, mapping):
     """Traces on networks with NPU counts 3, 6 and 12 under both queue policies
     (division mode of the ranked-list path: one size rank per (dimension, phase,
     order) and collective, equal sizes sharing a rank): bandwidths 2^a * (P-1)/P
@@ -217,11 +221,11 @@ def test_tie_rich_traces_with_other_npu_counts(gpu, oracle):
         assert np.isfinite(t).all()
 
 
-@pytest.mark.parametrize("mapping", ["lane", "quad"])
-def test_sweep_mappings_agree_with_the_oracle(gpu, oracle, mapping):
-    """themis_sweep under each of its two lane mappings (one lane per evaluation;
-    four lanes per evaluation, lane j owning dimension j), forced for every
-    chunk capacity: the tie-rich networks reach the quad mapping's loop that
+@pytest.mark.parametrize("lanes", ["lane", "quad"])
+def test_sweep_mappings_agree_with_the_oracle(gpu, oracle, lanes):
+    """themis_sweep under each of its two lane mappings (one lane per evaluation, up
+    to 64 chunks; four lanes per evaluation, lane j owning dimension j), forced for
+    every chunk capacity: the tie-rich networks reach the quad mapping's loop that
     appends the chunks of several stages ending at one instant one at a time,
     lowest chunk id first; the ragged batches (D 1..4, any C, scenarios without
     a fast path, a last wavefront with empty quads) its hand-over to the
@@ -229,15 +233,15 @@ def test_sweep_mappings_agree_with_the_oracle(gpu, oracle, mapping):
     import torch
     W = w()
     thr = torch.tensor([0.0, 1.0 / 16.0, 0.5], dtype=torch.float64, device="cuda")
-    gpu.themis_set_sweep_mapping({"lane": gpu.MAPPING_LANE, "quad": gpu.MAPPING_QUAD}[mapping])
+    gpu.themis_set_sweep_mapping({"lane": gpu.MAPPING_LANE, "quad": gpu.MAPPING_QUAD}[lanes])
     try:
-        for mc, n in ((16, 150), (64, 150), (200, 90), (512, 70)):
+        for mc, n in ((16, 150), (64, 150)) + (((200, 90), (512, 70)) if lanes == "quad" else ()):
             for b in (W.dyadic_ties(n, seed=7600 + mc, max_chunks=mc),
                       W.mixed(n + 3, seed=7700 + mc, max_chunks=mc, pow2=(mc != 200))):
                 d = gpu.to_device(b)
                 sw = gpu.themis_sweep(d, thr, 7)
                 torch.cuda.synchronize()
-                assert_close("sweep (%s, %d chunks)" % (mapping, mc), sw.cpu().numpy(),
+                assert_close("sweep (%s, %d chunks)" % (lanes, mc), sw.cpu().numpy(),
                              oracle.sweep(b, thr.cpu().numpy(), 7, threads=8))
     finally:
         gpu.themis_set_sweep_mapping(gpu.MAPPING_AUTO)

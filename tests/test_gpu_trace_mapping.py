@@ -10,8 +10,8 @@ import numpy as np
 import pytest
 
 from test_gpu_quads import _large_counts
-from test_gpu_parity import (_add_trace, _with_collective_types, _with_fixed_delay, check_batch, gpu,  # noqa: F401
-                             w)
+from test_gpu_parity import (_add_trace, _with_collective_types, _with_fixed_delay, assert_close,  # noqa: F401
+                             check_batch, gpu, mapping, w, widen_queue)
 
 pytestmark = pytest.mark.gpu
 
@@ -72,11 +72,11 @@ CASES = {
 
 
 @pytest.mark.parametrize("case", list(CASES))
-@pytest.mark.parametrize("mapping", ["lane", "quad", "wave"])
-def test_traces_agree_with_the_oracle(gpu, oracle, mapping, case):
+@pytest.mark.parametrize("lanes", ["lane", "quad", "wave"])
+def test_traces_agree_with_the_oracle(gpu, oracle, lanes, case):
     b = CASES[case]()
-    gpu.themis_set_batch_mapping(gpu.MAPPING_WAVE if mapping == "wave" else gpu.MAPPING_LANE)
-    gpu.themis_set_sweep_mapping(gpu.MAPPING_QUAD if mapping == "quad" else gpu.MAPPING_LANE)
+    gpu.themis_set_batch_mapping(gpu.MAPPING_WAVE if lanes == "wave" else gpu.MAPPING_LANE)
+    gpu.themis_set_sweep_mapping(gpu.MAPPING_QUAD if lanes == "quad" else gpu.MAPPING_LANE)
     try:
         t = check_batch(gpu, oracle, b)
         assert np.isfinite(t).all()
@@ -86,13 +86,35 @@ def test_traces_agree_with_the_oracle(gpu, oracle, mapping, case):
         gpu.themis_set_sweep_mapping(gpu.MAPPING_AUTO)
 
 
-def test_invalid_traces_on_wavefronts(gpu, oracle):
-    """Bad sizes, counts of collectives and networks: NaN and
-    all-ones, with valid traces beside them; stages that do not move the clock and
-    sizes that leave the normal range go on to the other paths."""
-    b = _released(_trace(64, 21, 9, 5), 7)
+@pytest.mark.parametrize("released", [True, False])
+def test_invalid_traces(gpu, oracle, mapping, released):
+    """Bad sizes, counts of collectives and networks, malformed order codes: NaN and
+    all-ones, with valid traces beside them in their wavefront; stages that do not move
+    the clock and sizes that leave the normal range go on to the other paths.
+    (Four lanes per trace take what is released together.)"""
+    import torch
+    b = _trace(64, 21, 9, 5)
+    if released:
+        b = _released(b, 7)
     b.coll_size[0, ::8], b.npus[0, 2::8] = 0.0, 1
     b.n_coll[3::8], b.n_coll[4::8] = 0, 6
     b.coll_size[:, 5::8] = 3e-307
     b.bw[0, 6::8] = 1e300
-    check_batch(gpu, oracle, b)
+    t = check_batch(gpu, oracle, b)
+    good = np.flatnonzero(np.isfinite(t))
+    assert len(good) >= 24
+    orders = oracle.plan_batch(b)[0].reshape(b.n, b.max_coll, b.max_chunks)
+    bad = good[::3]
+    for j, i in enumerate(bad):   # (of the first chunk, of some, of the last)
+        q, c = [(0, 0), (b.n_coll[i] // 2, b.chunks[i] // 2), (b.n_coll[i] - 1, b.chunks[i] - 1)][j % 3]
+        orders[i, q, c] = 0xff if j % 2 else (1 if b.ndims[i] == 1 else 0)
+    orders = np.ascontiguousarray(orders.reshape(b.n, -1))
+    want_t, want_qo, want_busy = oracle.simulate_batch(b, orders)
+    assert np.isnan(want_t[bad]).all()
+    d = gpu.to_device(b)
+    ws = gpu.alloc_workspace(gpu.themis_workspace_bytes(d.n, d.max_chunks, d.max_coll))
+    t, qo, busy = gpu.themis_simulate_batch(d, torch.from_numpy(orders).cuda(), workspace=ws)
+    torch.cuda.synchronize()
+    assert_close("t_done", t.cpu().numpy(), want_t)
+    assert np.array_equal(widen_queue(qo), want_qo)
+    assert_close("busy", busy.cpu().numpy(), want_busy)
