@@ -341,13 +341,6 @@ __device__ __forceinline__ LaneLds lane_lds(uint32_t* lds_block) {
   return lds;
 }
 
-// Chunk c's word / record in the lane's LDS block, whichever the layout keeps.
-template <typename L>
-__device__ __forceinline__ void init_chunk(const LaneLds& lds, uint32_t c, uint32_t code,
-                                           uint32_t state0, uint32_t D) {
-  L::init_chunk(lds, c, code, state0);
-}
-
 // The power-of-two event loop that goes with the layout.
 template <typename L, int kQueueOrder, bool kBusy, bool kFix>
 __device__ __forceinline__ FastResult simulate_pow2(const Scenario& s, const Pow2Model& model,
@@ -359,12 +352,6 @@ __device__ __forceinline__ FastResult simulate_pow2(const Scenario& s, const Pow
   } else {
     return simulate_fast<L, kQueueOrder, kBusy, kFix, Pow2Model>(s, model, lds, out);
   }
-}
-
-template <int kQueueOrder>
-__device__ __forceinline__ void put_queue_entry(uint8_t* rows, uint32_t at, uint32_t v) {
-  if (kQueueOrder == kShorts) ((uint16_t*)rows)[at] = (uint16_t)v;
-  else rows[at] = (uint8_t)v;
 }
 
 // All-ones from entry `used` of a row of `row_len` entries on.
@@ -543,7 +530,7 @@ simulate_kernel(themis_batch_t b, const uint8_t* __restrict__ orders,
             if (c4 + j < s.C) {
               uint32_t code = (v >> (8u * j)) & 0xffu;
               codes_ok = codes_ok && order_code_ok(code, s.D);
-              init_chunk<L>(lds, c4 + j, stored_code(s, fs, code), fs.state0, (uint32_t)s.D);
+              L::init_chunk(lds, c4 + j, stored_code(s, fs, code), fs.state0);
             }
           }
         }
@@ -551,7 +538,7 @@ simulate_kernel(themis_batch_t b, const uint8_t* __restrict__ orders,
         for (uint32_t c = 0; c < s.C; ++c) {
           uint32_t code = row[c];
           codes_ok = codes_ok && order_code_ok(code, s.D);
-          init_chunk<L>(lds, c, stored_code(s, fs, code), fs.state0, (uint32_t)s.D);
+          L::init_chunk(lds, c, stored_code(s, fs, code), fs.state0);
         }
       }
       if (!codes_ok) { invalid(); break; }
@@ -584,7 +571,7 @@ simulate_kernel(themis_batch_t b, const uint8_t* __restrict__ orders,
         } else if (kQueueOrder != kNoQueueOrder && out.queue_order) {
           for (int k = 0; k < kMaxDims; ++k)
             for (uint32_t e = r.executed[k]; e < 2u * b.max_chunks; ++e)
-              put_queue_entry<kQueueOrder>(fo.queue_order, (uint32_t)k * 2u * b.max_chunks + e, 0xFFFFu);
+              fo.queue_order[(uint32_t)k * 2u * b.max_chunks + e] = 0xFFu;
         }
         break;
       }
@@ -1583,7 +1570,7 @@ sweep_kernel(themis_batch_t b, int n_thr, const double* __restrict__ thr, int th
     const LaneLds lds = lane_lds<L>(lds_block);
     double load[kMaxDims];
     plan_fast(s, fs, it.themis_on, rel, it.th, load,
-              [&](uint32_t c, uint32_t code) { init_chunk<L>(lds, c, code, 0u, (uint32_t)s.D); });
+              [&](uint32_t c, uint32_t code) { L::init_chunk(lds, c, code, 0u); });
     FastOut fo;
     fo.queue_order = nullptr;
     fo.slots = b.max_chunks;
@@ -1786,7 +1773,7 @@ __device__ __forceinline__ void sweep_table_pass(
     if constexpr (kVariant >= 3) {
       DivModelT<LayoutTableWide> model(s, lds, chunk, it.scf);
       table_setup_packed<L>(s, it.scf, lds, code_at, model);
-      r = simulate_table_packed<L, kNoQueueOrder, false>(s, model, lds, fo);
+      r = simulate_table_packed<L>(s, model, lds);
     } else if constexpr (kWide) {
       DivModelT<L> model(s, lds, chunk, it.scf);
       table_setup_wide<L>(s, it.scf, lds, code_at, model);

@@ -93,8 +93,8 @@ struct Classes16 {
 template <uint32_t kChunks>
 struct LayoutByte {
   static constexpr uint32_t kCap = kChunks;
-  static_assert(kChunks <= 128, "chunk ids and the list end mark share 8 bits");
-  static constexpr bool kHeadInChunkWord = kChunks >= 64;
+  static_assert(kChunks <= 64, "operation counts of up to 2 * kChunks in 8 bits");
+  static constexpr bool kHeadInChunkWord = kChunks == 64;
   static constexpr uint32_t kTailBase = kHeadInChunkWord ? kChunks : kChunks + 16;
   static constexpr uint32_t kLaneWords = kTailBase + 16;
   // wavefronts per SIMD that the LDS block allows (160 KiB per CU, 4 SIMDs,
@@ -103,8 +103,7 @@ struct LayoutByte {
   static constexpr uint32_t kEnd = 0xffu;
   using Link = uint8_t;               // width of a chunk id in LDS
   using Classes = Classes16;
-  // per dimension: chunk id << 2 | dimension, and the operation count (up to 2 * kChunks)
-  using Ids = typename std::conditional<(kChunks <= 64), Pack4<uint32_t, 8>, Pack4<uint64_t, 16>>::type;
+  using Ids = Pack4<uint32_t, 8>;     // per dimension the operation count (up to 2 * kChunks)
   static __device__ __forceinline__ void init_chunk(const LaneLds& l, uint32_t c, uint32_t code,
                                                     uint32_t state0) {
     *(uint32_t*)l.dword(c) = (code << 16) | (kEnd << 8) | state0;
@@ -515,8 +514,8 @@ __device__ __forceinline__ uint32_t stages_ending(double now, Dims& d, uint32_t&
 }
 
 // How the per-dimension queue orders leave the kernel.
-// kBytes / kShorts store each 8- / 16-bit entry into the lane's own rows as
-// it is produced.  kWords (8-bit entries) collects four entries per dimension
+// kBytes / kShorts (four lanes per scenario only) store each 8- / 16-bit entry
+// into the lane's own rows as it is produced.  kWords (8-bit entries) collects four entries per dimension
 // in a register and stores them as one aligned dword (a quarter of the memory
 // transactions); it needs rows that start on a 4-byte boundary (an even number
 // of slots).  Either way every lane appends to its own four rows, so the
@@ -581,6 +580,7 @@ struct Pow2Model {
 template <typename L, int kQueueOrder, bool kBusy, bool kFix, typename Model>
 __device__ __forceinline__ FastResult simulate_fast(const Scenario& s, const Model& model,
                                                     const LaneLds& lds, const FastOut& out) {
+  static_assert(kQueueOrder != kShorts, "8-bit entries");
   using Link = typename L::Link;
   const uint32_t D = (uint32_t)s.D;
   const uint32_t C = s.C;
@@ -667,8 +667,6 @@ __device__ __forceinline__ FastResult simulate_fast(const Scenario& s, const Mod
         // pos < row_len always holds for a consistent plan; it keeps the store in bounds
         if (kQueueOrder == kBytes) {
           if (pos < row_len) out.queue_order[k * row_len + pos] = (uint8_t)entry;
-        } else if (kQueueOrder == kShorts) {
-          if (pos < row_len) ((uint16_t*)out.queue_order)[k * row_len + pos] = (uint16_t)entry;
         } else if (kQueueOrder == kStagedBytes) {
           // byte pos & 3 of dword pos >> 2 of row k; consecutive dwords of a lane lie 256 bytes apart
           const uint32_t at = min(pos, row_len - 1u);  // pos < row_len for a consistent plan

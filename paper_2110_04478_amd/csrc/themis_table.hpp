@@ -376,8 +376,8 @@ __device__ inline void table_setup_wide(const Scenario& s, bool scf, const LaneL
 // ---------------------------------------------------------------------------
 // More than 128 chunks with NPU counts that are not powers of two: 16-bit
 // chunk records with the chunk's slot (a slot stands for one order code, kept
-// in a small table) from which its stage follows, 64 classes per dimension as in the wide variant, and a stage time's
-// divisions redone at each dispatch.
+// in a small table) from which its stage follows, 64 classes per dimension as in the wide
+// variant, and a stage time's divisions redone at each dispatch.
 //   record: bits 0-8 next chunk of its list (its own id: the last one),
 //           bit 9 phase, bits 10-14 slot
 // Lane block: u16 record[kChunks], u16 head[256], u16 tail[256] (a tail entry
@@ -393,7 +393,6 @@ struct LayoutTablePacked {
   static constexpr uint32_t kClassBase = kTailBase + 128, kCodeBase = kClassBase + kSlots * 8u / 4u;
   static constexpr uint32_t kLaneWords = kCodeBase + kSlots / 4u;  // 438 / 566
   static constexpr uint32_t kIdMask = 0x1ffu;
-  using Ids = Pack4<uint64_t, 16>;
   static __device__ __forceinline__ uint16_t* half(const LaneLds& l, uint32_t base, uint32_t i) {
     return (uint16_t*)(l.base + ((base + (i >> 1)) << 8) + 2u * (i & 1u));
   }
@@ -471,14 +470,13 @@ __device__ inline void table_setup_packed(const Scenario& s, bool scf, const Lan
   }
 }
 
-// The event loop on these records: same contract as simulate_fast (result.ok false leaves the evaluation to the generic path).
+// The event loop on these records, times only (the sweeps'): contract of simulate_fast
+// (result.ok false leaves the evaluation to the generic path).
 // A chunk in the Reduce-Scatter phase at position pos of its order waits for
 // stage pos, in the All-Gather phase for stage 2 D - 1 - pos.
-template <typename L, int kQueueOrder, bool kBusy, typename Model>
+template <typename L, typename Model>
 __device__ __forceinline__ FastResult simulate_table_packed(const Scenario& s, const Model& model,
-                                                            const LaneLds& lds, const FastOut& out) {
-  static_assert(kQueueOrder == kNoQueueOrder || kQueueOrder == kBytes || kQueueOrder == kShorts,
-                "entries are stored one by one");
+                                                            const LaneLds& lds) {
   const uint32_t D = (uint32_t)s.D;
   const uint32_t C = s.C;
   const uint32_t full = (1u << D) - 1u;
@@ -487,17 +485,14 @@ __device__ __forceinline__ FastResult simulate_table_packed(const Scenario& s, c
   const bool scf = model.scf;
 
   double f0 = kInf, f1 = kInf, f2 = kInf, f3 = kInf;  // finish time, +inf = idle
-  double z0 = 0.0, z1 = 0.0, z2 = 0.0, z3 = 0.0;      // busy time
   // per dimension, the stage it serves and what its completion does: bits 0-7
   // list to join, 8-13 upper record bits then, 14 chunk is done, 15-16 the
   // dimension, 17-25 the chunk
   uint32_t v0 = 0, v1 = 0, v2 = 0, v3 = 0;
-  typename L::Ids executed;  // operations started per dimension (kept when queue orders are written)
   uint32_t started = 0;      // operations started in all
   Classes64 classes(lds);
   uint32_t work = 0;      // bit k: some list of dimension k holds chunks
   uint32_t idle = full;   // bit k: dimension k serves nothing
-  const uint32_t row_len = 2u * out.slots;
 
   // chunk c (upper record bits `up`: phase | slot << 1) becomes the last of list q = 64 * dim + class
   auto push = [&](uint32_t q, uint32_t c, uint32_t up) {
@@ -557,10 +552,6 @@ __device__ __forceinline__ FastResult simulate_table_packed(const Scenario& s, c
       const double f = now + t;
       const bool k0 = k == 0u, k1 = k == 1u, k2 = k == 2u, k3 = k == 3u;
       f0 = k0 ? f : f0; f1 = k1 ? f : f1; f2 = k2 ? f : f2; f3 = k3 ? f : f3;
-      if (kBusy) {
-        z0 = __builtin_fma(t, k0 ? 1.0 : 0.0, z0); z1 = __builtin_fma(t, k1 ? 1.0 : 0.0, z1);
-        z2 = __builtin_fma(t, k2 ? 1.0 : 0.0, z2); z3 = __builtin_fma(t, k3 ? 1.0 : 0.0, z3);
-      }
       // what the completion will do: a Reduce-Scatter goes on to the next
       // dimension of the order, the last one turns into the All-Gather on the
       // same dimension; an All-Gather goes back to the previous one
@@ -575,17 +566,6 @@ __device__ __forceinline__ FastResult simulate_table_packed(const Scenario& s, c
         const uint32_t qn = 64u * kn + class_of(slot, stage);
         const uint32_t v = qn | (up << 8) | (finished ? 0x4000u : 0u) | (k << 15) | (h << 17);
         v0 = k0 ? v : v0; v1 = k1 ? v : v1; v2 = k2 ? v : v2; v3 = k3 ? v : v3;
-      }
-      if (kQueueOrder != kNoQueueOrder) {
-        const uint32_t at = executed.get(k);
-        const uint32_t entry = (h << 1) | phase;
-        // at < row_len always holds for a consistent plan; it keeps the store in bounds
-        if (kQueueOrder == kBytes) {
-          if (at < row_len) out.queue_order[k * row_len + at] = (uint8_t)entry;
-        } else {
-          if (at < row_len) ((uint16_t*)out.queue_order)[k * row_len + at] = (uint16_t)entry;
-        }
-        executed.inc(k);
       }
       ++started;
     }
@@ -618,9 +598,6 @@ __device__ __forceinline__ FastResult simulate_table_packed(const Scenario& s, c
   const uint32_t stages = model.one_phase() ? D : 2u * D;
   res.ok = started == stages * C && idle == full && (now + 0.25 * t_min > now);
   res.t_done = now;
-  res.busy[0] = z0; res.busy[1] = z1; res.busy[2] = z2; res.busy[3] = z3;
-#pragma unroll
-  for (uint32_t k = 0; k < (uint32_t)kMaxDims; ++k) res.executed[k] = executed.get(k);
   return res;
 }
 
