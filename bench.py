@@ -98,7 +98,7 @@ def other_workload(args, np, torch, binding, workloads):
         def step():
             binding.themis_sweep(d, thr, mask, t_done=out)
         name = ("config4: %d scenarios x 8 thresholds x {FIFO,SCF}, 4-D P_k=2^U{1..6}, C=512, "
-                "themis_sweep, %s mapping" % (n, args.sweep_mapping))
+                "themis_sweep, %s mapping" % (n, "quad" if args.sweep_mapping == "lane" else args.sweep_mapping))
         kernel = "sweep"
     else:
         n = args.scenarios if args.scenarios != 1 << 20 else 16384
@@ -328,7 +328,7 @@ def main():
                     help="do not request the per-dimension queue orders")
     ap.add_argument("--workload", choices=("config3", "config4", "config5", "config5fifo6", "config5scf6", "extras", "small"), default="config3")
     ap.add_argument("--sweep-mapping", choices=("auto", "lane", "quad"), default="auto",
-                    help="lane mapping of themis_sweep's LDS kernel (auto: the library's choice)")
+                    help="lane mapping of themis_sweep's LDS kernel (auto: the library's choice; beyond 64 chunks only quad)")
     ap.add_argument("--copy-probe", type=int, default=0, metavar="MIB",
                     help="instead of the benchmark, run a plain device copy of MIB MiB "
                          "(known traffic, to calibrate the FETCH_SIZE / WRITE_SIZE counters)")

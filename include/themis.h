@@ -325,9 +325,12 @@ int themis_sweep_with_scratch(const themis_batch_t *batch, int n_thr,
  *   THEMIS_MAPPING_LANE : one lane per evaluation
  *   THEMIS_MAPPING_QUAD : four lanes per evaluation, one per dimension
  * LANE and QUAD also fix which of the two themis_simulate_batch takes where it does
- * not take a wavefront per scenario.  Beyond 64 chunks there is only QUAD, for
- * either.  Process-wide, takes effect with the next call; meant for measurements
- * and tests.  Returns THEMIS_ERR_INVALID_ARGUMENT for any other value.
+ * not take a wavefront per scenario or trace (AUTO: four lanes until one each fill
+ * the GPU).  On single collectives beyond 64 chunks there is only QUAD, for either;
+ * on traces QUAD takes those released together on power-of-two NPU counts, and the
+ * others run as if it were not there.  Process-wide, takes effect with the next call;
+ * meant for measurements and tests.  Returns THEMIS_ERR_INVALID_ARGUMENT for any
+ * other value.
  */
 #define THEMIS_MAPPING_AUTO 0
 #define THEMIS_MAPPING_LANE 1
@@ -337,12 +340,15 @@ int themis_set_sweep_mapping(int mapping);
 /*
  * themis_set_batch_mapping -- the same for themis_plan_batch and
  * themis_simulate_batch:
- *   THEMIS_MAPPING_AUTO : a wavefront per scenario (or trace) in small batches,
- *                         one lane per scenario in large ones (the default)
- *   THEMIS_MAPPING_LANE : one lane per scenario
+ *   THEMIS_MAPPING_AUTO : a wavefront per scenario (or trace) in small batches
+ *                         (the default)
+ *   THEMIS_MAPPING_LANE : no wavefront per scenario or trace
  *   THEMIS_MAPPING_WAVE : one wavefront per scenario (per scenario and
- *                         collective, in the planner)
- * Results are the same.  Process-wide, meant for measurements and tests.
+ *                         collective, in the planner), as long as a launch has room
+ *                         for that many
+ * What has no wavefront of its own is planned on a lane (other NPU counts than powers
+ * of two: on four) and simulated on one lane or four, as themis_set_sweep_mapping
+ * says.  Results are the same.  Process-wide, meant for measurements and tests.
  */
 #define THEMIS_MAPPING_WAVE 3
 int themis_set_batch_mapping(int mapping);

@@ -271,13 +271,16 @@ MAPPING_AUTO, MAPPING_LANE, MAPPING_QUAD, MAPPING_WAVE = 0, 1, 2, 3
 
 
 def themis_set_sweep_mapping(mapping: int) -> None:
-    """Lane mapping of themis_sweep's LDS kernel (MAPPING_AUTO / _LANE / _QUAD), process-wide."""
+    """One lane or four per evaluation (MAPPING_AUTO / _LANE / _QUAD) in themis_sweep, and in
+    themis_simulate_batch (single collectives and traces) where it does not take a wavefront each;
+    beyond 64 chunks there are only four.  Process-wide."""
     _check(lib().themis_set_sweep_mapping(int(mapping)))
 
 
 def themis_set_batch_mapping(mapping: int) -> None:
-    """Lanes per scenario of the planner and of single collectives' simulation (MAPPING_AUTO /
-    _LANE / _WAVE), process-wide."""
+    """Whether the planner and the simulation (single collectives and traces) take a wavefront per
+    scenario: in small batches (MAPPING_AUTO), never (_LANE: one lane or four, as
+    themis_set_sweep_mapping says) or wherever they can (_WAVE).  Process-wide."""
     _check(lib().themis_set_batch_mapping(int(mapping)))
 
 
