@@ -702,7 +702,6 @@ simulate_quad_kernel(themis_batch_t b, const uint8_t* __restrict__ orders, doubl
   __shared__ uint64_t lds_block[(kLdsBytes + 7u) / 8u];
   const uint32_t k = threadIdx.x & 3u;
   const uint64_t first = (uint64_t)block_index() * L::kQuads, at = first + (threadIdx.x >> 2);
-  if (first >= b.n) return;
   // a quad without a scenario stays: the wavefront leaves the event loop as a whole
   const bool exists = at < b.n;
   const uint64_t i = exists ? at : b.n - 1u;
