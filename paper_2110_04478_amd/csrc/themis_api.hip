@@ -455,12 +455,24 @@ __device__ __forceinline__ void quad_table_rounds(const themis_batch_t& b, const
   }
 }
 
+// As L, with registers for two wavefronts on a SIMD and no more: for batches that are all
+// resident so, whose time is that of the fullest SIMD.  With room for three the GPU gives
+// some SIMDs three and others one, or not, after what ran before: behind plan_kernel with
+// its four wavefronts 100,003 4-D scenarios of 64 chunks took 486 us, 128,299 of 61 chunks
+// 448; so they take 405 and 355, as behind a planner of one wavefront.
+template <typename L>
+struct TwoPerSimd : L {
+  static constexpr uint32_t kWavesPerSimd = 2;
+};
+
 template <typename L, int kQueueOrder, bool kBusy, bool kFix>
 __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(L::kWavesPerSimd)))
 simulate_kernel(themis_batch_t b, const uint8_t* __restrict__ orders,
                 double* __restrict__ t_done, void* __restrict__ queue_order, int entry_bytes,
                 double* __restrict__ busy, unsigned long long hand_over) {
   __shared__ __attribute__((aligned(8))) uint32_t lds_block[L::kLaneWords * kBlock];
+  // (a third of a SIMD's 512 registers per lane, and a few, see TwoPerSimd)
+  if constexpr (L::kWavesPerSimd == 2u) asm volatile("" : : : "v175");
   // (a lane beyond the batch stays for the exchanges between lanes)
   const uint64_t at = (uint64_t)blockIdx.x * kBlock + threadIdx.x;
   const bool exists = at < b.n;
@@ -2813,8 +2825,9 @@ static uint32_t layout_capacity(uint32_t max_chunks) {
        : max_chunks > 16u ? 64u : 16u;
 }
 
-static SimKernel pick_simulate_kernel(uint32_t cap, int mode, bool busy, bool fix) {
-  return cap == 16u ? pick_mode<Layout16>(mode, busy, fix) : pick_mode<LayoutRing>(mode, busy, fix);
+static SimKernel pick_simulate_kernel(uint32_t cap, int mode, bool busy, bool fix, bool two) {
+  return cap == 16u ? (two ? pick_mode<TwoPerSimd<Layout16>>(mode, busy, fix) : pick_mode<Layout16>(mode, busy, fix))
+                    : (two ? pick_mode<TwoPerSimd<LayoutRing>>(mode, busy, fix) : pick_mode<LayoutRing>(mode, busy, fix));
 }
 
 // The same with four lanes per scenario.
@@ -2910,7 +2923,8 @@ static bool on_wavefronts(uint64_t items, uint64_t most) {
 }
 // Wavefronts of plan_kernel for 64 scenarios: four where one each would leave the
 // SIMDs with two or fewer (64 chunks, us, one / four: 65,536 4-D scenarios of other
-// NPU counts 145 / 102, 100,003 ragged ones 143 / 128; 65,536 of powers of two 35 / 36).
+// NPU counts 177 / 103, 100,003 of them 205 / 146, ragged ones 163 / 131; 65,536 of powers
+// of two 38 / 44, 100,003 42 / 52).
 static unsigned plan_waves(uint64_t n) {
   return blocks_for(n) <= 8u * (compute_units() ? compute_units() : 256u) ? kPlanWaves : 1u;
 }
@@ -3181,8 +3195,9 @@ static int simulate_batch_impl(const themis_batch_t* batch, const uint8_t* order
                (batch->n + kBlock / 4u - 1u) / (kBlock / 4u), kBlock, *batch, orders, t_done, queue_order,
                entry_bytes, busy, call);
   } else {
-    go(pick_simulate_kernel(cap, mode, busy != nullptr, batch->fixed_delay != nullptr), blocks_for(batch->n), kBlock,
-       *batch, orders, t_done, queue_order, entry_bytes, busy, call);
+    const bool two = blocks_for(batch->n) <= 8u * (compute_units() ? compute_units() : 256u);
+    go(pick_simulate_kernel(cap, mode, busy != nullptr, batch->fixed_delay != nullptr, two), blocks_for(batch->n),
+       kBlock, *batch, orders, t_done, queue_order, entry_bytes, busy, call);
   }
   const Workspace ws = have_ws ? w : Workspace{};
   const uint32_t group = follow_up_group(batch->n);

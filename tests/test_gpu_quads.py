@@ -62,11 +62,18 @@ def test_lanes_and_quads_agree_with_the_oracle(gpu, oracle, mapping, case):
         gpu.themis_set_sweep_mapping(gpu.MAPPING_AUTO)
 
 
-@pytest.mark.parametrize("n,chunks", [(16385, 2), (32769, 2), (65536, 2), (65537, 2), (65600, 3), (17000, 70)])
+@pytest.mark.parametrize("n,chunks", [(16385, 2), (32769, 2), (65536, 2), (65537, 2), (65600, 3), (17000, 70),
+                                      (66001, 20), (131073, 1), (131100, 7), (131201, 16), (131300, 17), (131400, 22)])
 def test_batch_sizes_around_the_lines(gpu, oracle, n, chunks):
-    """Where the mapping changes, and where the follow-up kernel's workgroups look
-    at more scenarios each; all kinds of NPU counts."""
-    check_batch(gpu, oracle, _mixed_counts(n, 910 + chunks, 2, max_chunks=chunks), threads=16)
+    """Where the mapping changes (from 131,073 scenarios on the lanes' kernels are those
+    without a limit of two wavefronts on a SIMD: each layout with rows of whole and of
+    odd words, with queue orders and without, with delays), and where the follow-up
+    kernel's workgroups look at more scenarios each; all kinds of NPU counts."""
+    b = _mixed_counts(n, 910 + chunks, 2, max_chunks=chunks)
+    check_batch(gpu, oracle, b, threads=16)
+    if n > 65600:
+        check_batch(gpu, oracle, b, queue=False, threads=16)
+        check_batch(gpu, oracle, _with_fixed_delay(b, 19), threads=16)
 
 
 @pytest.mark.parametrize("max_chunks,n", [(65, 33), (127, 50), (128, 17), (129, 33), (256, 17), (257, 16)])

@@ -140,3 +140,15 @@ def test_four_lanes_per_scenario_until_one_each_fill_the_gpu(launches, cus):
     quads, lanes = launches([("simulate", line, 64, {}), ("simulate", line + 1, 64, {})], cus=cus)
     assert any("simulate_quad_kernel" in l[0] for l in quads[1])
     assert not any("simulate_quad_kernel" in l[0] for l in lanes[1]) and any("simulate_kernel" in l[0] for l in lanes[1])
+
+
+@pytest.mark.parametrize("cus", [256, 48])
+def test_batches_of_two_wavefronts_per_simd(launches, cus):
+    """Up to two wavefronts of lanes for every SIMD the simulation has registers for no
+    third one there."""
+    line = 512 * cus
+    for chunks in (9, 64):
+        for n, few in ((line - 100, True), (line, True), (line + 1, False)):
+            sim, = launches([("simulate", n, chunks, {})], cus=cus)
+            kernel = _blocks(sim, "simulate_kernel")[0]
+            assert ("TwoPerSimd" in kernel[0]) == few and kernel[1] == -(-n // 64), (n, chunks, sim)
