@@ -140,17 +140,24 @@ struct QuadTurns {
 // few thousand traces has too few scenarios to fill the GPU.
 // One or four wavefronts for 64 of them: the first plans those whose NPU counts are
 // powers of two, a lane each, and all of them the others, four lanes each, 16 at a
-// time (see plan_waves).
+// time (see plan_waves).  They are workgroups of their own, the first ones of all
+// groups before the second ones: as one workgroup of four, whose LDS is held until the
+// last of them is through, 65,536 scenarios of 32 chunks took 66 us on other NPU counts
+// and 29 on powers of two, now 59 and 26.
 constexpr uint32_t kPlanWaves = 4u;
 template <bool kPerCollective>
-__global__ void __launch_bounds__(kPlanWaves* kBlock)
+__global__ void __launch_bounds__(kBlock)
 plan_kernel(themis_batch_t b, uint8_t* __restrict__ orders, double* __restrict__ loads) {
   // the planner's order table, one entry per lane of the workgroup's first wavefront
   static_assert(kBlock == kPlanOrders, "one table entry per lane");
   __shared__ __attribute__((aligned(16))) uint32_t plan_orders[kPlanOrders * kPlanOrderWords];
-  const uint32_t lane = threadIdx.x & 63u;
-  const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x / kBlock));
-  uint32_t waves = blockDim.x / kBlock;
+  const uint32_t lane = threadIdx.x;
+  uint32_t wave = 0u, waves = 1u, group = blockIdx.x;
+  if (!kPerCollective) {
+    const uint32_t groups = (uint32_t)((b.n + kBlock - 1u) / kBlock);
+    if (gridDim.x > groups) waves = kPlanWaves;
+    for (; group >= groups; group -= groups) ++wave;
+  }
   if (wave == 0u) {   // (the only one that reads it; a wavefront's LDS accesses keep their order)
     plan_order_entry(lane, plan_orders + kPlanOrderWords * lane);
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -158,7 +165,7 @@ plan_kernel(themis_batch_t b, uint8_t* __restrict__ orders, double* __restrict__
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
   }
   const TraceView tv = trace_view(b);
-  const uint64_t first = (uint64_t)blockIdx.x * kBlock, e = first + lane;
+  const uint64_t first = (uint64_t)group * kBlock, e = first + lane;
   auto scenario_of = [&](uint64_t at) { return kPerCollective ? at / tv.mc : at; };
   const bool rel = b.threshold_mode == THEMIS_THR_REL;
   // a collective's codes, and from there to the end of its row
@@ -2923,8 +2930,8 @@ static bool on_wavefronts(uint64_t items, uint64_t most) {
 }
 // Wavefronts of plan_kernel for 64 scenarios: four where one each would leave the
 // SIMDs with two or fewer (64 chunks, us, one / four: 65,536 4-D scenarios of other
-// NPU counts 177 / 103, 100,003 of them 205 / 146, ragged ones 163 / 131; 65,536 of powers
-// of two 38 / 44, 100,003 42 / 52).
+// NPU counts 177 / 89, 100,003 of them 205 / 126, ragged ones 163 / 100; 65,536 of powers
+// of two 38 / 40, 100,003 42 / 45).
 static unsigned plan_waves(uint64_t n) {
   return blocks_for(n) <= 8u * (compute_units() ? compute_units() : 256u) ? kPlanWaves : 1u;
 }
@@ -3104,8 +3111,8 @@ int themis_plan_batch(const themis_batch_t* batch, uint8_t* orders, double* load
   if (plan_on_wavefronts(batch->n * tv.mc))
     go(plan_wave_kernel, (unsigned)(batch->n * tv.mc), kBlock, *batch, orders, loads);
   else
-    go(tv.mc > 1u ? plan_kernel<true> : plan_kernel<false>, blocks_for(batch->n * tv.mc),
-       (tv.mc > 1u ? 1u : plan_waves(batch->n)) * kBlock, *batch, orders, loads);
+    go(tv.mc > 1u ? plan_kernel<true> : plan_kernel<false>,
+       blocks_for(batch->n * tv.mc) * (tv.mc > 1u ? 1u : plan_waves(batch->n)), kBlock, *batch, orders, loads);
   return go.status();
 }
 

@@ -145,10 +145,11 @@ def test_four_lanes_per_scenario_until_one_each_fill_the_gpu(launches, cus):
 @pytest.mark.parametrize("cus", [256, 48])
 def test_batches_of_two_wavefronts_per_simd(launches, cus):
     """Up to two wavefronts of lanes for every SIMD the simulation has registers for no
-    third one there."""
+    third one there, and the planner takes four wavefronts for a group of 64."""
     line = 512 * cus
     for chunks in (9, 64):
         for n, few in ((line - 100, True), (line, True), (line + 1, False)):
-            sim, = launches([("simulate", n, chunks, {})], cus=cus)
+            plan, sim = launches([("plan", n, chunks, {}), ("simulate", n, chunks, {})], cus=cus)
+            assert plan[1][0][1] == -(-n // 64) * (4 if few else 1), (n, chunks, plan)
             kernel = _blocks(sim, "simulate_kernel")[0]
             assert ("TwoPerSimd" in kernel[0]) == few and kernel[1] == -(-n // 64), (n, chunks, sim)
