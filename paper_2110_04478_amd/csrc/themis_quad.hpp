@@ -22,9 +22,12 @@
 // (Before, with the lane whose stage ends appending, one loop round per completion
 // and the stage derived from the order field: 133 vector instructions a pass, now
 // some 65; 512-chunk sweep of 65,536 networks, 8 thresholds x 2 policies, 47.3 ->
-// 29.7 ms.  A wavefront alone on its SIMD takes 980 clocks a pass, four on one 350
+// 29.7 ms.  A wavefront alone on its SIMD takes 860 clocks a pass, four on one 350
 // each: the first is the chain of dependent instructions and the two trips, the
-// second issue.)
+// second issue.  The link behind a chunk that starts is stored whether the list goes on or
+// not, with no branch around it: 20,001 scenarios of 250 chunks 1,013 -> 890 us.)
+// Wavefronts of first-in-first-out evaluations alone have a loop without lists in LDS
+// (quad_loop_fifo).
 //
 // A record names a chunk and its state: bits 0-8 the chunk, 9-13 its order's
 // place among those of D dimensions, 14 the phase (up to three dimensions the
@@ -180,45 +183,51 @@ __device__ const QuadStages g_quad_stages = quad_stages();
 // power of two may come after the one with the latency as long as no result leaves
 // the normal range (t_min).
 // A running stage, as the quad passes it on: bits 1-3 the dimension the chunk waits
-// for then (4: none), 9-14 its row and phase then, 16-20 the list it joins, 22-30 the
+// for then (4: none), 9-14 its row and phase then, 16-19 the list it joins, 23-31 the
 // chunk.
 // The stage table is in LDS behind the lists (1 KiB, 60 clocks nearer than the
-// caches) where that costs no wavefront: up to 256 chunks.
+// caches) where that costs no wavefront: up to 256 chunks; and in the place of the
+// lists' ends where the wavefront does without them (fifo).
 template <typename L, bool kFix>
 struct QuadPow2 {
   static constexpr bool kTableInLds = L::kCap <= 256u;
+  static constexpr uint32_t kTableAt = kTableInLds ? L::kBytes : 0u;
   static constexpr uint32_t kBytes = L::kBytes + (kTableInLds ? 1024u : 0u);
+  static_assert(kTableInLds || L::kLinksAt >= 1024u, "the table fits the place of the lists' ends");
   static constexpr double kShortest = 2.2250738585072014e-308;   // (see above)
   static constexpr uint32_t kNobody = ~0u;   // above all stages, for dimension 7, list 31 (a place behind the lists)
   double whole, fix;
   uint64_t ranktab;
   int less;         // -log2 P_k in byte k
-  const uint8_t* table;
+  uint8_t* block;
   uint32_t at, wanted;
+  bool fifo;        // no evaluation of the wavefront has more than one class
   __device__ __forceinline__ QuadPow2(const Scenario& s, const Pow2Model& m, uint32_t k, void* lds)
       : whole(m.fs.base * sel4((int)k, s.coef[0], s.coef[1], s.coef[2], s.coef[3])),
         fix(kFix ? sel4((int)k, s.fix[0], s.fix[1], s.fix[2], s.fix[3]) : 0.0), ranktab(m.ranktab), less(0),
-        table(kTableInLds ? (const uint8_t*)lds + L::kBytes : (const uint8_t*)&g_quad_stages),
-        at(4u * ((k + quad_column((uint32_t)s.D)) & 3u)),
+        block((uint8_t*)lds), at(4u * ((k + quad_column((uint32_t)s.D)) & 3u)),
         // a stand-alone Reduce-Scatter is finished where the phase would turn
-        wanted(m.rs_only() ? 14u | 0x4000u : 14u) {
+        wanted(m.rs_only() ? 14u | 0x4000u : 14u), fifo(__builtin_amdgcn_ballot_w64(m.ranktab != 0ull) == 0ull) {
 #pragma unroll
     for (uint32_t d = 0; d < 4u; ++d) less |= (int)((0u - (m.fs.epack >> (8u * d) & 0xffu) & 0xffu) << (8u * d));
-    if (kTableInLds)
+    if (kTableInLds || fifo)
       for (uint32_t j = 0; j < 4u; ++j)
-        ((uint32_t*)((uint8_t*)lds + L::kBytes))[64u * j + threadIdx.x % 64u] = (&g_quad_stages.v[0][0])[64u * j + threadIdx.x % 64u];
+        ((typename L::Word*)(block + kTableAt))[64u * j + threadIdx.x % 64u] = (&g_quad_stages.v[0][0])[64u * j + threadIdx.x % 64u];
     __syncthreads();
   }
   __device__ __forceinline__ bool goes_to(uint32_t given, uint32_t k) const { return (given & wanted) == 2u * k; }
   static __device__ __forceinline__ uint32_t list(uint32_t given) { return (given >> 16) & 31u; }
-  static __device__ __forceinline__ uint32_t record(uint32_t given) { return (given & 0x7e00u) | given >> 22; }
-  // rec: the chunk's record in the low half
+  static __device__ __forceinline__ uint32_t record(uint32_t given) { return (given & 0x7e00u) | given >> 23; }
+  // rec: the chunk's record in the low half; kFifo: on a wavefront of one class
+  template <bool kFifo>
   __device__ __forceinline__ uint32_t stage(uint32_t rec, double& time) const {
-    const uint32_t v = *(const uint32_t*)(table + (((rec >> 5) & 0x3f0u) | at));
-    time = ldexp(whole, __builtin_amdgcn_sdot4((int)(v & 0x01010101u), less, 0, false));
+    const uint8_t* const table = kTableInLds || kFifo ? block + kTableAt : (const uint8_t*)&g_quad_stages;
+    const uint32_t v = *(const typename L::Word*)(table + (((rec >> 5) & 0x3f0u) | at));
+    time = ldexp(whole, __builtin_amdgcn_sdot4((int)(v & 0x01010101u), less, 0, true));
     if (kFix) time = fix + time;
+    if (kFifo) return (v & 0x7e0eu) | rec << 23;
     const uint32_t cls = (uint32_t)(ranktab >> ((v >> 17) & 63u)) & 15u;
-    return (v & 0x7e0eu) | (rec & 0x1ffu) << 22 | cls << 16;
+    return ((v & 0x7e0eu) | rec << 23) | cls << 16;
   }
 };
 
@@ -230,7 +239,7 @@ struct QuadPow2 {
 // 128 * (4 * o + k) + 8 * g, and what the completion does, 16 bits (0-2 the dimension
 // the chunk waits for then, 3-8 the list it joins, 9-14 its state), at
 // 32 * (4 * state + k) + 2 * g (state: order and phase as in a record); a running
-// stage is these bits and the chunk from bit 16 on; size classes of (state, k) while these are made, 8 bits, at
+// stage is these bits and the chunk from bit 23 on; size classes of (state, k) while these are made, 8 bits, at
 // 16 * (4 * state + k) + g.
 // L: layout; kDims: up to three dimensions (six orders, at most twelve sizes that
 // wait for one dimension), or four (24, 48).
@@ -249,6 +258,7 @@ struct QuadTable {
   uint8_t* block;
   double t_min;
   uint32_t cls0;
+  bool fifo;        // as in QuadPow2
   static __device__ __forceinline__ uint32_t quad8() { return (threadIdx.x >> 2) * 8u; }
   static __device__ __forceinline__ double* f64_at(uint8_t* b, uint32_t o, uint32_t k) {
     return (double*)(b + (o << 9 | k << 7 | quad8()));
@@ -264,7 +274,8 @@ struct QuadTable {
   }
   // used: bit o says that some chunk has order o.  All lanes of the wavefront.
   __device__ __forceinline__ QuadTable(const Scenario& s, double chunk, bool scf, uint32_t used, void* lds)
-      : block((uint8_t*)lds), t_min(inf64()), cls0(0u) {
+      : block((uint8_t*)lds), t_min(inf64()), cls0(0u),
+        fifo(__builtin_amdgcn_ballot_w64(scf) == 0ull) {
     const uint32_t k = threadIdx.x & 3u, D = min((uint32_t)s.D, kDims);
     const bool gather = s.ctype == THEMIS_COLL_ALL_GATHER, rs_only = s.ctype == THEMIS_COLL_REDUCE_SCATTER;
     uint8_t* const rs = block + kTimes;        // sizes before the Reduce-Scatter stages, then the times
@@ -329,13 +340,14 @@ struct QuadTable {
   }
   static __device__ __forceinline__ bool goes_to(uint32_t given, uint32_t k) { return (given & 7u) == k; }
   static __device__ __forceinline__ uint32_t list(uint32_t given) { return (given >> 3) & 63u; }
-  static __device__ __forceinline__ uint32_t record(uint32_t given) { return (given & 0x7e00u) | given >> 16; }
+  static __device__ __forceinline__ uint32_t record(uint32_t given) { return (given & 0x7e00u) | given >> 23; }
+  template <bool kFifo>
   __device__ __forceinline__ uint32_t stage(uint32_t rec, double& time) const {
     const uint32_t k = threadIdx.x & 3u;
     time = *(const double*)(block + kTimes + ((rec & (L::kPhaseBit == 14u ? 0x3e00u : 0xe00u)) | (k << 7 | quad8())));
     const uint32_t v = *(const uint16_t*)(block + kDoes + (((rec >> 2) & (L::kPhaseBit == 14u ? 0x1f80u : 0x780u)) |
                                                            (k << 5 | (threadIdx.x >> 2) * 2u)));
-    return v | (rec & 0x1ffu) << 16;
+    return v | rec << 23;
   }
 };
 
@@ -414,15 +426,98 @@ struct QuadResult {
   bool ok;             // false: leave the evaluation to the follow-up passes
 };
 
-// All four lanes of a quad call this with the same scenario and their own
-// dimension's queue; cls0: the size class its chunks wait in.  Every lane of the
-// wavefront has to be here (the quads exchange values with lane-crossing moves
-// and leave the loop together), with `stages` = 0 where there is nothing to do.
-// put(i, entry): the lane's dimension has started operation i (kPut).
+// The two event loops start 4 bytes behind a 32-byte line whatever comes before them: the
+// place in the instruction stream is worth up to 4 % where a SIMD has few wavefronts, and
+// moved with every change elsewhere (start modulo 32, us: 30,000 scenarios of 100 chunks
+// 28 431, 8 413, 4 411; 20,001 of 250 chunks 20 1,021, 8 1,017, 4 1,005; sweep of 20,000
+// with 200 chunks 16 3,315, 8 3,255, 4 3,206).
+__device__ __forceinline__ void quad_loop_place() {
+  asm volatile(".p2align 5\n\ts_nop 0\n\ts_nop 0\n\ts_nop 0\n\ts_nop 0\n\ts_nop 0\n\ts_nop 0\n\ts_nop 0");
+}
+
+// What the lane's dimension has come to (see simulate_quad).
+struct QuadRun {
+  double f = nan64();      // finish time of the stage it serves, NaN when idle
+  double busy = 0.0, now = 0.0;
+  uint32_t sv = 0u;        // that stage, as the model passes it on
+  uint32_t started = 0u;
+  bool waits = false;      // chunks wait
+};
+// A pass up to the hand-over.  next: the earliest completion of the evaluation (NaN:
+// nothing runs).  Returns the stage that is handed on; ending: the lanes whose stage ends now.
+template <typename Model>
+__device__ __forceinline__ uint32_t quad_hand_over(QuadRun& d, double next, uint64_t& ending) {
+  // a8: the clock moves there
+  d.now = max_f64(d.now, next);
+  // of the stages that end now the one of the lowest chunk hands it on
+  const bool ends = d.f == next;
+  ending = __builtin_amdgcn_ballot_w64(ends);
+  const uint32_t key = ends ? d.sv : Model::kNobody;
+  const uint32_t given = quad_min_u32(key);
+  if (ends && key == given) d.f = __hiloint2double(0x7ff80000, __double2loint(d.f));
+  return given;
+}
+// Once all completions of the instant are delivered.  running: the lanes of the quads where
+// something runs.
+__device__ __forceinline__ bool quad_all_delivered(bool starts, uint64_t ending, uint64_t running) {
+  if (__builtin_popcountll(ending) * 4 != __builtin_popcountll(running)) {   // more than one in some quad
+    uint32_t mine = (uint32_t)(ending >> (threadIdx.x & 60u)) & 15u;
+    asm volatile("" : "+v"(mine));   // (rare: a branch, not selects in every pass)
+    starts = starts && (mine & (mine - 1u)) == 0u;
+  }
+  return starts;
+}
+
+// One class, first-in-first-out: a dimension's list is its first and its last record, in
+// registers.  What a stage does depends on nothing that has to be read before, and the link
+// behind its chunk is looked at a pass later, so a pass is one LDS trip and 45 vector
+// instructions (the loop for any number of classes: two and 66).  65,536 3-D scenarios of
+// 64 chunks, with the planner: 278 -> 234 us.
 template <typename L, bool kPut, typename Model, typename Put>
-__device__ __forceinline__ QuadResult simulate_quad(const Model& model, QuadQueue<L>& queue, uint32_t cls0,
-                                                    uint32_t stages, double t_min, Put put) {
-  const uint32_t k = threadIdx.x & 3u;   // the lane's dimension
+__device__ __forceinline__ QuadRun quad_loop_fifo(const Model& model, const QuadQueue<L>& queue, Put put) {
+  const uint32_t k = threadIdx.x & 3u;
+  uint8_t* const block = queue.block;
+  QuadRun d;
+  uint32_t first = queue.first, last = queue.last;
+  d.waits = queue.any;
+  auto pass = [&](double next, uint64_t running) {
+    uint64_t ending;
+    const uint32_t given = quad_hand_over<Model>(d, next, ending);
+    const bool append = model.goes_to(given, k);
+    const uint32_t rec = Model::record(given);
+    asm volatile("" : "+v"(first));   // (the wait for it: before the store, whose wait it would be as well)
+    first = append && !d.waits ? rec : first;
+    if (append && d.waits) *L::link(block, last) = (uint16_t)rec;
+    last = append ? rec : last;
+    d.waits = d.waits || append;
+    if (quad_all_delivered(d.waits && !(d.f == d.f), ending, running)) {
+      double time;
+      const uint32_t link = *L::link(block, first);   // (only used where the list goes on)
+      d.sv = model.template stage<true>(first, time);
+      d.f = d.now + time;
+      d.busy = d.busy + time;
+      if (kPut) put(d.started, (first & L::kIdMask) << 1 | ((first >> L::kPhaseBit) & 1u));
+      ++d.started;
+      d.waits = first != last;
+      first = link;
+    }
+  };
+  pass(nan64(), 0ull);
+  quad_loop_place();
+  // (every pass in which something runs completes a stage)
+  for (uint32_t left = 2u * (uint32_t)kMaxDims * L::kCap + 16u; left != 0u; --left) {
+    const double next = quad_min_f64(d.f);
+    const uint64_t running = __builtin_amdgcn_ballot_w64(next == next);
+    if (running == 0ull) break;
+    pass(next, running);
+  }
+  return d;
+}
+
+// Any number of classes.
+template <typename L, bool kPut, typename Model, typename Put>
+__device__ __forceinline__ QuadRun quad_loop_classes(const Model& model, const QuadQueue<L>& queue, uint32_t cls0, Put put) {
+  const uint32_t k = threadIdx.x & 3u;
   uint8_t* const block = queue.block;
   using Mask = typename std::conditional<(L::kPerDim > 32u), uint64_t, uint32_t>::type;
   // bit c: list of class c holds chunks; one bit behind the classes is always set, so that
@@ -434,21 +529,10 @@ __device__ __forceinline__ QuadResult simulate_quad(const Model& model, QuadQueu
     *L::ends(block, cls0) = queue.first | queue.last << 16;
     lists |= (Mask)1 << cls0;
   }
-  double f = nan64();      // finish time of the stage the dimension serves, NaN when idle
-  double busy = 0.0, now = 0.0;
-  uint32_t sv = 0u;        // that stage, as the model passes it on
-  uint32_t started = 0u;
-  // One pass.  next: the earliest completion of the evaluation (NaN: nothing runs),
-  // running: the lanes for which that is a number.
+  QuadRun d;
   auto pass = [&](double next, uint64_t running) {
-    // a8: the clock moves there
-    now = max_f64(now, next);
-    // of the stages that end now the one of the lowest chunk hands it on
-    const bool ends = f == next;
-    const uint64_t ending = __builtin_amdgcn_ballot_w64(ends);
-    const uint32_t key = ends ? sv : Model::kNobody;
-    const uint32_t given = quad_min_u32(key);
-    if (ends && key == given) f = __hiloint2double(0x7ff80000, __double2loint(f));
+    uint64_t ending;
+    const uint32_t given = quad_hand_over<Model>(d, next, ending);
     // (dimension 4, and that of kNobody where nothing ends: no lane's)
     const bool append = model.goes_to(given, k);
     const uint32_t to = Model::list(given);
@@ -457,12 +541,7 @@ __device__ __forceinline__ QuadResult simulate_quad(const Model& model, QuadQueu
     if (append) lists |= to_bit;
     // an idle dimension with waiting chunks starts the first chunk of its lowest
     // class (smallest resident size), once all completions of the instant are delivered
-    bool starts = !(f == f) && lists != kNone;
-    if (__builtin_popcountll(ending) * 4 != __builtin_popcountll(running)) {   // more than one in some quad
-      uint32_t mine = (uint32_t)(ending >> (threadIdx.x & 60u)) & 15u;
-      asm volatile("" : "+v"(mine));   // (rare: a branch, not selects in every pass)
-      starts = starts && (mine & (mine - 1u)) == 0u;
-    }
+    const bool starts = quad_all_delivered(!(d.f == d.f) && lists != kNone, ending, running);
     const uint32_t from = sizeof(Mask) == 8u ? (uint32_t)__builtin_ctzll(lists) : (uint32_t)__builtin_ctz((uint32_t)lists);
     typename L::Word* const from_at = L::ends(block, from);
     typename L::Word* const to_at = L::ends(block, to);
@@ -476,40 +555,48 @@ __device__ __forceinline__ QuadResult simulate_quad(const Model& model, QuadQueu
       if (to == from) ends_from = ends_now;
     }
     if (starts) {
-      const uint32_t link = *L::link(block, ends_from);
       double time;
-      sv = model.stage(ends_from, time);
+      d.sv = model.template stage<false>(ends_from, time);
+      const uint32_t link = *L::link(block, ends_from);
       const bool last = ends_from == __builtin_amdgcn_alignbit(ends_from, ends_from, 16u);   // of its list
       lists &= last ? lists - 1u : ~(Mask)0;
-      if (!last) *(typename L::Half*)from_at = (uint16_t)link;
-      f = now + time;
-      busy = busy + time;
-      if (kPut) put(started, (ends_from & L::kIdMask) << 1 | ((ends_from >> L::kPhaseBit) & 1u));
-      ++started;
+      *(typename L::Half*)from_at = (uint16_t)link;   // (whatever it is where the list has ended)
+      d.f = d.now + time;
+      d.busy = d.busy + time;
+      if (kPut) put(d.started, (ends_from & L::kIdMask) << 1 | ((ends_from >> L::kPhaseBit) & 1u));
+      ++d.started;
     }
   };
   pass(nan64(), 0ull);
-  // The loop starts 4 bytes behind a 32-byte line whatever comes before it: its place in
-  // the instruction stream is worth up to 4 % where a SIMD has few wavefronts, and moved
-  // with every change elsewhere (start modulo 32, us: 30,000 scenarios of 100 chunks 28
-  // 431, 8 413, 4 411; 20,001 of 250 chunks 20 1,021, 8 1,017, 4 1,005; sweep of 20,000
-  // with 200 chunks 16 3,315, 8 3,255, 4 3,206).
-  asm volatile(".p2align 5\n\ts_nop 0\n\ts_nop 0\n\ts_nop 0\n\ts_nop 0\n\ts_nop 0\n\ts_nop 0\n\ts_nop 0");
-  // (every pass in which something runs completes a stage)
+  quad_loop_place();
   for (uint32_t left = 2u * (uint32_t)kMaxDims * L::kCap + 16u; left != 0u; --left) {
-    const double next = quad_min_f64(f);
+    const double next = quad_min_f64(d.f);
     const uint64_t running = __builtin_amdgcn_ballot_w64(next == next);
     if (running == 0ull) break;
     pass(next, running);
   }
+  d.waits = lists != kNone;
+  return d;
+}
+
+// All four lanes of a quad call this with the same scenario and their own
+// dimension's queue; cls0: the size class its chunks wait in.  Every lane of the
+// wavefront has to be here (the quads exchange values with lane-crossing moves
+// and leave the loop together), with `stages` = 0 where there is nothing to do.
+// put(i, entry): the lane's dimension has started operation i (kPut).
+template <typename L, bool kPut, typename Model, typename Put>
+__device__ __forceinline__ QuadResult simulate_quad(const Model& model, QuadQueue<L>& queue, uint32_t cls0,
+                                                    uint32_t stages, double t_min, Put put) {
+  const QuadRun d = model.fifo ? quad_loop_fifo<L, kPut>(model, queue, put)
+                               : quad_loop_classes<L, kPut>(model, queue, cls0, put);
   QuadResult res;
-  res.t_done = now;
-  res.busy = busy;
-  res.started = started;
+  res.t_done = d.now;
+  res.busy = d.busy;
+  res.started = d.started;
   // every stage ran and completed, and none was too short to move the clock, or for
   // the model
-  const uint32_t settled = quad_min_u32(!(f == f) && lists == kNone ? 1u : 0u);
-  res.ok = quad_sum(started) == stages && settled != 0u && now < inf64() && now + 0.25 * t_min > now &&
+  const uint32_t settled = quad_min_u32(!(d.f == d.f) && !d.waits ? 1u : 0u);
+  res.ok = quad_sum(d.started) == stages && settled != 0u && d.now < inf64() && d.now + 0.25 * t_min > d.now &&
            t_min >= Model::kShortest;
   return res;
 }

@@ -62,6 +62,26 @@ def test_lanes_and_quads_agree_with_the_oracle(gpu, oracle, mapping, case):
         gpu.themis_set_sweep_mapping(gpu.MAPPING_AUTO)
 
 
+@pytest.mark.parametrize("max_chunks", [1, 2, 64, 65, 128, 129, 256, 512])
+def test_wavefronts_of_one_policy_and_of_both(gpu, oracle, max_chunks):
+    """First-in-first-out alone has an event loop of its own: 16 scenarios of it, 16 of
+    Smallest-Chunk-First, 16 of either and so on, on powers of two, on other NPU counts
+    of up to three dimensions and of four, and with both in a wavefront."""
+    for every, dims in ((1, None), (10 ** 9, 3), (10 ** 9, 4), (3, None)):
+        b = _with_collective_types(_mixed_counts(131, 980 + max_chunks, every, dims=dims, max_chunks=max_chunks), 20)
+        b.chunks[::3] = max_chunks
+        kind = np.arange(b.n) // 16 % 3
+        b.intra_policy[kind < 2] = kind[kind < 2]
+        gpu.themis_set_batch_mapping(gpu.MAPPING_LANE)
+        gpu.themis_set_sweep_mapping(gpu.MAPPING_QUAD)
+        try:
+            check_batch(gpu, oracle, b)
+            check_batch(gpu, oracle, b, queue=False)
+        finally:
+            gpu.themis_set_batch_mapping(gpu.MAPPING_AUTO)
+            gpu.themis_set_sweep_mapping(gpu.MAPPING_AUTO)
+
+
 @pytest.mark.parametrize("n,chunks", [(16385, 2), (32769, 2), (65536, 2), (65537, 2), (65600, 3), (17000, 70),
                                       (66001, 20), (131073, 1), (131100, 7), (131201, 16), (131300, 17), (131400, 22)])
 def test_batch_sizes_around_the_lines(gpu, oracle, n, chunks):

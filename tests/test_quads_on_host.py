@@ -123,6 +123,18 @@ def test_single_collectives(oracle, queues, cap, chunks, n, kind):
     _check(oracle, queues, b, orders, cap, 0)
 
 
+@pytest.mark.parametrize("cap,chunks,n", [(64, 1, 14), (64, 64, 11), (128, 127, 11), (256, 256, 11), (512, 512, 11)])
+@pytest.mark.parametrize("dims", [0, 3, 4])
+def test_first_in_first_out_alone(oracle, queues, cap, chunks, n, dims):
+    """The event loop of wavefronts without Smallest-Chunk-First (dims: tables of that
+    many dimensions, 0: powers of two), every instant a tie, and none."""
+    for b in (_ties(n, 140 + cap, chunks), _mixed(n, 150 + cap, chunks, dims=dims or None, pow2=not dims)):
+        if dims:
+            b.ndims = np.minimum(b.ndims, dims)
+        b.intra_policy[:] = 0
+        _check(oracle, queues, b, _any_orders(b, cap), cap, dims)
+
+
 @pytest.mark.parametrize("max_chunks,max_coll,dims,n", [(1, 1, 3, 14), (5, 1, 4, 14), (9, 6, 3, 14), (16, 20, 4, 11), (8, 40, 3, 11)])
 def test_traces(oracle, queues, max_chunks, max_coll, dims, n):
     rng = np.random.default_rng(max_coll)
