@@ -104,8 +104,7 @@ constexpr uint32_t kGridRow = 1u << 25;
 __device__ __forceinline__ uint32_t block_index() { return blockIdx.y * kGridRow + blockIdx.x; }
 
 // Work of some lanes of a wavefront, taken by its quads 16 at a time, the longest
-// first: a turn takes as long as its longest (100,003 ragged scenarios of any NPU
-// counts, both simulation kernels: 1,503 us in the order they come, 995 so).
+// first: a turn takes as long as its longest.
 struct QuadTurns {
   uint64_t left;
   uint32_t place;   // of the lane's own work (all-ones: none)
@@ -130,6 +129,97 @@ struct QuadTurns {
     return exists;
   }
 };
+
+// Scenarios of a window of the batch in turns of 16, the longest first: a turn takes as
+// long as its longest, so scenarios of about the same length go together (100,003 ragged
+// scenarios of any NPU counts, planner and both simulation kernels: 16 out of 64 neighbours
+// 1,095 us, out of 512 656).  Every workgroup that takes turns of a window finds the order by itself,
+// from the inputs alone, so nothing is passed between them: lengths in 64 buckets, inside
+// of a bucket as they come.
+constexpr uint32_t kWindow = 512u, kWindowGroups = kWindow / kBlock, kWindowTurns = kWindow / 16u;
+struct QuadWindow {
+  uint32_t rank[kWindowGroups];   // of the scenarios of the lane, one in each 64 (all-ones: not among them)
+  uint32_t total;
+  // length(g): that of scenario 64 * g + lane of the window, 0: not among them; most: the
+  // largest there can be.  All lanes; lds: 320 bytes.
+  template <typename Length>
+  __device__ __forceinline__ QuadWindow(uint32_t most, void* lds, Length length) {
+    uint32_t* const count = (uint32_t*)lds;
+    const uint32_t lane = threadIdx.x & 63u, bits = 32u - (uint32_t)__clz((int)(most | 1u));
+    const uint32_t shift = bits > 6u ? bits - 6u : 0u;
+    __syncthreads();
+    count[lane] = 0u;
+    __syncthreads();
+    uint32_t bucket[kWindowGroups];
+#pragma unroll
+    for (uint32_t g = 0; g < kWindowGroups; ++g) {
+      const uint32_t events = length(g);
+      bucket[g] = 63u - min(events >> shift, 63u);
+      uint64_t same = __builtin_amdgcn_ballot_w64(events != 0u);
+#pragma unroll
+      for (uint32_t j = 0; j < 6u; ++j) {
+        const bool one = ((bucket[g] >> j) & 1u) != 0u;
+        const uint64_t ones = __builtin_amdgcn_ballot_w64(one);
+        same &= one ? ones : ~ones;
+      }
+      const uint32_t before = __builtin_amdgcn_mbcnt_hi((uint32_t)(same >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)same, 0u));
+      const uint32_t had = count[bucket[g]];
+      rank[g] = events != 0u ? had + before : ~0u;
+      __syncthreads();
+      if (events != 0u && before == 0u) count[bucket[g]] = had + (uint32_t)__builtin_popcountll(same);
+      __syncthreads();
+    }
+    const uint32_t mine = count[lane];
+    uint32_t upto = mine;
+    for (uint32_t off = 1u; off < 64u; off <<= 1) {
+      const uint32_t below = (uint32_t)__shfl_up((int)upto, off);
+      upto += lane >= off ? below : 0u;
+    }
+    total = (uint32_t)__builtin_amdgcn_readlane((int)upto, 63);
+    __syncthreads();
+    count[lane] = upto - mine;
+    __syncthreads();
+#pragma unroll
+    for (uint32_t g = 0; g < kWindowGroups; ++g) rank[g] = rank[g] != ~0u ? count[bucket[g]] + rank[g] : ~0u;
+  }
+  __device__ __forceinline__ uint32_t turns() const { return (total + 15u) / 16u; }
+  // which: the scenario of the window that the lane's quad takes; false: none.  All lanes.
+  __device__ __forceinline__ bool take(uint32_t turn, void* lds, uint32_t& which) const {
+    uint32_t* const chosen = (uint32_t*)lds + 64u;
+    const uint32_t lane = threadIdx.x & 63u;
+    __syncthreads();
+#pragma unroll
+    for (uint32_t g = 0; g < kWindowGroups; ++g)
+      if (rank[g] >> 4 == turn) chosen[rank[g] & 15u] = kBlock * g + lane;
+    __syncthreads();
+    const bool exists = 16u * turn + (lane >> 2) < total;
+    which = exists ? chosen[lane >> 2] : 0u;
+    __syncthreads();
+    return exists;
+  }
+};
+
+// What a window's order is made from.
+struct WindowScenario {
+  uint32_t D, events;
+  bool in_range;   // (dimensions and chunks; what else makes a scenario invalid is not looked at)
+};
+__device__ __forceinline__ WindowScenario window_scenario(const themis_batch_t& b, uint64_t i) {
+  WindowScenario w;
+  w.D = b.ndims[i];
+  const uint32_t C = b.chunks[i];
+  const bool one_phase = b.collective_type && b.collective_type[i] != THEMIS_COLL_ALL_REDUCE;
+  w.in_range = w.D - 1u < (uint32_t)kMaxDims && C - 1u < b.max_chunks;
+  w.events = w.in_range ? C * w.D * (one_phase ? 1u : 2u) : 1u;
+  return w;
+}
+// Does it have an NPU count that is not a power of two?
+__device__ __forceinline__ bool other_counts(const themis_batch_t& b, uint64_t i, uint32_t D) {
+  bool other = false;
+#pragma unroll
+  for (uint32_t k = 0; k < (uint32_t)kMaxDims; ++k) other = other || (k < D && !is_pow2(b.npus[(size_t)k * b.n + i]));
+  return other;
+}
 
 // ---------------------------------------------------------------------------
 // themis_plan_batch: Alg. 1 per scenario (hot-path steps a1-a5).
@@ -415,63 +505,56 @@ __device__ __forceinline__ void quad_outputs(const themis_batch_t& b, uint64_t i
   if (kQueueOrder != kNoQueueOrder) pad_row(row, done ? r.started : 0u, 2u * b.max_chunks, entry_bytes);
 }
 
-// The scenarios first + lane of the lanes in `left` (valid ones of up to kDims
-// dimensions and L::kCap chunks), whatever their NPU counts are (QuadTable), 16 at
-// a time.  What the event loop does not take is marked, unless it is marked already
-// (marked); malformed codes are for the caller's kernel or the generic one.  All
-// lanes of the wavefront; lds: QuadTable::kBytes.
+// One scenario (i) per quad, of up to kDims dimensions and L::kCap chunks, whatever its NPU
+// counts are (QuadTable).  What the event loop does not take is marked, unless it is
+// marked already (marked); malformed codes are for the caller's kernel or the generic
+// one, and so are invalid scenarios unless the caller leaves them here (invalid_too).
+// Returns whether it is (still) marked.  All lanes of the wavefront; lds: QuadTable::kBytes.
 template <typename L, uint32_t kDims, int kQueueOrder>
-__device__ __forceinline__ void quad_table_rounds(const themis_batch_t& b, const uint8_t* __restrict__ orders,
-                                                  double* __restrict__ t_done, void* __restrict__ queue_order,
-                                                  int entry_bytes, double* __restrict__ busy, uint64_t first,
-                                                  uint64_t left, bool marked, void* lds, unsigned long long call) {
+__device__ __forceinline__ bool quad_table_turn(const themis_batch_t& b, const uint8_t* __restrict__ orders,
+                                                double* __restrict__ t_done, void* __restrict__ queue_order,
+                                                int entry_bytes, double* __restrict__ busy, uint64_t i, bool exists,
+                                                bool marked, bool invalid_too, void* lds, unsigned long long call) {
   using Table = QuadTable<L, kDims>;
-  const uint32_t lane = threadIdx.x & 63u, k = lane & 3u;
-  uint32_t events = 0u;
-  if (((left >> lane) & 1ull) != 0ull) {
-    const uint64_t i = first + lane;
-    const bool one_phase = b.collective_type && b.collective_type[i] != THEMIS_COLL_ALL_REDUCE;
-    events = b.chunks[i] * b.ndims[i] * (one_phase ? 1u : 2u);
-  }
-  for (QuadTurns turns(left, events); turns.left != 0ull;) {
-    uint32_t which;
-    const bool exists = turns.take(which);
-    const uint64_t i = exists ? first + which : first;
-    const Scenario s = load_scenario(b, i);
-    const uint32_t D = (uint32_t)s.D;
-    const bool gather = s.ctype == THEMIS_COLL_ALL_GATHER;
-    uint32_t bad = 0u, used = 0u;
-    auto order_of = [&](uint32_t code) {
-      return quad_order(gather ? reverse_code(code, s.D) : code, D) % Table::kOrders;
-    };
-    if (exists)
-      for (uint32_t c = k; c < s.C; c += 4u) {
-        const uint32_t code = orders[(size_t)i * b.max_chunks + c];
-        if (!quad_code_ok(code, D)) bad = 1u;
-        used |= 1u << order_of(code);
-      }
-    const bool runs = exists && quad_sum(bad) == 0u;
-    used = runs ? quad_or(used) : 0u;
-    const Table model(s, b.size_bytes[i] / (double)s.C, b.intra_policy[i] == THEMIS_INTRA_SCF, used, lds);
-    QuadQueue<L> queue(lds);
-    quad_codes(b, orders, i, runs ? s.C : 0u,
-               [&](uint32_t code) { return Table::state_of(order_of(code), gather ? 1u : 0u) << 9 | (code & 3u) << 16; },
-               [&](uint32_t c, uint32_t taken) {
-                 if (taken >> 16 == k) queue.add(c | (taken & 0xffffu));
-               });
-    uint8_t* const row = queue_order ? (uint8_t*)queue_order + ((size_t)i * kMaxDims + k) * 2u * b.max_chunks * (uint32_t)entry_bytes
-                                     : nullptr;
-    const uint32_t stages = s.ctype == THEMIS_COLL_ALL_REDUCE ? 2u * D : D;
-    const QuadResult r = simulate_quad<L, kQueueOrder != kNoQueueOrder>(
-        model, queue, model.cls0, runs ? stages * s.C : 0u, model.t_min, [&](uint32_t e, uint32_t entry) {
-          if (kQueueOrder == kShorts) ((uint16_t*)row)[e] = (uint16_t)entry;
-          else row[e] = (uint8_t)entry;
-        });
-    const bool done = runs && r.ok;
-    if (exists && (done || !marked))
-      quad_outputs<kQueueOrder>(b, i, done, !done, r, t_done, row, entry_bytes, busy, call);
-    __syncthreads();
-  }
+  const uint32_t k = threadIdx.x & 3u;
+  const Scenario s = load_scenario(b, i);
+  const double S = b.size_bytes[i];
+  const bool ok = s.valid && finite_positive(S), invalid = exists && !ok && invalid_too;
+  exists = exists && ok;
+  const uint32_t D = (uint32_t)s.D;
+  const bool gather = s.ctype == THEMIS_COLL_ALL_GATHER;
+  uint32_t bad = 0u, used = 0u;
+  auto order_of = [&](uint32_t code) {
+    return quad_order(gather ? reverse_code(code, s.D) : code, D) % Table::kOrders;
+  };
+  if (exists)
+    for (uint32_t c = k; c < s.C; c += 4u) {
+      const uint32_t code = orders[(size_t)i * b.max_chunks + c];
+      if (!quad_code_ok(code, D)) bad = 1u;
+      used |= 1u << order_of(code);
+    }
+  const bool runs = exists && quad_sum(bad) == 0u;
+  used = runs ? quad_or(used) : 0u;
+  const Table model(s, S / (double)s.C, b.intra_policy[i] == THEMIS_INTRA_SCF, used, lds);
+  QuadQueue<L> queue(lds);
+  quad_codes(b, orders, i, runs ? s.C : 0u,
+             [&](uint32_t code) { return Table::state_of(order_of(code), gather ? 1u : 0u) << 9 | (code & 3u) << 16; },
+             [&](uint32_t c, uint32_t taken) {
+               if (taken >> 16 == k) queue.add(c | (taken & 0xffffu));
+             });
+  uint8_t* const row = queue_order ? (uint8_t*)queue_order + ((size_t)i * kMaxDims + k) * 2u * b.max_chunks * (uint32_t)entry_bytes
+                                   : nullptr;
+  const uint32_t stages = s.ctype == THEMIS_COLL_ALL_REDUCE ? 2u * D : D;
+  const QuadResult r = simulate_quad<L, kQueueOrder != kNoQueueOrder>(
+      model, queue, model.cls0, runs ? stages * s.C : 0u, model.t_min, [&](uint32_t e, uint32_t entry) {
+        if (kQueueOrder == kShorts) ((uint16_t*)row)[e] = (uint16_t)entry;
+        else row[e] = (uint8_t)entry;
+      });
+  const bool done = runs && r.ok;
+  if (invalid || (exists && (done || !marked)))
+    quad_outputs<kQueueOrder>(b, i, done, !done && !invalid, r, t_done, row, entry_bytes, busy, call);
+  __syncthreads();
+  return exists && !done;
 }
 
 // As L, with registers for two wavefronts on a SIMD and no more: for batches that are all
@@ -483,6 +566,12 @@ template <typename L>
 struct TwoPerSimd : L {
   static constexpr uint32_t kWavesPerSimd = 2;
 };
+
+// Do the scenarios of a wavefront of lanes that are powers of two go with the others?
+__device__ __forceinline__ bool lanes_few(bool in_range, bool others) {
+  return __builtin_amdgcn_ballot_w64(others) != 0ull &&
+         __builtin_popcountll(__builtin_amdgcn_ballot_w64(in_range && !others)) <= 16;
+}
 
 template <typename L, int kQueueOrder, bool kBusy, bool kFix>
 __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(L::kWavesPerSimd)))
@@ -505,9 +594,12 @@ simulate_kernel(themis_batch_t b, const uint8_t* __restrict__ orders,
   // NPU counts that are not powers of two: four lanes each at the end, up to three
   // dimensions, else left to the follow-up kernel; with them the other scenarios
   // of the wavefront where those are few (one round of 16 is cheaper than the lanes' loop)
-  const bool few = __builtin_amdgcn_ballot_w64(exists && ok && !eligible) != 0ull &&
-                   __builtin_popcountll(__builtin_amdgcn_ballot_w64(eligible)) <= 16;
+  // (in_range, others: as the other wavefronts of the window see the scenario)
+  const bool in_range = exists && b.ndims[i] - 1u < (uint32_t)kMaxDims && s.C - 1u < b.max_chunks;
+  const bool others = in_range && other_counts(b, i, b.ndims[i]);
+  const bool few = lanes_few(in_range, others);
   const bool fast = eligible && !few;
+  const bool tables = in_range && b.ndims[i] < 4u && (others || few);
 
   // Queue orders of a wavefront whose 64 scenarios all exist are staged
   // transposed inside the wavefront's own block of the output (kStagedBytes)
@@ -707,22 +799,47 @@ simulate_kernel(themis_batch_t b, const uint8_t* __restrict__ orders,
     }
   }
   // (what ran in the lanes' loop and stalled there goes on to the generic path)
-  const bool tables = left && !fast && s.D < 4;
   if (left && !tables) mark_left_to_generic(t_done + i, hand_over);
   using L3 = LayoutQuad<L::kCap, 12u, 3u>;
   static_assert(QuadTable<L3, 3>::kBytes <= sizeof(lds_block), "the tables fit the lanes' block");
-  const uint64_t quads = __builtin_amdgcn_ballot_w64(tables);
-  if (quads != 0ull) {
-    __syncthreads();
-    quad_table_rounds<L3, 3, kQueueOrder>(b, orders, t_done, queue_order, entry_bytes, busy,
-                                          (uint64_t)blockIdx.x * kBlock, quads, false, lds_block, hand_over);
+  const uint64_t own = __builtin_amdgcn_ballot_w64(tables);
+  if (own != 0ull) {
+    // The wavefronts of a window that have nothing else share the turns of all of them.  (One
+    // whose lanes ran has staged queue orders in the rows of all its scenarios, so nobody
+    // else may write any of those; it takes its own.)
+    const uint64_t window = blockIdx.x / kWindowGroups, from = window * kWindow, first = (uint64_t)blockIdx.x * kBlock;
+    uint32_t sharing = 0u;
+    const QuadWindow shared(2u * (uint32_t)kMaxDims * b.max_chunks, lds_block, [&](uint32_t g) {
+      const uint64_t j = from + kBlock * g + threadIdx.x;
+      const bool there = j < b.n;
+      const WindowScenario w = window_scenario(b, there ? j : b.n - 1u);
+      const bool range = there && w.in_range, other = range && other_counts(b, j, w.D), few_here = lanes_few(range, other);
+      const bool member = range && few_here && w.D < 4u;
+      if (__builtin_amdgcn_ballot_w64(member) != 0ull) sharing |= 1u << g;
+      return member ? w.events : 0u;
+    });
+    const uint32_t of = max((uint32_t)__builtin_popcount(sharing), 1u);
+    const uint32_t me = (uint32_t)__builtin_popcount(sharing & ((1u << blockIdx.x % kWindowGroups) - 1u));
+    // (workgroups go to the XCDs in turn: not every window's longest to the same one)
+    uint32_t turn = (me + (uint32_t)window) % of;
+    QuadTurns alone(few ? 0ull : own, tables ? window_scenario(b, i).events : 0u);
+    while (few ? turn < shared.turns() : alone.left != 0ull) {
+      uint32_t which;
+      const bool there = few ? shared.take(turn, lds_block, which) : alone.take(which);
+      turn += of;
+      quad_table_turn<L3, 3, kQueueOrder>(b, orders, t_done, queue_order, entry_bytes, busy,
+                                          there ? (few ? from : first) + which : first, there, false, false, lds_block,
+                                          hand_over);
+    }
   }
 }
 
 // Four lanes per scenario (themis_quad.hpp).  kOthers: scenarios of up to three
-// dimensions whose NPU counts are not powers of two are taken here as well (and
-// with them the other ones of up to three dimensions in their wavefront), by
-// tables of their own; else, and on four dimensions, they are left marked.
+// dimensions whose NPU counts are not powers of two are taken here as well, by tables of
+// their own; else, and on four dimensions, they are left marked.
+// Where all scenarios of a window have the same length a wavefront takes 16 neighbours,
+// with others among them those of up to three dimensions by tables, whatever their
+// counts; else one turn of the window: of the others, or of the rest.
 template <typename L, int kQueueOrder, bool kFix, bool kOthers>
 __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(L::kWavesPerSimd)))
 simulate_quad_kernel(themis_batch_t b, const uint8_t* __restrict__ orders, double* __restrict__ t_done,
@@ -732,60 +849,103 @@ simulate_quad_kernel(themis_batch_t b, const uint8_t* __restrict__ orders, doubl
   constexpr uint32_t kLdsBytes = kOthers && QuadTable<L3, 3>::kBytes > QuadPow2<L, kFix>::kBytes ? QuadTable<L3, 3>::kBytes : QuadPow2<L, kFix>::kBytes;
   __shared__ uint64_t lds_block[(kLdsBytes + 7u) / 8u];
   const uint32_t k = threadIdx.x & 3u;
-  const uint64_t first = (uint64_t)block_index() * L::kQuads, at = first + (threadIdx.x >> 2);
+  const uint64_t block = block_index(), window = block / kWindowTurns, from = window * kWindow;
+  if (block * L::kQuads >= b.n) return;   // (in the grid's last row)
+  uint32_t lengths[kWindowGroups], longest = 0u, shortest_inv = 0u;
+#pragma unroll
+  for (uint32_t g = 0; g < kWindowGroups; ++g) {
+    const uint64_t j = from + kBlock * g + threadIdx.x;
+    const uint32_t events = window_scenario(b, j < b.n ? j : b.n - 1u).events;
+    lengths[g] = j < b.n ? events : 0u;
+    longest = max(longest, events);
+    shortest_inv = max(shortest_inv, ~events);
+  }
+  const bool ragged = uniform(quad_wave_max(longest) != ~quad_wave_max(shortest_inv));
   // a quad without a scenario stays: the wavefront leaves the event loop as a whole
-  const bool exists = at < b.n;
-  const uint64_t i = exists ? at : b.n - 1u;
-  const Scenario s = load_scenario(b, i);
-  const uint32_t D = (uint32_t)s.D;
-  const double S = b.size_bytes[i];
-  FastScenario fs;
-  const bool ok = s.valid && finite_positive(S) && exists;
-  const bool eligible = fast_eligible(s, S / (double)s.C, L::kCap, fs) && ok;
-  const bool others = kOthers && __builtin_amdgcn_ballot_w64(ok && !eligible && D < 4u) != 0ull;
-  const bool tables = others && ok && D < 4u;
-  // a few powers of two of four dimensions beside other counts go with those
-  const bool few = __builtin_popcountll(__builtin_amdgcn_ballot_w64(eligible && !tables)) <= 16 &&
-                   __builtin_amdgcn_ballot_w64(ok && !eligible && D == 4u) != 0ull;
-  const bool fast = eligible && !tables && !few;
-  if (!others || __builtin_amdgcn_ballot_w64(exists && !tables) != 0ull) {
-    QuadQueue<L> queue(lds_block);
-    uint32_t bad = 0u;
-    // (a lane takes the chunks that start on its own dimension)
-    quad_codes(b, orders, i, fast ? s.C : 0u,
-               [&](uint32_t code) {
-                 if (!quad_code_ok(code, D)) bad = 1u;
-                 return ((quad_row(D) + quad_order(stored_code(s, fs, code), D)) & 31u) << 9 |
-                        (fs.gather ? 1u << L::kPhaseBit : 0u) | (code & 3u) << 16;
-               },
-               [&](uint32_t c, uint32_t taken) {
-                 if (taken >> 16 == k) queue.add(c | (taken & 0xffffu));
-               });
-    const bool runs = fast && quad_sum(bad) == 0u;
-    if (!runs) queue.any = false;
-    const Pow2Model pow2(s, fs, b.intra_policy[i] == THEMIS_INTRA_SCF);
-    uint8_t* const row = queue_order ? (uint8_t*)queue_order + ((size_t)i * kMaxDims + k) * 2u * b.max_chunks * (uint32_t)entry_bytes
-                                     : nullptr;
-    const QuadResult r = simulate_quad<L, kQueueOrder != kNoQueueOrder>(
-        QuadPow2<L, kFix>(s, pow2, k, lds_block), queue, (uint32_t)(pow2.ranktab >> (4u * (fs.state0 & 15u))) & 15u,
-        runs ? (pow2.one_phase() ? D : 2u * D) * s.C : 0u, pow2.t_min(D),
-        [&](uint32_t e, uint32_t entry) {
-          if (kQueueOrder == kShorts) ((uint16_t*)row)[e] = (uint16_t)entry;
-          else row[e] = (uint8_t)entry;
-        });
-    const bool malformed = fast && !runs, done = runs && r.ok;
-    if (exists && !tables)
-      quad_outputs<kQueueOrder>(b, i, done, ok && !malformed && !done, r, t_done, row, entry_bytes, busy, hand_over);
+  uint64_t i = block * L::kQuads + (threadIdx.x >> 2);
+  bool exists = i < b.n, runs_rest = true;
+  uint32_t turn = 0u, turns_of_rest = 0u, blocks = 1u;
+  // (of the window; 0: not one of the others)
+  auto length_of_other = [&](uint32_t g) {
+    const uint64_t j = from + kBlock * g + threadIdx.x;
+    if (!kOthers || j >= b.n) return 0u;
+    const WindowScenario w = window_scenario(b, j);
+    return w.in_range && w.D < 4u && other_counts(b, j, w.D) ? w.events : 0u;
+  };
+  if (ragged) {
+    const uint64_t size = b.n - from < kWindow ? b.n - from : kWindow;
+    blocks = ((uint32_t)size + 15u) / 16u;
+    // (workgroups go to the XCDs in turn: not every window's longest to the same one)
+    turn = ((uint32_t)(block % kWindowTurns) + (uint32_t)window) % blocks;
+    const QuadWindow rest(2u * (uint32_t)kMaxDims * b.max_chunks, lds_block,
+                          [&](uint32_t g) { return length_of_other(g) != 0u ? 0u : lengths[g]; });
+    turns_of_rest = rest.turns();
+    uint32_t which;
+    exists = rest.take(turn, lds_block, which);
+    i = from + which;
+    runs_rest = turn < turns_of_rest;
+  }
+  if (!exists) i = b.n - 1u;
+  bool tables = false;
+  if (runs_rest) {
+    const Scenario s = load_scenario(b, i);
+    const uint32_t D = (uint32_t)s.D;
+    const double S = b.size_bytes[i];
+    FastScenario fs;
+    const bool ok = s.valid && finite_positive(S) && exists;
+    const bool eligible = fast_eligible(s, S / (double)s.C, L::kCap, fs) && ok;
+    const bool others = kOthers && !ragged && __builtin_amdgcn_ballot_w64(ok && !eligible && D < 4u) != 0ull;
+    tables = others && ok && D < 4u;
+    // a few powers of two of four dimensions beside other counts go with those
+    const bool few = __builtin_popcountll(__builtin_amdgcn_ballot_w64(eligible && !tables)) <= 16 &&
+                     __builtin_amdgcn_ballot_w64(ok && !eligible && D == 4u) != 0ull;
+    const bool fast = eligible && !tables && !few;
+    if (!others || __builtin_amdgcn_ballot_w64(exists && !tables) != 0ull) {
+      QuadQueue<L> queue(lds_block);
+      uint32_t bad = 0u;
+      // (a lane takes the chunks that start on its own dimension)
+      quad_codes(b, orders, i, fast ? s.C : 0u,
+                 [&](uint32_t code) {
+                   if (!quad_code_ok(code, D)) bad = 1u;
+                   return ((quad_row(D) + quad_order(stored_code(s, fs, code), D)) & 31u) << 9 |
+                          (fs.gather ? 1u << L::kPhaseBit : 0u) | (code & 3u) << 16;
+                 },
+                 [&](uint32_t c, uint32_t taken) {
+                   if (taken >> 16 == k) queue.add(c | (taken & 0xffffu));
+                 });
+      const bool runs = fast && quad_sum(bad) == 0u;
+      if (!runs) queue.any = false;
+      const Pow2Model pow2(s, fs, b.intra_policy[i] == THEMIS_INTRA_SCF);
+      uint8_t* const row = queue_order ? (uint8_t*)queue_order + ((size_t)i * kMaxDims + k) * 2u * b.max_chunks * (uint32_t)entry_bytes
+                                       : nullptr;
+      const QuadResult r = simulate_quad<L, kQueueOrder != kNoQueueOrder>(
+          QuadPow2<L, kFix>(s, pow2, k, lds_block), queue, (uint32_t)(pow2.ranktab >> (4u * (fs.state0 & 15u))) & 15u,
+          runs ? (pow2.one_phase() ? D : 2u * D) * s.C : 0u, pow2.t_min(D),
+          [&](uint32_t e, uint32_t entry) {
+            if (kQueueOrder == kShorts) ((uint16_t*)row)[e] = (uint16_t)entry;
+            else row[e] = (uint8_t)entry;
+          });
+      const bool malformed = fast && !runs, done = runs && r.ok;
+      if (exists && !tables)
+        quad_outputs<kQueueOrder>(b, i, done, ok && !malformed && !done, r, t_done, row, entry_bytes, busy, hand_over);
+    }
   }
   if constexpr (kOthers) {
-    if (others) {
-      // (one bit per quad, as if 16 lanes had a scenario each)
-      const uint64_t quads = __builtin_amdgcn_ballot_w64(tables && k == 0u);
-      const uint32_t j = threadIdx.x;
-      const uint64_t left = __builtin_amdgcn_ballot_w64(j < L::kQuads && ((quads >> (4u * (j & 15u))) & 1ull) != 0ull);
+    if (ragged) {
+      // (the two kinds have a turn more than there are workgroups, or not)
+      const bool one_more = turn == 0u && runs_rest;
+      if (!runs_rest || one_more) {
+        const QuadWindow turns(2u * (uint32_t)kMaxDims * b.max_chunks, lds_block, length_of_other);
+        uint32_t which;
+        const bool there = turns.take(runs_rest ? blocks - turns_of_rest : turn - turns_of_rest, lds_block, which);
+        if (__builtin_amdgcn_ballot_w64(there) != 0ull)
+          quad_table_turn<L3, 3, kQueueOrder>(b, orders, t_done, queue_order, entry_bytes, busy, from + which, there, false,
+                                              true, lds_block, hand_over);
+      }
+    } else if (__builtin_amdgcn_ballot_w64(tables) != 0ull) {
       __syncthreads();
-      quad_table_rounds<L3, 3, kQueueOrder>(b, orders, t_done, queue_order, entry_bytes, busy, first, left, false,
-                                            lds_block, hand_over);
+      quad_table_turn<L3, 3, kQueueOrder>(b, orders, t_done, queue_order, entry_bytes, busy, i, tables, false, false,
+                                          lds_block, hand_over);
     }
   }
 }
@@ -881,36 +1041,28 @@ constexpr size_t generic_lds_bytes(uint32_t lds_slots) {
 }
 
 template <uint32_t kLdsSlots>
-__device__ __forceinline__ void simulate_generic_pass(
+__device__ __forceinline__ void simulate_generic_lane(
     const themis_batch_t& b, const uint8_t* __restrict__ orders, double* __restrict__ t_done,
-    void* __restrict__ queue_order, int entry_bytes, double* __restrict__ busy, Workspace w,
-    void* lds_block, uint32_t group) {
-  if (kLdsSlots) w = carve_workspace(lds_block, kBlock, kLdsSlots);
+    void* __restrict__ queue_order, int entry_bytes, double* __restrict__ busy, const Workspace& w, uint64_t i) {
   const TraceView tv = trace_view(b);
-  // a few workgroups walk all groups of scenarios: most have nothing marked
-  const uint64_t groups = (b.n + group - 1) / group;
-  for (uint64_t grp = blockIdx.x; grp < groups; grp += gridDim.x) {
-    const uint64_t i = grp * group + threadIdx.x;
-    if (threadIdx.x >= group || i >= b.n || !is_left_to_generic(t_done[i])) continue;
-    const uint64_t col = kLdsSlots ? threadIdx.x : i;
-    Scenario s = load_scenario(b, i);
-    const bool scf = b.intra_policy[i] == THEMIS_INTRA_SCF;
-    uint32_t Q;
-    collectives_ok(b, tv, i, Q);  // marked scenarios passed this check already
-    SimOut out;
-    out.t_done = t_done + i;
-    out.busy = busy ? busy + i : nullptr;
-    out.busy_stride = b.n;
-    out.entry_bytes = entry_bytes;
-    out.slots = tv.slots;
-    out.queue_order = queue_order
-        ? (void*)((uint8_t*)queue_order + (size_t)i * kMaxDims * 2u * tv.slots * entry_bytes)
-        : nullptr;
-    // beyond the LDS variant's chunk count the arrays need the caller's workspace
-    if (!kLdsSlots && !w.meta) { write_invalid(out); continue; }
-    simulate_generic_scenario<(kLdsSlots > 0)>(b, tv, s, Q, i, col, orders + (size_t)i * tv.slots,
-                                               scf, w, out);
-  }
+  const uint64_t col = kLdsSlots ? threadIdx.x : i;
+  Scenario s = load_scenario(b, i);
+  const bool scf = b.intra_policy[i] == THEMIS_INTRA_SCF;
+  uint32_t Q;
+  collectives_ok(b, tv, i, Q);  // marked scenarios passed this check already
+  SimOut out;
+  out.t_done = t_done + i;
+  out.busy = busy ? busy + i : nullptr;
+  out.busy_stride = b.n;
+  out.entry_bytes = entry_bytes;
+  out.slots = tv.slots;
+  out.queue_order = queue_order
+      ? (void*)((uint8_t*)queue_order + (size_t)i * kMaxDims * 2u * tv.slots * entry_bytes)
+      : nullptr;
+  // beyond the LDS variant's chunk count the arrays need the caller's workspace
+  if (!kLdsSlots && !w.meta) { write_invalid(out); return; }
+  simulate_generic_scenario<(kLdsSlots > 0)>(b, tv, s, Q, i, col, orders + (size_t)i * tv.slots,
+                                             scf, w, out);
 }
 
 template <uint32_t kLdsSlots>
@@ -921,20 +1073,29 @@ simulate_generic_kernel(themis_batch_t b, const uint8_t* __restrict__ orders,
                         unsigned long long call) {
   __shared__ double lds_block[kLdsSlots ? generic_lds_bytes(kLdsSlots) / sizeof(double) : 1u];
   if (nothing_marked(call)) return;
-  simulate_generic_pass<kLdsSlots>(b, orders, t_done, queue_order, entry_bytes, busy, w, lds_block, kBlock);
+  if (kLdsSlots) w = carve_workspace(lds_block, kBlock, kLdsSlots);
+  // a few workgroups walk all groups of scenarios: most have nothing marked
+  for (uint64_t i = (uint64_t)blockIdx.x * kBlock + threadIdx.x; i < b.n; i += (uint64_t)gridDim.x * kBlock)
+    if (is_left_to_generic(t_done[i]))
+      simulate_generic_lane<kLdsSlots>(b, orders, t_done, queue_order, entry_bytes, busy, w, i);
 }
 
 constexpr size_t max_bytes(size_t a, size_t b) { return a > b ? a : b; }
 constexpr uint32_t kNoGeneric = 0xffffffffu;
 
-// Everything that follows the LDS kernel of themis_simulate_batch, in one
-// launch: what is marked in quads on tables of its own, then the generic pass (kGeneric: its chunk slots in
-// LDS, 0: arrays in the workspace, kNoGeneric: none).  A workgroup walks the same
-// groups of `group` scenarios in every pass, so what one pass leaves marked is
-// seen by the next without any ordering between workgroups; the passes share one
-// LDS block of the largest size among them.
+// Everything that follows the LDS kernel of themis_simulate_batch, in one launch: what
+// is marked in quads on tables of its own, then by the generic loop (kGeneric: its
+// chunk slots in LDS, 0: arrays in the workspace, kNoGeneric: none).  An item of the
+// workgroups' work is a turn of a window of the scenarios of four dimensions, and beyond 64
+// chunks of the others (up to 64 the kernels before have taken those whose counts are
+// not powers of two, so few are left: by `group` neighbours).  A scenario belongs to one
+// item, whatever is marked, so what one workgroup finds does not depend on the others;
+// all that is left of a window's marks is looked at first.
 // (On four dimensions the tables of 24 orders and up to 48 sizes per dimension
 // take 37 KiB per wavefront, four wavefronts per CU.)
+__host__ __device__ inline uint64_t follow_up_turns(uint64_t n, uint32_t cap) {
+  return (n + kWindow - 1u) / kWindow * kWindowTurns * (cap > 64u ? 2u : 1u);
+}
 template <int kQueueOrder, uint32_t kCap, uint32_t kGeneric>
 __global__ void __launch_bounds__(kBlock)
 simulate_follow_up_kernel(themis_batch_t b, const uint8_t* __restrict__ orders,
@@ -947,23 +1108,57 @@ simulate_follow_up_kernel(themis_batch_t b, const uint8_t* __restrict__ orders,
   static_assert(QuadTable<L3, 3>::kBytes <= QuadTable<L4, 4>::kBytes, "one block for both");
   __shared__ double lds_block[(kBytes_ + 7u) / 8u];
   if (nothing_marked(call)) return;
-  const uint64_t groups = (b.n + group - 1u) / group;
-  for (uint64_t grp = blockIdx.x; grp < groups; grp += gridDim.x) {
-    const uint64_t first = grp * group, i = first + threadIdx.x;
-    const bool marked = threadIdx.x < group && i < b.n && is_left_to_generic(t_done[i]);
-    const uint32_t D = marked ? b.ndims[i] : 0u;
-    const uint64_t four = __builtin_amdgcn_ballot_w64(D == 4u);
-    if (four != 0ull)
-      quad_table_rounds<L4, 4, kQueueOrder>(b, orders, t_done, queue_order, entry_bytes, busy, first, four, true,
-                                            lds_block, call);
-    const uint64_t three = __builtin_amdgcn_ballot_w64(D - 1u < 3u);
-    if (three != 0ull)
-      quad_table_rounds<L3, 3, kQueueOrder>(b, orders, t_done, queue_order, entry_bytes, busy, first, three, true,
-                                            lds_block, call);
-  }
-  if constexpr (kGeneric != kNoGeneric) {
-    __syncthreads();
-    simulate_generic_pass<kGeneric>(b, orders, t_done, queue_order, entry_bytes, busy, w, lds_block, group);
+  constexpr uint32_t kLdsSlots = kGeneric == kNoGeneric ? 0u : kGeneric;
+  if (kLdsSlots) w = carve_workspace(lds_block, kBlock, kLdsSlots);
+  const uint32_t lane = threadIdx.x;
+  const uint64_t windows = (b.n + kWindow - 1u) / kWindow, turns = follow_up_turns(b.n, kCap);
+  const uint64_t items = turns + (kCap > 64u ? 0u : (b.n + group - 1u) / group);
+  for (uint64_t item = blockIdx.x; item < items; item += gridDim.x) {
+    uint64_t i;      // of the lane: what the generic loop is to look at
+    bool left;
+    if (item < turns) {
+      const bool four = item < windows * kWindowTurns;
+      const uint64_t from = item % windows * kWindow;
+      const uint32_t turn = (uint32_t)(item / windows) % kWindowTurns;
+      bool marked = false;
+      uint32_t length[kWindowGroups], members = 0u;
+#pragma unroll
+      for (uint32_t g = 0; g < kWindowGroups; ++g) {
+        const uint64_t j = from + kBlock * g + lane;
+        const WindowScenario v = window_scenario(b, j < b.n ? j : b.n - 1u);
+        length[g] = j < b.n && v.in_range && (v.D == 4u) == four ? v.events : 0u;
+        marked = marked || (length[g] != 0u && is_left_to_generic(t_done[j]));
+        members += (uint32_t)__builtin_popcountll(__builtin_amdgcn_ballot_w64(length[g] != 0u));
+      }
+      if (16u * turn >= members || __builtin_amdgcn_ballot_w64(marked) == 0ull) continue;
+      const QuadWindow order(2u * (uint32_t)kMaxDims * b.max_chunks, lds_block, [&](uint32_t g) { return length[g]; });
+      uint32_t which;
+      const bool there = order.take(turn, lds_block, which);
+      i = from + which;
+      const bool exists = there && is_left_to_generic(t_done[i]);
+      if (__builtin_amdgcn_ballot_w64(exists) == 0ull) continue;
+      left = four ? quad_table_turn<L4, 4, kQueueOrder>(b, orders, t_done, queue_order, entry_bytes, busy, i, exists, true,
+                                                        false, lds_block, call)
+                  : quad_table_turn<L3, 3, kQueueOrder>(b, orders, t_done, queue_order, entry_bytes, busy, i, exists, true,
+                                                        false, lds_block, call);
+      left = left && (lane & 3u) == 0u;
+    } else {
+      const uint64_t first = (item - turns) * group;
+      i = first + lane;
+      left = lane < group && i < b.n && is_left_to_generic(t_done[i]) && b.ndims[i] < 4u;
+      for (QuadTurns rounds(__builtin_amdgcn_ballot_w64(left), 0u); rounds.left != 0ull;) {
+        uint32_t which;
+        const bool exists = rounds.take(which);
+        quad_table_turn<L3, 3, kQueueOrder>(b, orders, t_done, queue_order, entry_bytes, busy,
+                                            exists ? first + which : first, exists, true, false, lds_block, call);
+      }
+      left = left && is_left_to_generic(t_done[i]);
+    }
+    if (kGeneric != kNoGeneric) {
+      __syncthreads();
+      if (left) simulate_generic_lane<kLdsSlots>(b, orders, t_done, queue_order, entry_bytes, busy, w, i);
+      __syncthreads();
+    }
   }
 }
 
@@ -2885,9 +3080,8 @@ static unsigned blocks_for(uint64_t items) { return (unsigned)((items + kBlock -
 // evaluations): enough to fill the device, no more.
 static unsigned follow_up_blocks(uint64_t items) {
   const unsigned cus = compute_units();
-  const unsigned cap = 8u * (cus ? cus : 256u);
-  const unsigned all = blocks_for(items);
-  return all < cap ? all : cap;
+  const uint64_t cap = 8u * (cus ? cus : 256u), all = (items + kBlock - 1u) / kBlock;
+  return (unsigned)(all < cap ? all : cap);
 }
 
 // Which mapping themis_sweep's LDS kernel uses for a layout capacity: beyond 64
@@ -3220,7 +3414,7 @@ static int simulate_batch_impl(const themis_batch_t* batch, const uint8_t* order
   }
   const Workspace ws = have_ws ? w : Workspace{};
   const uint32_t group = follow_up_group(batch->n);
-  const unsigned fb = follow_up_blocks((batch->n + group - 1u) / group * kBlock);
+  const unsigned fb = follow_up_blocks((follow_up_turns(batch->n, cap) + (batch->n + group - 1u) / group) * kBlock);
 #define THEMIS_FOLLOW_UP(MODE, CAP, G) \
   go(simulate_follow_up_kernel<MODE, CAP, G>, fb, kBlock, *batch, orders, t_done, queue_order, \
      entry_bytes, busy, ws, group, call)

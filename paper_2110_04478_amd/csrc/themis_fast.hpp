@@ -572,6 +572,17 @@ struct Pow2Model {
   }
 };
 
+// An event loop starts kWords * 4 bytes behind a line of the instruction cache whatever
+// comes before it, which otherwise moves it with every change elsewhere.  The ring loop
+// (themis_ring.hpp; words, us, period 8): 1,048,576 4-D scenarios with queue orders 2 2,272, 0
+// 2,252, 4 2,241, 6 2,237; sweep of 65,536 networks, 8 thresholds, 6 1,333, 4 1,323, 0 1,315,
+// 2 1,311; searches of 16,384 2 477, 0 474, 4 470.  simulate_fast: 220,953 scenarios of 11
+// chunks with queue orders 3 213, 6 212, 5 210, 0 206, without 6 191, 0 188.
+template <uint32_t kWords>
+__device__ __forceinline__ void loop_place() {
+  asm volatile(".p2align 6\n\t.rept %0\n\ts_nop 0\n\t.endr" :: "n"(kWords));
+}
+
 // Chunk dwords must already be initialised with L::init_chunk().
 // kFix: the batch carries fixed per-stage delays (a compile-time switch: even a
 // wave-uniform run-time branch around the four-way selection cost 4 % on
@@ -631,6 +642,7 @@ __device__ __forceinline__ FastResult simulate_fast(const Scenario& s, const Mod
   // the wavefront go on with their own events meanwhile instead of waiting
   // through a second round of starts.
   const uint32_t max_steps = 4u * D * C + 16u;
+  loop_place<0u>();
   for (uint32_t step = 0; step <= max_steps; ++step) {
     // a7: an idle dimension with waiting chunks starts its first one
     if (const uint32_t need = idle & work) {

@@ -82,6 +82,31 @@ def test_wavefronts_of_one_policy_and_of_both(gpu, oracle, max_chunks):
             gpu.themis_set_sweep_mapping(gpu.MAPPING_AUTO)
 
 
+@pytest.mark.parametrize("n", [15, 17, 511, 512, 513, 1040, 2047])
+@pytest.mark.parametrize("max_chunks", [24, 64, 90])
+@pytest.mark.parametrize("every", [1, 2, 5, 10 ** 9])
+def test_ragged_scenarios_in_turns_of_a_window(gpu, oracle, n, max_chunks, every):
+    """512 neighbours are taken by length, 16 at a time; powers of two, and others all or
+    every so many (up to three dimensions in the first kernel up to 64 chunks, else in the
+    follow-up), with invalid scenarios of every kind among them."""
+    b = _mixed_counts(n, 1000 + n, every, max_chunks=max_chunks)
+    b = _with_collective_types(b, 21)
+    b.bw[0, 3::41] = -1.0
+    b.size_bytes[5::43] = np.nan
+    b.chunks[7::47] = 0
+    b.chunks[9::53] = max_chunks + 1
+    b.ndims[11::59] = 5
+    for quads in (False, True):
+        gpu.themis_set_batch_mapping(gpu.MAPPING_LANE)
+        gpu.themis_set_sweep_mapping(gpu.MAPPING_QUAD if quads else gpu.MAPPING_LANE)
+        try:
+            check_batch(gpu, oracle, b)
+            check_batch(gpu, oracle, b, queue=False, workspace=max_chunks > 64)
+        finally:
+            gpu.themis_set_batch_mapping(gpu.MAPPING_AUTO)
+            gpu.themis_set_sweep_mapping(gpu.MAPPING_AUTO)
+
+
 @pytest.mark.parametrize("n,chunks", [(16385, 2), (32769, 2), (65536, 2), (65537, 2), (65600, 3), (17000, 70),
                                       (66001, 20), (131073, 1), (131100, 7), (131201, 16), (131300, 17), (131400, 22)])
 def test_batch_sizes_around_the_lines(gpu, oracle, n, chunks):
