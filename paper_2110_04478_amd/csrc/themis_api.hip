@@ -302,7 +302,7 @@ plan_kernel(themis_batch_t b, uint8_t* __restrict__ orders, double* __restrict__
       chunks = s.C;
       if (!left && wave == 0u) {
         uint32_t acc = 0;
-        plan_fast<true>(s, fs, b.inter_policy[i] != THEMIS_INTER_BASELINE, rel, thr, load, [&](uint32_t c, uint32_t code) {
+        plan_fast(s, fs, b.inter_policy[i] != THEMIS_INTER_BASELINE, rel, thr, load, [&](uint32_t c, uint32_t code) {
           if (words) {
             acc |= code << (8u * (c & 3u));
             if ((c & 3u) == 3u) { ((uint32_t*)r)[c >> 2] = acc; acc = 0; }
@@ -1613,7 +1613,7 @@ sweep_plans_kernel(themis_batch_t b, int n_thr, uint32_t width, const double* __
       double load[kMaxDims];
       FastScenario fs;
       if (fast_eligible(s, chunk, THEMIS_MAX_CHUNKS, fs)) {
-        plan_fast<true>(s, fs, true, rel, th, load, compare, plan_orders);
+        plan_fast(s, fs, true, rel, th, load, compare, plan_orders);
       } else {
 #pragma unroll
         for (int k = 0; k < kMaxDims; ++k) load[k] = (k < s.D) ? tracker_start(s, k) : inf64();
@@ -1766,7 +1766,13 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(L::
 sweep_kernel(themis_batch_t b, int n_thr, const double* __restrict__ thr, int thr_per_scenario,
              unsigned policy_mask, int n_pol, double* __restrict__ t_done,
              unsigned long long hand_over, SweepJobs jobs) {
-  __shared__ uint32_t lds_block[L::kLaneWords * kBlock];
+  __shared__ __attribute__((aligned(16))) uint32_t lds_block[L::kLaneWords * kBlock];
+  // the planner's order table, in the place of the lists
+  uint32_t* const plan_orders = lds_block + L::kPlanTableAt / 4u;
+  plan_order_entry(threadIdx.x, plan_orders + kPlanOrderWords * threadIdx.x);
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
   // A wavefront takes 64 consecutive scenarios under one threshold and one
   // scheduler: its lanes read consecutive inputs, and on a batch that keeps to
   // one network they all take the same path through the event loop.
@@ -1799,7 +1805,9 @@ sweep_kernel(themis_batch_t b, int n_thr, const double* __restrict__ thr, int th
     const LaneLds lds = lane_lds<L>(lds_block);
     double load[kMaxDims];
     plan_fast(s, fs, it.themis_on, rel, it.th, load,
-              [&](uint32_t c, uint32_t code) { L::init_chunk(lds, c, code, 0u); });
+              [&](uint32_t c, uint32_t code) { L::init_chunk(lds, c, code, 0u); }, plan_orders);
+    // (every lane is through with the table before a list is in its place)
+    __builtin_amdgcn_wave_barrier();
     FastOut fo;
     fo.queue_order = nullptr;
     fo.slots = b.max_chunks;

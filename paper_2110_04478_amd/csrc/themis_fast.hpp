@@ -101,6 +101,8 @@ struct LayoutByte {
   // rounded up): the kernels ask for a register budget that does not cap it lower
   static constexpr uint32_t kWavesPerSimd = (160u * 1024u / (kLaneWords * 256u) + 3u) / 4u;
   static constexpr uint32_t kEnd = 0xffu;
+  static constexpr uint32_t kPlanTableAt = kChunks * 256u;   // (room for a planner's table before the lists are in use)
+  static_assert((kLaneWords - kChunks) * 256u >= 2048u, "kPlanOrders * kPlanOrderWords dwords");
   using Link = uint8_t;               // width of a chunk id in LDS
   using Classes = Classes16;
   using Ids = Pack4<uint32_t, 8>;     // per dimension the operation count (up to 2 * kChunks)
@@ -253,99 +255,76 @@ __device__ __forceinline__ void plan_order_entry(uint32_t outcome, uint32_t* ent
   entry[5] = entry[6] = entry[7] = 0u;
 }
 
-// kTable: orders points to kPlanOrders entries of plan_order_entry() in LDS
-// (16-byte aligned);
-// the order and the sizes then come from one table read instead of the
-// comparisons' arithmetic (the results are the same).
-template <bool kTable = false, typename Emit>
+// Minimum of two doubles in one instruction (fmin() would first canonicalise
+// both operands); of a quiet NaN and a number it returns the number.  And the maximum.
+__device__ __forceinline__ double min_f64(double a, double b) {
+  double r;
+  asm("v_min_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+  return r;
+}
+__device__ __forceinline__ double max_f64(double a, double b) {
+  double r;
+  asm("v_max_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+  return r;
+}
+
+// orders: kPlanOrders entries of plan_order_entry() in LDS (16-byte aligned).
+// What bounds it is vector issue, on few wavefronts the chain of a chunk; 55 vector
+// instructions a chunk.  (106 with a threshold, a size and a doubling chosen by selects; planner
+// and simulation of 1,048,576 4-D scenarios 2,246 -> 2,205 us, of 20,001 with 250 chunks 820 ->
+// 793, sweep of 65,536 networks of 64 chunks, 8 thresholds x 3 schedulers, 1,311 -> 1,289.)
+template <typename Emit>
 __device__ __forceinline__ void plan_fast(const Scenario& s, const FastScenario& fs, bool themis,
                                           bool rel, double thr, double (&load)[kMaxDims],
-                                          Emit emit, const uint32_t* orders = nullptr) {
+                                          Emit emit, const uint32_t* orders) {
   const int D = s.D;
-  uint32_t e[kMaxDims];
-  double coef[kMaxDims];
+  double coef[kMaxDims], below[kMaxDims];
 #pragma unroll
   for (int k = 0; k < kMaxDims; ++k) {
-    e[k] = (fs.epack >> (8 * k)) & 0xffu;
-    coef[k] = (k < D) ? s.coef[k] : 0.0;   // unused dimensions: zero time, load stays +inf
-    load[k] = (k < D) ? tracker_start(s, k) : inf64();  // tracker starts at A_K
+    const uint32_t e = (fs.epack >> (8 * k)) & 0xffu;
+    coef[k] = (k < D) ? s.coef[k] : 0.0;
+    load[k] = (k < D) ? tracker_start(s, k) : nan64();  // tracker starts at A_K; unused: no comparison holds
+    // the threshold where this dimension is the least loaded: of a whole-chunk stage there (an
+    // All-Gather moves the grown size chunk * P)
+    below[k] = rel ? thr * ((fs.gather ? scale_up(fs.chunk, e) : fs.chunk) * coef[k]) : thr;
   }
+  const double times = s.ctype == THEMIS_COLL_ALL_REDUCE ? 2.0 : 1.0;
   const uint32_t field_mask = (1u << (2 * D)) - 1u;
+  const int high = __double2hiint(fs.base), low = __double2loint(fs.base);
+  int exponent = -(1 << 20);
+  asm volatile("" : "+s"(exponent));   // (a multiply-add, not a shift and a subtraction)
   for (uint32_t c = 0; c < s.C; ++c) {
-    // least / most loaded dimension, ties to the lower index
-    double lo = load[0], hi = load[0], cmin = coef[0];
-    uint32_t emin = e[0];
+    // after<a><b> (a < b): does a come after b?  Stable ascending sort: only when a's
+    // load is strictly larger.
+    const bool after01 = load[0] > load[1], after02 = load[0] > load[2], after03 = load[0] > load[3];
+    const bool after12 = load[1] > load[2], after13 = load[1] > load[3], after23 = load[2] > load[3];
+    const double lo = min_f64(min_f64(load[0], load[1]), min_f64(load[2], load[3]));
+    const double hi = max_f64(max_f64(load[0], load[1]), max_f64(load[2], load[3]));
+    const double gap = hi - lo;
+    // (asked of the least loaded dimension, ties to the lower index)
+    const bool within0 = gap < below[0], within1 = gap < below[1], within2 = gap < below[2], within3 = gap < below[3];
+    const bool keeps = (within0 && !after01 && !after02 && !after03) || (within1 && after01 && !after12 && !after13) ||
+                       (within2 && after02 && after12 && !after23) || (within3 && after03 && after13 && after23);
+    uint32_t outcome = after23 ? 1u : 0u;   // (one add with carry each)
+    outcome = outcome + outcome + (after13 ? 1u : 0u);
+    outcome = outcome + outcome + (after12 ? 1u : 0u);
+    outcome = outcome + outcome + (after03 ? 1u : 0u);
+    outcome = outcome + outcome + (after02 ? 1u : 0u);
+    outcome = outcome + outcome + (after01 ? 1u : 0u);
+    const bool sorts = themis && !keeps;
+    const uint32_t* entry = orders + kPlanOrderWords * (sorts ? outcome : 0u);
+    const uint4 before = *(const uint4*)entry;
+    uint32_t code = entry[4] & field_mask;
+    // The resident size at the stage on k: the exponents of the dimensions before it off
+    // the whole one.  (An All-Gather visits them in the reverse order and moves the grown
+    // size: E(after k) + e_k = etot - E(before k), off the base chunk * 2^etot.)
+    if (fs.gather) code = reverse_code(code, D);
+    const uint32_t of[kMaxDims] = {before.x, before.y, before.z, before.w};
 #pragma unroll
-    for (int k = 1; k < kMaxDims; ++k) {
-      bool used = k < D;
-      bool less = used && load[k] < lo;
-      lo = less ? load[k] : lo;
-      cmin = less ? coef[k] : cmin;
-      emin = less ? e[k] : emin;
-      hi = (used && load[k] > hi) ? load[k] : hi;
-    }
-    // a whole-chunk stage on the least-loaded dimension: an All-Gather moves
-    // the grown size chunk * P
-    const double whole = fs.gather ? scale_up(fs.chunk, emin) : fs.chunk;
-    double t = rel ? thr * (whole * cmin) : thr;
-    bool sort = themis && !((hi - lo) < t);
-    // after[a][b] (a < b): does a come after b in the chosen order?
-    // stable ascending sort: only when a's load is strictly larger.
-    bool after01 = sort && load[0] > load[1], after02 = sort && load[0] > load[2];
-    bool after03 = sort && load[0] > load[3], after12 = sort && load[1] > load[2];
-    bool after13 = sort && load[1] > load[3], after23 = sort && load[2] > load[3];
-    uint32_t code, E0, E1, E2, E3;
-    if (kTable) {
-      const uint32_t outcome = (after01 ? 1u : 0u) | (after02 ? 2u : 0u) | (after03 ? 4u : 0u) |
-                               (after12 ? 8u : 0u) | (after13 ? 16u : 0u) | (after23 ? 32u : 0u);
-      const uint32_t* entry = orders + kPlanOrderWords * outcome;
-      const uint4 before = *(const uint4*)entry;
-      code = entry[4] & field_mask;
-      E0 = __builtin_amdgcn_udot4(before.x, fs.epack, 0u, false);
-      E1 = __builtin_amdgcn_udot4(before.y, fs.epack, 0u, false);
-      E2 = __builtin_amdgcn_udot4(before.z, fs.epack, 0u, false);
-      E3 = __builtin_amdgcn_udot4(before.w, fs.epack, 0u, false);
-    } else {
-      // before[j][k]: j precedes k
-      const bool b10 = after01, b20 = after02, b30 = after03;
-      const bool b01 = !after01, b21 = after12, b31 = after13;
-      const bool b02 = !after02, b12 = !after12, b32 = after23;
-      const bool b03 = !after03, b13 = !after13, b23 = !after23;
-      uint32_t r1 = (uint32_t)b01 + b21 + b31;
-      uint32_t r2 = (uint32_t)b02 + b12 + b32, r3 = (uint32_t)b03 + b13 + b23;
-      code = ((1u << (2 * r1)) | (2u << (2 * r2)) | (3u << (2 * r3))) & field_mask;
-      // resident size before the Reduce-Scatter on k: chunk / prod of P_j, j before k
-      E0 = (b10 ? e[1] : 0u) + (b20 ? e[2] : 0u) + (b30 ? e[3] : 0u);
-      E1 = (b01 ? e[0] : 0u) + (b21 ? e[2] : 0u) + (b31 ? e[3] : 0u);
-      E2 = (b02 ? e[0] : 0u) + (b12 ? e[1] : 0u) + (b32 ? e[3] : 0u);
-      E3 = (b03 ? e[0] : 0u) + (b13 ? e[1] : 0u) + (b23 ? e[2] : 0u);
-    }
-    double t0, t1, t2, t3;
-    if (fs.gather) {
-      // the All-Gather visits the dimensions in the reverse order: the ones
-      // after k in the ascending order are gathered before it, and its stage
-      // moves the size grown by P_k as well:  E(after k) + e_k = etot - E(before k)
-      code = reverse_code(code, D);
-      t0 = scale_up(fs.chunk, fs.etot - E0) * coef[0];
-      t1 = scale_up(fs.chunk, fs.etot - E1) * coef[1];
-      t2 = scale_up(fs.chunk, fs.etot - E2) * coef[2];
-      t3 = scale_up(fs.chunk, fs.etot - E3) * coef[3];
-    } else {
-      t0 = scale_down(fs.chunk, E0) * coef[0];
-      t1 = scale_down(fs.chunk, E1) * coef[1];
-      t2 = scale_down(fs.chunk, E2) * coef[2];
-      t3 = scale_down(fs.chunk, E3) * coef[3];
-    }
-    if (s.ctype == THEMIS_COLL_ALL_REDUCE) {
-      load[0] = load[0] + (t0 + t0);
-      load[1] = load[1] + (t1 + t1);
-      load[2] = load[2] + (t2 + t2);
-      load[3] = load[3] + (t3 + t3);
-    } else {
-      load[0] = load[0] + t0;
-      load[1] = load[1] + t1;
-      load[2] = load[2] + t2;
-      load[3] = load[3] + t3;
+    for (int k = 0; k < kMaxDims; ++k) {
+      const int e = (int)__builtin_amdgcn_udot4(of[k], fs.epack, 0u, false);
+      const double t = __hiloint2double(__mul24(e, exponent) + high, low) * coef[k];
+      load[k] = __builtin_fma(times, t, load[k]);   // (t + t is exact)
     }
     emit(c, code);
   }
@@ -387,14 +366,6 @@ __device__ __forceinline__ uint64_t build_rank_table(uint32_t epack, bool scf) {
     tab |= (uint64_t)r << (4 * m);
   }
   return tab;
-}
-
-// Minimum of two doubles in one instruction (fmin() would first canonicalise
-// both operands); of a quiet NaN and a number it returns the number.
-__device__ __forceinline__ double min_f64(double a, double b) {
-  double r;
-  asm("v_min_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
-  return r;
 }
 
 // Dimension k (0..3, differing from lane to lane) starts a stage at `now`:

@@ -120,13 +120,6 @@ __device__ __forceinline__ uint32_t quad_wave_max(uint32_t v) {
   for (int off = 32; off > 0; off >>= 1) v = max(v, (uint32_t)__shfl_xor((int)v, off));
   return v;
 }
-// The later of two doubles; of a quiet NaN and a number the number.
-__device__ __forceinline__ double max_f64(double a, double b) {
-  double r;
-  asm("v_max_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
-  return r;
-}
-
 // Place of an order code among the orders of D dimensions (lexicographic).
 __device__ __forceinline__ uint32_t quad_order(uint32_t code, uint32_t D) {
   const uint32_t r = ring_order_rank(code, D);

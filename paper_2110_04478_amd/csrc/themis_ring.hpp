@@ -56,6 +56,7 @@ struct LayoutRing {
   static constexpr uint32_t kTableBytes = 24u * 8u * 2u;  // the wavefront's stage table (ring_loop)
   static_assert(kLaneWords * 256u >= kRecBytes + kTailBytes + kTableBytes, "block holds records, tails and table");
   static constexpr uint32_t kWavesPerSimd = 3;
+  static constexpr uint32_t kPlanTableAt = kRecBytes;   // (room for a planner's table before the lists are in use)
   using Ids = Pack4<uint32_t, 8>;
   static __device__ __forceinline__ uint32_t lane_term_rec(uint32_t lane) {
     return (lane & 31u) * 4u + (lane >> 5) * 2u;
