@@ -135,27 +135,29 @@ struct QuadTurns {
 // scenarios of any NPU counts, planner and both simulation kernels: 16 out of 64 neighbours
 // 1,095 us, out of 512 656).  Every workgroup that takes turns of a window finds the order by itself,
 // from the inputs alone, so nothing is passed between them: lengths in 64 buckets, inside
-// of a bucket as they come.
+// of a bucket as they come.  (The policies apart, each with its event loop, 32 buckets either:
+// no gain, the longest chain bounds it, and 680 us of the above for 642.)
 constexpr uint32_t kWindow = 512u, kWindowGroups = kWindow / kBlock, kWindowTurns = kWindow / 16u;
+constexpr uint32_t kWindowLds = 2u * 64u * kWindowGroups + 32u;
 struct QuadWindow {
   uint32_t rank[kWindowGroups];   // of the scenarios of the lane, one in each 64 (all-ones: not among them)
   uint32_t total;
-  // length(g): that of scenario 64 * g + lane of the window, 0: not among them; most: the
-  // largest there can be.  All lanes; lds: 320 bytes.
-  template <typename Length>
-  __device__ __forceinline__ QuadWindow(uint32_t most, void* lds, Length length) {
-    uint32_t* const count = (uint32_t*)lds;
+  // lengths[g]: that of scenario 64 * g + lane of the window, 0: not among them; most: the
+  // largest there can be.  All lanes; lds: kWindowLds bytes.
+  __device__ __forceinline__ QuadWindow(uint32_t most, void* lds, const uint32_t (&lengths)[kWindowGroups]) {
+    uint16_t* const count = (uint16_t*)lds;   // of the scenarios of each 64 in each bucket, then how many come before
     const uint32_t lane = threadIdx.x & 63u, bits = 32u - (uint32_t)__clz((int)(most | 1u));
     const uint32_t shift = bits > 6u ? bits - 6u : 0u;
     __syncthreads();
-    count[lane] = 0u;
+#pragma unroll
+    for (uint32_t g = 0; g < kWindowGroups; ++g) count[64u * g + lane] = 0u;
     __syncthreads();
     uint32_t bucket[kWindowGroups];
 #pragma unroll
     for (uint32_t g = 0; g < kWindowGroups; ++g) {
-      const uint32_t events = length(g);
-      bucket[g] = 63u - min(events >> shift, 63u);
-      uint64_t same = __builtin_amdgcn_ballot_w64(events != 0u);
+      const bool member = lengths[g] != 0u;
+      bucket[g] = 63u - min(lengths[g] >> shift, 63u);
+      uint64_t same = __builtin_amdgcn_ballot_w64(member);
 #pragma unroll
       for (uint32_t j = 0; j < 6u; ++j) {
         const bool one = ((bucket[g] >> j) & 1u) != 0u;
@@ -163,34 +165,41 @@ struct QuadWindow {
         same &= one ? ones : ~ones;
       }
       const uint32_t before = __builtin_amdgcn_mbcnt_hi((uint32_t)(same >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)same, 0u));
-      const uint32_t had = count[bucket[g]];
-      rank[g] = events != 0u ? had + before : ~0u;
-      __syncthreads();
-      if (events != 0u && before == 0u) count[bucket[g]] = had + (uint32_t)__builtin_popcountll(same);
-      __syncthreads();
+      rank[g] = member ? before : ~0u;
+      if (member && before == 0u) count[64u * g + bucket[g]] = (uint16_t)__builtin_popcountll(same);
     }
-    const uint32_t mine = count[lane];
-    uint32_t upto = mine;
+    __syncthreads();
+    uint32_t mine[kWindowGroups], all = 0u;   // (of bucket `lane`)
+#pragma unroll
+    for (uint32_t g = 0; g < kWindowGroups; ++g) mine[g] = count[64u * g + lane];
+#pragma unroll
+    for (uint32_t g = 0; g < kWindowGroups; ++g) all += mine[g];
+    uint32_t upto = all;
     for (uint32_t off = 1u; off < 64u; off <<= 1) {
       const uint32_t below = (uint32_t)__shfl_up((int)upto, off);
       upto += lane >= off ? below : 0u;
     }
     total = (uint32_t)__builtin_amdgcn_readlane((int)upto, 63);
-    __syncthreads();
-    count[lane] = upto - mine;
+    uint32_t at = upto - all;
+#pragma unroll
+    for (uint32_t g = 0; g < kWindowGroups; ++g) {
+      count[64u * g + lane] = (uint16_t)at;
+      at += mine[g];
+    }
     __syncthreads();
 #pragma unroll
-    for (uint32_t g = 0; g < kWindowGroups; ++g) rank[g] = rank[g] != ~0u ? count[bucket[g]] + rank[g] : ~0u;
+    for (uint32_t g = 0; g < kWindowGroups; ++g)
+      rank[g] = rank[g] != ~0u ? count[64u * g + bucket[g]] + rank[g] : ~0u;
   }
   __device__ __forceinline__ uint32_t turns() const { return (total + 15u) / 16u; }
   // which: the scenario of the window that the lane's quad takes; false: none.  All lanes.
   __device__ __forceinline__ bool take(uint32_t turn, void* lds, uint32_t& which) const {
-    uint32_t* const chosen = (uint32_t*)lds + 64u;
+    uint16_t* const chosen = (uint16_t*)lds + 64u * kWindowGroups;
     const uint32_t lane = threadIdx.x & 63u;
     __syncthreads();
 #pragma unroll
     for (uint32_t g = 0; g < kWindowGroups; ++g)
-      if (rank[g] >> 4 == turn) chosen[rank[g] & 15u] = kBlock * g + lane;
+      if (rank[g] >> 4 == turn) chosen[rank[g] & 15u] = (uint16_t)(kBlock * g + lane);
     __syncthreads();
     const bool exists = 16u * turn + (lane >> 2) < total;
     which = exists ? chosen[lane >> 2] : 0u;
@@ -201,7 +210,7 @@ struct QuadWindow {
 
 // What a window's order is made from.
 struct WindowScenario {
-  uint32_t D, events;
+  uint32_t D, length;   // (length: events)
   bool in_range;   // (dimensions and chunks; what else makes a scenario invalid is not looked at)
 };
 __device__ __forceinline__ WindowScenario window_scenario(const themis_batch_t& b, uint64_t i) {
@@ -210,15 +219,18 @@ __device__ __forceinline__ WindowScenario window_scenario(const themis_batch_t& 
   const uint32_t C = b.chunks[i];
   const bool one_phase = b.collective_type && b.collective_type[i] != THEMIS_COLL_ALL_REDUCE;
   w.in_range = w.D - 1u < (uint32_t)kMaxDims && C - 1u < b.max_chunks;
-  w.events = w.in_range ? C * w.D * (one_phase ? 1u : 2u) : 1u;
+  w.length = w.in_range ? C * w.D * (one_phase ? 1u : 2u) : 1u;
   return w;
 }
 // Does it have an NPU count that is not a power of two?
 __device__ __forceinline__ bool other_counts(const themis_batch_t& b, uint64_t i, uint32_t D) {
-  bool other = false;
+  uint32_t more = 0u;   // bits beside the lowest one of each
 #pragma unroll
-  for (uint32_t k = 0; k < (uint32_t)kMaxDims; ++k) other = other || (k < D && !is_pow2(b.npus[(size_t)k * b.n + i]));
-  return other;
+  for (uint32_t k = 0; k < (uint32_t)kMaxDims; ++k) {
+    const uint32_t p = b.npus[(size_t)k * b.n + i];
+    more |= k < D ? p & (p - 1u) : 0u;
+  }
+  return more != 0u;
 }
 
 // ---------------------------------------------------------------------------
@@ -528,10 +540,15 @@ __device__ __forceinline__ bool quad_table_turn(const themis_batch_t& b, const u
     return quad_order(gather ? reverse_code(code, s.D) : code, D) % Table::kOrders;
   };
   if (exists)
-    for (uint32_t c = k; c < s.C; c += 4u) {
-      const uint32_t code = orders[(size_t)i * b.max_chunks + c];
-      if (!quad_code_ok(code, D)) bad = 1u;
-      used |= 1u << order_of(code);
+    for (uint32_t c16 = k; c16 < s.C; c16 += 16u) {
+      uint32_t code[4];
+#pragma unroll
+      for (uint32_t j = 0; j < 4u; ++j) code[j] = orders[(size_t)i * b.max_chunks + min(c16 + 4u * j, s.C - 1u)];
+#pragma unroll
+      for (uint32_t j = 0; j < 4u; ++j) {
+        if (!quad_code_ok(code[j], D)) bad = 1u;
+        used |= 1u << order_of(code[j]);
+      }
     }
   const bool runs = exists && quad_sum(bad) == 0u;
   used = runs ? quad_or(used) : 0u;
@@ -809,20 +826,24 @@ simulate_kernel(themis_batch_t b, const uint8_t* __restrict__ orders,
     // else may write any of those; it takes its own.)
     const uint64_t window = blockIdx.x / kWindowGroups, from = window * kWindow, first = (uint64_t)blockIdx.x * kBlock;
     uint32_t sharing = 0u;
-    const QuadWindow shared(2u * (uint32_t)kMaxDims * b.max_chunks, lds_block, [&](uint32_t g) {
+    uint32_t lengths[kWindowGroups];
+#pragma unroll
+    for (uint32_t g = 0; g < kWindowGroups; ++g) {
       const uint64_t j = from + kBlock * g + threadIdx.x;
       const bool there = j < b.n;
       const WindowScenario w = window_scenario(b, there ? j : b.n - 1u);
-      const bool range = there && w.in_range, other = range && other_counts(b, j, w.D), few_here = lanes_few(range, other);
-      const bool member = range && few_here && w.D < 4u;
+      const bool other = other_counts(b, there ? j : b.n - 1u, w.D), range = there && w.in_range;
+      lengths[g] = w.length;
+      const bool few_here = lanes_few(range, range && other), member = range && few_here && w.D < 4u;
       if (__builtin_amdgcn_ballot_w64(member) != 0ull) sharing |= 1u << g;
-      return member ? w.events : 0u;
-    });
+      if (!member) lengths[g] = 0u;
+    }
+    const QuadWindow shared(2u * (uint32_t)kMaxDims * b.max_chunks, lds_block, lengths);
     const uint32_t of = max((uint32_t)__builtin_popcount(sharing), 1u);
     const uint32_t me = (uint32_t)__builtin_popcount(sharing & ((1u << blockIdx.x % kWindowGroups) - 1u));
     // (workgroups go to the XCDs in turn: not every window's longest to the same one)
     uint32_t turn = (me + (uint32_t)window) % of;
-    QuadTurns alone(few ? 0ull : own, tables ? window_scenario(b, i).events : 0u);
+    QuadTurns alone(few ? 0ull : own, tables ? window_scenario(b, i).length : 0u);
     while (few ? turn < shared.turns() : alone.left != 0ull) {
       uint32_t which;
       const bool there = few ? shared.take(turn, lds_block, which) : alone.take(which);
@@ -855,30 +876,36 @@ simulate_quad_kernel(themis_batch_t b, const uint8_t* __restrict__ orders, doubl
 #pragma unroll
   for (uint32_t g = 0; g < kWindowGroups; ++g) {
     const uint64_t j = from + kBlock * g + threadIdx.x;
-    const uint32_t events = window_scenario(b, j < b.n ? j : b.n - 1u).events;
-    lengths[g] = j < b.n ? events : 0u;
-    longest = max(longest, events);
-    shortest_inv = max(shortest_inv, ~events);
+    const uint32_t length = window_scenario(b, j < b.n ? j : b.n - 1u).length;
+    lengths[g] = j < b.n ? length : 0u;
+    longest = max(longest, length);
+    shortest_inv = max(shortest_inv, ~length);
   }
   const bool ragged = uniform(quad_wave_max(longest) != ~quad_wave_max(shortest_inv));
   // a quad without a scenario stays: the wavefront leaves the event loop as a whole
   uint64_t i = block * L::kQuads + (threadIdx.x >> 2);
   bool exists = i < b.n, runs_rest = true;
   uint32_t turn = 0u, turns_of_rest = 0u, blocks = 1u;
-  // (of the window; 0: not one of the others)
-  auto length_of_other = [&](uint32_t g) {
-    const uint64_t j = from + kBlock * g + threadIdx.x;
-    if (!kOthers || j >= b.n) return 0u;
-    const WindowScenario w = window_scenario(b, j);
-    return w.in_range && w.D < 4u && other_counts(b, j, w.D) ? w.events : 0u;
+  // (0: not one of the others)
+  auto lengths_of_others = [&](uint32_t (&of)[kWindowGroups]) {
+#pragma unroll
+    for (uint32_t g = 0; g < kWindowGroups; ++g) {
+      const uint64_t j = from + kBlock * g + threadIdx.x, at = j < b.n ? j : b.n - 1u;
+      const WindowScenario w = window_scenario(b, at);
+      const bool other = kOthers && other_counts(b, at, w.D);
+      of[g] = j < b.n && other && w.in_range && w.D < 4u ? w.length : 0u;
+    }
   };
   if (ragged) {
     const uint64_t size = b.n - from < kWindow ? b.n - from : kWindow;
     blocks = ((uint32_t)size + 15u) / 16u;
     // (workgroups go to the XCDs in turn: not every window's longest to the same one)
     turn = ((uint32_t)(block % kWindowTurns) + (uint32_t)window) % blocks;
-    const QuadWindow rest(2u * (uint32_t)kMaxDims * b.max_chunks, lds_block,
-                          [&](uint32_t g) { return length_of_other(g) != 0u ? 0u : lengths[g]; });
+    uint32_t of_others[kWindowGroups];
+    lengths_of_others(of_others);
+#pragma unroll
+    for (uint32_t g = 0; g < kWindowGroups; ++g) lengths[g] = of_others[g] != 0u ? 0u : lengths[g];
+    const QuadWindow rest(2u * (uint32_t)kMaxDims * b.max_chunks, lds_block, lengths);
     turns_of_rest = rest.turns();
     uint32_t which;
     exists = rest.take(turn, lds_block, which);
@@ -918,7 +945,8 @@ simulate_quad_kernel(themis_batch_t b, const uint8_t* __restrict__ orders, doubl
       const Pow2Model pow2(s, fs, b.intra_policy[i] == THEMIS_INTRA_SCF);
       uint8_t* const row = queue_order ? (uint8_t*)queue_order + ((size_t)i * kMaxDims + k) * 2u * b.max_chunks * (uint32_t)entry_bytes
                                        : nullptr;
-      const QuadResult r = simulate_quad<L, kQueueOrder != kNoQueueOrder>(
+      QuadResult r{nan64(), nan64(), 0u, false};
+      if (__builtin_amdgcn_ballot_w64(runs) != 0ull) r = simulate_quad<L, kQueueOrder != kNoQueueOrder>(
           QuadPow2<L, kFix>(s, pow2, k, lds_block), queue, (uint32_t)(pow2.ranktab >> (4u * (fs.state0 & 15u))) & 15u,
           runs ? (pow2.one_phase() ? D : 2u * D) * s.C : 0u, pow2.t_min(D),
           [&](uint32_t e, uint32_t entry) {
@@ -935,7 +963,8 @@ simulate_quad_kernel(themis_batch_t b, const uint8_t* __restrict__ orders, doubl
       // (the two kinds have a turn more than there are workgroups, or not)
       const bool one_more = turn == 0u && runs_rest;
       if (!runs_rest || one_more) {
-        const QuadWindow turns(2u * (uint32_t)kMaxDims * b.max_chunks, lds_block, length_of_other);
+        lengths_of_others(lengths);
+        const QuadWindow turns(2u * (uint32_t)kMaxDims * b.max_chunks, lds_block, lengths);
         uint32_t which;
         const bool there = turns.take(runs_rest ? blocks - turns_of_rest : turn - turns_of_rest, lds_block, which);
         if (__builtin_amdgcn_ballot_w64(there) != 0ull)
@@ -1126,12 +1155,12 @@ simulate_follow_up_kernel(themis_batch_t b, const uint8_t* __restrict__ orders,
       for (uint32_t g = 0; g < kWindowGroups; ++g) {
         const uint64_t j = from + kBlock * g + lane;
         const WindowScenario v = window_scenario(b, j < b.n ? j : b.n - 1u);
-        length[g] = j < b.n && v.in_range && (v.D == 4u) == four ? v.events : 0u;
+        length[g] = j < b.n && v.in_range && (v.D == 4u) == four ? v.length : 0u;
         marked = marked || (length[g] != 0u && is_left_to_generic(t_done[j]));
         members += (uint32_t)__builtin_popcountll(__builtin_amdgcn_ballot_w64(length[g] != 0u));
       }
       if (16u * turn >= members || __builtin_amdgcn_ballot_w64(marked) == 0ull) continue;
-      const QuadWindow order(2u * (uint32_t)kMaxDims * b.max_chunks, lds_block, [&](uint32_t g) { return length[g]; });
+      const QuadWindow order(2u * (uint32_t)kMaxDims * b.max_chunks, lds_block, length);
       uint32_t which;
       const bool there = order.take(turn, lds_block, which);
       i = from + which;

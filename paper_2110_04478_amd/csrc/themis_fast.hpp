@@ -291,8 +291,9 @@ __device__ __forceinline__ void plan_fast(const Scenario& s, const FastScenario&
   const double times = s.ctype == THEMIS_COLL_ALL_REDUCE ? 2.0 : 1.0;
   const uint32_t field_mask = (1u << (2 * D)) - 1u;
   const int high = __double2hiint(fs.base), low = __double2loint(fs.base);
-  int exponent = -(1 << 20);
-  asm volatile("" : "+s"(exponent));   // (a multiply-add, not a shift and a subtraction)
+  int less = 0;   // -log2 P_k in byte k
+#pragma unroll
+  for (int k = 0; k < kMaxDims; ++k) less |= (int)((0u - (fs.epack >> (8 * k) & 0xffu) & 0xffu) << (8 * k));
   for (uint32_t c = 0; c < s.C; ++c) {
     // after<a><b> (a < b): does a come after b?  Stable ascending sort: only when a's
     // load is strictly larger.
@@ -322,8 +323,8 @@ __device__ __forceinline__ void plan_fast(const Scenario& s, const FastScenario&
     const uint32_t of[kMaxDims] = {before.x, before.y, before.z, before.w};
 #pragma unroll
     for (int k = 0; k < kMaxDims; ++k) {
-      const int e = (int)__builtin_amdgcn_udot4(of[k], fs.epack, 0u, false);
-      const double t = __hiloint2double(__mul24(e, exponent) + high, low) * coef[k];
+      const uint32_t e = (uint32_t)__builtin_amdgcn_sdot4((int)of[k], less, 0, true);
+      const double t = __hiloint2double(high + (int)(e << 20), low) * coef[k];
       load[k] = __builtin_fma(times, t, load[k]);   // (t + t is exact)
     }
     emit(c, code);

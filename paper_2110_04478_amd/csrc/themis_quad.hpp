@@ -41,6 +41,8 @@
 // without a use for it: one of the next dimension, or links.)
 #pragma once
 
+#include <stddef.h>
+
 #include "themis_fast.hpp"
 #include "themis_ring.hpp"
 
@@ -133,8 +135,12 @@ __device__ __forceinline__ uint32_t quad_order(uint32_t code, uint32_t D) {
 // next (4: it is finished), 9-14 its row and phase then, 17-22 four times the mask
 // of its reduced dimensions then; bits 0, 8, 16, 24: dimension 0, 1, 2, 3 comes
 // before k in its order.
+// turned: the same where a chunk's last Reduce-Scatter and its first All-Gather, on the
+// same dimension, are one stage (bit 31) that takes the time of one twice.  Under
+// Smallest-Chunk-First nothing comes between them: the chunk is smaller then than any that
+// waits there, and moves the same bytes again.
 struct QuadStages {
-  uint32_t v[64][4];
+  uint32_t v[64][4], turned[64][4];
   uint8_t code[4][24];   // the order codes themselves, by (dimensions - 1)
 };
 __host__ __device__ constexpr uint32_t quad_row(uint32_t D) { return D >= 4u ? 0u : D == 3u ? 24u : 30u; }
@@ -168,6 +174,11 @@ constexpr QuadStages quad_stages() {
             (j == 0u ? 4u : perm[j - (j ? 1u : 0u)]) << 1 | (row + 32u) << 9 | (4u * before) << 17 | bits;
         before = with;
       }
+      for (uint32_t k = 0; k < D; ++k) {
+        const uint32_t column = k + quad_column(D), v = t.v[row][column];
+        t.turned[row][column] = ((v >> 14) & 1u) != 0u ? t.v[32u + row][column] | 1u << 31 : v;
+        t.turned[32u + row][column] = t.v[32u + row][column];
+      }
       ++n;
     }
   }
@@ -183,15 +194,17 @@ __device__ const QuadStages g_quad_stages = quad_stages();
 // A running stage, as the quad passes it on: bits 1-3 the dimension the chunk waits
 // for then (4: none), 9-14 its row and phase then, 16-19 the list it joins, 23-31 the
 // chunk.
-// The stage table is in LDS behind the lists (1 KiB, 60 clocks nearer than the
-// caches) where that costs no wavefront: up to 256 chunks; and in the place of the
-// lists' ends where the wavefront does without them (fifo).
+// The stage tables are in LDS behind the lists (2 KiB, 60 clocks nearer than the
+// caches) where that costs no wavefront: up to 256 chunks; the one without turns in the
+// place of the lists' ends where the wavefront does without them (fifo).
 template <typename L, bool kFix>
 struct QuadPow2 {
   static constexpr bool kTableInLds = L::kCap <= 256u;
   static constexpr uint32_t kTableAt = kTableInLds ? L::kBytes : 0u;
-  static constexpr uint32_t kBytes = L::kBytes + (kTableInLds ? 1024u : 0u);
-  static_assert(kTableInLds || L::kLinksAt >= 1024u, "the table fits the place of the lists' ends");
+  static constexpr uint32_t kTable = 1024u;   // bytes of each
+  static_assert(sizeof(QuadStages::v) == kTable && offsetof(QuadStages, turned) == kTable, "one behind the other");
+  static constexpr uint32_t kBytes = L::kBytes + (kTableInLds ? 2u * kTable : 0u);
+  static_assert(kTableInLds || L::kLinksAt >= 1024u, "a table fits the place of the lists' ends");
   static constexpr double kShortest = 2.2250738585072014e-308;   // (see above)
   static constexpr uint32_t kNobody = ~0u;   // above all stages, for dimension 7, list 31 (a place behind the lists)
   double whole, fix;
@@ -203,26 +216,29 @@ struct QuadPow2 {
   __device__ __forceinline__ QuadPow2(const Scenario& s, const Pow2Model& m, uint32_t k, void* lds)
       : whole(m.fs.base * sel4((int)k, s.coef[0], s.coef[1], s.coef[2], s.coef[3])),
         fix(kFix ? sel4((int)k, s.fix[0], s.fix[1], s.fix[2], s.fix[3]) : 0.0), ranktab(m.ranktab), less(0),
-        block((uint8_t*)lds), at(4u * ((k + quad_column((uint32_t)s.D)) & 3u)),
+        block((uint8_t*)lds),
+        at(4u * ((k + quad_column((uint32_t)s.D)) & 3u) | (m.ranktab != 0ull && !m.rs_only() ? kTable : 0u)),
         // a stand-alone Reduce-Scatter is finished where the phase would turn
         wanted(m.rs_only() ? 14u | 0x4000u : 14u), fifo(__builtin_amdgcn_ballot_w64(m.ranktab != 0ull) == 0ull) {
 #pragma unroll
     for (uint32_t d = 0; d < 4u; ++d) less |= (int)((0u - (m.fs.epack >> (8u * d) & 0xffu) & 0xffu) << (8u * d));
     if (kTableInLds || fifo)
-      for (uint32_t j = 0; j < 4u; ++j)
+      for (uint32_t j = 0; j < (kTableInLds ? 8u : 4u); ++j)
         ((typename L::Word*)(block + kTableAt))[64u * j + threadIdx.x % 64u] = (&g_quad_stages.v[0][0])[64u * j + threadIdx.x % 64u];
     __syncthreads();
   }
   __device__ __forceinline__ bool goes_to(uint32_t given, uint32_t k) const { return (given & wanted) == 2u * k; }
   static __device__ __forceinline__ uint32_t list(uint32_t given) { return (given >> 16) & 31u; }
   static __device__ __forceinline__ uint32_t record(uint32_t given) { return (given & 0x7e00u) | given >> 23; }
-  // rec: the chunk's record in the low half; kFifo: on a wavefront of one class
+  // rec: the chunk's record in the low half; kFifo: on a wavefront of one class; turned: it takes
+  // the time twice
   template <bool kFifo>
-  __device__ __forceinline__ uint32_t stage(uint32_t rec, double& time) const {
+  __device__ __forceinline__ uint32_t stage(uint32_t rec, double& time, bool& turned) const {
     const uint8_t* const table = kTableInLds || kFifo ? block + kTableAt : (const uint8_t*)&g_quad_stages;
     const uint32_t v = *(const typename L::Word*)(table + (((rec >> 5) & 0x3f0u) | at));
     time = ldexp(whole, __builtin_amdgcn_sdot4((int)(v & 0x01010101u), less, 0, true));
     if (kFix) time = fix + time;
+    turned = (int)v < 0;
     if (kFifo) return (v & 0x7e0eu) | rec << 23;
     const uint32_t cls = (uint32_t)(ranktab >> ((v >> 17) & 63u)) & 15u;
     return ((v & 0x7e0eu) | rec << 23) | cls << 16;
@@ -235,7 +251,7 @@ struct QuadPow2 {
 // of divisions and multiplications, once per order that some chunk has.
 // In LDS behind the lists (quad g): time of order o on dimension k, binary64, at
 // 128 * (4 * o + k) + 8 * g, and what the completion does, 16 bits (0-2 the dimension
-// the chunk waits for then, 3-8 the list it joins, 9-14 its state), at
+// the chunk waits for then, 3-8 the list it joins, 9-14 its state, 15: turned, see QuadStages), at
 // 32 * (4 * state + k) + 2 * g (state: order and phase as in a record); a running
 // stage is these bits and the chunk from bit 23 on; size classes of (state, k) while these are made, 8 bits, at
 // 16 * (4 * state + k) + g.
@@ -280,15 +296,24 @@ struct QuadTable {
     uint8_t* const ag = block;                 // sizes before the All-Gather stages, in the place of the lists
     // sizes: lane j of the quad takes the orders j, j + 4, ..  (NaN, below no
     // size, where there is none)
-    for (uint32_t o = k; o < kOrders; o += 4u) {
+    constexpr uint32_t kTakes = (kOrders + 3u) / 4u;
+    uint32_t codes[kTakes];
+#pragma unroll
+    for (uint32_t j = 0; j < kTakes; ++j) codes[j] = g_quad_stages.code[(D - 1u) & 3u][min(k + 4u * j, kOrders - 1u)];
+    double least = inf64();
+#pragma unroll
+    for (uint32_t j4 = 0; j4 < kTakes; ++j4) {
+      const uint32_t o = k + 4u * j4;
+      if (o >= kOrders) break;
       const bool has = ((used >> o) & 1u) != 0u;
-      const uint32_t code = has ? (uint32_t)g_quad_stages.code[(D - 1u) & 3u][o] : 0xe4u;
+      const uint32_t code = has ? codes[j4] : 0xe4u;
       double x = has ? chunk : nan64();
       for (uint32_t j = 0; j < kDims; ++j) {
         const uint32_t kj = j < D ? (code >> (2u * j)) & 3u : j;
         *f64_at(rs, o, kj) = j < D && !gather ? x : nan64();
         if (!gather && j < D) x = x / (double)sel4((int)kj, s.P[0], s.P[1], s.P[2], s.P[3]);
       }
+      least = min_f64(least, x);
       for (uint32_t j = kDims; j-- > 0u;) {
         const uint32_t kj = j < D ? (code >> (2u * j)) & 3u : j;
         *f64_at(ag, o, kj) = j < D && !rs_only ? x : nan64();
@@ -296,41 +321,61 @@ struct QuadTable {
       }
     }
     __syncthreads();
-    // classes: the number of smaller sizes among those that wait for the lane's
-    // dimension, a comparison with each (reads that do not wait for each other)
-    for (uint32_t phase = gather ? 1u : 0u; phase < (rs_only ? 1u : 2u); ++phase) {
-      for (uint32_t m = k < D ? used : 0u; m != 0u; m &= m - 1u) {
-        const uint32_t o = (uint32_t)__builtin_ctz(m);
-        const double v = *f64_at(phase ? ag : rs, o, k);
-        uint32_t r = 0u;
-        if (scf) {
+    // Classes: the number of smaller sizes among those that wait for the lane's dimension.
+    // The lane's own sizes and counts are in registers, and each size is read once for all
+    // of them (each comparison with a read of its own: 57 us of 264 for 750 turns of four
+    // dimensions, 64 chunks).  A chunk waits for its first stage at its whole size.
+    uint32_t rank[2u * kOrders];
 #pragma unroll
-          for (uint32_t o2 = 0; o2 < kOrders; ++o2)
-            r += (*f64_at(rs, o2, k) < v ? 1u : 0u) + (*f64_at(ag, o2, k) < v ? 1u : 0u);
-        }
-        *class_at(block, state_of(o, phase), k) = (uint8_t)r;
-        // (a chunk waits for its first stage at the same size whatever its order)
-        const uint32_t code = g_quad_stages.code[(D - 1u) & 3u][o];
-        if (((code >> (gather ? 2u * (D - 1u) : 0u)) & 3u) == k && phase == (gather ? 1u : 0u)) cls0 = r;
+    for (uint32_t i = 0; i < 2u * kOrders; ++i) rank[i] = 0u;
+    if (scf) {
+      double own[2u * kOrders];
+#pragma unroll
+      for (uint32_t i = 0; i < 2u * kOrders; ++i) own[i] = *f64_at(i < kOrders ? rs : ag, i % kOrders, k);
+      for (uint32_t o = 0; o < kOrders; ++o) {
+        const double v = *f64_at(rs, o, k), w = *f64_at(ag, o, k);
+        cls0 += (v < chunk ? 1u : 0u) + (w < chunk ? 1u : 0u);
+#pragma unroll
+        for (uint32_t i = 0; i < 2u * kOrders; ++i) rank[i] += (v < own[i] ? 1u : 0u) + (w < own[i] ? 1u : 0u);
       }
     }
+#pragma unroll
+    for (uint32_t i = 0; i < 2u * kOrders; ++i) *class_at(block, state_of(i % kOrders, i / kOrders), k) = (uint8_t)rank[i];
     __syncthreads();
     const double coef = sel4((int)k, s.coef[0], s.coef[1], s.coef[2], s.coef[3]);
     const double fix = sel4((int)k, s.fix[0], s.fix[1], s.fix[2], s.fix[3]);
+    // (sizes that have left the normal range may be equal)
+    least = quad_min_f64(least);
+    const bool turns = scf && !rs_only && least >= 2.2250738585072014e-308;
     const double grow = gather ? (double)sel4((int)k, s.P[0], s.P[1], s.P[2], s.P[3]) : 1.0;
-    for (uint32_t m = k < D ? used : 0u; m != 0u; m &= m - 1u) {
-      const uint32_t o = (uint32_t)__builtin_ctz(m);
-      const double moved = gather ? *f64_at(ag, o, k) * grow : *f64_at(rs, o, k);
-      double time = moved * coef;
-      if (s.has_fix) time = fix + time;
-      *f64_at(rs, o, k) = time;
-      t_min = min_f64(t_min, time);
-      for (uint32_t phase = gather ? 1u : 0u; phase < (rs_only ? 1u : 2u); ++phase) {
-        const uint32_t v = g_quad_stages.v[32u * phase + quad_row(D) + o][k + quad_column(D)];
-        const uint32_t turned = (v >> 14) & 1u, next = state_of(o, turned);
-        const uint32_t to = rs_only && turned != 0u ? 4u : (v >> 1) & 7u;
-        const uint32_t cls = to < 4u ? *class_at(block, next, to) : 0u;
-        *does_at(block, state_of(o, phase), k) = (uint16_t)(to | cls << 3 | next << 9);
+    const uint32_t* const stages = (turns ? &g_quad_stages.turned[0][0] : &g_quad_stages.v[0][0]) +
+                                   4u * quad_row(D) + ((k + quad_column(D)) & 3u);
+    constexpr uint32_t kAtOnce = kOrders % 4u == 0u ? 4u : 3u;   // (loads that do not wait for each other)
+    for (uint32_t from = 0; from < kOrders; from += kAtOnce) {
+      uint32_t given[2][kAtOnce];
+#pragma unroll
+      for (uint32_t j = 0; j < kAtOnce; ++j) {
+        given[0][j] = stages[4u * min(from + j, 31u - quad_row(D))];
+        given[1][j] = stages[4u * (32u + min(from + j, 31u - quad_row(D)))];
+      }
+#pragma unroll
+      for (uint32_t j = 0; j < kAtOnce; ++j) {
+        const uint32_t o = from + j;
+        if (k >= D || ((used >> o) & 1u) == 0u) continue;
+        const double moved = gather ? *f64_at(ag, o, k) * grow : *f64_at(rs, o, k);
+        double time = moved * coef;
+        if (s.has_fix) time = fix + time;
+        *f64_at(rs, o, k) = time;
+        t_min = min_f64(t_min, time);
+#pragma unroll
+        for (uint32_t phase = 0; phase < 2u; ++phase) {
+          if (phase == 0u ? gather : rs_only) continue;
+          const uint32_t v = given[phase][j];
+          const uint32_t turned = (v >> 14) & 1u, next = state_of(o, turned);
+          const uint32_t to = rs_only && turned != 0u ? 4u : (v >> 1) & 7u;
+          const uint32_t cls = to < 4u ? *class_at(block, next, to) : 0u;
+          *does_at(block, state_of(o, phase), k) = (uint16_t)(to | cls << 3 | next << 9 | (v >> 31) << 15);
+        }
       }
     }
     t_min = quad_min_f64(t_min);
@@ -340,11 +385,12 @@ struct QuadTable {
   static __device__ __forceinline__ uint32_t list(uint32_t given) { return (given >> 3) & 63u; }
   static __device__ __forceinline__ uint32_t record(uint32_t given) { return (given & 0x7e00u) | given >> 23; }
   template <bool kFifo>
-  __device__ __forceinline__ uint32_t stage(uint32_t rec, double& time) const {
+  __device__ __forceinline__ uint32_t stage(uint32_t rec, double& time, bool& turned) const {
     const uint32_t k = threadIdx.x & 3u;
     time = *(const double*)(block + kTimes + ((rec & (L::kPhaseBit == 14u ? 0x3e00u : 0xe00u)) | (k << 7 | quad8())));
     const uint32_t v = *(const uint16_t*)(block + kDoes + (((rec >> 2) & (L::kPhaseBit == 14u ? 0x1f80u : 0x780u)) |
                                                            (k << 5 | (threadIdx.x >> 2) * 2u)));
+    turned = (v & 0x8000u) != 0u;
     return v | rec << 23;
   }
 };
@@ -540,8 +586,9 @@ __device__ __forceinline__ QuadRun quad_loop_fifo(const Model& model, const Quad
     d.waits = d.waits || append;
     if (quad_all_delivered(d.waits && !(d.f == d.f), ending, running)) {
       double time;
+      bool turned;   // (never)
       const uint32_t link = *L::link(block, first);   // (only used where the list goes on)
-      d.sv = model.template stage<true>(first, time);
+      d.sv = model.template stage<true>(first, time, turned);
       d.f = d.now + time;
       d.busy = d.busy + time;
       if (kPut) put(d.started, (first & L::kIdMask) << 1 | ((first >> L::kPhaseBit) & 1u));
@@ -604,7 +651,8 @@ __device__ __forceinline__ QuadRun quad_loop_classes(const Model& model, const Q
     }
     if (starts) {
       double time;
-      d.sv = model.template stage<false>(ends_from, time);
+      bool turned;
+      d.sv = model.template stage<false>(ends_from, time, turned);
       const uint32_t link = *L::link(block, ends_from);
       const bool last = ends_from == __builtin_amdgcn_alignbit(ends_from, ends_from, 16u);   // of its list
       lists &= last ? lists - 1u : ~(Mask)0;
@@ -613,6 +661,12 @@ __device__ __forceinline__ QuadRun quad_loop_classes(const Model& model, const Q
       d.busy = d.busy + time;
       if (kPut) put(d.started, (ends_from & L::kIdMask) << 1 | ((ends_from >> L::kPhaseBit) & 1u));
       ++d.started;
+      if (turned) {
+        d.f = d.f + time;
+        d.busy = d.busy + time;
+        if (kPut) put(d.started, (ends_from & L::kIdMask) << 1 | 1u);
+        ++d.started;
+      }
     }
   };
   pass(nan64(), 0ull);
