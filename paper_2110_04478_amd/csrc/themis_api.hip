@@ -138,12 +138,11 @@ struct QuadTurns {
 // of a bucket as they come.  (The policies apart, each with its event loop, 32 buckets either:
 // no gain, the longest chain bounds it, and 680 us of the above for 642.)
 constexpr uint32_t kWindow = 512u, kWindowGroups = kWindow / kBlock, kWindowTurns = kWindow / 16u;
-constexpr uint32_t kWindowLds = 2u * 64u * kWindowGroups + 32u;
 struct QuadWindow {
   uint32_t rank[kWindowGroups];   // of the scenarios of the lane, one in each 64 (all-ones: not among them)
   uint32_t total;
   // lengths[g]: that of scenario 64 * g + lane of the window, 0: not among them; most: the
-  // largest there can be.  All lanes; lds: kWindowLds bytes.
+  // largest there can be.  All lanes; lds: 1,056 bytes.
   __device__ __forceinline__ QuadWindow(uint32_t most, void* lds, const uint32_t (&lengths)[kWindowGroups]) {
     uint16_t* const count = (uint16_t*)lds;   // of the scenarios of each 64 in each bucket, then how many come before
     const uint32_t lane = threadIdx.x & 63u, bits = 32u - (uint32_t)__clz((int)(most | 1u));
@@ -2232,7 +2231,7 @@ search_few_kernel(themis_batch_t b, uint32_t max_assign, uint32_t lane_blocks, u
     const Scenario s = load_scenario(b, i);
     const double S = b.size_bytes[i];
     const uint32_t count = count_of(s, S);
-    const SharedSetup setup = shared_table(s, S / (double)s.C, b.intra_policy[i] == THEMIS_INTRA_SCF,
+    const SharedSetup setup = shared_table<false>(s, S / (double)s.C, b.intra_policy[i] == THEMIS_INTRA_SCF,
                                            block.shared.tab);
     __syncthreads();
     if (!setup.ok) {
@@ -2257,8 +2256,7 @@ search_few_kernel(themis_batch_t b, uint32_t max_assign, uint32_t lane_blocks, u
         return (uint32_t)block.shared.tab.rank_of[digit];
       };
       const SharedModel model(block.shared.tab, setup, s.ctype, rank_at);
-      const FastResult r = ring_loop<true, kNoQueueOrder, false, false, true>(
-          s, model, lds, none, (const uint8_t*)block.shared.tab.step);
+      const FastResult r = shared_ring<false>(s, model, lds);
       bad = !r.ok;
       if (r.ok) { best = r.t_done; arg = lane; }
     }
@@ -2309,7 +2307,7 @@ search_kernel(themis_batch_t b, uint64_t max_assign, uint32_t parts, double* __r
   if (all == 0u) { report(false, nan64(), 0u); return; }
   const Index count = (Index)all;
   const double chunk = S / (double)s.C;
-  const SharedSetup setup = shared_table(s, chunk, scf, tab);
+  const SharedSetup setup = shared_table<false>(s, chunk, scf, tab);
   __syncthreads();
   if (!setup.ok) {
     for (uint64_t a = (uint64_t)part * kBlock + lane; a < max_assign; a += (uint64_t)parts * kBlock)
@@ -2336,9 +2334,6 @@ search_kernel(themis_batch_t b, uint64_t max_assign, uint32_t parts, double* __r
   LaneLds lds;
   lds.base = ring + LayoutRing::lane_term_rec(lane);
   lds.aux = ring + kCap * 128u + (LayoutRing::lane_term_tail(lane) - LayoutRing::kRecBytes);
-  FastOut none;
-  none.queue_order = nullptr;
-  none.slots = b.max_chunks;
 
   const Index first = (Index)part * kBlock, step = (Index)parts * kBlock;
   // (one group per wavefront: all of it at once, no bounds)
@@ -2396,8 +2391,7 @@ search_kernel(themis_batch_t b, uint64_t max_assign, uint32_t parts, double* __r
         return (uint32_t)tab.rank_of[digit];
       };
       const SharedModel model(tab, setup, s.ctype, rank_at);
-      const FastResult r =
-          ring_loop<true, kNoQueueOrder, false, false, true>(s, model, lds, none, (const uint8_t*)tab.step);
+      const FastResult r = shared_ring<false>(s, model, lds);
       bad = bad || !r.ok;
       if (r.ok && (r.t_done < best || (r.t_done == best && a < arg))) { best = r.t_done; arg = a; }
     }
@@ -2745,9 +2739,6 @@ beam_kernel(themis_batch_t b, BeamLayout l, uint8_t* __restrict__ ws, unsigned l
   }
   const uint32_t D = (uint32_t)s.D, C = s.C, F = factorial_u32(D);
   const bool both = s.ctype == THEMIS_COLL_ALL_REDUCE;
-  FastOut none;
-  none.queue_order = nullptr;
-  none.slots = b.max_chunks;
   const DivideByOrders by_orders(D);
   SharedSetup setup;
   double made_for = -1.0;   // chunk size of the table
@@ -2760,7 +2751,7 @@ beam_kernel(themis_batch_t b, BeamLayout l, uint8_t* __restrict__ ws, unsigned l
     const uint32_t nc = live * F, kept = nc < l.width ? nc : l.width;
     for (uint32_t x = lane; x < nc; x += kBlock) { k.lb[x] = 0u; k.tb[x] = ~0u; }
     if (chunk != made_for) {   // (the m-th part of m chunks is nearly always the same)
-      setup = shared_table(s, chunk, scf, tab);
+      setup = shared_table<true>(s, chunk, scf, tab);
       made_for = chunk;
     }
     __syncthreads();
@@ -2819,8 +2810,7 @@ beam_kernel(themis_batch_t b, BeamLayout l, uint8_t* __restrict__ ws, unsigned l
           return c + 1u == m ? last : four & 0xffu;
         };
         const SharedModel model(tab, setup, s.ctype, rank_at);
-        const FastResult r =
-            ring_loop<true, kNoQueueOrder, false, false, true>(s, model, lds, none, (const uint8_t*)tab.step);
+        const FastResult r = shared_ring<true>(s, model, lds);
         bad = bad || !r.ok;
         k.time[x] = r.t_done;
         // (a NaN or negative time is not possible where r.ok)

@@ -148,6 +148,21 @@ __device__ __forceinline__ uint32_t whole_code(uint32_t code6) {
 struct RingPlaces { uint32_t w0, w1, w2, w3; };
 #define THEMIS_W_OPERANDS [w0] "+v"(w.w0), [w1] "+v"(w.w1), [w2] "+v"(w.w2), [w3] "+v"(w.w3)
 
+// (the time as it is, from `now` on)
+#define THEMIS_RING_GIVEN(J, IE, KEEP) \
+  THEMIS_LANES_OF(J) THEMIS_END(J) THEMIS_SERVE(J) "v_and_b32_e32 %[" #IE "], %[" #KEEP "], %[" #IE "]\n\t" THEMIS_ALL_LANES
+
+// Dimension k starts a stage that takes t from `now` on: no product, no busy time.
+__device__ __forceinline__ void ring_start_given(uint32_t k, uint32_t val, double now, double t, DimState& d,
+                                                 uint32_t& ie_lo, uint32_t& ie_hi) {
+  uint64_t act;
+  asm volatile("s_mov_b64 %[act], exec\n\t"
+      THEMIS_RING_GIVEN(0, iel, upper) THEMIS_RING_GIVEN(1, iel, lower)
+      THEMIS_RING_GIVEN(2, ieh, upper) THEMIS_RING_GIVEN(3, ieh, lower) THEMIS_PAD1
+      : [act] "=&s"(act), [iel] "+v"(ie_lo), [ieh] "+v"(ie_hi), THEMIS_F_OPERANDS, THEMIS_S_OPERANDS
+      : [k] "v"(k), [val] "v"(val), [now] "v"(now), [t] "v"(t), THEMIS_RING_HALVES : "vcc");
+}
+
 // Returns the place of this stage's queue-order entry (kStaged, else 0).
 template <bool kBusy, bool kFix, bool kStaged>
 __device__ __forceinline__ uint32_t ring_start_stage(uint32_t k, uint32_t val, double now, double x,
@@ -331,12 +346,16 @@ __device__ inline uint32_t ring_table_entry(uint32_t r, uint32_t behind, uint32_
 // orders.  The stage times then sit in the table too, so nothing here depends
 // on the NPU counts being powers of two (Model: SharedModel, themis_shared.hpp),
 // and the records need no initialisation: the model gives the chunks' orders.
-template <bool kTable, int kQueueOrder, bool kBusy, bool kFix, bool kShared = false, typename Model>
+// Its table has, in place of the exponent, how many stages the entry stands for: two where
+// a chunk turns from Reduce-Scatter to All-Gather under Smallest-Chunk-First (kTurns; see
+// QuadStages; beam search of 4,096 scenarios, width 4: 25.1 -> 21.6 ms).
+template <bool kTable, int kQueueOrder, bool kBusy, bool kFix, bool kShared = false, bool kTurns = false, typename Model>
 __device__ __forceinline__ FastResult ring_loop(const Scenario& s, const Model& model,
                                                 const LaneLds& lds, const FastOut& out,
                                                 const uint8_t* table) {
   static_assert(kQueueOrder == kNoQueueOrder || kQueueOrder == kBytes || kQueueOrder == kStagedBytes,
                 "entries are stored one by one");
+  static_assert(!kShared || (kTable && kQueueOrder == kNoQueueOrder && !kBusy && !kFix), "times alone");
   using L = LayoutRing;
   const uint32_t D = (uint32_t)s.D;
   const uint32_t C = s.C;
@@ -344,7 +363,7 @@ __device__ __forceinline__ FastResult ring_loop(const Scenario& s, const Model& 
   const double kInf = inf64();
   const uint32_t epack = model.epack();
   const uint64_t ranktab = model.ranks();
-  // (kShared: times as they are, one way to multiply by them)
+  // (kShared: times as they are; without turns multiplied by one, which is no slower than the shorter block)
   const double coef[kMaxDims] = {kShared ? 1.0 : s.coef[0], kShared ? 1.0 : s.coef[1],
                                  kShared ? 1.0 : s.coef[2], kShared ? 1.0 : s.coef[3]};
   // a chunk is finished when its mask comes back to zero (the last All-Gather
@@ -443,7 +462,7 @@ __device__ __forceinline__ FastResult ring_loop(const Scenario& s, const Model& 
   // 4 * D * C passes and a few always suffice; the bound is the same for all
   // lanes (it only has to end the loop whatever the records hold).
   constexpr uint32_t kMaxSteps = 4u * (uint32_t)kMaxDims * L::kCap + 16u;
-  loop_place<kShared ? 4u : kQueueOrder == kNoQueueOrder ? 2u : 6u>();
+  loop_place<kTurns ? 0u : kShared ? 4u : kQueueOrder == kNoQueueOrder ? 2u : 6u>();
   for (uint32_t step = 0; step < kMaxSteps; ++step) {
     // a7: the lowest idle dimension with chunks waiting starts the first chunk
     // of its lowest class -- the lowest set bit among the lists of idle dimensions
@@ -462,6 +481,7 @@ __device__ __forceinline__ FastResult ring_loop(const Scenario& s, const Model& 
       *rt_p = (uint16_t)bfi(0x3ffu, rt, rh);
       const uint64_t gone = (uint64_t)(((h ^ t) - 1u) >> 31) << q;  // the list's bit if h == t
       uint32_t entry, val;   // entry: chunk << 1 | All-Gather
+      uint32_t stages_now = 1u;
       double bytes;
       if (kTable) {
         const uint32_t e = *(const uint16_t*)(table + 2u * (rh & 0xffu));
@@ -470,7 +490,8 @@ __device__ __forceinline__ FastResult ring_loop(const Scenario& s, const Model& 
         entry = he >> 9;  // the phase is the bit below the id
         // byte 0: list and finished bit, byte 1: the record's low byte then (one
         // more stage behind it), byte 2: the chunk << 2 (and the phase below it)
-        val = __builtin_amdgcn_perm(rh + 1u, he, 0x0c010400u);
+        if (kTurns) stages_now = e >> 10;
+        val = __builtin_amdgcn_perm(rh + stages_now, he, 0x0c010400u);
         if constexpr (kShared) bytes = model.stage_time(rh & 0xffu);
         else bytes = __hiloint2double(__double2hiint(model.fs.base) - (int)((e << 10) & 0x03f00000u),
                                       __double2loint(model.fs.base));
@@ -497,8 +518,14 @@ __device__ __forceinline__ FastResult ring_loop(const Scenario& s, const Model& 
       }
       // bytes moved on k = resident size before the chunk's Reduce-Scatter on
       // k, i.e. with every reduced dimension but k itself taken off
-      const uint32_t at = ring_start_stage<kBusy, kFix, kStaged>(k, val, now, bytes, coef, s.fix, d,
-                                                                 ie_lo, ie_hi, place);
+      uint32_t at = 0u;
+      if constexpr (kTurns) {
+        double from = now;
+        if (stages_now != 1u) from = now + bytes;
+        ring_start_given(k, val, from, bytes, d, ie_lo, ie_hi);
+      } else {
+        at = ring_start_stage<kBusy, kFix, kStaged>(k, val, now, bytes, coef, s.fix, d, ie_lo, ie_hi, place);
+      }
       if (kStaged) {
         __builtin_amdgcn_raw_buffer_store_b8((uint8_t)entry, staging, (int)at, 0, 0);
       } else if (kQueueOrder == kBytes) {
@@ -507,7 +534,7 @@ __device__ __forceinline__ FastResult ring_loop(const Scenario& s, const Model& 
         if (pos_k < row_len) out.queue_order[k * row_len + pos_k] = (uint8_t)entry;
         executed.inc(k);
       } else {
-        ++started;
+        started += stages_now;
       }
       // k is no longer among the idle dimensions, so whether its list has just
       // emptied does not matter here: the bit is taken out afterwards

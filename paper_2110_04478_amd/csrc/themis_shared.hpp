@@ -31,6 +31,7 @@ struct SharedSetup {
   double t_min;      // smallest stage time
   double t_max;      // no schedule of C chunks takes longer than C * t_max
   bool ok;           // the ring loop can run on the table
+  bool turns;        // it has entries that stand for two stages (see ring_loop)
   // where a chunk waits first: bits 0 and 1 of the dimension, a bit per order
   // rank, and the class there, four bits per dimension (all chunks start with
   // the same size)
@@ -61,7 +62,9 @@ struct SharedModel {
 };
 
 // Fills the table for all orders of the scenario (all 64 lanes are here and
-// have the same arguments; a barrier of the caller's follows).
+// have the same arguments; a barrier of the caller's follows).  kTurns: with entries that
+// stand for two stages where the queues are Smallest-Chunk-First.
+template <bool kTurns>
 __device__ __forceinline__ SharedSetup shared_table(const Scenario& s, double chunk, bool scf,
                                                     SharedTable& tab) {
   const uint32_t D = (uint32_t)s.D, lane = lane_id();
@@ -72,7 +75,7 @@ __device__ __forceinline__ SharedSetup shared_table(const Scenario& s, double ch
   const uint64_t orders = __builtin_amdgcn_ballot_w64(
       lane < kWaveOrders && (code >> (2u * D)) == (0xe4u >> (2u * D)));
   WaveTables t;
-  wave_tables(s, chunk, scf, (uint32_t)orders, t);
+  wave_tables(s, chunk, scf, (uint32_t)orders, t, false);
   const uint32_t phase = lane >= kWaveOrders ? 1u : 0u, rank = lane - (phase ? kWaveOrders : 0u);
   const bool mine = lane < 2u * kWaveOrders && ((orders >> rank) & 1ull) != 0ull;
   double total = 0.0;
@@ -91,9 +94,12 @@ __device__ __forceinline__ SharedSetup shared_table(const Scenario& s, double ch
       const uint32_t stage = both ? (phase ? 2u * D - 1u - p : p) : (gather ? D - 1u - p : p);
       if (both || phase == (gather ? 1u : 0u)) {
         tab.time[rank * 8u + stage] = time;
-        tab.step[rank * 8u + stage] =
-            (uint16_t)(((next >> kWaveDimShift) << 4) | ((next >> kWaveClassShift) & 15u) |
-                       ((next & kWaveFinished) ? kRingFinished : 0u) | (phase << 9));
+        const uint32_t step = ((next >> kWaveDimShift) << 4) | ((next >> kWaveClassShift) & 15u) |
+                              ((next & kWaveFinished) ? kRingFinished : 0u) | (phase << 9);
+        // (the last Reduce-Scatter stands for the first All-Gather too, with what that one does)
+        const bool turns = kTurns && both && scf;
+        if (!(turns && phase == 0u && p + 1u == D)) tab.step[rank * 8u + stage] = (uint16_t)(step | 1u << 10);
+        if (turns && phase != 0u && p + 1u == D) tab.step[rank * 8u + stage - 1u] = (uint16_t)(step | 2u << 10);
       }
       if (phase == (gather ? 1u : 0u)) {
         const float tk = (float)time;
@@ -131,7 +137,22 @@ __device__ __forceinline__ SharedSetup shared_table(const Scenario& s, double ch
   r.t_min = t.t_min;
   r.t_max = total;
   r.ok = t.normal && t.few_classes;
+  r.turns = kTurns && both && scf;
   return r;
+}
+
+// The event loop on the table: completion time only.  kTurns: as the table's.  (A second loop in
+// the exhaustive search's kernel costs first-in-first-out, which has no turns, 472 -> 480 us.)
+template <bool kTurns, typename RankAt>
+__device__ __forceinline__ FastResult shared_ring(const Scenario& s, const SharedModel<RankAt>& model, const LaneLds& lds) {
+  FastOut none;
+  none.queue_order = nullptr;
+  none.slots = 0u;
+  const uint8_t* const table = (const uint8_t*)model.tab.step;
+  if constexpr (kTurns)
+    if (first_lane(model.setup.turns ? 1u : 0u) != 0u)
+      return ring_loop<true, kNoQueueOrder, false, false, true, true>(s, model, lds, none, table);
+  return ring_loop<true, kNoQueueOrder, false, false, true, false>(s, model, lds, none, table);
 }
 
 // Lower bound of the completion time of chunks with the given orders: a

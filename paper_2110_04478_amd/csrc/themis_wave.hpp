@@ -156,6 +156,7 @@ constexpr uint32_t kWaveStateShift = 9u;      // order rank + 24 * phase: bits 9
 constexpr uint32_t kWaveFinished = 1u << 15;  // (of a running stage only)
 constexpr uint32_t kWaveClassShift = 16u;     // list the chunk joins then: class bits 16-21,
 constexpr uint32_t kWaveDimShift = 22u;       // dimension bits 22-23
+constexpr uint32_t kWaveTurned = 1u << 24;    // (of a table's entry) the stage and the one after it, see QuadStages
 
 // Per-order tables of one evaluation, lane = order rank + 24 * phase.
 struct WaveTables {
@@ -167,9 +168,9 @@ struct WaveTables {
   bool few_classes;          // at most 16 classes on every dimension (all lanes)
 };
 
-// orders_used: bit r says that some chunk has the order of rank r.
+// orders_used: bit r says that some chunk has the order of rank r.  turns: with kWaveTurned.
 __device__ __forceinline__ void wave_tables(const Scenario& s, double chunk, bool scf,
-                                            uint32_t orders_used, WaveTables& t) {
+                                            uint32_t orders_used, WaveTables& t, bool turns) {
   const uint32_t D = (uint32_t)s.D;
   const bool rs_only = s.ctype == THEMIS_COLL_REDUCE_SCATTER;
   const bool gather = s.ctype == THEMIS_COLL_ALL_GATHER;
@@ -258,6 +259,12 @@ __device__ __forceinline__ void wave_tables(const Scenario& s, double chunk, boo
     }
     t.next[k] = ((rank + kWaveOrders * ph) & 63u) << kWaveStateShift | (fin ? kWaveFinished : 0u) |
                 (c & 63u) << kWaveClassShift | kn << kWaveDimShift;
+    // Smallest-Chunk-First: the last Reduce-Scatter and the All-Gather that follows it at once
+    // (same dimension, same time, no smaller chunk waits) are one stage of twice the time
+    if (turns && scf && !rs_only) {
+      const uint32_t after = (uint32_t)__shfl((int)t.next[k], (int)((lane + kWaveOrders) & 63u));
+      if (phase == 0u && p + 1u == D) t.next[k] = after | kWaveTurned;
+    }
   }
 }
 
@@ -306,7 +313,7 @@ struct WaveLds {
 #define THEMIS_W_LOG_1(K) "v_writelane_b32 %[g" #K "], %[rc], m0\n\t"
 #define THEMIS_W_FLUSH(K, E) \
   "s_and_b32 %[t], %[c" #K "], 63\n\t" "s_cbranch_scc0 .Lwf" #E "_%=\n\t" ".Lwg" #E "_%=:\n\t"
-#define THEMIS_W_START(K, E, LOG)                                                     \
+#define THEMIS_W_START(K, E, LOG, P)                                                  \
   "s_lshr_b32 %[t], %[rc], 9\n\t"                                                     \
   "s_mov_b32 m0, %[c" #K "]\n\t"                                                      \
   "v_readlane_b32 vcc_lo, %[a" #K "], %[t]\n\t"                                       \
@@ -317,7 +324,24 @@ struct WaveLds {
   "v_add_f64 %[f" #K "], %[now], vcc\n\t"                                             \
   "v_add_f64 %[z" #K "], %[z" #K "], vcc\n\t"                                         \
   "s_or_b32 %[r" #K "], %[t], %[nx]\n\t"                                              \
-  "s_bitset0_b32 %[idle], " #K "\n\t" THEMIS_W_FLUSH(K, E)
+  "s_bitset0_b32 %[idle], " #K "\n\t" THEMIS_W_FLUSH(K, E) THEMIS_W_TURN_##P(K, E)
+// the stage is two (kWaveTurned): the second one out of line
+#define THEMIS_W_TURN_FIFO1(K, E)
+#define THEMIS_W_TURN_FIFO2(K, E)
+#define THEMIS_W_TURN_SCF1(K, E) \
+  "s_bitcmp1_b32 %[r" #K "], 24\n\t" "s_cbranch_scc1 .Lwu" #E "_%=\n\t" ".Lwv" #E "_%=:\n\t"
+#define THEMIS_W_TURN_SCF2(K, E) THEMIS_W_TURN_SCF1(K, E)
+#define THEMIS_W_TURN_AWAY_FIFO1(K, E, LOG)
+#define THEMIS_W_TURN_AWAY_FIFO2(K, E, LOG)
+#define THEMIS_W_TURN_AWAY_SCF1(K, E, LOG)                                            \
+  ".Lwu" #E "_%=:\n\t" "s_mov_b32 m0, %[c" #K "]\n\t" "s_bitset0_b32 %[r" #K "], 24\n\t" \
+  "v_add_f64 %[f" #K "], %[f" #K "], vcc\n\t" "v_add_f64 %[z" #K "], %[z" #K "], vcc\n\t" \
+  "s_add_u32 %[rc], %[rc], 24*512\n\t" "s_add_u32 %[c" #K "], %[c" #K "], 1\n\t" "s_nop 1\n\t" \
+  THEMIS_W_LOG_##LOG(K)                                                               \
+  "s_and_b32 %[t], %[c" #K "], 63\n\t" "s_cbranch_scc1 .Lwv" #E "_%=\n\t"             \
+  "s_cmp_gt_u32 %[c" #K "], %[most]\n\t" "s_cbranch_scc1 .Lwend_%=\n\t"               \
+  THEMIS_W_STORE_##LOG(K) "s_branch .Lwv" #E "_%=\n\t"
+#define THEMIS_W_TURN_AWAY_SCF2(K, E, LOG) THEMIS_W_TURN_AWAY_SCF1(K, E, LOG)
 // out of line, every 64 operations of the dimension: the end of a loop whose
 // records are broken, else 64 records of the log to LDS (rb: bytes of a
 // dimension's log)
@@ -325,9 +349,9 @@ struct WaveLds {
 #define THEMIS_W_STORE_1(K)                                                           \
   "s_mul_i32 %[nx], %[rb], " #K "\n\t" "s_lshl1_add_u32 %[t], %[c" #K "], %[nx]\n\t" \
   "v_add_u32_e32 %[va], %[t], %[logat]\n\t" "ds_write_b16 %[va], %[g" #K "]\n\t"
-#define THEMIS_W_START_AWAY(K, E, LOG)                                                \
+#define THEMIS_W_START_AWAY(K, E, LOG, P)                                             \
   ".Lwf" #E "_%=:\n\t" "s_cmp_gt_u32 %[c" #K "], %[most]\n\t" "s_cbranch_scc1 .Lwend_%=\n\t" \
-  THEMIS_W_STORE_##LOG(K) "s_branch .Lwg" #E "_%=\n\t"
+  THEMIS_W_STORE_##LOG(K) "s_branch .Lwg" #E "_%=\n\t" THEMIS_W_TURN_AWAY_##P(K, E, LOG)
 
 // --- first-in-first-out, up to 64 chunks: the ring is a register
 #define THEMIS_W_PUSH_FIFO1(N, E)                                                     \
@@ -337,8 +361,8 @@ struct WaveLds {
 #define THEMIS_W_PICK_FIFO1(K, E, DONE, LOG)                                          \
   "s_cmp_eq_u32 %[i" #K "], %[o" #K "]\n\t" "s_cbranch_scc1 " DONE "\n\t"             \
   "v_readlane_b32 %[rc], %[q" #K "], %[i" #K "]\n\t"                                  \
-  "s_add_u32 %[i" #K "], %[i" #K "], 1\n\t" THEMIS_W_START(K, E, LOG)
-#define THEMIS_W_PICK_AWAY_FIFO1(K, E, DONE, LOG) THEMIS_W_START_AWAY(K, E, LOG)
+  "s_add_u32 %[i" #K "], %[i" #K "], 1\n\t" THEMIS_W_START(K, E, LOG, FIFO1)
+#define THEMIS_W_PICK_AWAY_FIFO1(K, E, DONE, LOG) THEMIS_W_START_AWAY(K, E, LOG, FIFO1)
 
 // --- beyond 64 chunks: the ring in LDS, the block that is being taken from
 // also in the register
@@ -359,13 +383,13 @@ struct WaveLds {
   "v_readlane_b32 %[rc], %[q" #K "], %[i" #K "]\n\t"                                  \
   "s_add_u32 %[i" #K "], %[i" #K "], 1\n\t"                                           \
   "s_and_b32 %[t], %[i" #K "], 63\n\t" "s_cbranch_scc0 .Lwr" #E "_%=\n\t"             \
-  ".Lws" #E "_%=:\n\t" THEMIS_W_START(K, E, LOG)
+  ".Lws" #E "_%=:\n\t" THEMIS_W_START(K, E, LOG, FIFO2)
 #define THEMIS_W_RELOAD(K, E)                                                         \
   ".Lwr" #E "_%=:\n\t" "s_and_b32 %[t], %[i" #K "], %[cap]-1\n\t" "s_lshl_b32 %[t], %[t], 1\n\t" \
   "v_add_u32_e32 %[va], %[t], %[queuelane]\n\t"                                       \
   "ds_read_u16 %[q" #K "], %[va] offset:%[cap]*2*" #K "\n\t" "s_waitcnt lgkmcnt(0)\n\t" \
   "s_branch .Lws" #E "_%=\n\t"
-#define THEMIS_W_PICK_AWAY_FIFO2(K, E, DONE, LOG) THEMIS_W_RELOAD(K, E) THEMIS_W_START_AWAY(K, E, LOG)
+#define THEMIS_W_PICK_AWAY_FIFO2(K, E, DONE, LOG) THEMIS_W_RELOAD(K, E) THEMIS_W_START_AWAY(K, E, LOG, FIFO2)
 
 // --- Smallest-Chunk-First, up to 64 chunks: links in lane = chunk
 #define THEMIS_W_PUSH_SCF1(N, E)                                                      \
@@ -388,11 +412,11 @@ struct WaveLds {
   "v_readlane_b32 %[t], %[lk], %[t]\n\t"                                              \
   "s_cmp_eq_u32 %[rc], %[nx]\n\t" "s_cselect_b32 %[nx], 1, 0\n\t"                     \
   "s_bfm_b64 vcc, %[nx], %[c]\n\t" "s_xor_b64 %[x" #K "], %[x" #K "], vcc\n\t"        \
-  "v_writelane_b32 %[h" #K "], %[t], m0\n\t" ".Lws" #E "_%=:\n\t" THEMIS_W_START(K, E, LOG)
+  "v_writelane_b32 %[h" #K "], %[t], m0\n\t" ".Lws" #E "_%=:\n\t" THEMIS_W_START(K, E, LOG, SCF1)
 #define THEMIS_W_PICK_AWAY_SCF1(K, E, DONE, LOG)                                      \
   ".Lwi" #E "_%=:\n\t" "s_cmp_eq_u32 %[i" #K "], %[o" #K "]\n\t" "s_cbranch_scc1 " DONE "\n\t" \
   "v_readlane_b32 %[rc], %[q" #K "], %[i" #K "]\n\t" "s_add_u32 %[i" #K "], %[i" #K "], 1\n\t" \
-  "s_branch .Lws" #E "_%=\n\t" THEMIS_W_START_AWAY(K, E, LOG)
+  "s_branch .Lws" #E "_%=\n\t" THEMIS_W_START_AWAY(K, E, LOG, SCF1)
 
 // --- beyond 64 chunks: links in LDS; the link of the chunk taken is on its way
 // while its stage starts
@@ -415,7 +439,7 @@ struct WaveLds {
   "v_mov_b32_e32 %[va], %[t]\n\t" "ds_read_u16 %[vd], %[va]\n\t"                      \
   "s_cmp_eq_u32 %[rc], %[nx]\n\t" "s_cselect_b32 %[nx], 1, 0\n\t"                     \
   "s_bfm_b64 vcc, %[nx], %[c]\n\t" "s_xor_b64 %[x" #K "], %[x" #K "], vcc\n\t"        \
-  THEMIS_W_START(K, E, LOG)                                                           \
+  THEMIS_W_START(K, E, LOG, SCF2)                                                           \
   "s_waitcnt lgkmcnt(0)\n\t" "s_mov_b32 m0, %[c]\n\t"                                 \
   "v_readfirstlane_b32 %[t], %[vd]\n\t" "s_nop 1\n\t"                                 \
   "v_writelane_b32 %[h" #K "], %[t], m0\n\t"
@@ -423,8 +447,8 @@ struct WaveLds {
   ".Lwi" #E "_%=:\n\t" "s_cmp_eq_u32 %[i" #K "], %[o" #K "]\n\t" "s_cbranch_scc1 " DONE "\n\t" \
   "v_readlane_b32 %[rc], %[q" #K "], %[i" #K "]\n\t" "s_add_u32 %[i" #K "], %[i" #K "], 1\n\t" \
   "s_and_b32 %[t], %[i" #K "], 63\n\t" "s_cbranch_scc0 .Lwr" #E "_%=\n\t"             \
-  ".Lws" #E "_%=:\n\t" THEMIS_W_START(K, E##i, LOG) "s_branch " DONE "\n\t"           \
-  THEMIS_W_RELOAD(K, E) THEMIS_W_START_AWAY(K, E, LOG) THEMIS_W_START_AWAY(K, E##i, LOG)
+  ".Lws" #E "_%=:\n\t" THEMIS_W_START(K, E##i, LOG, SCF2) "s_branch " DONE "\n\t"           \
+  THEMIS_W_RELOAD(K, E) THEMIS_W_START_AWAY(K, E, LOG, SCF2) THEMIS_W_START_AWAY(K, E##i, LOG, SCF2)
 
 // The stage that has ended on K (one completion at this instant): its chunk
 // joins its next list, or starts at once where that dimension is idle; then K
@@ -432,10 +456,13 @@ struct WaveLds {
 #define THEMIS_W_HAND_ON(K, N, P, LOG)                                                \
   "s_bitcmp1_b32 %[idle], " #N "\n\t" "s_cbranch_scc1 .Lwd" #K #N "_%=\n\t"           \
   THEMIS_W_PUSH_##P(N, K##N) "s_branch .Lwk" #K "_%=\n\t"
+// (in front of what only branches lead to: at the start of a 32-byte line; 50 first-in-first-out
+// scenarios of 64 chunks 118 -> 115.7 us)
+#define THEMIS_W_LINE ".p2align 5\n\t"
 #define THEMIS_W_HAND_ON_AWAY(K, N, P, LOG)                                           \
   THEMIS_W_PUSH_AWAY_##P(N, K##N)                                                     \
-  ".Lwd" #K #N "_%=:\n\t" THEMIS_W_START(N, d##K##N, LOG) "s_branch .Lwk" #K "_%=\n\t" \
-  THEMIS_W_START_AWAY(N, d##K##N, LOG)
+  THEMIS_W_LINE ".Lwd" #K #N "_%=:\n\t" THEMIS_W_START(N, d##K##N, LOG, P) "s_branch .Lwk" #K "_%=\n\t" \
+  THEMIS_W_START_AWAY(N, d##K##N, LOG, P)
 // A, B, C: the other dimensions
 #define THEMIS_W_ENDED(K, A, B, C, P, LOG)                                            \
   ".Lwc" #K "_%=:\n\t"                                                                \
@@ -449,9 +476,9 @@ struct WaveLds {
   THEMIS_W_PUSH_##P(K, K##K)                                                          \
   ".Lwl" #K "_%=:\n\t" "s_bitset1_b32 %[idle], " #K "\n\t"                            \
   ".Lwk" #K "_%=:\n\t" THEMIS_W_PICK_##P(K, K, ".Lwnext_%=", LOG) "s_branch .Lwnext_%=\n\t" \
-  ".Lwt" #K #A "_%=:\n\t" "s_bitset1_b32 %[idle], " #K "\n\t" THEMIS_W_HAND_ON(K, A, P, LOG) \
-  ".Lwt" #K #B "_%=:\n\t" "s_bitset1_b32 %[idle], " #K "\n\t" THEMIS_W_HAND_ON(K, B, P, LOG) \
-  ".Lwt" #K #C "_%=:\n\t" "s_bitset1_b32 %[idle], " #K "\n\t" THEMIS_W_HAND_ON(K, C, P, LOG) \
+  THEMIS_W_LINE ".Lwt" #K #A "_%=:\n\t" "s_bitset1_b32 %[idle], " #K "\n\t" THEMIS_W_HAND_ON(K, A, P, LOG) \
+  THEMIS_W_LINE ".Lwt" #K #B "_%=:\n\t" "s_bitset1_b32 %[idle], " #K "\n\t" THEMIS_W_HAND_ON(K, B, P, LOG) \
+  THEMIS_W_LINE ".Lwt" #K #C "_%=:\n\t" "s_bitset1_b32 %[idle], " #K "\n\t" THEMIS_W_HAND_ON(K, C, P, LOG) \
   THEMIS_W_PUSH_AWAY_##P(K, K##K) THEMIS_W_PICK_AWAY_##P(K, K, ".Lwnext_%=", LOG)     \
   THEMIS_W_HAND_ON_AWAY(K, A, P, LOG) THEMIS_W_HAND_ON_AWAY(K, B, P, LOG)             \
   THEMIS_W_HAND_ON_AWAY(K, C, P, LOG)
@@ -494,8 +521,15 @@ struct WaveLds {
   THEMIS_W_PICK_AWAY_##P(0, a0, ".Lwa0_%=", LOG) THEMIS_W_PICK_AWAY_##P(1, a1, ".Lwa1_%=", LOG) \
   THEMIS_W_PICK_AWAY_##P(2, a2, ".Lwa2_%=", LOG) THEMIS_W_PICK_AWAY_##P(3, a3, ".Lwa3_%=", LOG)
 
+// The loop's place in the instruction stream (words behind a line of 64 bytes; us: the
+// platforms of Table 2 0 135.3, 4 133.2, 6 136.7, 2 139.3; two first-in-first-out scenarios of 295
+// chunks 0 and 4 424, 2 436, 6 438; as it came 135.4 and 438).
+#define THEMIS_W_PLACE_FIFO1 ".p2align 6\n\t"
+#define THEMIS_W_PLACE_FIFO2 ".p2align 6\n\t"
+#define THEMIS_W_PLACE_SCF1 ".p2align 6\n\t.rept 4\n\ts_nop 0\n\t.endr\n\t"
+#define THEMIS_W_PLACE_SCF2 ".p2align 6\n\t"
 #define THEMIS_W_LOOP(P, LOG)                                                         \
-  "s_nop 4\n\t" "s_branch .Lwall_%=\n\t"                                              \
+  "s_nop 4\n\t" "s_branch .Lwall_%=\n\t" THEMIS_W_PLACE_##P                          \
   ".Lwnext_%=:\n\t"                                                                   \
   "v_min_f64 %[vt], %[f0], %[f1]\n\t" "v_min_f64 %[vn], %[f2], %[f3]\n\t"             \
   "v_min_f64 %[vt], %[vt], %[vn]\n\t"                                                 \
@@ -510,9 +544,9 @@ struct WaveLds {
   "s_and_b32 %[t], %[t], vcc_lo\n\t" "s_cbranch_scc1 .Lwm_%=\n\t"                     \
   "s_cmp_gt_u32 %[ends], 2\n\t" "s_cbranch_scc1 .Lw23_%=\n\t"                         \
   "s_bitcmp1_b32 %[ends], 1\n\t" "s_cbranch_scc1 .Lwc1_%=\n\t"                        \
-  THEMIS_W_ENDED(0, 1, 2, 3, P, LOG) THEMIS_W_ENDED(1, 0, 2, 3, P, LOG)               \
-  ".Lw23_%=:\n\t" "s_bitcmp1_b32 %[ends], 3\n\t" "s_cbranch_scc1 .Lwc3_%=\n\t"        \
-  THEMIS_W_ENDED(2, 0, 1, 3, P, LOG) THEMIS_W_ENDED(3, 0, 1, 2, P, LOG)               \
+  THEMIS_W_ENDED(0, 1, 2, 3, P, LOG) THEMIS_W_LINE THEMIS_W_ENDED(1, 0, 2, 3, P, LOG) \
+  THEMIS_W_LINE ".Lw23_%=:\n\t" "s_bitcmp1_b32 %[ends], 3\n\t" "s_cbranch_scc1 .Lwc3_%=\n\t"        \
+  THEMIS_W_ENDED(2, 0, 1, 3, P, LOG) THEMIS_W_LINE THEMIS_W_ENDED(3, 0, 1, 2, P, LOG) \
   THEMIS_W_SEVERAL(P, LOG)                                                            \
   ".Lwend_%=:\n\t" "s_mov_b64 exec, -1\n\t" "s_waitcnt lgkmcnt(0)\n\t" "s_nop 4\n\t"
 
@@ -662,7 +696,7 @@ __device__ __forceinline__ WaveOutcome wave_simulate(const Scenario& s, double c
     d[k].lists = first_lane((uint32_t)d[k].lists);   // (class 0 at most)
   }
   WaveTables t;
-  wave_tables(s, chunk, scf, used, t);
+  wave_tables(s, chunk, scf, used, t, true);
   if (!t.normal) return WaveOutcome::kNotTaken;
   const uint32_t stages = s.ctype == THEMIS_COLL_ALL_REDUCE ? 2u * D : D;
   r = scf ? wave_events<kWords, true, kLog>(t, stages, C, d, link, lds)

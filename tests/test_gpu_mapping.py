@@ -209,6 +209,29 @@ def test_sweeps_whose_thresholds_share_plans(gpu, oracle, n, max_chunks, n_thr, 
     assert_close("sweep", out.cpu().numpy()[few], want)
 
 
+@pytest.mark.parametrize("chunks", [1, 15, 16, 31, 32, 33, 63, 64, 65, 127, 128, 512])
+@pytest.mark.parametrize("mapping", ["wave", "quad", "lane"])
+def test_turns_under_smallest_chunk_first(gpu, oracle, mapping, chunks):
+    """A chunk's last Reduce-Scatter and first All-Gather are one stage on wavefronts and
+    quads: two records of a log that leaves 64 at a time, two operations in the counts; with
+    sizes at the end of the normal range, where equal ones would have to wait for each other."""
+    from test_gpu_parity import _with_fixed_delay
+    b = w().mixed(72, seed=1100 + chunks, max_chunks=chunks, pow2=False)
+    b.ndims[:] = 1 + np.arange(b.n) % 4
+    b.npus[:, ::3] = 2 ** (1 + np.arange(4 * 24).reshape(4, 24) % 5)
+    b.chunks[:] = chunks
+    b.intra_policy[:] = np.arange(b.n) % 5 != 0
+    b.size_bytes[6::17] = 2.3e-308 * chunks * 2.0 ** np.arange(b.n)[6::17]
+    gpu.themis_set_batch_mapping({"wave": gpu.MAPPING_WAVE}.get(mapping, gpu.MAPPING_LANE))
+    gpu.themis_set_sweep_mapping({"quad": gpu.MAPPING_QUAD, "lane": gpu.MAPPING_LANE}.get(mapping, gpu.MAPPING_AUTO))
+    try:
+        check_batch(gpu, oracle, b)
+        check_batch(gpu, oracle, _with_fixed_delay(b, 22), queue=False)
+    finally:
+        gpu.themis_set_batch_mapping(gpu.MAPPING_AUTO)
+        gpu.themis_set_sweep_mapping(gpu.MAPPING_AUTO)
+
+
 def test_a_sweep_whose_scratch_does_not_fit_goes_without(gpu, monkeypatch):
     """The list of plans is an extra: a caller whose batch leaves no room for it
     gets the same results, and one that keeps it around hands it in."""
