@@ -41,8 +41,6 @@
 // without a use for it: one of the next dimension, or links.)
 #pragma once
 
-#include <stddef.h>
-
 #include "themis_fast.hpp"
 #include "themis_ring.hpp"
 
@@ -129,20 +127,25 @@ __device__ __forceinline__ uint32_t quad_order(uint32_t code, uint32_t D) {
 }
 
 // What the stage of a chunk on dimension k does, as far as it does not depend on
-// the sizes: by row + 32 * phase, k; the rows of the orders of D dimensions start
-// at quad_row(D), where those of four leave room (an order of one dimension has
-// the third column of one of two).  Bits 1-3 the dimension the chunk waits for
+// the sizes: by row + 32 * phase, k (quad_stage_at); the rows of the orders of D
+// dimensions start at quad_row(D), where those of four leave room (an order of one
+// dimension has the third column of one of two).  Bits 1-3 the dimension the chunk waits for
 // next (4: it is finished), 9-14 its row and phase then, 17-22 four times the mask
 // of its reduced dimensions then; bits 0, 8, 16, 24: dimension 0, 1, 2, 3 comes
 // before k in its order.
-// turned: the same where a chunk's last Reduce-Scatter and its first All-Gather, on the
+// The second half is the same where a chunk's last Reduce-Scatter and its first All-Gather, on the
 // same dimension, are one stage (bit 31) that takes the time of one twice.  Under
 // Smallest-Chunk-First nothing comes between them: the chunk is smaller then than any that
 // waits there, and moves the same bytes again.
+// (One array for both, since they are copied to LDS in one go.)
+constexpr uint32_t kQuadStageWords = 64u * 4u;   // of each half
 struct QuadStages {
-  uint32_t v[64][4], turned[64][4];
+  uint32_t v[2u * kQuadStageWords];
   uint8_t code[4][24];   // the order codes themselves, by (dimensions - 1)
 };
+__host__ __device__ constexpr uint32_t quad_stage_at(uint32_t row, uint32_t column) { return 4u * row + column; }
+// Word i of the two halves, as the copies read it.
+__host__ __device__ constexpr uint32_t quad_stage_word(const QuadStages& t, uint32_t i) { return t.v[i]; }
 __host__ __device__ constexpr uint32_t quad_row(uint32_t D) { return D >= 4u ? 0u : D == 3u ? 24u : 30u; }
 __host__ __device__ constexpr uint32_t quad_column(uint32_t D) { return D == 1u ? 2u : 0u; }
 constexpr QuadStages quad_stages() {
@@ -168,16 +171,16 @@ constexpr QuadStages quad_stages() {
         const bool last = with == full;
         uint32_t bits = 0;
         for (uint32_t d = 0; d < 4u; ++d) bits |= ((before >> d) & 1u) << (8u * d);
-        t.v[row][column] = (last ? k : perm[j + 1u < 4u ? j + 1u : 3u]) << 1 | (row + (last ? 32u : 0u)) << 9 |
-                           (4u * with) << 17 | bits;
-        t.v[32u + row][column] =
+        t.v[quad_stage_at(row, column)] = (last ? k : perm[j + 1u < 4u ? j + 1u : 3u]) << 1 | (row + (last ? 32u : 0u)) << 9 |
+                                          (4u * with) << 17 | bits;
+        t.v[quad_stage_at(32u + row, column)] =
             (j == 0u ? 4u : perm[j - (j ? 1u : 0u)]) << 1 | (row + 32u) << 9 | (4u * before) << 17 | bits;
         before = with;
       }
       for (uint32_t k = 0; k < D; ++k) {
-        const uint32_t column = k + quad_column(D), v = t.v[row][column];
-        t.turned[row][column] = ((v >> 14) & 1u) != 0u ? t.v[32u + row][column] | 1u << 31 : v;
-        t.turned[32u + row][column] = t.v[32u + row][column];
+        const uint32_t scatter = quad_stage_at(row, k + quad_column(D)), gather = quad_stage_at(32u + row, k + quad_column(D));
+        t.v[kQuadStageWords + scatter] = ((t.v[scatter] >> 14) & 1u) != 0u ? t.v[gather] | 1u << 31 : t.v[scatter];
+        t.v[kQuadStageWords + gather] = t.v[gather];
       }
       ++n;
     }
@@ -201,10 +204,9 @@ template <typename L, bool kFix>
 struct QuadPow2 {
   static constexpr bool kTableInLds = L::kCap <= 256u;
   static constexpr uint32_t kTableAt = kTableInLds ? L::kBytes : 0u;
-  static constexpr uint32_t kTable = 1024u;   // bytes of each
-  static_assert(sizeof(QuadStages::v) == kTable && offsetof(QuadStages, turned) == kTable, "one behind the other");
+  static constexpr uint32_t kTable = 4u * kQuadStageWords;   // bytes of each
   static constexpr uint32_t kBytes = L::kBytes + (kTableInLds ? 2u * kTable : 0u);
-  static_assert(kTableInLds || L::kLinksAt >= 1024u, "a table fits the place of the lists' ends");
+  static_assert(kTableInLds || L::kLinksAt >= kTable, "a table fits the place of the lists' ends");
   static constexpr double kShortest = 2.2250738585072014e-308;   // (see above)
   static constexpr uint32_t kNobody = ~0u;   // above all stages, for dimension 7, list 31 (a place behind the lists)
   double whole, fix;
@@ -224,7 +226,7 @@ struct QuadPow2 {
     for (uint32_t d = 0; d < 4u; ++d) less |= (int)((0u - (m.fs.epack >> (8u * d) & 0xffu) & 0xffu) << (8u * d));
     if (kTableInLds || fifo)
       for (uint32_t j = 0; j < (kTableInLds ? 8u : 4u); ++j)
-        ((typename L::Word*)(block + kTableAt))[64u * j + threadIdx.x % 64u] = (&g_quad_stages.v[0][0])[64u * j + threadIdx.x % 64u];
+        ((typename L::Word*)(block + kTableAt))[64u * j + threadIdx.x % 64u] = quad_stage_word(g_quad_stages, 64u * j + threadIdx.x % 64u);
     __syncthreads();
   }
   __device__ __forceinline__ bool goes_to(uint32_t given, uint32_t k) const { return (given & wanted) == 2u * k; }
@@ -234,7 +236,7 @@ struct QuadPow2 {
   // the time twice
   template <bool kFifo>
   __device__ __forceinline__ uint32_t stage(uint32_t rec, double& time, bool& turned) const {
-    const uint8_t* const table = kTableInLds || kFifo ? block + kTableAt : (const uint8_t*)&g_quad_stages;
+    const uint8_t* const table = kTableInLds || kFifo ? block + kTableAt : (const uint8_t*)g_quad_stages.v;
     const uint32_t v = *(const typename L::Word*)(table + (((rec >> 5) & 0x3f0u) | at));
     time = ldexp(whole, __builtin_amdgcn_sdot4((int)(v & 0x01010101u), less, 0, true));
     if (kFix) time = fix + time;
@@ -348,8 +350,8 @@ struct QuadTable {
     least = quad_min_f64(least);
     const bool turns = scf && !rs_only && least >= 2.2250738585072014e-308;
     const double grow = gather ? (double)sel4((int)k, s.P[0], s.P[1], s.P[2], s.P[3]) : 1.0;
-    const uint32_t* const stages = (turns ? &g_quad_stages.turned[0][0] : &g_quad_stages.v[0][0]) +
-                                   4u * quad_row(D) + ((k + quad_column(D)) & 3u);
+    const uint32_t* const stages = g_quad_stages.v + (turns ? kQuadStageWords : 0u) +
+                                   quad_stage_at(quad_row(D), (k + quad_column(D)) & 3u);
     constexpr uint32_t kAtOnce = kOrders % 4u == 0u ? 4u : 3u;   // (loads that do not wait for each other)
     for (uint32_t from = 0; from < kOrders; from += kAtOnce) {
       uint32_t given[2][kAtOnce];

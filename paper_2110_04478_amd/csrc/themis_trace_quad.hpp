@@ -88,7 +88,7 @@ __device__ __forceinline__ TraceQuadResult simulate_trace_quad(const Scenario& s
 
 #pragma unroll
   for (uint32_t j = 0; j < 4u; ++j)
-    ((uint32_t*)(lds + l.table))[64u * j + threadIdx.x] = (&g_quad_stages.v[0][0])[64u * j + threadIdx.x];
+    ((uint32_t*)(lds + l.table))[64u * j + threadIdx.x] = quad_stage_word(g_quad_stages, 64u * j + threadIdx.x);
   for (uint32_t q = k; q < Q; q += 4u) chunk[16u * q] = chunk_at(q);
   __syncthreads();
 

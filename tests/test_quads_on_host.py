@@ -34,13 +34,18 @@ def _without_assembly(text):
     return "".join(out) + text[at:]
 
 
-@pytest.fixture(scope="module")
-def queues(tmp_path_factory):
-    d = tmp_path_factory.mktemp("host_wave")
+def _headers(d):
+    """The headers as g++ takes them."""
     (d / "hip").mkdir()
     (d / "hip" / "hip_runtime.h").write_text(open(os.path.join(HERE, "host_wave", "hip_runtime.h")).read())
     for h in HEADERS:
         (d / h).write_text(_without_assembly(open(os.path.join(CSRC, h)).read()))
+    return d
+
+
+@pytest.fixture(scope="module")
+def queues(tmp_path_factory):
+    d = _headers(tmp_path_factory.mktemp("host_wave"))
     subprocess.run(["g++", "-std=c++17", "-O1", "-ffp-contract=off", "-w", "-fsanitize=shift-exponent,builtin,integer-divide-by-zero",
                     "-fsanitize-undefined-trap-on-error", "-I", str(d), "-I", os.path.join(HERE, "..", "include"),
                     "-o", str(d / "queues"), os.path.join(HERE, "host_wave", "queues.cpp")], check=True)
@@ -167,6 +172,32 @@ def test_times_below_the_normal_range(oracle, queues, dims):
     t, _, taken, _ = queues(b, orders, 128, 0)
     assert (taken == 0).sum() > b.n // 2 and np.array_equal(t[taken == 1], want[taken == 1])
     _check(oracle, queues, b, orders, 128, dims)
+
+
+TABLES = """
+#include "themis_quad.hpp"
+using namespace themis;
+constexpr QuadStages kTables = quad_stages();
+constexpr bool copied_words_are_the_tables() {
+  for (uint32_t i = 0; i < 512u; ++i)
+    if (quad_stage_word(kTables, i) != kTables.v[i]) return false;
+  return true;
+}
+static_assert(copied_words_are_the_tables(), "");
+static_assert(sizeof(kTables.v) == 2048u, "");
+int main() { return 0; }
+"""
+
+
+def test_the_stage_tables_are_copied_inside_their_array(tmp_path):
+    """The copy to LDS takes both tables in one go.  The compiler evaluates it as a
+    constant here, for every word: a read beyond the end of an array, also into the one that
+    happens to follow it, is an error there."""
+    _headers(tmp_path)
+    (tmp_path / "tables.cpp").write_text(TABLES)
+    p = subprocess.run(["g++", "-std=c++17", "-fsyntax-only", "-w", "-I", str(tmp_path), "-I", os.path.join(HERE, "..", "include"),
+                        str(tmp_path / "tables.cpp")], capture_output=True, text=True)
+    assert p.returncode == 0, p.stderr[-2000:]
 
 
 PROBE = """
