@@ -20,6 +20,7 @@
 #include "themis_trace_quad.hpp"
 #include "themis_trace_wave.hpp"
 #include "themis_wave.hpp"
+#include "themis_window.hpp"
 
 // Scratch of themis_simulate_batch_noalloc: device memory the library itself
 // brings along, one copy per GPU that loads the code object.  Host code never
@@ -129,108 +130,6 @@ struct QuadTurns {
     return exists;
   }
 };
-
-// Scenarios of a window of the batch in turns of 16, the longest first: a turn takes as
-// long as its longest, so scenarios of about the same length go together (100,003 ragged
-// scenarios of any NPU counts, planner and both simulation kernels: 16 out of 64 neighbours
-// 1,095 us, out of 512 656).  Every workgroup that takes turns of a window finds the order by itself,
-// from the inputs alone, so nothing is passed between them: lengths in 64 buckets, inside
-// of a bucket as they come.  (The policies apart, each with its event loop, 32 buckets either:
-// no gain, the longest chain bounds it, and 680 us of the above for 642.)
-constexpr uint32_t kWindow = 512u, kWindowGroups = kWindow / kBlock, kWindowTurns = kWindow / 16u;
-struct QuadWindow {
-  uint32_t rank[kWindowGroups];   // of the scenarios of the lane, one in each 64 (all-ones: not among them)
-  uint32_t total;
-  // lengths[g]: that of scenario 64 * g + lane of the window, 0: not among them; most: the
-  // largest there can be.  All lanes; lds: 1,056 bytes.
-  __device__ __forceinline__ QuadWindow(uint32_t most, void* lds, const uint32_t (&lengths)[kWindowGroups]) {
-    uint16_t* const count = (uint16_t*)lds;   // of the scenarios of each 64 in each bucket, then how many come before
-    const uint32_t lane = threadIdx.x & 63u, bits = 32u - (uint32_t)__clz((int)(most | 1u));
-    const uint32_t shift = bits > 6u ? bits - 6u : 0u;
-    __syncthreads();
-#pragma unroll
-    for (uint32_t g = 0; g < kWindowGroups; ++g) count[64u * g + lane] = 0u;
-    __syncthreads();
-    uint32_t bucket[kWindowGroups];
-#pragma unroll
-    for (uint32_t g = 0; g < kWindowGroups; ++g) {
-      const bool member = lengths[g] != 0u;
-      bucket[g] = 63u - min(lengths[g] >> shift, 63u);
-      uint64_t same = __builtin_amdgcn_ballot_w64(member);
-#pragma unroll
-      for (uint32_t j = 0; j < 6u; ++j) {
-        const bool one = ((bucket[g] >> j) & 1u) != 0u;
-        const uint64_t ones = __builtin_amdgcn_ballot_w64(one);
-        same &= one ? ones : ~ones;
-      }
-      const uint32_t before = __builtin_amdgcn_mbcnt_hi((uint32_t)(same >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)same, 0u));
-      rank[g] = member ? before : ~0u;
-      if (member && before == 0u) count[64u * g + bucket[g]] = (uint16_t)__builtin_popcountll(same);
-    }
-    __syncthreads();
-    uint32_t mine[kWindowGroups], all = 0u;   // (of bucket `lane`)
-#pragma unroll
-    for (uint32_t g = 0; g < kWindowGroups; ++g) mine[g] = count[64u * g + lane];
-#pragma unroll
-    for (uint32_t g = 0; g < kWindowGroups; ++g) all += mine[g];
-    uint32_t upto = all;
-    for (uint32_t off = 1u; off < 64u; off <<= 1) {
-      const uint32_t below = (uint32_t)__shfl_up((int)upto, off);
-      upto += lane >= off ? below : 0u;
-    }
-    total = (uint32_t)__builtin_amdgcn_readlane((int)upto, 63);
-    uint32_t at = upto - all;
-#pragma unroll
-    for (uint32_t g = 0; g < kWindowGroups; ++g) {
-      count[64u * g + lane] = (uint16_t)at;
-      at += mine[g];
-    }
-    __syncthreads();
-#pragma unroll
-    for (uint32_t g = 0; g < kWindowGroups; ++g)
-      rank[g] = rank[g] != ~0u ? count[64u * g + bucket[g]] + rank[g] : ~0u;
-  }
-  __device__ __forceinline__ uint32_t turns() const { return (total + 15u) / 16u; }
-  // which: the scenario of the window that the lane's quad takes; false: none.  All lanes.
-  __device__ __forceinline__ bool take(uint32_t turn, void* lds, uint32_t& which) const {
-    uint16_t* const chosen = (uint16_t*)lds + 64u * kWindowGroups;
-    const uint32_t lane = threadIdx.x & 63u;
-    __syncthreads();
-#pragma unroll
-    for (uint32_t g = 0; g < kWindowGroups; ++g)
-      if (rank[g] >> 4 == turn) chosen[rank[g] & 15u] = (uint16_t)(kBlock * g + lane);
-    __syncthreads();
-    const bool exists = 16u * turn + (lane >> 2) < total;
-    which = exists ? chosen[lane >> 2] : 0u;
-    __syncthreads();
-    return exists;
-  }
-};
-
-// What a window's order is made from.
-struct WindowScenario {
-  uint32_t D, length;   // (length: events)
-  bool in_range;   // (dimensions and chunks; what else makes a scenario invalid is not looked at)
-};
-__device__ __forceinline__ WindowScenario window_scenario(const themis_batch_t& b, uint64_t i) {
-  WindowScenario w;
-  w.D = b.ndims[i];
-  const uint32_t C = b.chunks[i];
-  const bool one_phase = b.collective_type && b.collective_type[i] != THEMIS_COLL_ALL_REDUCE;
-  w.in_range = w.D - 1u < (uint32_t)kMaxDims && C - 1u < b.max_chunks;
-  w.length = w.in_range ? C * w.D * (one_phase ? 1u : 2u) : 1u;
-  return w;
-}
-// Does it have an NPU count that is not a power of two?
-__device__ __forceinline__ bool other_counts(const themis_batch_t& b, uint64_t i, uint32_t D) {
-  uint32_t more = 0u;   // bits beside the lowest one of each
-#pragma unroll
-  for (uint32_t k = 0; k < (uint32_t)kMaxDims; ++k) {
-    const uint32_t p = b.npus[(size_t)k * b.n + i];
-    more |= k < D ? p & (p - 1u) : 0u;
-  }
-  return more != 0u;
-}
 
 // ---------------------------------------------------------------------------
 // themis_plan_batch: Alg. 1 per scenario (hot-path steps a1-a5).

@@ -109,6 +109,11 @@ static inline int __shfl_xor(int x, int off) {
   const uint32_t l = me();
   return (int)meet((uint32_t)x, 0x1000u)[l ^ (uint32_t)off];
 }
+static inline int __shfl_up(int x, uint32_t off) {
+  const uint32_t l = me();
+  return (int)meet((uint32_t)x, 0x1001u)[l < off ? l : l - off];
+}
+static inline int __builtin_amdgcn_readlane(int x, int l) { return (int)meet((uint32_t)x, 0x1002u)[l]; }
 static inline uint32_t __builtin_amdgcn_mbcnt_lo(uint32_t m, uint32_t n) {
   return n + (uint32_t)__builtin_popcount(me() < 32u ? m & ((1u << me()) - 1u) : m);
 }

@@ -14,7 +14,7 @@ import pytest
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(os.path.dirname(HERE), "paper_2110_04478_amd", "csrc")
 HEADERS = ("themis_device.hpp", "themis_fast.hpp", "themis_ring.hpp", "themis_quad.hpp", "themis_generic.hpp", "themis_trace.hpp",
-           "themis_trace_quad.hpp")
+           "themis_trace_quad.hpp", "themis_window.hpp")
 INSTEAD = {"v_min_f64": "r = fmin(a, b);", "v_max_f64": "r = fmax(a, b);", "": ""}
 
 
@@ -43,12 +43,17 @@ def _headers(d):
     return d
 
 
-@pytest.fixture(scope="module")
-def queues(tmp_path_factory):
+def _program(tmp_path_factory, name):
     d = _headers(tmp_path_factory.mktemp("host_wave"))
     subprocess.run(["g++", "-std=c++17", "-O1", "-ffp-contract=off", "-w", "-fsanitize=shift-exponent,builtin,integer-divide-by-zero",
                     "-fsanitize-undefined-trap-on-error", "-I", str(d), "-I", os.path.join(HERE, "..", "include"),
-                    "-o", str(d / "queues"), os.path.join(HERE, "host_wave", "queues.cpp")], check=True)
+                    "-o", str(d / name), os.path.join(HERE, "host_wave", name + ".cpp")], check=True)
+    return d
+
+
+@pytest.fixture(scope="module")
+def queues(tmp_path_factory):
+    d = _program(tmp_path_factory, "queues")
 
     def run(b, orders, *kind):
         """-> (t_done, busy [4, n], taken, queue orders) of the batch."""
@@ -172,6 +177,43 @@ def test_times_below_the_normal_range(oracle, queues, dims):
     t, _, taken, _ = queues(b, orders, 128, 0)
     assert (taken == 0).sum() > b.n // 2 and np.array_equal(t[taken == 1], want[taken == 1])
     _check(oracle, queues, b, orders, 128, dims)
+
+
+@pytest.fixture(scope="module")
+def window(tmp_path_factory):
+    d = _program(tmp_path_factory, "window")
+
+    def run(most, lengths):
+        """-> the scenarios of a window of 512 in the order in which its turns take them, 16 each."""
+        (d / "in").write_bytes(np.ascontiguousarray(lengths, dtype=np.uint32).tobytes())
+        p = subprocess.run([str(d / "window"), str(most), str(d / "in"), str(d / "out")], capture_output=True, text=True, timeout=60)
+        assert p.returncode == 0 and p.stdout == "ran\n", (p.returncode, p.stdout[-500:])
+        taken = np.fromfile(d / "out", dtype=np.uint32)
+        count = int((lengths != 0).sum())
+        assert len(taken) == -(-count // 16) * 16 and (taken[count:] == 0xffffffff).all()
+        return taken[:count].astype(int)
+
+    return run
+
+
+@pytest.mark.parametrize("max_chunks", [1, 8, 24, 64, 90, 250, 512])
+@pytest.mark.parametrize("members", [0, 1, 17, 300, 512])
+def test_turns_of_a_window_are_the_longest_first(window, max_chunks, members):
+    """64 lengths apart where the largest there can be is a power of two (64 chunks: 8 events),
+    33 at least; those of a length as they come; the largest length itself among them."""
+    rng = np.random.default_rng(members + max_chunks)
+    most = 8 * max_chunks
+    lengths = np.zeros(512, np.uint32)
+    at = np.sort(rng.permutation(512)[:members])
+    lengths[at] = rng.integers(1, most + 1, members)
+    lengths[at[:1]] = most
+    taken = window(most, lengths)
+    assert np.array_equal(np.sort(taken), at)
+    width = 1
+    while 64 * width < most:
+        width *= 2
+    bucket = np.minimum(lengths[taken].astype(int) // width, 63)
+    assert np.array_equal(taken, sorted(at, key=lambda i: (-min(int(lengths[i]) // width, 63), i))), (bucket, width)
 
 
 TABLES = """
