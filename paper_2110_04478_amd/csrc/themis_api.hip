@@ -756,9 +756,9 @@ simulate_kernel(themis_batch_t b, const uint8_t* __restrict__ orders,
 // Four lanes per scenario (themis_quad.hpp).  kOthers: scenarios of up to three
 // dimensions whose NPU counts are not powers of two are taken here as well, by tables of
 // their own; else, and on four dimensions, they are left marked.
-// Where all scenarios of a window have the same length a wavefront takes 16 neighbours,
-// with others among them those of up to three dimensions by tables, whatever their
-// counts; else one turn of the window: of the others, or of the rest.
+// A wavefront takes 16 neighbours, with others among them those of up to three dimensions by
+// tables, whatever their counts; in ragged batches (in_turns()) one turn of a window: of the
+// others, or of the rest.
 template <typename L, int kQueueOrder, bool kFix, bool kOthers>
 __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(L::kWavesPerSimd)))
 simulate_quad_kernel(themis_batch_t b, const uint8_t* __restrict__ orders, double* __restrict__ t_done,
@@ -767,42 +767,29 @@ simulate_quad_kernel(themis_batch_t b, const uint8_t* __restrict__ orders, doubl
   using L3 = LayoutQuad<L::kCap, 12u, 3u>;
   constexpr uint32_t kLdsBytes = kOthers && QuadTable<L3, 3>::kBytes > QuadPow2<L, kFix>::kBytes ? QuadTable<L3, 3>::kBytes : QuadPow2<L, kFix>::kBytes;
   __shared__ uint64_t lds_block[(kLdsBytes + 7u) / 8u];
-  const uint32_t k = threadIdx.x & 3u;
-  const uint64_t block = block_index(), window = block / kWindowTurns, from = window * kWindow;
-  if (block * L::kQuads >= b.n) return;   // (in the grid's last row)
-  uint32_t lengths[kWindowGroups], longest = 0u, shortest_inv = 0u;
-#pragma unroll
-  for (uint32_t g = 0; g < kWindowGroups; ++g) {
-    const uint64_t j = from + kBlock * g + threadIdx.x;
-    const uint32_t length = window_scenario(b, j < b.n ? j : b.n - 1u).length;
-    lengths[g] = j < b.n ? length : 0u;
-    longest = max(longest, length);
-    shortest_inv = max(shortest_inv, ~length);
-  }
-  const bool ragged = uniform(quad_wave_max(longest) != ~quad_wave_max(shortest_inv));
+  const uint32_t k = threadIdx.x & 3u, block = block_index();
+  if ((uint64_t)block * L::kQuads >= b.n) return;   // (in the grid's last row)
+  const bool ragged = in_turns(b);
   // a quad without a scenario stays: the wavefront leaves the event loop as a whole
-  uint64_t i = block * L::kQuads + (threadIdx.x >> 2);
+  uint64_t i = (uint64_t)block * L::kQuads + (threadIdx.x >> 2);
   bool exists = i < b.n, runs_rest = true;
-  uint32_t turn = 0u, turns_of_rest = 0u, blocks = 1u;
-  // (0: not one of the others)
-  auto lengths_of_others = [&](uint32_t (&of)[kWindowGroups]) {
+  const WindowTurn mine = ragged ? window_turn(b.n, block) : WindowTurn{};
+  const uint64_t from = mine.window * kWindow;
+  const uint32_t turn = mine.turn, blocks = mine.turns;
+  uint32_t turns_of_rest = 0u;
+  // of the others or of the rest (0: not one of them)
+  auto lengths_of = [&](bool others, uint32_t (&lengths)[kWindowGroups]) {
 #pragma unroll
     for (uint32_t g = 0; g < kWindowGroups; ++g) {
       const uint64_t j = from + kBlock * g + threadIdx.x, at = j < b.n ? j : b.n - 1u;
       const WindowScenario w = window_scenario(b, at);
-      const bool other = kOthers && other_counts(b, at, w.D);
-      of[g] = j < b.n && other && w.in_range && w.D < 4u ? w.length : 0u;
+      const bool other = kOthers && w.in_range && w.D < 4u && other_counts(b, at, w.D);
+      lengths[g] = j < b.n && other == others ? w.length : 0u;
     }
   };
   if (ragged) {
-    const uint64_t size = b.n - from < kWindow ? b.n - from : kWindow;
-    blocks = ((uint32_t)size + 15u) / 16u;
-    // (workgroups go to the XCDs in turn: not every window's longest to the same one)
-    turn = ((uint32_t)(block % kWindowTurns) + (uint32_t)window) % blocks;
-    uint32_t of_others[kWindowGroups];
-    lengths_of_others(of_others);
-#pragma unroll
-    for (uint32_t g = 0; g < kWindowGroups; ++g) lengths[g] = of_others[g] != 0u ? 0u : lengths[g];
+    uint32_t lengths[kWindowGroups];
+    lengths_of(false, lengths);
     const QuadWindow rest(2u * (uint32_t)kMaxDims * b.max_chunks, lds_block, lengths);
     turns_of_rest = rest.turns();
     uint32_t which;
@@ -860,13 +847,15 @@ simulate_quad_kernel(themis_batch_t b, const uint8_t* __restrict__ orders, doubl
   }
   if constexpr (kOthers) {
     if (ragged) {
-      // (the two kinds have a turn more than there are workgroups, or not)
+      // (the longest of them last, see window_turn(); the two kinds have a turn more than there
+      // are workgroups, or not)
       const bool one_more = turn == 0u && runs_rest;
       if (!runs_rest || one_more) {
-        lengths_of_others(lengths);
+        uint32_t lengths[kWindowGroups];
+        lengths_of(true, lengths);
         const QuadWindow turns(2u * (uint32_t)kMaxDims * b.max_chunks, lds_block, lengths);
         uint32_t which;
-        const bool there = turns.take(runs_rest ? blocks - turns_of_rest : turn - turns_of_rest, lds_block, which);
+        const bool there = turns.take(runs_rest ? blocks - turns_of_rest : blocks - 1u - turn, lds_block, which);
         if (__builtin_amdgcn_ballot_w64(there) != 0ull)
           quad_table_turn<L3, 3, kQueueOrder>(b, orders, t_done, queue_order, entry_bytes, busy, from + which, there, false,
                                               true, lds_block, hand_over);

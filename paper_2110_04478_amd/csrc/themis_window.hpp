@@ -83,6 +83,29 @@ struct QuadWindow {
   }
 };
 
+// The turn that a workgroup of 16 quads takes, where there is one for each: in ragged batches.
+// Turns are a window's longest (0) to its shortest ones.  The windows' longest and shortest
+// start first and the ones in between last; every power of two of workgroups in a row has as
+// many of the one as of the other (the Thue-Morse sequence), so that a SIMD, which gets
+// workgroups some power of two apart, has not only long ones, whatever the batch's size is.
+// (With a turn further on from window to window, which gave SIMDs turns of one length: 60,000
+// scenarios of powers of two and both policies, 64 chunks, 311 us, now 219, of 128 chunks 591 ->
+// 412; the longest first all over: 216, 417, but 60,000 4-D of 250 chunks 1,119 for 995.)
+struct WindowTurn {
+  uint64_t window;
+  uint32_t turn, turns;   // (turns: of the window)
+};
+__host__ __device__ constexpr WindowTurn window_turn(uint64_t n, uint32_t block) {
+  const uint32_t whole = (uint32_t)(n / kWindow);   // (blocks are 32-bit numbers)
+  if (block >= (uint64_t)whole * kWindowTurns)   // the last window, not a whole one
+    return {whole, block % kWindowTurns, (uint32_t)(n % kWindow + 15u) / 16u};
+  const uint32_t slot = block / whole;
+  uint32_t odd = slot ^ slot >> 4;
+  odd = odd ^ odd >> 2;
+  odd = (odd ^ odd >> 1) & 1u;
+  return {block % whole, odd != 0u ? kWindowTurns - 1u - (slot >> 1) : slot >> 1, kWindowTurns};
+}
+
 // What a window's order is made from.
 struct WindowScenario {
   uint32_t D, length;   // (length: events)
@@ -96,6 +119,17 @@ __device__ __forceinline__ WindowScenario window_scenario(const themis_batch_t& 
   w.in_range = w.D - 1u < (uint32_t)kMaxDims && C - 1u < b.max_chunks;
   w.length = w.in_range ? C * w.D * (one_phase ? 1u : 2u) : 1u;
   return w;
+}
+// Is a batch to be taken in turns of its windows, not 16 neighbours at a time?  Where 64 of its
+// scenarios do not all have the same length (the same answer in every workgroup), and where
+// finding the order, some 10 us beside other work, is little beside a turn (60,000 scenarios,
+// neighbours / turns, us: powers of two of up to 8 chunks 46 / 50, 16 77 / 69 and on four
+// dimensions 78 / 82, 24 109 / 91 and 110 / 110, 32 135 / 116 and 140 / 131; any NPU counts on three
+// dimensions 8 35 / 50, 24 74 / 85, 32 93 / 100).
+__device__ __forceinline__ bool in_turns(const themis_batch_t& b) {
+  const uint32_t length = window_scenario(b, (b.n - 1u) * (threadIdx.x & 63u) / 63u).length;
+  const bool differ = __builtin_amdgcn_ballot_w64(length != (uint32_t)__builtin_amdgcn_readfirstlane((int)length)) != 0ull;
+  return b.max_chunks > 24u && differ;
 }
 // Does it have an NPU count that is not a power of two?
 __device__ __forceinline__ bool other_counts(const themis_batch_t& b, uint64_t i, uint32_t D) {

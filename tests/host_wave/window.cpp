@@ -2,6 +2,8 @@
 //   window <largest length there can be> in out
 // in: 512 lengths (u32, 0: not among them).  out: turn by turn the scenario of each quad
 // (u32, all-ones: none), until the last turn.
+//   window turns <n> out
+// out: window, turn and turns of the window of every workgroup of a batch of n (u32).
 #include "themis_window.hpp"
 
 using namespace themis;
@@ -23,6 +25,18 @@ static void order(void*) {
 }
 
 int main(int, char** argv) {
+  if (strcmp(argv[1], "turns") == 0) {
+    const uint64_t n = (uint64_t)atoll(argv[2]);
+    FILE* out = fopen(argv[3], "wb");
+    for (uint32_t block = 0; block * 16ull < n; ++block) {
+      const WindowTurn t = window_turn(n, block);
+      const uint32_t v[3] = {(uint32_t)t.window, t.turn, t.turns};
+      fwrite(v, sizeof v, 1, out);
+    }
+    fclose(out);
+    printf("ran\n");
+    return 0;
+  }
   most = (uint32_t)atoi(argv[1]);
   FILE* f = fopen(argv[2], "rb");
   if (!f || fread(lengths, sizeof lengths, 1, f) != 1) return 5;

@@ -193,6 +193,13 @@ def window(tmp_path_factory):
         assert len(taken) == -(-count // 16) * 16 and (taken[count:] == 0xffffffff).all()
         return taken[:count].astype(int)
 
+    def turns(n):
+        """-> window, turn and turns of the window of every workgroup of a batch of n."""
+        p = subprocess.run([str(d / "window"), "turns", str(n), str(d / "out")], capture_output=True, text=True, timeout=60)
+        assert p.returncode == 0 and p.stdout == "ran\n", (p.returncode, p.stdout[-500:])
+        return np.fromfile(d / "out", dtype=np.uint32).reshape(-1, 3).astype(int)
+
+    run.turns = turns
     return run
 
 
@@ -214,6 +221,21 @@ def test_turns_of_a_window_are_the_longest_first(window, max_chunks, members):
         width *= 2
     bucket = np.minimum(lengths[taken].astype(int) // width, 63)
     assert np.array_equal(taken, sorted(at, key=lambda i: (-min(int(lengths[i]) // width, 63), i))), (bucket, width)
+
+
+@pytest.mark.parametrize("n", [1, 16, 511, 512, 513, 1040, 5003, 60000, 65536, 250001])
+def test_every_turn_has_a_workgroup_and_long_ones_are_spread(window, n):
+    """Each turn of each window once; of the turns of a window those 1, 2, 4 or 8 apart in the
+    order in which they start are of middle length together."""
+    turns = window.turns(n)
+    of = np.minimum(n - np.arange(-(-n // 512)) * 512, 512)
+    assert len(turns) == -(-n // 16)
+    assert sorted(map(tuple, turns[:, :2].tolist())) == [(w, t) for w, m in enumerate(of) for t in range(-(-int(m) // 16))]
+    assert np.array_equal(turns[:, 2], -(-of[turns[:, 0]] // 16))
+    whole = turns[:n // 512 * 32, 1].reshape(32, -1)   # (by place, window)
+    for step in (1, 2, 4, 8):
+        for first in range(step if whole.size else 0):
+            assert (2 * whole[first::step].sum(axis=0) == 31 * 32 // step).all(), (step, first)
 
 
 TABLES = """
