@@ -326,23 +326,30 @@ struct QuadTable {
     // Classes: the number of smaller sizes among those that wait for the lane's dimension.
     // The lane's own sizes and counts are in registers, and each size is read once for all
     // of them (each comparison with a read of its own: 57 us of 264 for 750 turns of four
-    // dimensions, 64 chunks).  A chunk waits for its first stage at its whole size.
-    uint32_t rank[2u * kOrders];
-#pragma unroll
-    for (uint32_t i = 0; i < 2u * kOrders; ++i) rank[i] = 0u;
+    // dimensions, 64 chunks), on four dimensions those of orders that some chunk has, since a
+    // few chunks have few (all of them: 8,000 scenarios of 2 chunks 52 us for 36, 65,536 of
+    // 4 chunks 238 for 182, of 16 378 for 346).  A chunk waits for its first stage at its whole size.
     if (scf) {
+      uint32_t rank[2u * kOrders];
       double own[2u * kOrders];
 #pragma unroll
-      for (uint32_t i = 0; i < 2u * kOrders; ++i) own[i] = *f64_at(i < kOrders ? rs : ag, i % kOrders, k);
-      for (uint32_t o = 0; o < kOrders; ++o) {
+      for (uint32_t i = 0; i < 2u * kOrders; ++i) {
+        rank[i] = 0u;
+        own[i] = *f64_at(i < kOrders ? rs : ag, i % kOrders, k);
+      }
+      auto count = [&](uint32_t o) {
         const double v = *f64_at(rs, o, k), w = *f64_at(ag, o, k);
         cls0 += (v < chunk ? 1u : 0u) + (w < chunk ? 1u : 0u);
 #pragma unroll
         for (uint32_t i = 0; i < 2u * kOrders; ++i) rank[i] += (v < own[i] ? 1u : 0u) + (w < own[i] ? 1u : 0u);
-      }
-    }
+      };
+      if (kDims < 4u)   // (six orders: no faster by the ones in use)
+        for (uint32_t o = 0; o < kOrders; ++o) count(o);
+      else
+        for (uint32_t m = used; m != 0u; m &= m - 1u) count((uint32_t)__builtin_ctz(m));
 #pragma unroll
-    for (uint32_t i = 0; i < 2u * kOrders; ++i) *class_at(block, state_of(i % kOrders, i / kOrders), k) = (uint8_t)rank[i];
+      for (uint32_t i = 0; i < 2u * kOrders; ++i) *class_at(block, state_of(i % kOrders, i / kOrders), k) = (uint8_t)rank[i];
+    }
     __syncthreads();
     const double coef = sel4((int)k, s.coef[0], s.coef[1], s.coef[2], s.coef[3]);
     const double fix = sel4((int)k, s.fix[0], s.fix[1], s.fix[2], s.fix[3]);
@@ -375,7 +382,7 @@ struct QuadTable {
           const uint32_t v = given[phase][j];
           const uint32_t turned = (v >> 14) & 1u, next = state_of(o, turned);
           const uint32_t to = rs_only && turned != 0u ? 4u : (v >> 1) & 7u;
-          const uint32_t cls = to < 4u ? *class_at(block, next, to) : 0u;
+          const uint32_t cls = scf && to < 4u ? *class_at(block, next, to) : 0u;
           *does_at(block, state_of(o, phase), k) = (uint16_t)(to | cls << 3 | next << 9 | (v >> 31) << 15);
         }
       }

@@ -117,7 +117,7 @@ def _check(oracle, queues, b, orders, *kind):
     assert np.array_equal(entries, want_entries)
 
 
-@pytest.mark.parametrize("cap,chunks,n", [(64, 9, 30), (64, 64, 11), (128, 128, 11), (256, 200, 11), (512, 300, 11)])
+@pytest.mark.parametrize("cap,chunks,n", [(64, 2, 30), (64, 9, 30), (64, 64, 11), (128, 128, 11), (256, 200, 11), (512, 300, 11)])
 @pytest.mark.parametrize("kind", ["powers of two", "ties", "any orders", "tables"])
 def test_single_collectives(oracle, queues, cap, chunks, n, kind):
     if kind == "tables":   # every NPU count, ties among them, up to three dimensions and four
