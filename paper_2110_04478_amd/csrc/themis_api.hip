@@ -1004,21 +1004,28 @@ constexpr uint32_t kNoGeneric = 0xffffffffu;
 // Everything that follows the LDS kernel of themis_simulate_batch, in one launch: what
 // is marked in quads on tables of its own, then by the generic loop (kGeneric: its
 // chunk slots in LDS, 0: arrays in the workspace, kNoGeneric: none).  An item of the
-// workgroups' work is a turn of a window of the scenarios of four dimensions, and beyond 64
-// chunks of the others (up to 64 the kernels before have taken those whose counts are
-// not powers of two, so few are left: by `group` neighbours).  A scenario belongs to one
-// item, whatever is marked, so what one workgroup finds does not depend on the others;
-// all that is left of a window's marks is looked at first.
+// workgroups' work is a share of a window: every `shares`th of the turns of its scenarios of
+// four dimensions, or of the others.  It looks at the window once and leaves where nothing
+// is marked.  A scenario belongs to one item, whatever is marked, so what one workgroup finds
+// does not depend on the others.  (Up to 64 chunks the kernels before have taken what has other
+// counts on up to three dimensions, and leave a few powers of two that were beside those.)
+// (Before, every turn of a window was an item that looked at all of it, and turns were of all
+// its scenarios; us, then / now: 1,048,576 4-D scenarios of 64 chunks, one of other counts 2,448 /
+// 2,306, 10,000 6,054 / 2,640, every eighth 15,032 / 4,494; 65,537, every eighth 1,434 / 662;
+// 100,000 3-D of 128 chunks, every eighth 2,474 / 995, all 1,908 / 1,898.)
 // (On four dimensions the tables of 24 orders and up to 48 sizes per dimension
 // take 37 KiB per wavefront, four wavefronts per CU.)
-__host__ __device__ inline uint64_t follow_up_turns(uint64_t n, uint32_t cap) {
-  return (n + kWindow - 1u) / kWindow * kWindowTurns * (cap > 64u ? 2u : 1u);
+__host__ __device__ inline uint32_t follow_up_shares_of_others(uint32_t shares, uint32_t cap) {
+  return cap > 64u ? shares : (shares + 7u) / 8u;
+}
+__host__ __device__ inline uint64_t follow_up_items(uint64_t n, uint32_t cap, uint32_t shares) {
+  return (n + kWindow - 1u) / kWindow * (shares + follow_up_shares_of_others(shares, cap));
 }
 template <int kQueueOrder, uint32_t kCap, uint32_t kGeneric>
 __global__ void __launch_bounds__(kBlock)
 simulate_follow_up_kernel(themis_batch_t b, const uint8_t* __restrict__ orders,
                           double* __restrict__ t_done, void* __restrict__ queue_order,
-                          int entry_bytes, double* __restrict__ busy, Workspace w, uint32_t group,
+                          int entry_bytes, double* __restrict__ busy, Workspace w, uint32_t shares,
                           unsigned long long call) {
   using L4 = LayoutQuad<kCap, 48u>;
   using L3 = LayoutQuad<kCap, 12u, 3u>;
@@ -1029,53 +1036,40 @@ simulate_follow_up_kernel(themis_batch_t b, const uint8_t* __restrict__ orders,
   constexpr uint32_t kLdsSlots = kGeneric == kNoGeneric ? 0u : kGeneric;
   if (kLdsSlots) w = carve_workspace(lds_block, kBlock, kLdsSlots);
   const uint32_t lane = threadIdx.x;
-  const uint64_t windows = (b.n + kWindow - 1u) / kWindow, turns = follow_up_turns(b.n, kCap);
-  const uint64_t items = turns + (kCap > 64u ? 0u : (b.n + group - 1u) / group);
+  const uint64_t windows = (b.n + kWindow - 1u) / kWindow, items = follow_up_items(b.n, kCap, shares);
+  const LeftFirst others_first = mostly_others(b) ? LeftFirst::kAll : LeftFirst::kOthers;
   for (uint64_t item = blockIdx.x; item < items; item += gridDim.x) {
-    uint64_t i;      // of the lane: what the generic loop is to look at
-    bool left;
-    if (item < turns) {
-      const bool four = item < windows * kWindowTurns;
-      const uint64_t from = item % windows * kWindow;
-      const uint32_t turn = (uint32_t)(item / windows) % kWindowTurns;
-      bool marked = false;
-      uint32_t length[kWindowGroups], members = 0u;
+    const uint64_t from = item % windows * kWindow;
+    const uint32_t place = (uint32_t)(item / windows);
+    const bool four = place < shares;
+    const uint32_t share = four ? place : place - shares, step = four ? shares : follow_up_shares_of_others(shares, kCap);
+    MarkedWindow window(b, from, four);
+    uint32_t marked = 0u;
 #pragma unroll
-      for (uint32_t g = 0; g < kWindowGroups; ++g) {
-        const uint64_t j = from + kBlock * g + lane;
-        const WindowScenario v = window_scenario(b, j < b.n ? j : b.n - 1u);
-        length[g] = j < b.n && v.in_range && (v.D == 4u) == four ? v.length : 0u;
-        marked = marked || (length[g] != 0u && is_left_to_generic(t_done[j]));
-        members += (uint32_t)__builtin_popcountll(__builtin_amdgcn_ballot_w64(length[g] != 0u));
-      }
-      if (16u * turn >= members || __builtin_amdgcn_ballot_w64(marked) == 0ull) continue;
-      const QuadWindow order(2u * (uint32_t)kMaxDims * b.max_chunks, lds_block, length);
+    for (uint32_t g = 0; g < kWindowGroups; ++g) {
+      const uint64_t j = from + kBlock * g + lane;
+      if (is_left_to_generic(t_done[j < b.n ? j : b.n - 1u])) marked |= 1u << g;
+    }
+    if (!window.any(marked)) continue;
+    uint32_t turns;
+    const QuadWindow order = window.order(b, from, !four && kCap <= 64u ? LeftFirst::kPow2 : others_first, marked, lds_block, turns);
+    for (; turns != 0u; turns &= turns - 1u) {
+      const uint32_t turn = (uint32_t)__builtin_ctz(turns);
+      if (turn % step != share) continue;
       uint32_t which;
       const bool there = order.take(turn, lds_block, which);
-      i = from + which;
+      const uint64_t i = from + which;   // (from, where there is none)
       const bool exists = there && is_left_to_generic(t_done[i]);
-      if (__builtin_amdgcn_ballot_w64(exists) == 0ull) continue;
-      left = four ? quad_table_turn<L4, 4, kQueueOrder>(b, orders, t_done, queue_order, entry_bytes, busy, i, exists, true,
-                                                        false, lds_block, call)
-                  : quad_table_turn<L3, 3, kQueueOrder>(b, orders, t_done, queue_order, entry_bytes, busy, i, exists, true,
-                                                        false, lds_block, call);
+      bool left = four ? quad_table_turn<L4, 4, kQueueOrder>(b, orders, t_done, queue_order, entry_bytes, busy, i, exists,
+                                                             true, false, lds_block, call)
+                       : quad_table_turn<L3, 3, kQueueOrder>(b, orders, t_done, queue_order, entry_bytes, busy, i, exists,
+                                                             true, false, lds_block, call);
       left = left && (lane & 3u) == 0u;
-    } else {
-      const uint64_t first = (item - turns) * group;
-      i = first + lane;
-      left = lane < group && i < b.n && is_left_to_generic(t_done[i]) && b.ndims[i] < 4u;
-      for (QuadTurns rounds(__builtin_amdgcn_ballot_w64(left), 0u); rounds.left != 0ull;) {
-        uint32_t which;
-        const bool exists = rounds.take(which);
-        quad_table_turn<L3, 3, kQueueOrder>(b, orders, t_done, queue_order, entry_bytes, busy,
-                                            exists ? first + which : first, exists, true, false, lds_block, call);
+      if (kGeneric != kNoGeneric) {
+        __syncthreads();
+        if (left) simulate_generic_lane<kLdsSlots>(b, orders, t_done, queue_order, entry_bytes, busy, w, i);
+        __syncthreads();
       }
-      left = left && is_left_to_generic(t_done[i]);
-    }
-    if (kGeneric != kNoGeneric) {
-      __syncthreads();
-      if (left) simulate_generic_lane<kLdsSlots>(b, orders, t_done, queue_order, entry_bytes, busy, w, i);
-      __syncthreads();
     }
   }
 }
@@ -2978,11 +2972,15 @@ static SimKernel pick_quad_kernel(uint32_t cap, int mode, bool fix) {
        : cap == 256u ? pick_quad_mode<256>(mode, fix) : pick_quad_mode<512>(mode, fix);
 }
 
-// Scenarios a workgroup of the follow-up kernel looks at: 64 where there are as
-// many workgroups as the GPU holds, fewer where it would stay idle.
-static uint32_t follow_up_group(uint64_t n) {
-  const uint64_t resident = 4u * (compute_units() ? compute_units() : 256u);
-  return n > 64u * resident ? 64u : n > 32u * resident ? 32u : 16u;
+// Into how many shares the follow-up kernel divides a window's turns.  A share of many turns is
+// one after the other, and every share looks at the whole window: eight for every workgroup
+// that the GPU holds, two where turns are short, and at most one for each turn (any NPU
+// counts, two / eight, us: 100,003 4-D ragged scenarios of 64 chunks 1,164 / 855, 100,003 of 24
+// 824 / 734, 1,048,576 with 10,000 of other counts 2,614 / 2,640).
+static uint32_t follow_up_shares(uint64_t n, uint32_t max_chunks) {
+  const uint64_t wanted = (max_chunks > 8u ? 32u : 8u) * (compute_units() ? compute_units() : 256u);
+  const uint64_t windows = (n + kWindow - 1u) / kWindow;
+  return (uint32_t)std::max<uint64_t>(1u, std::min<uint64_t>(kWindowTurns, (wanted + windows - 1u) / windows));
 }
 
 // The generic area comes first in the workspace, rounded up so that the trace
@@ -3330,11 +3328,11 @@ static int simulate_batch_impl(const themis_batch_t* batch, const uint8_t* order
        kBlock, *batch, orders, t_done, queue_order, entry_bytes, busy, call);
   }
   const Workspace ws = have_ws ? w : Workspace{};
-  const uint32_t group = follow_up_group(batch->n);
-  const unsigned fb = follow_up_blocks((follow_up_turns(batch->n, cap) + (batch->n + group - 1u) / group) * kBlock);
+  const uint32_t shares = follow_up_shares(batch->n, batch->max_chunks);
+  const unsigned fb = follow_up_blocks(follow_up_items(batch->n, cap, shares) * kBlock);
 #define THEMIS_FOLLOW_UP(MODE, CAP, G) \
   go(simulate_follow_up_kernel<MODE, CAP, G>, fb, kBlock, *batch, orders, t_done, queue_order, \
-     entry_bytes, busy, ws, group, call)
+     entry_bytes, busy, ws, shares, call)
   // (8-bit entries up to 64 chunks, either up to 128, 16-bit entries beyond)
 #define THEMIS_FOLLOW_UP_MODES(CAP, G)                                \
   if (mode == kNoQueueOrder) THEMIS_FOLLOW_UP(kNoQueueOrder, CAP, G); \

@@ -67,6 +67,15 @@ struct QuadWindow {
       rank[g] = rank[g] != ~0u ? count[64u * g + bucket[g]] + rank[g] : ~0u;
   }
   __device__ __forceinline__ uint32_t turns() const { return (total + 15u) / 16u; }
+  // A bit for each turn with one of the lanes' chosen scenarios (bit g: that of rank[g]).  All lanes.
+  __device__ __forceinline__ uint32_t turns_of(uint32_t chosen) const {
+    uint32_t turns = 0u;
+#pragma unroll
+    for (uint32_t g = 0; g < kWindowGroups; ++g)
+      if (((chosen >> g) & 1u) != 0u && rank[g] != ~0u) turns |= 1u << (rank[g] >> 4);
+    for (int off = 32; off > 0; off >>= 1) turns |= (uint32_t)__shfl_xor((int)turns, off);
+    return (uint32_t)__builtin_amdgcn_readfirstlane((int)turns);
+  }
   // which: the scenario of the window that the lane's quad takes; false: none.  All lanes.
   __device__ __forceinline__ bool take(uint32_t turn, void* lds, uint32_t& which) const {
     uint16_t* const chosen = (uint16_t*)lds + 64u * kWindowGroups;
@@ -141,5 +150,54 @@ __device__ __forceinline__ bool other_counts(const themis_batch_t& b, uint64_t i
   }
   return more != 0u;
 }
+
+// Are three quarters of a batch of other counts, by 64 of its scenarios?  (The same answer in
+// every workgroup.)
+__device__ __forceinline__ bool mostly_others(const themis_batch_t& b) {
+  const uint64_t i = (b.n - 1u) * (threadIdx.x & 63u) / 63u;
+  return __builtin_popcountll(__builtin_amdgcn_ballot_w64(other_counts(b, i, b.ndims[i]))) >= 48;
+}
+
+// What is left marked of a window's scenarios of four dimensions, or of the others (four), in
+// turns.  The kernels before leave those of other counts, or powers of two beside such.  What is
+// left as a rule comes first where that is a part of the scenarios, so a few of them share
+// turns.  The longest first.  From the inputs alone, as every workgroup of the window has to
+// find the same turns whatever the others have done already.  All lanes.
+enum class LeftFirst { kAll, kOthers, kPow2 };
+struct MarkedWindow {
+  uint32_t length[kWindowGroups];   // as in QuadWindow
+  __device__ __forceinline__ MarkedWindow(const themis_batch_t& b, uint64_t from, bool four) {
+#pragma unroll
+    for (uint32_t g = 0; g < kWindowGroups; ++g) {
+      const uint64_t j = from + kBlock * g + (threadIdx.x & 63u);
+      const WindowScenario w = window_scenario(b, j < b.n ? j : b.n - 1u);
+      length[g] = j < b.n && w.in_range && (w.D == 4u) == four ? w.length : 0u;
+    }
+  }
+  // marked: bit g of the lane's scenarios.  Are there any among them?
+  __device__ __forceinline__ bool any(uint32_t marked) const {
+    uint32_t here = 0u;
+#pragma unroll
+    for (uint32_t g = 0; g < kWindowGroups; ++g) here |= length[g] != 0u ? 1u << g : 0u;
+    return __builtin_amdgcn_ballot_w64((here & marked) != 0u) != 0ull;
+  }
+  // turns: those with marks
+  __device__ __forceinline__ QuadWindow order(const themis_batch_t& b, uint64_t from, LeftFirst first, uint32_t marked,
+                                              void* lds, uint32_t& turns) {
+    const uint32_t most = 2u * (uint32_t)kMaxDims * b.max_chunks;
+    if (first != LeftFirst::kAll) {
+#pragma unroll
+      for (uint32_t g = 0; g < kWindowGroups; ++g) {
+        const uint64_t j = from + kBlock * g + (threadIdx.x & 63u), at = j < b.n ? j : b.n - 1u;
+        const bool sooner = other_counts(b, at, b.ndims[at]) == (first == LeftFirst::kOthers);
+        // (one less: the longest of the rest are not in the bucket of the shortest that come first)
+        length[g] = length[g] == 0u ? 0u : sooner ? length[g] + most : max(length[g] - 1u, 1u);
+      }
+    }
+    const QuadWindow w(first != LeftFirst::kAll ? 2u * most : most, lds, length);
+    turns = w.turns_of(marked);
+    return w;
+  }
+};
 
 }  // namespace themis

@@ -107,6 +107,31 @@ def test_ragged_scenarios_in_turns_of_a_window(gpu, oracle, n, max_chunks, every
             gpu.themis_set_sweep_mapping(gpu.MAPPING_AUTO)
 
 
+@pytest.mark.parametrize("max_chunks", [9, 64, 90])
+@pytest.mark.parametrize("others", [1, 17, 300, 900])
+def test_a_few_scenarios_of_other_counts(gpu, oracle, others, max_chunks):
+    """Of 1,100, for the follow-up kernel: those of four dimensions up to 64 chunks, beyond all,
+    with scenarios that stall among the powers of two; of one length and ragged."""
+    rng = np.random.default_rng(others)
+    for ragged in (False, True):
+        b = w().mixed(1100, seed=1200 + others, max_chunks=max_chunks)
+        if not ragged:
+            b.ndims[:] = 4
+            b.chunks[:] = max_chunks
+        b.npus[:, rng.permutation(b.n)[:others]] = rng.integers(3, 40, (4, others))
+        for k in range(4):   # (a stage too short to move the clock)
+            b.bw[k, 7 + k::301] = 1e300
+        for quads in (False, True):
+            gpu.themis_set_batch_mapping(gpu.MAPPING_LANE)
+            gpu.themis_set_sweep_mapping(gpu.MAPPING_QUAD if quads else gpu.MAPPING_LANE)
+            try:
+                check_batch(gpu, oracle, b)
+                check_batch(gpu, oracle, b, queue=False, workspace=max_chunks > 64)
+            finally:
+                gpu.themis_set_batch_mapping(gpu.MAPPING_AUTO)
+                gpu.themis_set_sweep_mapping(gpu.MAPPING_AUTO)
+
+
 @pytest.mark.parametrize("n,chunks", [(16385, 2), (32769, 2), (65536, 2), (65537, 2), (65600, 3), (17000, 70),
                                       (66001, 20), (131073, 1), (131100, 7), (131201, 16), (131300, 17), (131400, 22)])
 def test_batch_sizes_around_the_lines(gpu, oracle, n, chunks):

@@ -199,7 +199,17 @@ def window(tmp_path_factory):
         assert p.returncode == 0 and p.stdout == "ran\n", (p.returncode, p.stdout[-500:])
         return np.fromfile(d / "out", dtype=np.uint32).reshape(-1, 3).astype(int)
 
-    run.turns = turns
+    def marked(b, is_marked, dims):
+        """-> {turn: its scenarios} of the turns of a batch of one window that have marks."""
+        (d / "in").write_bytes(b.ndims.tobytes() + np.ascontiguousarray(b.npus, np.uint32).tobytes() +
+                               np.ascontiguousarray(b.chunks, np.uint32).tobytes() + is_marked.astype(np.uint8).tobytes())
+        p = subprocess.run([str(d / "window"), "marked", str(b.n), str(b.max_chunks), str(dims), str(d / "in"), str(d / "out")],
+                           capture_output=True, text=True, timeout=60)
+        assert p.returncode == 0 and p.stdout == "ran\n", (p.returncode, p.stdout[-500:])
+        rows = np.fromfile(d / "out", dtype=np.uint32).reshape(-1, 17)
+        return {int(r[0]): [int(v) for v in r[1:] if v != 0xffffffff] for r in rows}
+
+    run.turns, run.marked = turns, marked
     return run
 
 
@@ -236,6 +246,36 @@ def test_every_turn_has_a_workgroup_and_long_ones_are_spread(window, n):
     for step in (1, 2, 4, 8):
         for first in range(step if whole.size else 0):
             assert (2 * whole[first::step].sum(axis=0) == 31 * 32 // step).all(), (step, first)
+
+
+@pytest.mark.parametrize("n,others,max_chunks", [(512, 8, 64), (512, 1, 64), (512, 100, 24), (512, 383, 64),
+                                                 (512, 512, 128), (300, 40, 250), (17, 3, 512), (17, 16, 512)])
+@pytest.mark.parametrize("dims", [3, 4])
+@pytest.mark.parametrize("first", ["", "o", "p"])
+def test_a_few_marked_scenarios_share_turns(window, first, dims, n, others, max_chunks):
+    """Scenarios of other NPU counts, or powers of two, in as few turns as hold them, however
+    few they are; else all in one order.  The longest first, and only turns with marks."""
+    from paper_2110_04478_amd import workloads
+    rng = np.random.default_rng(n + others)
+    b = workloads.mixed(n, seed=n + others, max_chunks=max_chunks)
+    b.ndims[:] = dims
+    at = rng.permutation(n)[:others]
+    b.npus[:, at] = 2 * rng.integers(1, 20, (4, others)) + 1
+    is_other = np.isin(np.arange(n), at)
+    left = ~is_other if first == "p" else is_other
+    width, count = 1, int(left.sum())
+    while 64 * width < 16 * max_chunks:
+        width *= 2
+    turns = window.marked(b, left, str(dims) + first)
+    taken = [i for t in sorted(turns) for i in turns[t]]
+    assert set(np.flatnonzero(left)) <= set(taken)
+    if first:
+        assert sorted(turns) == list(range(-(-count // 16))) and left[taken[:count]].all()
+        taken = taken[:count]
+    assert (np.diff(2 * dims * b.chunks.astype(int)[taken]) <= width).all()
+    one = np.arange(n) == rng.integers(n)
+    assert [int(np.flatnonzero(one)[0]) in v for v in window.marked(b, one, str(dims) + first).values()] == [True]
+    assert window.marked(b, np.zeros(n, bool), str(dims) + first) == {} == window.marked(b, left, str(7 - dims) + first)
 
 
 TABLES = """
