@@ -16,7 +16,7 @@ pytestmark = pytest.mark.gpu
 
 
 def _mixed_counts(n, seed, every, dims=None, max_chunks=40):
-    """Powers of two, and every so many scenarios other NPU counts."""
+    """Other NPU counts, and every so many scenarios powers of two."""
     b = w().mixed(n, seed=seed, max_chunks=max_chunks)
     if dims:
         b.ndims[:] = dims
@@ -102,6 +102,42 @@ def test_ragged_scenarios_in_turns_of_a_window(gpu, oracle, n, max_chunks, every
         try:
             check_batch(gpu, oracle, b)
             check_batch(gpu, oracle, b, queue=False, workspace=max_chunks > 64)
+        finally:
+            gpu.themis_set_batch_mapping(gpu.MAPPING_AUTO)
+            gpu.themis_set_sweep_mapping(gpu.MAPPING_AUTO)
+
+
+@pytest.mark.parametrize("n", [1024, 1500, 2047])
+@pytest.mark.parametrize("max_chunks", [8, 38, 64])
+def test_windows_of_wavefronts_that_differ(gpu, oracle, n, max_chunks):
+    """One lane per scenario: in a window of eight wavefronts those with few powers of two
+    share turns among each other, and those whose lanes ran, with rows staged in their
+    block, take what they have of other counts themselves.  0 to 64 of the 64 scenarios of a
+    wavefront are of other counts, up to four dimensions and of three alone, of one length
+    and ragged, with invalid ones of every kind."""
+    rng = np.random.default_rng(n + max_chunks)
+    for ragged, dims in ((True, None), (False, 3), (True, 3)):
+        b = w().mixed(n, seed=1300 + n, max_chunks=max_chunks)
+        if dims:
+            b.ndims[:] = dims
+        if not ragged:
+            b.chunks[:] = max_chunks
+        shares = rng.permutation(np.resize([0, 1, 20, 48, 50, 60, 64, 0], -(-n // 64)))
+        for wave, share in enumerate(shares):
+            at = 64 * wave + rng.permutation(64)[:share]
+            at = at[at < n]
+            b.npus[:, at] = rng.integers(3, 40, (4, at.size))
+        b = _with_collective_types(b, 23)
+        b.bw[0, 3::41] = -1.0
+        b.size_bytes[5::43] = np.nan
+        b.chunks[7::47] = 0
+        b.chunks[9::53] = max_chunks + 1
+        b.ndims[11::59] = 5
+        gpu.themis_set_batch_mapping(gpu.MAPPING_LANE)
+        gpu.themis_set_sweep_mapping(gpu.MAPPING_LANE)
+        try:
+            check_batch(gpu, oracle, b)
+            check_batch(gpu, oracle, b, queue=False, workspace=False)
         finally:
             gpu.themis_set_batch_mapping(gpu.MAPPING_AUTO)
             gpu.themis_set_sweep_mapping(gpu.MAPPING_AUTO)
