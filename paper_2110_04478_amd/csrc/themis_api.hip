@@ -2974,13 +2974,15 @@ static SimKernel pick_quad_kernel(uint32_t cap, int mode, bool fix) {
 
 // Into how many shares the follow-up kernel divides a window's turns.  A share of many turns is
 // one after the other, and every share looks at the whole window: eight for every workgroup
-// that the GPU holds, two where turns are short, and at most one for each turn (any NPU
-// counts, two / eight, us: 100,003 4-D ragged scenarios of 64 chunks 1,164 / 855, 100,003 of 24
-// 824 / 734, 1,048,576 with 10,000 of other counts 2,614 / 2,640).
+// that the GPU holds and at most one for each turn (any NPU counts, two / eight, us: 100,003 4-D
+// ragged scenarios of 64 chunks 1,164 / 855, 100,003 of 24 824 / 734, 1,048,576 with 10,000 of
+// other counts 2,614 / 2,640); where turns are short, of two turns unless there are too few
+// windows.
 static uint32_t follow_up_shares(uint64_t n, uint32_t max_chunks) {
-  const uint64_t wanted = (max_chunks > 8u ? 32u : 8u) * (compute_units() ? compute_units() : 256u);
-  const uint64_t windows = (n + kWindow - 1u) / kWindow;
-  return (uint32_t)std::max<uint64_t>(1u, std::min<uint64_t>(kWindowTurns, (wanted + windows - 1u) / windows));
+  const uint64_t resident = 4u * (compute_units() ? compute_units() : 256u), windows = (n + kWindow - 1u) / kWindow;
+  auto shares_for = [&](uint64_t items) { return std::min<uint64_t>(kWindowTurns, (items + windows - 1u) / windows); };
+  const uint64_t shares = shares_for(8u * resident);
+  return (uint32_t)(max_chunks > 8u ? shares : std::min(shares, std::max<uint64_t>(kWindowTurns / 2u, shares_for(2u * resident))));
 }
 
 // The generic area comes first in the workspace, rounded up so that the trace
