@@ -548,7 +548,9 @@ struct Pow2Model {
 // comes before it, which otherwise moves it with every change elsewhere.  The ring loop
 // (themis_ring.hpp; words, us, period 8): 1,048,576 4-D scenarios with queue orders 2 2,272, 0
 // 2,252, 4 2,241, 6 2,237; sweep of 65,536 networks, 8 thresholds, 6 1,333, 4 1,323, 0 1,315,
-// 2 1,311; searches of 16,384 2 477, 0 474, 4 470.  simulate_fast: 220,953 scenarios of 11
+// 2 1,311; searches of 16,384 2 477, 0 474, 4 470.  Where the lanes' networks differ (no stage table
+// of the wavefront): sweep of 244 networks of 52 chunks 2 278, 1 278, 0 277, 3 272, 4 270, 5
+// 270, 7 269, 6 268, of 65,536 2 1,235, 6 1,220.  simulate_fast: 220,953 scenarios of 11
 // chunks with queue orders 3 213, 6 212, 5 210, 0 206, without 6 191, 0 188.
 template <uint32_t kWords>
 __device__ __forceinline__ void loop_place() {

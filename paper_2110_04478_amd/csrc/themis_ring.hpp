@@ -462,7 +462,7 @@ __device__ __forceinline__ FastResult ring_loop(const Scenario& s, const Model& 
   // 4 * D * C passes and a few always suffice; the bound is the same for all
   // lanes (it only has to end the loop whatever the records hold).
   constexpr uint32_t kMaxSteps = 4u * (uint32_t)kMaxDims * L::kCap + 16u;
-  loop_place<kTurns ? 0u : kShared ? 4u : kQueueOrder == kNoQueueOrder ? 2u : 6u>();
+  loop_place<kTurns ? 0u : kShared ? 4u : kTable && kQueueOrder == kNoQueueOrder ? 2u : 6u>();
   for (uint32_t step = 0; step < kMaxSteps; ++step) {
     // a7: the lowest idle dimension with chunks waiting starts the first chunk
     // of its lowest class -- the lowest set bit among the lists of idle dimensions
