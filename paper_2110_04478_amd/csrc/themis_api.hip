@@ -3003,11 +3003,13 @@ static unsigned follow_up_blocks(uint64_t items) {
 
 // Which mapping themis_sweep's LDS kernel uses for a layout capacity: beyond 64
 // chunks four lanes per evaluation, where LDS held back the lanes (four wavefronts
-// per CU at 128 chunks, three at 256, two at 512; quads 16, 12 and 8).  Measured (us,
-// lane / quads): 100 chunks, all schedulers and 8 thresholds, 300 4-D scenarios 506 /
-// 320, 30,000 2,208 / 1,779; 60,000 of 128 chunks, Themis schedulers, 5,400 / 4,355; 70
-// chunks 2,734 / 1,974; 30,001 of 200 chunks 10,508 / 4,479.  At 64 chunks the lanes
-// are faster: twelve wavefronts per CU.
+// per CU at 128 chunks, three at 256, two at 512; quads 16, 12 and 8).  Measured (us, a
+// lane each, as long as there was that / quads): 100 chunks, all schedulers and 8 thresholds,
+// 300 4-D scenarios 506 / 246, 30,000 2,208 / 1,389; 60,000 of 128 chunks, Themis schedulers,
+// 5,400 / 3,490; 70 chunks 2,734 / 1,555; 30,001 of 200 chunks 10,508 / 3,890.  Up to 64 chunks
+// the lanes, twelve wavefronts per CU, are faster where they fill the GPU (64 chunks, all
+// schedulers, 30,000 4-D scenarios 712 / 858, on one network 697 / 969), and slower where
+// they do not (2,000 366 / 212, 244 of 52 chunks 279 / 132).
 static std::atomic<int> sweep_mapping{THEMIS_MAPPING_AUTO};
 static bool sweep_mapping_is_quad(uint32_t cap) {
   const int forced = sweep_mapping.load(std::memory_order_relaxed);
@@ -3015,34 +3017,41 @@ static bool sweep_mapping_is_quad(uint32_t cap) {
 }
 
 // Four lanes per scenario (themis_quad.hpp) or one?  A pass of the quads' loop
-// takes a wavefront some 980 clocks on its own and a SIMD 350, for 16 scenarios;
+// takes a wavefront some 860 clocks on its own and a SIMD 350, for 16 scenarios;
 // the lanes' loop takes 1,300 and 620 for 64.  So quads are faster until the
 // lanes fill the GPU (a wavefront on each SIMD: 65,536 scenarios on 256 CUs), and beyond 64
-// chunks always, where LDS held back the lanes.  Measured (us, quads / lanes): 64
-// chunks, four dimensions 8,192 scenarios 224 / 317, 32,768 273 / 336, 65,536 351 /
-// 353, 262,144 1,192 / 747; 3-D first-in-first-out 65,536 271 / 282; 8 chunks 32,768
-// 48 / 70, 131,072 108 / 81; 128 chunks 16,384 474 / 730, 262,144 2,613 / 2,925; 250
-// chunks 20,001 932 / 1,530; 512 chunks 32,768 1,853 / 3,246.  Other NPU counts, 64
-// chunks (us, now / with a lane each on per-order tables): three dimensions 20,000
-// scenarios 351 / 906, 130,000 1,033 / 2,379, four 993 / 2,549, 2,690 / 8,327.
+// chunks always, where LDS held back the lanes (a lane each, before there were only
+// quads: 250 chunks 20,001 scenarios 1,530 us, 712 on quads).  Measured (us, simulation
+// with queue orders, quads / lanes), 64 chunks:
+//   4-D Smallest-Chunk-First    32,768 184 / 334, 65,536 271 / 346, 70,000 358 / 397, 131,072 498 / 411
+//   the same on one network     32,768 184 / 299, 65,536 281 / 310, 70,000 365 / 345, 131,072 510 / 362
+//   3-D first-in-first-out      32,768 128 / 272, 65,536 177 / 280, 70,000 242 / 324, 131,072 327 / 343
+//   3-D, other NPU counts       32,768 157 / 572, 65,536 224 / 589, 70,000 300 / 631, 131,072 412 / 629
+// and 8 chunks, 4-D Smallest-Chunk-First: 32,768 32 / 62, 65,536 46 / 62, 131,072 79 / 72.  Other
+// counts on four dimensions are left to the follow-up kernel either way (65,536 972 / 945).
+// Above the line lanes are up to 1.4 times as fast on a network that all scenarios share, and
+// quads up to 2.1 times on other NPU counts, which the host does not see.
 static bool simulate_on_quads(uint64_t n, uint32_t cap) {
   const int forced = sweep_mapping.load(std::memory_order_relaxed);
   const uint64_t lanes = 4u * (uint64_t)kBlock * (compute_units() ? compute_units() : 256u);
   return cap > 64u || (forced != THEMIS_MAPPING_AUTO ? forced == THEMIS_MAPPING_QUAD : n <= lanes);
 }
 
-// Whole wavefronts per scenario (themis_wave.hpp) or one lane each?  A
-// wavefront's event costs a SIMD some 300 clocks (three resident wavefronts),
-// one alone takes 560; with one lane per scenario an event takes about 1,300
-// clocks whatever the number of scenarios, until every SIMD has a wavefront of
-// 64.  Measured on 64 chunks and four dimensions (us, wavefront / lane): 256
-// scenarios 138 / 306, 2,048 164 / 314, 4,096 227 / 311, 8,192 420 / 314; NPU
-// counts that are not powers of two: 137 / 1,835, 226 / 2,274, 416 / 2,272.
-// Planner: 2,048 23 / 26, 4,096 36 / 26 (24 / 144, 36 / 149).
-// What the lines cost on power-of-two counts, and what they give the others:
-// one chunk on four dimensions, where setting the tables up is most of it, 2,048
-// scenarios 13 / 13, 4,096 18 / 13 (18 / 28), two chunks 21 / 22 (21 / 52); planner
-// at 3,072 28 / 26 on four dimensions (28 / 147), 19 / 26 on two, 11 / 26 on one.
+// Whole wavefronts per scenario (themis_wave.hpp) or not?  A wavefront's event costs a
+// SIMD some 300 clocks (three resident wavefronts), one alone takes 560.  What runs above
+// the line is quads: 860 clocks a pass for 16 scenarios, whatever their number until
+// every SIMD has a wavefront of them.  Simulation with queue orders (us, wavefront / quads), four
+// dimensions, Smallest-Chunk-First, powers of two:
+//   8 chunks     512 24 / 29, 2,048 28 / 26, 3,072 32 / 26, 4,096 37 / 27, 8,192 61 / 28
+//   64 chunks    512 121 / 183, 2,048 142 / 158, 3,072 166 / 158, 4,096 195 / 158, 8,192 341 / 168
+//   250 chunks   512 460 / 693, 2,048 547 / 593, 3,072 1,000 / 593, 4,096 1,142 / 595
+// Other NPU counts: 8 chunks 4,096 38 / 58, 64 chunks 4,096 196 / 209, 8,192 343 / 224, 250 chunks
+// 2,048 547 / 677, 4,096 1,140 / 678.  So the line is where other counts of up to 64 chunks are
+// the same on both sides (the host does not see the counts); powers of two are up to 1.4 times as fast
+// on quads from 2,500 scenarios on, and beyond 64 chunks, where LDS holds eight wavefronts
+// a CU, both are up to 1.9 times from 2,049 on.
+// Planner (us, wavefront / lane): 2,048 23 / 26, 4,096 36 / 26 (other counts 24 / 144, 36 / 149);
+// 3,072 28 / 26 on four dimensions (28 / 147), 19 / 26 on two, 11 / 26 on one.
 constexpr uint64_t kWaveSimulate = 4096, kWavePlan = 3072;
 constexpr uint64_t kMostWavefronts = 0xffffffffull / kBlock;   // of a launch with a workgroup each
 static std::atomic<int> batch_mapping{THEMIS_MAPPING_AUTO};
@@ -3128,11 +3137,12 @@ static TracePlan trace_plan(const themis_batch_t& b, uint32_t slots, uint32_t re
   return p;
 }
 
-// A wavefront per evaluation in a sweep of few: the lanes' own planning and
-// their 300 us per 64 chunks otherwise.  The line lies where themis_simulate_batch's
-// does; 4,080 evaluations on four dimensions of power-of-two counts, us, wavefront /
-// other mapping: 1 chunk 18 / 12 (other counts 18 / 23), 4 28 / 32, 64 235 / 338,
-// 256 1,330 / 1,656, 512 2,640 / 2,285 (2,640 / 7,800; two dimensions 1,260 / 1,757).
+// A wavefront per evaluation in a sweep of few: what comes after it takes other NPU counts
+// a lane each.  The line lies where themis_simulate_batch's does; 4,080 evaluations on four
+// dimensions, us, wavefront / other mapping (powers of two on lanes, beyond 64 chunks on quads):
+//   1 chunk 18 / 12 (other counts 18 / 21), 4 27 / 31 (28 / 74), 64 217 / 296 (219 / 1,790),
+//   256 1,279 / 622 (1,278 / 3,547), 512 2,550 / 1,235 (2,552 / 6,500; two dimensions 1,221 / 631,
+//   1,230 / 3,238).
 static bool sweep_on_wavefronts(uint64_t evaluations) {
   return sweep_mapping.load(std::memory_order_relaxed) == THEMIS_MAPPING_AUTO && evaluations <= kWaveSimulate;
 }
